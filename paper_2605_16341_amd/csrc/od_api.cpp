@@ -738,12 +738,12 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
       WsArr rb{reinterpret_cast<float*>(ws + b.off_rb), b.st_r};
       WsArr gram{reinterpret_cast<float*>(ws + b.off_gram), b.st_rr}, tmp{reinterpret_cast<float*>(ws + b.off_tmp), b.st_rr};
       WsArr tq1{reinterpret_cast<float*>(ws + b.off_tq1), b.st_rr}, tq2{reinterpret_cast<float*>(ws + b.off_tq2), b.st_rr};
-      if (h->cfg.variant == ORTHDION_QR) OD_TRY(od::launch_diag_trace(d.nb, d.r, tq1, tq2, v.dacc, st));
       OD_TRY(od::launch_gather_q(d.nb, d.n, d.r, v.ptrs, rb, st));
       OD_TRY(od::launch_gram(d.nb, d.n, d.r, rb, v.part, b.splits_gram_q, od::kGramBF3, st));
       OD_TRY(od::launch_reduce(d.nb, v.part, b.splits_gram_q, (int64_t)d.r * d.r, gram, st));
-      OD_TRY(od::launch_power(d.nb, d.r, gram, tmp, 128, v.dacc, st));
-      OD_TRY(od::launch_diag_final(d.nb, v.dpart, v.dacc, h->cfg.variant == ORTHDION_COLNORM ? 1 : 0,
+      WsArr w{reinterpret_cast<float*>(ws + b.off_w), b.st_rr};
+      OD_TRY(od::launch_power(d.nb, d.r, gram, tmp, w, v.part, v.dacc, st));
+      OD_TRY(od::launch_diag_final(d.nb, d.r, v.dpart, v.dacc, tq1, tq2, h->cfg.variant == ORTHDION_COLNORM ? 1 : 0,
                                    diag_all + (size_t)b.slot_base * od::kDiagPerMat, st));
     }
     OD_PHASE_KERNEL(ORTHDION_PHASE_EFX);

@@ -14,6 +14,7 @@
 #include "od_kernels.h"
 
 #include "od_common.h"
+#include "od_gemm.h"
 
 namespace od {
 
@@ -39,31 +40,34 @@ OD_DEV double block_sum_256(double v, double* red) {
 // ------------------------------------------------------------------------------------
 // sums of squares of M_prev, G and B = M_prev + G, one partial triple per workgroup
 // ------------------------------------------------------------------------------------
+// One wave per row at a time: addresses advance without a division, and kDiagBlocks workgroups keep
+// enough loads in flight for the memory system (2048 x 5632: 44 us with a 64-bit division per four
+// elements and 128 workgroups, 15 us like this: 4.8 TB/s, the rate of a large copy).
 template <bool GBF>
 __global__ __launch_bounds__(256) void k_diag_norms(ClassDims d, MatPtrs ptrs, double* dpart) {
-  const int z = blockIdx.y, tid = threadIdx.x;
-  const float* mp = ptrs.M[z];
-  const int n4 = d.n / 4;
-  const int64_t groups = (int64_t)d.m * n4;
+  const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   double sm = 0.0, sg = 0.0, sb = 0.0;
-  for (int64_t idx = (int64_t)blockIdx.x * 256 + tid; idx < groups; idx += (int64_t)gridDim.x * 256) {
-    const int64_t i = idx / n4;
-    const int j = (int)(idx - i * n4) * 4;
-    f32x4 mv = *reinterpret_cast<const f32x4*>(mp + i * d.ldm + j);
-    float g[4];
-    if constexpr (GBF) {
-      u32x2 raw = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(ptrs.G[z]) + i * d.ldg + j);
-      g[0] = bf16_lo(raw[0]); g[1] = bf16_hi(raw[0]); g[2] = bf16_lo(raw[1]); g[3] = bf16_hi(raw[1]);
-    } else {
-      f32x4 raw = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(ptrs.G[z]) + i * d.ldg + j);
-      g[0] = raw[0]; g[1] = raw[1]; g[2] = raw[2]; g[3] = raw[3];
-    }
+  for (int i = (int)blockIdx.x * 4 + (tid >> 6); i < d.m; i += (int)gridDim.x * 4) {
+    const float* mp = ptrs.M[z] + (int64_t)i * d.ldm;
+    const char* gp = reinterpret_cast<const char*>(ptrs.G[z]) + (int64_t)i * d.ldg * (GBF ? 2 : 4);
+#pragma unroll 2
+    for (int j = lane * 4; j < d.n; j += 256) {
+      const f32x4 mv = *reinterpret_cast<const f32x4*>(mp + j);
+      float g[4];
+      if constexpr (GBF) {
+        const u32x2 raw = *reinterpret_cast<const u32x2*>(gp + j * 2);
+        g[0] = bf16_lo(raw[0]); g[1] = bf16_hi(raw[0]); g[2] = bf16_lo(raw[1]); g[3] = bf16_hi(raw[1]);
+      } else {
+        const f32x4 raw = *reinterpret_cast<const f32x4*>(gp + j * 4);
+        g[0] = raw[0]; g[1] = raw[1]; g[2] = raw[2]; g[3] = raw[3];
+      }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const double a = (double)mv[e], b = (double)g[e], c = a + b;
-      sm += a * a;
-      sg += b * b;
-      sb += c * c;
+      for (int e = 0; e < 4; ++e) {
+        const double a = (double)mv[e], b = (double)g[e], c = a + b;
+        sm += a * a;
+        sg += b * b;
+        sb += c * c;
+      }
     }
   }
   __shared__ double red[256];
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(256) void k_diag_cols_final(int r, WsArr part, int 
   double s2 = 0.0, sl = 0.0, sll = 0.0;
   for (int c = tid; c < r; c += 256) {
     double s = 0.0;
-#pragma unroll 8
+#pragma unroll 16
     for (int k = 0; k < slabs; ++k) s += (double)part.base[(int64_t)z * part.stride + (int64_t)k * r + c];
     s2 += s;
     const double len = sqrt(s);
@@ -116,18 +120,6 @@ __global__ __launch_bounds__(256) void k_diag_cols_final(int r, WsArr part, int 
   }
 }
 
-// trace of T2 * T1 (both upper triangular): sum of products of the diagonals
-__global__ __launch_bounds__(256) void k_diag_trace(int r, WsArr t1, WsArr t2, double* dacc) {
-  const int z = blockIdx.x, tid = threadIdx.x;
-  const float* a = t1.base + (int64_t)z * t1.stride;
-  const float* b = t2.base + (int64_t)z * t2.stride;
-  double s = 0.0;
-  for (int i = tid; i < r; i += 256) s += (double)a[(int64_t)i * r + i] * (double)b[(int64_t)i * r + i];
-  __shared__ double red[256];
-  const double t = block_sum_256(s, red);
-  if (tid == 0) dacc[(int64_t)z * kDaccPerMat + 6] = t;
-}
-
 // copy of the callers' Q (n x r, ld r) into a workspace array
 __global__ __launch_bounds__(256) void k_gather_q(int n, int r, MatPtrs ptrs, WsArr out) {
   const int z = blockIdx.y;
@@ -138,29 +130,71 @@ __global__ __launch_bounds__(256) void k_gather_q(int n, int r, MatPtrs ptrs, Ws
 }
 
 // ------------------------------------------------------------------------------------
-// largest eigenvalue of the r x r Gram matrix of Q by power iteration; nu = sqrt of it.
-// x <- G x / ||x||; after the last product ||G x^|| estimates the eigenvalue from below with
-// relative error O((lambda_2 / lambda_1)^(2 k)).
+// largest eigenvalue of the r x r Gram matrix G of Q by power iteration; nu = sqrt of it.
+// ||G v|| / ||v|| with v = G^(2^kPowerSquarings) x0 estimates the eigenvalue from below with
+// relative error O((lambda_2 / lambda_1)^(2^(kPowerSquarings + 1))).  The power is formed by
+// squaring: 7 symmetric r x r products on the matrix cores instead of 128 dependent
+// matrix-vector products (r = 256: 863 us in one workgroup before, 66 us for the 7 launches and 15 us
+// for the estimate now; above r = 512 it was one launch per iteration).  Each square is taken of the matrix divided by its
+// largest diagonal entry - for a positive semidefinite matrix the largest entry - so that nothing
+// leaves the range of fp32 on the way.
 // ------------------------------------------------------------------------------------
 constexpr int kPowerThreads = 1024;
 constexpr int kPowerMaxR = 2048;          // x kept in LDS
+constexpr int kPowerSquarings = 7;
+constexpr int kPowerRowsPerWg = 16;
 
 OD_DEV float power_start(int i) { return 1.f + 0.5f * __sinf(0.7f * (float)i); }
 
-// y[i] = scale * sum_j g[i][j] x[j] for rows i = row0 + wave, row0 + wave + nwaves, ... < row1
+// out = (a / max diagonal of a)^2 for symmetric a: row i of the left and row j of the right operand
+// are both read along k.
+template <class T>
+__global__ __launch_bounds__(T::THREADS) void k_power_square(int r, WsArr a, WsArr out) {
+  typedef NumBF<3> Num;
+  extern __shared__ __align__(16) char lds[];
+  __shared__ float red[T::THREADS / 64];
+  const int z = blockIdx.z, tid = threadIdx.x;
+  const int tiles = (r + T::NT - 1) / T::NT;
+  const int tn = blockIdx.x % tiles, tm = blockIdx.x / tiles;
+  const SrcF32 s{a.base + (int64_t)z * a.stride, r, r, r};
+  float md = 0.f;
+  for (int i = tid; i < r; i += T::THREADS) md = fmaxf(md, s.p[(int64_t)i * r + i]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) md = fmaxf(md, __shfl_xor(md, off, 64));
+  if ((tid & 63) == 0) red[tid >> 6] = md;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < T::THREADS / 64; ++w) md = fmaxf(md, red[w]);
+  const float inv = md > 0.f ? 1.f / md : 0.f;
+  f32x16 acc[T::FM][T::FN];
+  zero_acc<T>(acc);
+  gemm_mainloop_deep<T, Num, KC, SrcF32, KC, SrcF32, 3>(s, s, tm * T::MT, tn * T::NT, 0, r, 1.f, 1.f, lds, acc);
+  float* o = out.base + (int64_t)z * out.stride;
+  for_each_acc<T>(acc, tm * T::MT, tn * T::NT, [&](int row, int col, float v) {
+    if (row < r && col < r) o[(int64_t)row * r + col] = v * inv * inv;
+  });
+}
+
+// y[i] = scale * sum_j g[i][j] x[j], row0 <= i < row1: four consecutive rows per wave and turn, so that
+// their loads are in flight together
 OD_DEV void power_rows(const float* g, const float* x_lds, int r, int row0, int row1, float scale, float* y) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int i = row0 + wave; i < row1; i += nw) {
-    const float* row = g + (int64_t)i * r;
-    float acc = 0.f;
+  for (int i = row0 + 4 * wave; i < row1; i += 4 * nw) {
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int j = lane * 4; j < r; j += 256) {
-      f32x4 a = *reinterpret_cast<const f32x4*>(row + j);
-      f32x4 b = *reinterpret_cast<const f32x4*>(x_lds + j);
-      acc += a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + a[3] * b[3];
+      const f32x4 b = *reinterpret_cast<const f32x4*>(x_lds + j);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(g + (int64_t)min(i + q, row1 - 1) * r + j);
+        acc[q] += a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + a[3] * b[3];
+      }
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) y[i] = acc * scale;
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off, 64);
+      if (lane == 0 && i + q < row1) y[i + q] = acc[q] * scale;
+    }
   }
 }
 
@@ -178,66 +212,73 @@ OD_DEV float block_sumsq(const float* v, int r, float* red) {
   return t;
 }
 
-// one workgroup per matrix, all iterations inside (small r: the matrix stays in L2)
-__global__ __launch_bounds__(kPowerThreads) void k_power(int r, WsArr gram, int iters, double* dacc) {
+// The two matrix-vector products after the squarings, v = P x0 and G v / ||v||.  Up to r = 512 one
+// workgroup per matrix does both.
+__global__ __launch_bounds__(kPowerThreads) void k_power_estimate(int r, WsArr power, WsArr gram, double* dacc) {
   __shared__ __align__(16) float x[kPowerMaxR];
   __shared__ __align__(16) float y[kPowerMaxR];
   __shared__ float red[kPowerThreads / 64];
   const int z = blockIdx.x, tid = threadIdx.x;
-  const float* g = gram.base + (int64_t)z * gram.stride;
   for (int i = tid; i < r; i += kPowerThreads) x[i] = power_start(i);
-  float lam = 0.f;
-  for (int it = 0; it < iters; ++it) {
-    const float s = block_sumsq(x, r, red);          // barriers inside: x complete
-    const float inv = s > 0.f ? rsqrtf(s) : 0.f;
-    power_rows(g, x, r, 0, r, inv, y);
-    __syncthreads();
-    for (int i = tid; i < r; i += kPowerThreads) x[i] = y[i];
-    __syncthreads();
-  }
-  lam = sqrtf(block_sumsq(x, r, red));
+  __syncthreads();
+  power_rows(power.base + (int64_t)z * power.stride, x, r, 0, r, 1.f, y);
+  __syncthreads();
+  const float s = block_sumsq(y, r, red);
+  const float inv = s > 0.f ? rsqrtf(s) : 0.f;
+  power_rows(gram.base + (int64_t)z * gram.stride, y, r, 0, r, inv, x);
+  __syncthreads();
+  const float lam = sqrtf(block_sumsq(x, r, red));
   if (tid == 0) dacc[(int64_t)z * kDaccPerMat + 7] = (double)lam;
 }
 
-// large r: one launch per iteration, rows spread over workgroups; xin / xout ping-pong
-__global__ __launch_bounds__(256) void k_power_init(int r, WsArr xbuf) {
-  const int z = blockIdx.y;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < r) xbuf.base[(int64_t)z * xbuf.stride + i] = power_start(i);
-}
-__global__ __launch_bounds__(256) void k_power_step(int r, WsArr gram, WsArr xbuf, int src_half, int rows_per_wg) {
+// Larger r: rows spread over workgroups, one launch per product; `first` starts from x0
+__global__ __launch_bounds__(256) void k_power_step(int r, WsArr mat, WsArr xbuf, int first) {
   __shared__ __align__(16) float x[kPowerMaxR];
   __shared__ float red[4];
   const int z = blockIdx.y, tid = threadIdx.x;
-  const float* g = gram.base + (int64_t)z * gram.stride;
-  const float* xin = xbuf.base + (int64_t)z * xbuf.stride + (int64_t)src_half * r;
-  float* xout = xbuf.base + (int64_t)z * xbuf.stride + (int64_t)(src_half ^ 1) * r;
-  for (int i = tid; i < r; i += 256) x[i] = xin[i];
-  const float s = block_sumsq(x, r, red);
-  const float inv = s > 0.f ? rsqrtf(s) : 0.f;
-  const int row0 = blockIdx.x * rows_per_wg;
-  const int row1 = (row0 + rows_per_wg) < r ? (row0 + rows_per_wg) : r;
-  power_rows(g, x, r, row0, row1, inv, xout);
+  const float* g = mat.base + (int64_t)z * mat.stride;
+  float* xb = xbuf.base + (int64_t)z * xbuf.stride;
+  for (int i = tid; i < r; i += 256) x[i] = first ? power_start(i) : xb[i];
+  __syncthreads();
+  float inv = 1.f;
+  if (!first) {
+    const float s = block_sumsq(x, r, red);
+    inv = s > 0.f ? rsqrtf(s) : 0.f;
+  }
+  const int row0 = blockIdx.x * kPowerRowsPerWg;
+  const int row1 = (row0 + kPowerRowsPerWg) < r ? (row0 + kPowerRowsPerWg) : r;
+  power_rows(g, x, r, row0, row1, inv, first ? xb : xb + r);
 }
-__global__ __launch_bounds__(256) void k_power_final(int r, WsArr xbuf, int src_half, double* dacc) {
+__global__ __launch_bounds__(256) void k_power_final(int r, WsArr xbuf, double* dacc) {
   __shared__ float red[4];
   const int z = blockIdx.x;
-  const float* x = xbuf.base + (int64_t)z * xbuf.stride + (int64_t)src_half * r;
+  const float* x = xbuf.base + (int64_t)z * xbuf.stride + r;
   const float s = block_sumsq(x, r, red);
   if (threadIdx.x == 0) dacc[(int64_t)z * kDaccPerMat + 7] = (double)sqrtf(s);
 }
 
 // ------------------------------------------------------------------------------------
-// the reported scalars, one thread per matrix
+// the reported scalars, one workgroup per matrix; QR variant: also the trace of T2 T1 (both upper
+// triangular: the sum of products of the diagonals), which is <B, P Q^T>
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_diag_final(int nb, const double* dpart, const double* dacc, int colnorm, float* diag) {
-  const int z = blockIdx.x * 64 + threadIdx.x;
-  if (z >= nb) return;
-  double sm = 0.0, sg = 0.0, sb = 0.0;
-  for (int k = 0; k < kDiagBlocks; ++k) {
+__global__ __launch_bounds__(256) void k_diag_final(int r, const double* dpart, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag) {
+  const int z = blockIdx.x, tid = threadIdx.x;
+  __shared__ double red[256];
+  double sm = 0.0, sg = 0.0, sb = 0.0, tr = 0.0;
+  for (int k = tid; k < kDiagBlocks; k += 256) {
     const double* p = dpart + ((int64_t)z * kDiagBlocks + k) * 4;
     sm += p[0]; sg += p[1]; sb += p[2];
   }
+  if (!colnorm) {
+    const float* a1 = t1.base + (int64_t)z * t1.stride;
+    const float* a2 = t2.base + (int64_t)z * t2.stride;
+    for (int i = tid; i < r; i += 256) tr += (double)a1[(int64_t)i * r + i] * (double)a2[(int64_t)i * r + i];
+  }
+  sm = block_sum_256(sm, red);
+  sg = block_sum_256(sg, red);
+  sb = block_sum_256(sb, red);
+  tr = block_sum_256(tr, red);
+  if (tid != 0) return;
   const double* a = dacc + (int64_t)z * kDaccPerMat;
   const double r2 = a[3], sl = a[4], sll = a[5];
   float* o = diag + (int64_t)z * kDiagPerMat;
@@ -246,7 +287,7 @@ __global__ __launch_bounds__(64) void k_diag_final(int nb, const double* dpart, 
   o[1] = (float)sqrt(r2);
   o[2] = sb > 0.0 ? (float)sqrt((gap > 0.0 ? gap : 0.0) / sb) : 0.f;
   o[3] = sg > 0.0 ? (float)sqrt(sm / sg) : 0.f;
-  o[4] = (float)(colnorm ? sl : a[6]);
+  o[4] = (float)(colnorm ? sl : tr);
   o[5] = (float)sqrt(a[7]);
   o[6] = sl > 0.0 ? (float)exp(log(sl) - sll / sl) : 0.f;
   o[7] = (float)sqrt(sg);
@@ -285,12 +326,6 @@ hipError_t launch_diag_cols(int nb, int n, int r, WsArr rr, WsArr part, int slab
   return hipSuccess;
 }
 
-hipError_t launch_diag_trace(int nb, int r, WsArr t1, WsArr t2, double* dacc, hipStream_t st) {
-  hipLaunchKernelGGL(k_diag_trace, dim3(nb), dim3(256), 0, st, r, t1, t2, dacc);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
 hipError_t launch_gather_q(int nb, int n, int r, const MatPtrs& ptrs, WsArr out, hipStream_t st) {
   int64_t n4 = (int64_t)n * r / 4;
   int blocks = (int)((n4 + 255) / 256);
@@ -300,29 +335,46 @@ hipError_t launch_gather_q(int nb, int n, int r, const MatPtrs& ptrs, WsArr out,
   return hipSuccess;
 }
 
-hipError_t launch_power(int nb, int r, WsArr gram, WsArr xbuf, int iters, double* dacc, hipStream_t st) {
-  if (r > kPowerMaxR || xbuf.stride < 2 * (int64_t)r) return hipErrorInvalidValue;
-  if (r <= 512) {
-    hipLaunchKernelGGL(k_power, dim3(nb), dim3(kPowerThreads), 0, st, r, gram, iters, dacc);
-    OD_CHECK_LAUNCH();
-    return hipSuccess;
-  }
-  hipLaunchKernelGGL(k_power_init, dim3((r + 255) / 256, nb), dim3(256), 0, st, r, xbuf);
-  OD_CHECK_LAUNCH();
-  const int rows_per_wg = 8;
-  int half = 0;
-  for (int it = 0; it < iters; ++it) {
-    hipLaunchKernelGGL(k_power_step, dim3((r + rows_per_wg - 1) / rows_per_wg, nb), dim3(256), 0, st, r, gram, xbuf, half, rows_per_wg);
-    OD_CHECK_LAUNCH();
-    half ^= 1;
-  }
-  hipLaunchKernelGGL(k_power_final, dim3(nb), dim3(256), 0, st, r, xbuf, half, dacc);
+template <class T>
+static hipError_t power_square(int nb, int r, WsArr a, WsArr out, hipStream_t st) {
+  constexpr int lds = T::template lds_bytes<NumBF<3>>();
+  const hipError_t e = lds > 64 * 1024
+      ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_power_square<T>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) : hipSuccess;
+  if (e != hipSuccess) return e;
+  const int tiles = (r + T::NT - 1) / T::NT;
+  hipLaunchKernelGGL(k_power_square<T>, dim3(tiles * tiles, 1, nb), dim3(T::THREADS), lds, st, r, a, out);
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }
 
-hipError_t launch_diag_final(int nb, const double* dpart, const double* dacc, int colnorm, float* diag, hipStream_t st) {
-  hipLaunchKernelGGL(k_diag_final, dim3((nb + 63) / 64), dim3(64), 0, st, nb, dpart, dacc, colnorm, diag);
+hipError_t launch_power(int nb, int r, WsArr gram, WsArr tmp1, WsArr tmp2, WsArr xbuf, double* dacc, hipStream_t st) {
+  if (r > kPowerMaxR || xbuf.stride < 2 * (int64_t)r) return hipErrorInvalidValue;
+  // 64 x 64 tiles until 128 x 128 ones fill the chip by themselves
+  const bool big = (int64_t)((r + 127) / 128) * ((r + 127) / 128) * nb >= 256;
+  WsArr cur = gram, nxt = tmp1;
+  for (int i = 0; i < kPowerSquarings; ++i) {
+    const hipError_t e = big ? power_square<Tile<128, 128, 32, 2, 2>>(nb, r, cur, nxt, st) : power_square<Tile<64, 64, 64, 2, 2>>(nb, r, cur, nxt, st);
+    if (e != hipSuccess) return e;
+    cur = nxt;
+    nxt = cur.base == tmp1.base ? tmp2 : tmp1;
+  }
+  if (r <= 512) {
+    hipLaunchKernelGGL(k_power_estimate, dim3(nb), dim3(kPowerThreads), 0, st, r, cur, gram, dacc);
+    OD_CHECK_LAUNCH();
+    return hipSuccess;
+  }
+  const dim3 grid((r + kPowerRowsPerWg - 1) / kPowerRowsPerWg, nb);
+  hipLaunchKernelGGL(k_power_step, grid, dim3(256), 0, st, r, cur, xbuf, 1);
+  OD_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_power_step, grid, dim3(256), 0, st, r, gram, xbuf, 0);
+  OD_CHECK_LAUNCH();
+  hipLaunchKernelGGL(k_power_final, dim3(nb), dim3(256), 0, st, r, xbuf, dacc);
+  OD_CHECK_LAUNCH();
+  return hipSuccess;
+}
+
+hipError_t launch_diag_final(int nb, int r, const double* dpart, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag, hipStream_t st) {
+  hipLaunchKernelGGL(k_diag_final, dim3(nb), dim3(256), 0, st, r, dpart, dacc, t1, t2, colnorm, diag);
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }

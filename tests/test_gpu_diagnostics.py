@@ -92,6 +92,14 @@ def test_diagnostics_rank_above_512(variant):
     run_case([(768, 640)], 520, "f32", variant, steps=2, seed=720)
 
 
+@pytest.mark.parametrize("count,m,n,r", [(29, 272, 264, 264), (1, 96, 72, 8), (2, 528, 512, 512)])
+def test_diagnostics_power_iteration_tiles(count, m, n, r):
+    """nu = sigma_1(Q) by squared powers at the edges of its tiles: enough matrices for 128 x 128
+    tiles with a ragged last one, one tile with 8 rows, the largest rank of the one-workgroup
+    estimate.  ColNorm, whose factor has a spread of singular values."""
+    run_case([(m, n)] * count, r, "f32", "colnorm", steps=1, seed=735)
+
+
 @pytest.mark.parametrize("variant", ["qr", "colnorm"])
 def test_diagnostics_c2_shape(variant):
     w = synth.WORKLOADS["C2"]
