@@ -6,7 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
-#include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -15,10 +15,11 @@
 
 namespace {
 
+using od::BatchRef;
 using od::ClassDims;
-using od::MatPtrs;
-using od::WsArr;
 using od::HalfArr;
+using od::MatEntry;
+using od::WsArr;
 
 constexpr size_t kAlign = 256;
 // Two groups by default between these numbers of matrix elements.  A set below is a chain of
@@ -30,9 +31,18 @@ constexpr size_t kAlign = 256;
 constexpr double kGroupMinElements = 64.0 * 1024 * 1024;
 constexpr double kGroupMaxElements = 512.0 * 1024 * 1024;
 
+// Matrices of one shape class step in launch batches of at most this many matrices, or more while
+// they hold less than kBatchElements: what a batch's kernels leave behind for the next one (partial
+// sums, factors) should still be in the Infinity Cache when it is read.
+constexpr int kBatchMatrices = 32;
+constexpr double kBatchElements = 64.0 * 1024 * 1024;
+// Batches of different shapes share their launches (a cluster) up to this many elements: below it
+// the launches of one shape leave most of the chip idle, above it every batch fills the chip by itself.
+constexpr double kClusterElements = 128.0 * 1024 * 1024;
+
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-// A batch: up to kMaxBatchHost matrices of identical shape and leading dimensions.
+// A batch: matrices of identical shape and leading dimensions.
 struct Batch {
   ClassDims d;
   std::vector<int> members;          // indices into the caller's arrays
@@ -41,9 +51,11 @@ struct Batch {
       off_tmp, off_colsq;
   size_t off_ph, off_pht, off_rh, off_qh, off_qht;   // pre-scaled fp16 copies of the factors (uint16 arrays)
   int64_t st_p, st_r, st_part, st_rr, st_colsq;
-  int splits_proj, splits_back, splits_gram_p, splits_gram_q, slabs;
+  int splits_proj, splits_back, splits_gram[2], slabs;
   int slot_base;                     // first row of this batch in the scal / info tables
   int rank_class;
+  int cluster;                       // batches of one cluster share their launches
+  int64_t peers;                     // matrices of this shape that make up the same work as the cluster
 };
 
 // All batches of one rank r.  The r x r work of the orthogonalisations (Cholesky factor and
@@ -57,7 +69,16 @@ struct RankClass {
   size_t off_gram, off_tp1, off_tp2, off_tq1, off_tq2, off_w, off_tmp;
 };
 
-int pick_splits(int64_t tiles, int nb, int64_t k, int kt_min) {
+// What runs in lockstep: the rank classes up to 256 of a group together, a larger rank by itself.
+// Its batches are enqueued cluster by cluster, piece by piece.
+struct Unit {
+  int group;
+  bool wide_guard;                   // ranks above 256: the class-wide guard of the second pass
+  std::vector<int> classes;
+  std::vector<std::vector<int>> clusters;   // batches that share launches
+};
+
+int pick_splits(int64_t tiles, int64_t nb, int64_t k, int kt_min) {
   int64_t want = (512 + tiles * nb - 1) / (tiles * nb);
   int64_t cap = k / kt_min;
   if (cap < 1) cap = 1;
@@ -71,7 +92,7 @@ int pick_splits(int64_t tiles, int nb, int64_t k, int kt_min) {
 // that fit one CU).  A workgroup's time is proportional to 1 / splits, so rounds / splits
 // measures the launch; the fewest splits (least partial-sum traffic) within 15 % of the best
 // are taken.
-int pick_splits_by_rounds(int64_t tiles, int nb, int64_t k, int kt_min, int64_t slots) {
+int pick_splits_by_rounds(int64_t tiles, int64_t nb, int64_t k, int kt_min, int64_t slots) {
   int64_t cap = k / kt_min;
   if (cap < 1) cap = 1;
   if (cap > 32) cap = 32;
@@ -90,8 +111,9 @@ struct orthdion_ctx {
   orthdion_config cfg;
   std::vector<Batch> batches;
   std::vector<RankClass> classes;
+  std::vector<Unit> units;
   std::vector<int> batch_of, slot_of;     // per matrix
-  size_t off_scal, off_info, off_diag, off_dacc, off_dpart, ws_bytes;
+  size_t off_mats, off_scal, off_info, off_diag, off_dacc, off_dpart, ws_bytes;
   void* last_ws;
   bool diag_on = false, diag_valid = false;
   // optional phase timing with HIP events (host resources only)
@@ -99,7 +121,7 @@ struct orthdion_ctx {
   unsigned prof_mask = 0;
   int prof_max_steps = 0, prof_steps = 0;
   std::vector<hipEvent_t> prof_events;    // [step][batch][phase][begin/end]
-  std::vector<char> prof_recorded;        // [step][batch][phase]: an interval was recorded
+  std::vector<int> prof_recorded;         // [step][batch][phase]: batches the recorded interval covers, 0 = none
   // a second stream for the guard of the second CholeskyQR pass (ranks above 256): its launch
   // chain returns at once for every well-conditioned matrix, and beside the main stream those
   // empty launches cost nothing (host resources; made at the first step that is not being captured)
@@ -140,11 +162,11 @@ static bool ensure_side_stream(orthdion_ctx* h, hipStream_t st) {
   return true;
 }
 
-static hipEvent_t* prof_slot(orthdion_ctx* h, int batch, int phase, int end) {
+static hipEvent_t* prof_slot(orthdion_ctx* h, int batch, int phase, int end, int covers) {
   if (!h->prof_on || h->prof_steps >= h->prof_max_steps || !(h->prof_mask & (1u << phase))) return nullptr;
   size_t nb = h->batches.size();
   size_t idx = (((size_t)h->prof_steps * nb + (size_t)batch) * ORTHDION_NPHASE + (size_t)phase) * 2 + (size_t)end;
-  if (end) h->prof_recorded[idx / 2] = 1;
+  if (end) h->prof_recorded[idx / 2] = covers;
   return &h->prof_events[idx];
 }
 
@@ -235,7 +257,8 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     const orthdion_matdesc& a = mats[i];
     int found = -1;
     for (size_t b = 0; b < h->batches.size(); ++b) {
-      if (same_shape(h->batches[b].d, a) && (int)h->batches[b].members.size() < od::kMaxBatchHost) found = (int)b;
+      const double held = (double)h->batches[b].members.size();
+      if (same_shape(h->batches[b].d, a) && (held < kBatchMatrices || (held + 1) * (double)a.m * (double)a.n <= kBatchElements)) found = (int)b;
     }
     if (found < 0) {
       Batch nb = {};
@@ -251,8 +274,37 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     h->batches[found].members.push_back(i);
   }
 
+  // Clusters, in batch order: the ranks up to 256 together, every larger rank by itself.  They do not
+  // depend on the groups below (nor does anything chosen from them), so that the groups leave the
+  // results alone bit for bit.
+  {
+    struct Open { int key, id; double elems; };
+    std::vector<Open> open;
+    std::vector<double> cluster_elems;
+    for (Batch& b : h->batches) {
+      const int key = b.d.r <= od::kLeafRank ? 0 : b.d.r;
+      const double e = (double)b.d.m * b.d.n * (double)b.members.size();
+      size_t k = 0;
+      while (k < open.size() && open[k].key != key) ++k;
+      if (k == open.size()) open.push_back(Open{key, -1, 0.0});
+      if (open[k].id < 0 || open[k].elems + e > kClusterElements) {
+        open[k].id = (int)cluster_elems.size();
+        open[k].elems = 0.0;
+        cluster_elems.push_back(0.0);
+      }
+      open[k].elems += e;
+      b.cluster = open[k].id;
+      cluster_elems[b.cluster] += e;
+    }
+    for (Batch& b : h->batches) {
+      b.peers = (int64_t)(cluster_elems[b.cluster] / ((double)b.d.m * b.d.n));
+      if (b.peers < (int64_t)b.members.size()) b.peers = (int64_t)b.members.size();
+    }
+  }
+
   // workspace plan
   size_t off = 0;
+  h->off_mats = off; off = align_up(off + (size_t)nmat * sizeof(MatEntry));
   h->off_scal = off; off = align_up(off + (size_t)nmat * od::kScalPerMat * sizeof(float));
   h->off_info = off; off = align_up(off + (size_t)nmat * od::kInfoPerMat * sizeof(int));
   h->off_diag = off; off = align_up(off + (size_t)nmat * od::kDiagPerMat * sizeof(float));
@@ -294,6 +346,34 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     h->classes[found].batches.push_back((int)bi);
     h->classes[found].count += b.d.nb;
   }
+  // units: what steps in lockstep
+  for (size_t ci = 0; ci < h->classes.size(); ++ci) {
+    const RankClass& c = h->classes[ci];
+    const bool wide = c.r > od::kLeafRank;
+    int found = -1;
+    for (size_t u = 0; u < h->units.size() && !wide; ++u)
+      if (h->units[u].group == c.group && !h->units[u].wide_guard) found = (int)u;
+    if (found < 0) {
+      Unit u = {};
+      u.group = c.group;
+      u.wide_guard = wide;
+      h->units.push_back(u);
+      found = (int)h->units.size() - 1;
+    }
+    h->units[found].classes.push_back((int)ci);
+  }
+  for (size_t bi = 0; bi < h->batches.size(); ++bi) {
+    Batch& b = h->batches[bi];
+    for (Unit& u : h->units) {
+      bool mine = false;
+      for (int c : u.classes) mine = mine || c == b.rank_class;
+      if (!mine) continue;
+      size_t k = 0;
+      while (k < u.clusters.size() && h->batches[u.clusters[k][0]].cluster != b.cluster) ++k;
+      if (k == u.clusters.size()) u.clusters.push_back({});
+      u.clusters[k].push_back((int)bi);
+    }
+  }
   int slot_base = 0;
   for (RankClass& c : h->classes) {
     c.slot_base = slot_base;
@@ -309,44 +389,36 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     ClassDims& d = b.d;
     const RankClass& rcl = h->classes[b.rank_class];
     const int64_t m = d.m, n = d.n, r = d.r;
-    const int nt = r <= 64 ? 64 : (r <= 128 ? 128 : 256);
-    const int64_t tiles_r = (r + nt - 1) / nt;
-    // the projection's fast-precision kernel for r > 128 works on 64-row panels: as many
-    // workgroups from half the splits, hence half the partial sums to write and add up
-    const int proj_rows = (resolve_prec(*cfg) == od::PREC_F16 && od::proj_uses_flat_tiles((int)m, (int)r, d.nb)) ? 64 : 128;
-    b.splits_proj = pick_splits(((m + proj_rows - 1) / proj_rows) * tiles_r, d.nb, n, 128);
-    b.splits_back = pick_splits(((n + 127) / 128) * tiles_r, d.nb, m, 128);
-    if (resolve_prec(*cfg) == od::PREC_F16 && od::stream_kernel_eligible(d)) {
-      // one 8-wave workgroup per CU and 128 x 256 / 512 tiles
-      const int64_t tiles_c = (r + od::stream_tile_cols((int)r) - 1) / od::stream_tile_cols((int)r);
-      b.splits_proj = pick_splits_by_rounds(((m + 127) / 128) * tiles_c, d.nb, n, 256, 256);
-      b.splits_back = pick_splits_by_rounds(((n + 127) / 128) * tiles_c, d.nb, m, 256, 256);
-    }
+    const od::Prec prec = resolve_prec(*cfg);
+    auto splits_for = [&](bool back) {
+      int rows, cols, slots;
+      if (back) od::back_tiling(d, prec, &rows, &cols, &slots);
+      else od::proj_tiling(d, prec, b.peers, &rows, &cols, &slots);
+      const int64_t out = back ? n : m, k = back ? m : n;
+      const int64_t tiles = ((out + rows - 1) / rows) * ((r + cols - 1) / cols);
+      // one 8-wave workgroup per CU is scheduled in whole rounds; two smaller ones mix
+      return slots == 256 ? pick_splits_by_rounds(tiles, b.peers, k, 256, slots) : pick_splits(tiles, b.peers, k, 128);
+    };
+    b.splits_proj = splits_for(false);
+    b.splits_back = splits_for(true);
     // Gram tiles on and above the diagonal (the ones that are computed)
     const int64_t gt1 = (r + 127) / 128;
     const int64_t gt = gt1 * (gt1 + 1) / 2;
-    if (r <= 32) {
-      // one 32 x 32 tile, one thread per row: 256-row slabs (k_small_gram, k_small_first_pass)
-      b.splits_gram_p = pick_splits(1, d.nb, m, 256);
-      b.splits_gram_q = pick_splits(1, d.nb, n, 256);
-    } else {
-      // two workgroups of the Gram kernel fit one CU
-      b.splits_gram_p = pick_splits_by_rounds(gt, d.nb, m, 256, 512);
-      b.splits_gram_q = pick_splits_by_rounds(gt, d.nb, n, 256, 512);
+    for (int side = 0; side < 2; ++side) {
+      const int64_t rows = side == 0 ? m : n;
+      // r <= 32: one 32 x 32 tile, one thread per row: 256-row slabs (k_small_gram, k_small_first_pass);
+      // else two workgroups of the Gram kernel fit one CU
+      int sg = r <= 32 ? pick_splits(1, b.peers, rows, 256) : pick_splits_by_rounds(gt, b.peers, rows, 256, 512);
+      if (sg > 32) sg = 32;
+      b.splits_gram[side] = sg;
     }
-    if (b.splits_gram_p > 32) b.splits_gram_p = 32;
-    if (b.splits_gram_q > 32) b.splits_gram_q = 32;
     b.slabs = (int)((n + 31) / 32);           // row slabs of the column-norm kernels: many, so the grid fills the chip
     if (b.slabs > 256) b.slabs = 256;
     int64_t part = (int64_t)b.splits_proj * m * r;
     if ((int64_t)b.splits_back * n * r > part) part = (int64_t)b.splits_back * n * r;
-    if ((int64_t)b.splits_gram_p * r * r > part) part = (int64_t)b.splits_gram_p * r * r;
-    if ((int64_t)b.splits_gram_q * r * r > part) part = (int64_t)b.splits_gram_q * r * r;
     // r <= 32: the Gram partials of both CholeskyQR passes live side by side
-    if (r <= 32) {
-      const int64_t sg = b.splits_gram_p > b.splits_gram_q ? b.splits_gram_p : b.splits_gram_q;
-      if (2 * sg * r * r > part) part = 2 * sg * r * r;
-    }
+    for (int sg : b.splits_gram)
+      if ((int64_t)sg * r * r * (r <= 32 ? 2 : 1) > part) part = (int64_t)sg * r * r * (r <= 32 ? 2 : 1);
     if ((int64_t)b.slabs * r > part) part = (int64_t)b.slabs * r;
     // strides rounded so that every matrix slice stays 256-byte aligned
     auto rnd = [](int64_t e) { return (e + 63) / 64 * 64; };
@@ -400,128 +472,51 @@ extern "C" int orthdion_set_variant(orthdion_handle h, orthdion_variant v) {
     if ((expr) != hipSuccess) return ORTHDION_E_HIP;  \
   } while (0)
 
-// orth() of `a0` (rows x r) by CholeskyQR2 comes in pieces, so that the two r x r stages in the
-// middle (which do not depend on rows) can be launched once for every matrix of a rank:
-//   orth_gram : Gram matrix of a0, reduced into this batch's slices of the class array
-//   class_cholinv over the rank class : T1, W1
-//   orth_second_pass, class_guard, orth_result : see below.
-static int orth_gram(const Batch& b, char* ws, int rows, size_t off_a0, int64_t st_a, int splits, bool fast, int side,
-                     const float* scal, hipStream_t st) {
-  // fast precision has the sampled scale of B at hand: two-term fp16 operands (half the
-  // matrix-core work of the three-way bf16 split at 22 instead of 24 bits)
-  const int mode = fast ? od::kGramH2 : od::kGramBF3;
-  WsArr a0{reinterpret_cast<float*>(ws + off_a0), st_a};
-  WsArr part{reinterpret_cast<float*>(ws + b.off_part), b.st_part};
-  WsArr gram{reinterpret_cast<float*>(ws + b.off_gram), b.st_rr};
-  // one 32 x 32 tile: partial sums in plain fp32, left in the first half of `part` for the
-  // kernel that factors them (its own partials go to the second half)
-  if (b.d.r <= 32) {
-    OD_TRY(od::launch_small_gram(b.d.nb, rows, b.d.r, a0, part, splits, st));
-    return ORTHDION_OK;
-  }
-  // a single split is the Gram matrix itself: written straight into the class array
-  if (splits == 1) {
-    OD_TRY(od::launch_gram(b.d.nb, rows, b.d.r, a0, gram, 1, mode, st, &b.d, scal, side));
-    return ORTHDION_OK;
-  }
-  OD_TRY(od::launch_gram(b.d.nb, rows, b.d.r, a0, part, splits, mode, st, &b.d, scal, side));
-  // ordered reduction of the split partial sums on many workgroups: the factorisation runs on
-  // one workgroup per matrix and should not spend its time summing
-  OD_TRY(od::launch_reduce(b.d.nb, part, splits, (int64_t)b.d.r * b.d.r, gram, st));
-  return ORTHDION_OK;
-}
+// orth() by CholeskyQR2 comes in pieces (od_kernels.h), so that the r x r stages in its middle, which
+// do not depend on the number of rows, can be launched once for every matrix of a rank.
 
-// Ranks of one 32 x 32 tile take the first pass in a single launch (factorisation included), so
-// the class-wide Cholesky step is skipped for them.
-static bool first_pass_in_one_launch(int r) { return r <= 32; }
-
-// The rest of orth() after the first factorisation, in three pieces so that the guard in
-// the middle can be launched once for every matrix of a rank:
-//   orth_second_pass : a1 = a0 W1, Gram of a1, k_corr (T2 = I + Phi(E), Phi^T or W2, max|E|);
-//                      r > 256: the summed Gram matrix of a flagged matrix goes to the class array
-//   class_guard      : r > 256 only: Cholesky factor and inverse of I + E for every matrix of the
-//                      class whose max|E| is above kFirstOrderDeviation (T2 and W2 are overwritten)
-//   orth_result      : the correction a1 - a1 Phi(E) (fast precision) or a1 W2, for a flagged
-//                      matrix the full product a1 W2 -> a0 | callers' Q (+ fp16 copies);
-//                      r <= 256: the guard runs here, per batch (one launch: k_chol256 sums the
-//                      partials itself).
-// A matrix is flagged when its first pass left a deviation too large for the first-order form
-// (an ill-conditioned B Q or R).  Every launch of the guard returns at once for the others.
-static bool guard_is_class_wide(int r) { return r > 256; }
-
-static int orth_second_pass(const Batch& b, char* ws, int rows, size_t off_a0, size_t off_a1, int64_t st_a, int splits,
-                            size_t off_t1, size_t off_t2, int info_slot, float* scal, int* info, int exact, hipStream_t st) {
-  const int nb = b.d.nb, r = b.d.r;
-  WsArr a0{reinterpret_cast<float*>(ws + off_a0), st_a}, a1{reinterpret_cast<float*>(ws + off_a1), st_a};
-  WsArr part{reinterpret_cast<float*>(ws + b.off_part), b.st_part};
-  WsArr w{reinterpret_cast<float*>(ws + b.off_w), b.st_rr};
-  WsArr t1{reinterpret_cast<float*>(ws + off_t1), b.st_rr}, t2{reinterpret_cast<float*>(ws + off_t2), b.st_rr};
-  const HalfArr none{nullptr, 0};
-  if (first_pass_in_one_launch(r)) {
-    const WsArr part1 = part;                                   // Gram partials of a0 (orth_gram)
-    part.base += (int64_t)splits * r * r;                       // Gram partials of a1, read by the second pass
-    OD_TRY(od::launch_small_first_pass(nb, rows, r, a0, part1, splits, t1, w, a1, part, splits, info, info_slot, st));
-  } else {
-    OD_TRY(od::launch_apply(nb, rows, r, a0, w, a1, nullptr, none, none, exact, st));
-    OD_TRY(od::launch_gram(nb, rows, r, a1, part, splits, exact ? od::kGramBF3 : od::kGramH2, st, nullptr, nullptr, 2));
-  }
-  // fast precision: Phi^T as fp16 operand words lives in the r x r scratch the factorisation no
-  // longer needs; exact precision: W2 = I - Phi(E)
-  const HalfArr phit{exact ? nullptr : reinterpret_cast<uint16_t*>(ws + b.off_tmp), 2 * b.st_rr};
-  OD_TRY(od::launch_corr(nb, r, part, splits, t1, t2, w, phit, scal, 2 + info_slot, info, info_slot, st));
-  if (guard_is_class_wide(r)) {
-    const od::Pred big{scal, 2 + info_slot, od::kFirstOrderDeviation, 1};
-    WsArr gram{reinterpret_cast<float*>(ws + b.off_gram), b.st_rr};
-    OD_TRY(od::launch_reduce(nb, part, splits, (int64_t)r * r, gram, st, big));
+// Cholesky factor and inverse of the first pass for every matrix of a unit; side 0: left factor.
+// (Ranks up to 32 factor inside the first kernel of the second pass.)
+static int unit_cholinv(const orthdion_ctx* h, const Unit& u, char* ws, int side, int* info_all, hipStream_t st) {
+  for (size_t i = 0; i < u.classes.size();) {
+    od::CholJob jobs[8];
+    int n = 0;
+    for (; i < u.classes.size() && n < 8; ++i) {
+      const RankClass& c = h->classes[u.classes[i]];
+      if (c.r <= 32) continue;
+      od::CholJob& j = jobs[n++];
+      j = od::CholJob{};
+      j.nb = c.count;
+      j.r = c.r;
+      j.gram = WsArr{reinterpret_cast<float*>(ws + c.off_gram), c.st_rr};
+      j.t = WsArr{reinterpret_cast<float*>(ws + (side == 0 ? c.off_tp1 : c.off_tq1)), c.st_rr};
+      j.w = WsArr{reinterpret_cast<float*>(ws + c.off_w), c.st_rr};
+      j.tmp = WsArr{reinterpret_cast<float*>(ws + c.off_tmp), c.st_rr};
+      j.info = info_all + (size_t)c.slot_base * od::kInfoPerMat;
+      j.info_slot = side;
+      j.splits = 1;
+    }
+    OD_TRY(od::launch_cholinv(jobs, n, st));
   }
   return ORTHDION_OK;
 }
 
-// `which`: 0 = everything; 1 = only the first-order correction of the well-conditioned matrices,
-// 2 = only the full product of the flagged ones (the two halves of a step that runs the guard on
-// a second stream; fast precision and a class-wide guard only).
-static int orth_result(const Batch& b, char* ws, int rows, size_t off_a0, size_t off_a1, int64_t st_a, int splits,
-                       size_t off_t2, int info_slot, const MatPtrs* q_out, HalfArr hn, HalfArr ht, float* scal, int* info,
-                       int exact, hipStream_t st, int which = 0) {
-  const int nb = b.d.nb, r = b.d.r;
-  WsArr a0{reinterpret_cast<float*>(ws + off_a0), st_a}, a1{reinterpret_cast<float*>(ws + off_a1), st_a};
-  WsArr w{reinterpret_cast<float*>(ws + b.off_w), b.st_rr}, tmp{reinterpret_cast<float*>(ws + b.off_tmp), b.st_rr};
-  WsArr t2{reinterpret_cast<float*>(ws + off_t2), b.st_rr};
-  const od::Pred big{scal, 2 + info_slot, od::kFirstOrderDeviation, 1}, small{scal, 2 + info_slot, od::kFirstOrderDeviation, 0};
-  if (!guard_is_class_wide(r)) {
-    WsArr part{reinterpret_cast<float*>(ws + b.off_part), b.st_part};
-    if (first_pass_in_one_launch(r)) part.base += (int64_t)splits * r * r;
-    OD_TRY(od::launch_cholinv(nb, r, part, t2, w, tmp, info, info_slot, st, big, splits, (int64_t)r * r));
-  }
-  if (exact) {
-    OD_TRY(od::launch_apply(nb, rows, r, a1, w, a0, q_out, hn, ht, exact, st));
-  } else {
-    const HalfArr phit{reinterpret_cast<uint16_t*>(ws + b.off_tmp), 2 * b.st_rr};
-    if (which != 2) OD_TRY(od::launch_apply_correction(nb, rows, r, a1, phit, a0, q_out, hn, ht, st, small));
-    if (which != 1) OD_TRY(od::launch_apply(nb, rows, r, a1, w, a0, q_out, hn, ht, exact, st, big));
-  }
-  return ORTHDION_OK;
-}
-
-// Cholesky factor and inverse for every matrix of a rank class; `off_t1` names the class array
-// that receives the factors (left or right side).
-static int class_cholinv(const RankClass& c, char* ws, size_t off_t1, int info_slot, int* info_all, hipStream_t st) {
-  if (first_pass_in_one_launch(c.r)) return ORTHDION_OK;
-  WsArr gram{reinterpret_cast<float*>(ws + c.off_gram), c.st_rr};
-  WsArr w{reinterpret_cast<float*>(ws + c.off_w), c.st_rr}, tmp{reinterpret_cast<float*>(ws + c.off_tmp), c.st_rr};
-  WsArr t1{reinterpret_cast<float*>(ws + off_t1), c.st_rr};
-  OD_TRY(od::launch_cholinv(c.count, c.r, gram, t1, w, tmp, info_all + (size_t)c.slot_base * od::kInfoPerMat, info_slot, st));
-  return ORTHDION_OK;
-}
-
-// The guard of the second pass for every matrix of a rank class above 256 (see orth_second_pass).
-static int class_guard(const RankClass& c, char* ws, size_t off_t2, int info_slot, float* scal_all, int* info_all, hipStream_t st) {
-  if (!guard_is_class_wide(c.r)) return ORTHDION_OK;
-  WsArr gram{reinterpret_cast<float*>(ws + c.off_gram), c.st_rr};
-  WsArr w{reinterpret_cast<float*>(ws + c.off_w), c.st_rr}, tmp{reinterpret_cast<float*>(ws + c.off_tmp), c.st_rr};
-  WsArr t2{reinterpret_cast<float*>(ws + off_t2), c.st_rr};
-  const od::Pred big{scal_all + (size_t)c.slot_base * od::kScalPerMat, 2 + info_slot, od::kFirstOrderDeviation, 1};
-  OD_TRY(od::launch_cholinv(c.count, c.r, gram, t2, w, tmp, info_all + (size_t)c.slot_base * od::kInfoPerMat, info_slot, st, big));
+// The guard of the second pass for a class of rank above 256: Cholesky factor and inverse of I + E for
+// the matrices whose first pass left a deviation too large for the first-order form (T2 and W2 are
+// overwritten); every launch returns at once for the others.
+static int class_guard(const RankClass& c, char* ws, int side, float* scal_all, int* info_all, hipStream_t st) {
+  od::CholJob j = {};
+  j.nb = c.count;
+  j.r = c.r;
+  j.gram = WsArr{reinterpret_cast<float*>(ws + c.off_gram), c.st_rr};
+  j.t = WsArr{reinterpret_cast<float*>(ws + (side == 0 ? c.off_tp2 : c.off_tq2)), c.st_rr};
+  j.w = WsArr{reinterpret_cast<float*>(ws + c.off_w), c.st_rr};
+  j.tmp = WsArr{reinterpret_cast<float*>(ws + c.off_tmp), c.st_rr};
+  j.info = info_all + (size_t)c.slot_base * od::kInfoPerMat;
+  j.info_slot = side;
+  j.splits = 1;
+  j.pred = od::Pred{scal_all + (size_t)c.slot_base * od::kScalPerMat, 2 + side, od::kFirstOrderDeviation, 1};
+  OD_TRY(od::launch_cholinv(&j, 1, st));
   return ORTHDION_OK;
 }
 
@@ -542,13 +537,12 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
         reinterpret_cast<uintptr_t>(M[i]) % 16 || reinterpret_cast<uintptr_t>(Q[i]) % 16)
       return ORTHDION_E_MISALIGNED;
   }
-  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  const hipStream_t caller_st = reinterpret_cast<hipStream_t>(stream);
   char* ws = reinterpret_cast<char*>(workspace);
   // Launch errors are read back with hipGetLastError; drop whatever an earlier, unrelated
   // HIP call of this thread left there (e.g. a not-ready event query of the caller).
   (void)hipGetLastError();
   const od::Prec prec = resolve_prec(h->cfg);
-  const int exact = prec == od::PREC_BF3 ? 1 : 0;
   float a_coef, b_coef;
   if (h->cfg.ef == ORTHDION_EF_DION) { a_coef = 1.f; b_coef = 1.f - h->cfg.mu; }
   else if (h->cfg.ef == ORTHDION_EF_PAPER) { a_coef = h->cfg.mu; b_coef = h->cfg.mu; }
@@ -556,221 +550,169 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
 
   int* info_all = reinterpret_cast<int*>(ws + h->off_info);
   float* scal_all = reinterpret_cast<float*>(ws + h->off_scal);
-  if (prec != od::PREC_F16) {     // in fast precision the first kernel of every batch clears its own words
-    // the scale words and, right behind them in the workspace, the info words: one fill (0.f and
-    // 0 are the same bits)
-    static_assert(sizeof(float) == sizeof(int), "one fill clears both tables");
-    const int64_t words = (int64_t)((h->off_info - h->off_scal) / sizeof(int)) + (int64_t)nmat * od::kInfoPerMat;
-    OD_TRY(od::launch_fill_int(reinterpret_cast<int*>(scal_all), words, 0, st));
-  }
   h->last_ws = workspace;
   const bool diag = h->diag_on;
   h->diag_valid = diag;
   float* diag_all = reinterpret_cast<float*>(ws + h->off_diag);
   double* dacc_all = reinterpret_cast<double*>(ws + h->off_dacc);
   double* dpart_all = reinterpret_cast<double*>(ws + h->off_dpart);
-
-#define OD_PHASE_BEGIN(ph)                                                   \
-  do {                                                                       \
-    if (hipEvent_t* e_ = prof_slot(h, bi, ph, 0)) OD_TRY(hipEventRecord(*e_, st)); \
-  } while (0)
-#define OD_PHASE_END(ph)                                                     \
-  do {                                                                       \
-    if (hipEvent_t* e_ = prof_slot(h, bi, ph, 1)) OD_TRY(hipEventRecord(*e_, st)); \
-  } while (0)
-
-  // phases that are one kernel: the kernel's own start / stop time stamps
-#define OD_PHASE_KERNEL(ph)                                                  \
-  do {                                                                       \
-    hipEvent_t* e0_ = prof_slot(h, bi, ph, 0);                               \
-    hipEvent_t* e1_ = prof_slot(h, bi, ph, 1);                               \
-    if (e0_ && e1_) od::time_next_launch(*e0_, *e1_);                        \
-  } while (0)
-
-  // what every piece of a batch's work needs
-  struct BatchView {
-    MatPtrs ptrs;
-    float* scal; int* info;
-    WsArr pa, ra, part, colsq;
-    HalfArr ph, pht, rh, qh, qht;
-    double *dacc, *dpart;
-  };
   const bool fast = prec == od::PREC_F16;
-  const HalfArr none{nullptr, 0};
-  auto view_of = [&](const Batch& b, BatchView& v) {
-    std::memset(&v.ptrs, 0, sizeof(v.ptrs));
+
+  // the caller's buffers in slot order, and every batch with its workspace arrays
+  const std::unique_ptr<MatEntry[]> entries(new (std::nothrow) MatEntry[nmat]);
+  const std::unique_ptr<BatchRef[]> refs(new (std::nothrow) BatchRef[h->batches.size()]);
+  const std::unique_ptr<const BatchRef*[]> list(new (std::nothrow) const BatchRef*[h->batches.size()]);
+  if (!entries || !refs || !list) return ORTHDION_E_NO_MEMORY;
+  for (size_t bi = 0; bi < h->batches.size(); ++bi) {
+    const Batch& b = h->batches[bi];
     for (int s = 0; s < b.d.nb; ++s) {
-      int i = b.members[s];
-      v.ptrs.X[s] = X[i]; v.ptrs.G[s] = G[i]; v.ptrs.M[s] = M[i]; v.ptrs.Q[s] = Q[i];
+      const int i = b.members[s];
+      entries[b.slot_base + s] = MatEntry{X[i], G[i], M[i], Q[i]};
     }
+    auto f32 = [&](size_t off, int64_t stride) { return WsArr{reinterpret_cast<float*>(ws + off), stride}; };
+    auto f16 = [&](size_t off, int64_t stride) { return HalfArr{reinterpret_cast<uint16_t*>(ws + off), stride}; };
+    BatchRef& v = refs[bi];
+    v.d = b.d;
+    v.mats = reinterpret_cast<const MatEntry*>(ws + h->off_mats) + b.slot_base;
+    v.host_mats = entries.get() + b.slot_base;
     v.scal = scal_all + (size_t)b.slot_base * od::kScalPerMat;
     v.info = info_all + (size_t)b.slot_base * od::kInfoPerMat;
-    v.pa = WsArr{reinterpret_cast<float*>(ws + b.off_pa), b.st_p};
-    v.ra = WsArr{reinterpret_cast<float*>(ws + b.off_ra), b.st_r};
-    v.part = WsArr{reinterpret_cast<float*>(ws + b.off_part), b.st_part};
-    v.colsq = WsArr{reinterpret_cast<float*>(ws + b.off_colsq), b.st_colsq};
-    v.ph = HalfArr{reinterpret_cast<uint16_t*>(ws + b.off_ph), b.st_p};
-    v.pht = HalfArr{reinterpret_cast<uint16_t*>(ws + b.off_pht), b.st_p};
-    v.rh = HalfArr{reinterpret_cast<uint16_t*>(ws + b.off_rh), b.st_r};
-    v.qh = HalfArr{reinterpret_cast<uint16_t*>(ws + b.off_qh), b.st_r};
-    v.qht = HalfArr{reinterpret_cast<uint16_t*>(ws + b.off_qht), b.st_r};
-    v.dacc = dacc_all + (size_t)b.slot_base * od::kDaccPerMat;
-    v.dpart = dpart_all + (size_t)b.slot_base * od::kDiagBlocks * 4;
+    v.pa = f32(b.off_pa, b.st_p); v.pb = f32(b.off_pb, b.st_p);
+    v.ra = f32(b.off_ra, b.st_r); v.rb = f32(b.off_rb, b.st_r);
+    v.part = f32(b.off_part, b.st_part); v.gram = f32(b.off_gram, b.st_rr);
+    v.t1[0] = f32(b.off_tp1, b.st_rr); v.t1[1] = f32(b.off_tq1, b.st_rr);
+    v.t2[0] = f32(b.off_tp2, b.st_rr); v.t2[1] = f32(b.off_tq2, b.st_rr);
+    v.w = f32(b.off_w, b.st_rr); v.tmp = f32(b.off_tmp, b.st_rr);
+    v.colsq = f32(b.off_colsq, b.st_colsq);
+    v.ph = f16(b.off_ph, b.st_p); v.pht = f16(b.off_pht, b.st_p);
+    v.rh = f16(b.off_rh, b.st_r); v.qh = f16(b.off_qh, b.st_r); v.qht = f16(b.off_qht, b.st_r);
+    v.splits_proj = b.splits_proj; v.splits_back = b.splits_back;
+    v.splits_gram[0] = b.splits_gram[0]; v.splits_gram[1] = b.splits_gram[1];
+    v.slabs = b.slabs;
+    v.peers = b.peers;
+  }
+
+  // `covers`: how many batches (or, for the factorisations, ranks) the interval stands for; it is
+  // booked on the first of them
+#define OD_PHASE_BEGIN(ph)                                                              \
+  do {                                                                                  \
+    if (hipEvent_t* e_ = prof_slot(h, bi, ph, 0, covers)) OD_TRY(hipEventRecord(*e_, st)); \
+  } while (0)
+#define OD_PHASE_END(ph)                                                                \
+  do {                                                                                  \
+    if (hipEvent_t* e_ = prof_slot(h, bi, ph, 1, covers)) OD_TRY(hipEventRecord(*e_, st)); \
+  } while (0)
+
+  // phases of streaming kernels only: the dispatches' own start / stop time stamps
+#define OD_PHASE_KERNEL(ph)                                                             \
+  do {                                                                                  \
+    hipEvent_t* e0_ = prof_slot(h, bi, ph, 0, covers);                                  \
+    hipEvent_t* e1_ = prof_slot(h, bi, ph, 1, covers);                                  \
+    if (e0_ && e1_) od::time_next_launch(*e0_, *e1_);                                   \
+  } while (0)
+
+  hipStream_t st = caller_st;
+  // a cluster as the launchers take it
+  int bi = 0, covers = 0;
+  auto select = [&](const std::vector<int>& cluster) {
+    for (size_t k = 0; k < cluster.size(); ++k) list[k] = &refs[cluster[k]];
+    bi = cluster[0];
+    covers = (int)cluster.size();
+    return covers;
   };
 
   // Alg. 1 lines 1-2, first part: P_raw = (M + G) Q and its Gram matrix
-  auto left_head = [&](int bi) -> int {
-    const Batch& b = h->batches[bi];
-    const ClassDims& d = b.d;
-    BatchView v;
-    view_of(b, v);
-    if (diag) OD_TRY(od::launch_diag_norms(d, v.ptrs, v.dpart, st));
+  auto head = [&](const std::vector<int>& cluster) -> int {
+    const int n = select(cluster);
     OD_PHASE_BEGIN(ORTHDION_PHASE_STATS);
-    if (fast) OD_TRY(od::launch_stats(d, v.ptrs, v.scal, v.info, v.qht, st));
+    OD_TRY(od::launch_begin(list.get(), n, prec, st));
     OD_PHASE_END(ORTHDION_PHASE_STATS);
+    if (diag)
+      for (int k : cluster) OD_TRY(od::launch_diag_norms(refs[k].d, refs[k].mats, dpart_all + (size_t)h->batches[k].slot_base * od::kDiagBlocks * 4, st));
     OD_PHASE_KERNEL(ORTHDION_PHASE_PROJ);
-    // a single split is the result itself: written straight to its place, nothing to add up
-    const bool proj_direct = b.splits_proj == 1;
-    OD_TRY(od::launch_proj(d, v.ptrs, prec, v.scal, proj_direct ? v.pa : v.part, b.splits_proj, v.qht, st));
+    OD_TRY(od::launch_proj(list.get(), n, prec, st));
     OD_PHASE_BEGIN(ORTHDION_PHASE_PROJ_REDUCE);
-    if (!proj_direct) OD_TRY(od::launch_reduce(d.nb, v.part, b.splits_proj, (int64_t)d.m * d.r, v.pa, st));
+    OD_TRY(od::launch_proj_reduce(list.get(), n, st));
     OD_PHASE_END(ORTHDION_PHASE_PROJ_REDUCE);
     OD_PHASE_BEGIN(ORTHDION_PHASE_GRAM_LEFT);
-    int rc = orth_gram(b, ws, d.m, b.off_pa, b.st_p, b.splits_gram_p, fast, 0, v.scal, st);
-    if (rc != ORTHDION_OK) return rc;
+    OD_TRY(od::launch_orth_gram(list.get(), n, 0, prec, st));
     OD_PHASE_END(ORTHDION_PHASE_GRAM_LEFT);
     return ORTHDION_OK;
   };
-
-  // rest of line 2 (P = orth(P_raw)): second pass up to its deviation
-  auto left_second = [&](int bi) -> int {
-    const Batch& b = h->batches[bi];
-    BatchView v;
-    view_of(b, v);
-    OD_PHASE_BEGIN(ORTHDION_PHASE_ORTH_LEFT);
-    int rc = orth_second_pass(b, ws, b.d.m, b.off_pa, b.off_pb, b.st_p, b.splits_gram_p, b.off_tp1, b.off_tp2, 0, v.scal, v.info,
-                              exact, st);
-    if (rc != ORTHDION_OK) return rc;
-    OD_PHASE_END(ORTHDION_PHASE_ORTH_LEFT);
+  // second CholeskyQR pass of the factor of `side`, up to its deviation
+  auto second = [&](const std::vector<int>& cluster, int side) -> int {
+    const int n = select(cluster), ph = side == 0 ? ORTHDION_PHASE_ORTH_LEFT : ORTHDION_PHASE_ORTH_RIGHT;
+    OD_PHASE_BEGIN(ph);
+    OD_TRY(od::launch_orth_second(list.get(), n, side, prec, st));
+    OD_PHASE_END(ph);
     return ORTHDION_OK;
   };
-  // P itself, line 3 (R = (M + G)^T P), and the head of line 4
-  // `mode` (also for `tail`): 0 = the whole piece on `st`; with the guard on the second stream the
-  // piece is enqueued in three parts: 1 = the result of the well-conditioned matrices on `st`,
-  // 2 = the result of the flagged ones on the second stream, 3 = everything after the result
-  auto middle = [&](int bi, int mode) -> int {
-    const Batch& b = h->batches[bi];
-    const ClassDims& d = b.d;
-    BatchView v;
-    view_of(b, v);
-    int rc;
-    if (mode == 2) {
-      return orth_result(b, ws, d.m, b.off_pa, b.off_pb, b.st_p, b.splits_gram_p, b.off_tp2, 0, nullptr,
-                         fast ? v.ph : none, fast ? v.pht : none, v.scal, v.info, exact, h->side, 2);
-    }
-    if (mode != 3) {
-      OD_PHASE_BEGIN(ORTHDION_PHASE_FINISH_LEFT);
-      rc = orth_result(b, ws, d.m, b.off_pa, b.off_pb, b.st_p, b.splits_gram_p, b.off_tp2, 0, nullptr,
-                       fast ? v.ph : none, fast ? v.pht : none, v.scal, v.info, exact, st, mode);
-      if (rc != ORTHDION_OK) return rc;
-      OD_PHASE_END(ORTHDION_PHASE_FINISH_LEFT);
-      if (mode == 1) return ORTHDION_OK;
-    }
+  // its result; `which` and `on` as launch_orth_result takes them (2: the flagged matrices, on the second stream)
+  auto result = [&](const std::vector<int>& cluster, int side, int which, hipStream_t on) -> int {
+    const int n = select(cluster), ph = side == 0 ? ORTHDION_PHASE_FINISH_LEFT : ORTHDION_PHASE_FINISH_RIGHT;
+    if (which != 2) OD_PHASE_BEGIN(ph);
+    OD_TRY(od::launch_orth_guard(list.get(), n, side, on));
+    OD_TRY(od::launch_orth_result(list.get(), n, side, prec, which, on));
+    if (which != 2) OD_PHASE_END(ph);
+    return ORTHDION_OK;
+  };
+  // line 3 (R = (M + G)^T P), and the head of line 4
+  auto back = [&](const std::vector<int>& cluster) -> int {
+    const int n = select(cluster);
     OD_PHASE_KERNEL(ORTHDION_PHASE_BACK);
-    // as for the projection: a single split goes straight to its place; fast precision still
-    // needs the fp16 copy of R, made from there
-    const bool back_direct = b.splits_back == 1;
-    const bool copy_in_kernel = od::back_writes_fp16_copy(d, prec, b.splits_back);
-    OD_TRY(od::launch_back(d, v.ptrs, prec, v.scal, v.pa, back_direct ? v.ra : v.part, b.splits_back, v.pht, st, v.rh, v.info));
+    OD_TRY(od::launch_back(list.get(), n, prec, st));
     OD_PHASE_BEGIN(ORTHDION_PHASE_BACK_REDUCE);
-    if (fast && !copy_in_kernel) OD_TRY(od::launch_reduce_r(d, back_direct ? v.ra : v.part, b.splits_back, v.ra, v.rh, v.scal, v.info, st));
-    else if (!back_direct) OD_TRY(od::launch_reduce(d.nb, v.part, b.splits_back, (int64_t)d.n * d.r, v.ra, st));
+    OD_TRY(od::launch_back_reduce(list.get(), n, prec, st));
     OD_PHASE_END(ORTHDION_PHASE_BACK_REDUCE);
-    if (diag) OD_TRY(od::launch_diag_cols(d.nb, d.n, d.r, v.ra, v.part, b.slabs, v.dacc, st));
+    if (diag)
+      for (int k : cluster)
+        OD_TRY(od::launch_diag_cols(refs[k].d.nb, refs[k].d.n, refs[k].d.r, refs[k].ra, refs[k].part, refs[k].slabs,
+                                    dacc_all + (size_t)h->batches[k].slot_base * od::kDaccPerMat, st));
     if (h->cfg.variant == ORTHDION_QR) {
       OD_PHASE_BEGIN(ORTHDION_PHASE_GRAM_RIGHT);
-      rc = orth_gram(b, ws, d.n, b.off_ra, b.st_r, b.splits_gram_q, fast, 1, v.scal, st);
-      if (rc != ORTHDION_OK) return rc;
+      OD_TRY(od::launch_orth_gram(list.get(), n, 1, prec, st));
       OD_PHASE_END(ORTHDION_PHASE_GRAM_RIGHT);
     }
     return ORTHDION_OK;
   };
-
-  // rest of line 4 for the QR variant: second pass of Q = orth(R) up to its deviation
-  auto right_second = [&](int bi) -> int {
-    const Batch& b = h->batches[bi];
-    BatchView v;
-    view_of(b, v);
-    OD_PHASE_BEGIN(ORTHDION_PHASE_ORTH_RIGHT);
-    int rc = orth_second_pass(b, ws, b.d.n, b.off_ra, b.off_rb, b.st_r, b.splits_gram_q, b.off_tq1, b.off_tq2, 1, v.scal, v.info,
-                              exact, st);
-    if (rc != ORTHDION_OK) return rc;
-    OD_PHASE_END(ORTHDION_PHASE_ORTH_RIGHT);
+  // nu = sigma_1(Q_new): Gram matrix of the new right factor, then power iteration; the table's row
+  auto diagnose = [&](int k) -> int {
+    const BatchRef& v = refs[k];
+    const ClassDims& d = v.d;
+    const int slot = h->batches[k].slot_base, sg = v.splits_gram[1];
+    double* dacc = dacc_all + (size_t)slot * od::kDaccPerMat;
+    OD_TRY(od::launch_gather_q(d.nb, d.n, d.r, v.mats, v.rb, st));
+    OD_TRY(od::launch_gram_plain(d.nb, d.n, d.r, v.rb, v.part, sg, st));
+    OD_TRY(od::launch_reduce(d.nb, v.part, sg, (int64_t)d.r * d.r, v.gram, st));
+    OD_TRY(od::launch_power(d.nb, d.r, v.gram, v.tmp, v.w, v.part, dacc, st));
+    OD_TRY(od::launch_diag_final(d.nb, d.r, dpart_all + (size_t)slot * od::kDiagBlocks * 4, dacc, v.t1[1], v.t2[1],
+                                 h->cfg.variant == ORTHDION_COLNORM ? 1 : 0, diag_all + (size_t)slot * od::kDiagPerMat, st));
     return ORTHDION_OK;
   };
-
-  // rest of line 4: Q = orth(R) or ColNorm(R), written to the callers' Q (Q_prev is no longer
-  // needed); lines 5-7: parameter update and error feedback in one pass
-  auto tail = [&](int bi, int mode) -> int {
-    const Batch& b = h->batches[bi];
-    const ClassDims& d = b.d;
-    BatchView v;
-    view_of(b, v);
-    if (mode == 2) {
-      return orth_result(b, ws, d.n, b.off_ra, b.off_rb, b.st_r, b.splits_gram_q, b.off_tq2, 1, &v.ptrs,
-                         fast ? v.qh : none, none, v.scal, v.info, exact, h->side, 2);
-    }
-    if (mode != 3) {
-      OD_PHASE_BEGIN(ORTHDION_PHASE_FINISH_RIGHT);
-      if (h->cfg.variant == ORTHDION_QR) {
-        int rc = orth_result(b, ws, d.n, b.off_ra, b.off_rb, b.st_r, b.splits_gram_q, b.off_tq2, 1, &v.ptrs,
-                             fast ? v.qh : none, none, v.scal, v.info, exact, st, mode);
+  // lines 5-7: parameter update and error feedback in one pass
+  auto update = [&](const std::vector<int>& cluster) -> int {
+    const int n = select(cluster);
+    if (diag)
+      for (int k : cluster) {
+        const int rc = diagnose(k);
         if (rc != ORTHDION_OK) return rc;
-      } else {
-        OD_TRY(od::launch_colnorm(d.nb, d.n, d.r, v.ra, v.ptrs, v.part, b.slabs, v.colsq, v.scal, v.info,
-                                  fast ? v.qh : none, st));
       }
-      OD_PHASE_END(ORTHDION_PHASE_FINISH_RIGHT);
-      if (mode == 1) return ORTHDION_OK;
-    }
-    if (diag) {
-      // nu = sigma_1(Q_new): Gram matrix of the new right factor, then power iteration
-      WsArr rb{reinterpret_cast<float*>(ws + b.off_rb), b.st_r};
-      WsArr gram{reinterpret_cast<float*>(ws + b.off_gram), b.st_rr}, tmp{reinterpret_cast<float*>(ws + b.off_tmp), b.st_rr};
-      WsArr tq1{reinterpret_cast<float*>(ws + b.off_tq1), b.st_rr}, tq2{reinterpret_cast<float*>(ws + b.off_tq2), b.st_rr};
-      OD_TRY(od::launch_gather_q(d.nb, d.n, d.r, v.ptrs, rb, st));
-      OD_TRY(od::launch_gram(d.nb, d.n, d.r, rb, v.part, b.splits_gram_q, od::kGramBF3, st));
-      OD_TRY(od::launch_reduce(d.nb, v.part, b.splits_gram_q, (int64_t)d.r * d.r, gram, st));
-      WsArr w{reinterpret_cast<float*>(ws + b.off_w), b.st_rr};
-      OD_TRY(od::launch_power(d.nb, d.r, gram, tmp, w, v.part, v.dacc, st));
-      OD_TRY(od::launch_diag_final(d.nb, d.r, v.dpart, v.dacc, tq1, tq2, h->cfg.variant == ORTHDION_COLNORM ? 1 : 0,
-                                   diag_all + (size_t)b.slot_base * od::kDiagPerMat, st));
-    }
     OD_PHASE_KERNEL(ORTHDION_PHASE_EFX);
-    if (fast) OD_TRY(od::launch_efx_h(d, v.ptrs, v.scal, v.info, v.ph, v.rh, v.qh, a_coef, b_coef, h->cfg.lr, st));
-    else OD_TRY(od::launch_efx(d, v.ptrs, prec, v.scal, v.info, v.pa, v.ra, a_coef, b_coef, h->cfg.lr, st));
+    OD_TRY(od::launch_efx(list.get(), n, prec, a_coef, b_coef, h->cfg.lr, st));
     return ORTHDION_OK;
   };
 
-  // Rank class by rank class; inside a class the batches run piece by piece, so that each of
-  // the two Cholesky steps is one launch sequence over all matrices of the class.  Its time is
-  // booked on the first batch of the class.
-  const hipStream_t caller_st = st;
-  // pieces of a class between its two Cholesky steps
-  auto class_head = [&](const RankClass& c) -> int {
-    int rc;
-    for (int b2 : c.batches)
-      if ((rc = left_head(b2)) != ORTHDION_OK) return rc;
-    return ORTHDION_OK;
-  };
-  auto class_chol = [&](const RankClass& c, int side, hipStream_t on) -> int {
-    const int bi = c.batches[0];
-    st = on;
-    OD_PHASE_BEGIN(side == 0 ? ORTHDION_PHASE_CHOL_LEFT : ORTHDION_PHASE_CHOL_RIGHT);
-    int rc = class_cholinv(c, ws, side == 0 ? c.off_tp1 : c.off_tq1, side, info_all, on);
+  // Unit by unit; inside a unit the clusters run piece by piece, so that each of the two Cholesky
+  // steps is one launch sequence over all matrices of the unit.  Its time is booked on the unit's
+  // first batch.
+  auto chol = [&](const Unit& u, int side) -> int {
+    const int ph = side == 0 ? ORTHDION_PHASE_CHOL_LEFT : ORTHDION_PHASE_CHOL_RIGHT;
+    bi = u.clusters[0][0];
+    covers = (int)u.classes.size();
+    OD_PHASE_BEGIN(ph);
+    const int rc = unit_cholinv(h, u, ws, side, info_all, st);
     if (rc != ORTHDION_OK) return rc;
-    OD_PHASE_END(side == 0 ? ORTHDION_PHASE_CHOL_LEFT : ORTHDION_PHASE_CHOL_RIGHT);
-    st = caller_st;
+    OD_PHASE_END(ph);
     return ORTHDION_OK;
   };
   // Ranks above 256 in fast precision: the guard (a launch chain over the class that returns at
@@ -778,59 +720,30 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
   // the second stream beside the first-order result of the others; the streams join before
   // anything reads a factor.  (With two groups side by side the guard stays on its group's
   // stream: the other group fills the chip meanwhile.)
-  auto class_middle = [&](const RankClass& c, bool fork_guard) -> int {
+  auto finish = [&](const Unit& u, int side, bool fork_guard) -> int {
     int rc;
-    const int bi = c.batches[0];
-    for (int b2 : c.batches)
-      if ((rc = left_second(b2)) != ORTHDION_OK) return rc;
-    const bool forked = fork_guard && allow_second_stream && fast && guard_is_class_wide(c.r) && ensure_side_stream(h, st);
+    for (const auto& c : u.clusters)
+      if ((rc = second(c, side)) != ORTHDION_OK) return rc;
+    const RankClass& cls = h->classes[u.classes[0]];
+    const bool forked = fork_guard && allow_second_stream && fast && u.wide_guard && ensure_side_stream(h, st);
     if (forked) {
       OD_TRY(hipEventRecord(h->ev_fork, st));
       OD_TRY(hipStreamWaitEvent(h->side, h->ev_fork, 0));
-      if ((rc = class_guard(c, ws, c.off_tp2, 0, scal_all, info_all, h->side)) != ORTHDION_OK) return rc;
-      for (int b2 : c.batches)
-        if ((rc = middle(b2, 2)) != ORTHDION_OK) return rc;
+      if ((rc = class_guard(cls, ws, side, scal_all, info_all, h->side)) != ORTHDION_OK) return rc;
+      for (const auto& c : u.clusters)
+        if ((rc = result(c, side, 2, h->side)) != ORTHDION_OK) return rc;
       OD_TRY(hipEventRecord(h->ev_join, h->side));
-      for (int b2 : c.batches)
-        if ((rc = middle(b2, 1)) != ORTHDION_OK) return rc;
+      for (const auto& c : u.clusters)
+        if ((rc = result(c, side, 1, st)) != ORTHDION_OK) return rc;
       OD_TRY(hipStreamWaitEvent(st, h->ev_join, 0));
-      for (int b2 : c.batches)
-        if ((rc = middle(b2, 3)) != ORTHDION_OK) return rc;
-    } else {
-      OD_PHASE_BEGIN(ORTHDION_PHASE_GUARD_LEFT);
-      if ((rc = class_guard(c, ws, c.off_tp2, 0, scal_all, info_all, st)) != ORTHDION_OK) return rc;
-      OD_PHASE_END(ORTHDION_PHASE_GUARD_LEFT);
-      for (int b2 : c.batches)
-        if ((rc = middle(b2, 0)) != ORTHDION_OK) return rc;
+      return ORTHDION_OK;
     }
-    return ORTHDION_OK;
-  };
-  auto class_tail = [&](const RankClass& c, bool fork_guard) -> int {
-    int rc;
-    const int bi = c.batches[0];
-    bool forked_right = false;
-    if (h->cfg.variant == ORTHDION_QR) {
-      for (int b2 : c.batches)
-        if ((rc = right_second(b2)) != ORTHDION_OK) return rc;
-      forked_right = fork_guard && allow_second_stream && fast && guard_is_class_wide(c.r) && ensure_side_stream(h, st);
-      if (forked_right) {
-        OD_TRY(hipEventRecord(h->ev_fork, st));
-        OD_TRY(hipStreamWaitEvent(h->side, h->ev_fork, 0));
-        if ((rc = class_guard(c, ws, c.off_tq2, 1, scal_all, info_all, h->side)) != ORTHDION_OK) return rc;
-        for (int b2 : c.batches)
-          if ((rc = tail(b2, 2)) != ORTHDION_OK) return rc;
-        OD_TRY(hipEventRecord(h->ev_join, h->side));
-        for (int b2 : c.batches)
-          if ((rc = tail(b2, 1)) != ORTHDION_OK) return rc;
-        OD_TRY(hipStreamWaitEvent(st, h->ev_join, 0));
-      } else {
-        OD_PHASE_BEGIN(ORTHDION_PHASE_GUARD_RIGHT);
-        if ((rc = class_guard(c, ws, c.off_tq2, 1, scal_all, info_all, st)) != ORTHDION_OK) return rc;
-        OD_PHASE_END(ORTHDION_PHASE_GUARD_RIGHT);
-      }
-    }
-    for (int b2 : c.batches)
-      if ((rc = tail(b2, forked_right ? 3 : 0)) != ORTHDION_OK) return rc;
+    const int ph = side == 0 ? ORTHDION_PHASE_GUARD_LEFT : ORTHDION_PHASE_GUARD_RIGHT;
+    bi = u.clusters[0][0];
+    covers = (int)u.classes.size();
+    OD_PHASE_BEGIN(ph);
+    if (u.wide_guard && (rc = class_guard(cls, ws, side, scal_all, info_all, st)) != ORTHDION_OK) return rc;
+    OD_PHASE_END(ph);
     return ORTHDION_OK;
   };
 
@@ -844,18 +757,35 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     OD_TRY(hipEventRecord(h->ev_group_fork, caller_st));
     OD_TRY(hipStreamWaitEvent(h->group_stream, h->ev_group_fork, 0));
   }
-  const bool right_chol = h->cfg.variant == ORTHDION_QR;
-  for (const RankClass& c : h->classes) {
+  const bool qr = h->cfg.variant == ORTHDION_QR;
+  for (const Unit& u : h->units) {
     int rc;
-    const hipStream_t on = (side_by_side && c.group == 1) ? h->group_stream : caller_st;
-    st = on;
-    if ((rc = class_head(c)) != ORTHDION_OK) return rc;
-    if ((rc = class_chol(c, 0, on)) != ORTHDION_OK) return rc;
-    st = on;
-    if ((rc = class_middle(c, !side_by_side)) != ORTHDION_OK) return rc;
-    if (right_chol && (rc = class_chol(c, 1, on)) != ORTHDION_OK) return rc;
-    st = on;
-    if ((rc = class_tail(c, !side_by_side)) != ORTHDION_OK) return rc;
+    st = (side_by_side && u.group == 1) ? h->group_stream : caller_st;
+    // whether the results are enqueued by finish() itself (the guard on the second stream)
+    const bool forks = !side_by_side && allow_second_stream && fast && u.wide_guard && ensure_side_stream(h, st);
+    for (const auto& c : u.clusters)
+      if ((rc = head(c)) != ORTHDION_OK) return rc;
+    if ((rc = chol(u, 0)) != ORTHDION_OK) return rc;
+    if ((rc = finish(u, 0, forks)) != ORTHDION_OK) return rc;
+    for (const auto& c : u.clusters) {
+      if (!forks && (rc = result(c, 0, 0, st)) != ORTHDION_OK) return rc;
+      if ((rc = back(c)) != ORTHDION_OK) return rc;
+    }
+    if (qr) {
+      if ((rc = chol(u, 1)) != ORTHDION_OK) return rc;
+      if ((rc = finish(u, 1, forks)) != ORTHDION_OK) return rc;
+    }
+    for (const auto& c : u.clusters) {
+      if (!qr) {
+        const int n = select(c);
+        OD_PHASE_BEGIN(ORTHDION_PHASE_FINISH_RIGHT);
+        OD_TRY(od::launch_colnorm(list.get(), n, prec, st));
+        OD_PHASE_END(ORTHDION_PHASE_FINISH_RIGHT);
+      } else if (!forks && (rc = result(c, 1, 0, st)) != ORTHDION_OK) {
+        return rc;
+      }
+      if ((rc = update(c)) != ORTHDION_OK) return rc;
+    }
   }
   st = caller_st;
   if (side_by_side) {
@@ -910,7 +840,7 @@ extern "C" int orthdion_profile_end(orthdion_handle h, float* ms_per_phase, int3
           continue;
         }
         ms_per_phase[ph] += ms;
-        count_per_phase[ph] += 1;
+        count_per_phase[ph] += h->prof_recorded[idx / 2];
       }
   for (hipEvent_t e : h->prof_events)
     if (e) (void)hipEventDestroy(e);

@@ -39,7 +39,7 @@
 
 namespace od {
 
-constexpr int kCholMax = 256;          // largest block one workgroup factors
+constexpr int kCholMax = kLeafRank;    // largest block one workgroup factors
 constexpr int kCT = 32;                // tile size
 constexpr int kCNT = kCholMax / kCT;   // 8 tiles per side
 constexpr int kCTiles = kCNT * (kCNT + 1) / 2;   // 36
@@ -577,11 +577,6 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
     atomicOr(&a.info[z * kInfoPerMat + kWarnSlot], kWarnWaitExpired);
     atomicCAS(&a.info[z * kInfoPerMat + a.info_slot], 0, o + 1);
   }
-}
-
-__global__ __launch_bounds__(kCholThreads) void k_chol256(CholArgs a) {
-  extern __shared__ __align__(16) char lds_raw[];
-  chol256_block(a, blockIdx.x, lds_raw);
 }
 
 }  // namespace od

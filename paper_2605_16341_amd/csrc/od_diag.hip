@@ -44,12 +44,12 @@ OD_DEV double block_sum_256(double v, double* red) {
 // enough loads in flight for the memory system (2048 x 5632: 44 us with a 64-bit division per four
 // elements and 128 workgroups, 15 us like this: 4.8 TB/s, the rate of a large copy).
 template <bool GBF>
-__global__ __launch_bounds__(256) void k_diag_norms(ClassDims d, MatPtrs ptrs, double* dpart) {
+__global__ __launch_bounds__(256) void k_diag_norms(ClassDims d, const MatEntry* mats, double* dpart) {
   const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   double sm = 0.0, sg = 0.0, sb = 0.0;
   for (int i = (int)blockIdx.x * 4 + (tid >> 6); i < d.m; i += (int)gridDim.x * 4) {
-    const float* mp = ptrs.M[z] + (int64_t)i * d.ldm;
-    const char* gp = reinterpret_cast<const char*>(ptrs.G[z]) + (int64_t)i * d.ldg * (GBF ? 2 : 4);
+    const float* mp = mats[z].M + (int64_t)i * d.ldm;
+    const char* gp = reinterpret_cast<const char*>(mats[z].G) + (int64_t)i * d.ldg * (GBF ? 2 : 4);
 #pragma unroll 2
     for (int j = lane * 4; j < d.n; j += 256) {
       const f32x4 mv = *reinterpret_cast<const f32x4*>(mp + j);
@@ -121,9 +121,9 @@ __global__ __launch_bounds__(256) void k_diag_cols_final(int r, WsArr part, int 
 }
 
 // copy of the callers' Q (n x r, ld r) into a workspace array
-__global__ __launch_bounds__(256) void k_gather_q(int n, int r, MatPtrs ptrs, WsArr out) {
+__global__ __launch_bounds__(256) void k_gather_q(int n, int r, const MatEntry* mats, WsArr out) {
   const int z = blockIdx.y;
-  const f32x4* src = reinterpret_cast<const f32x4*>(ptrs.Q[z]);
+  const f32x4* src = reinterpret_cast<const f32x4*>(mats[z].Q);
   f32x4* dst = reinterpret_cast<f32x4*>(out.base + (int64_t)z * out.stride);
   const int64_t n4 = (int64_t)n * r / 4;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) dst[i] = src[i];
@@ -311,9 +311,9 @@ __global__ __launch_bounds__(256) void k_resize_q(const float* q_old, int64_t n,
 // ------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------
-hipError_t launch_diag_norms(const ClassDims& d, const MatPtrs& ptrs, double* dpart, hipStream_t st) {
-  if (d.g_bf16) hipLaunchKernelGGL(k_diag_norms<true>, dim3(kDiagBlocks, d.nb), dim3(256), 0, st, d, ptrs, dpart);
-  else hipLaunchKernelGGL(k_diag_norms<false>, dim3(kDiagBlocks, d.nb), dim3(256), 0, st, d, ptrs, dpart);
+hipError_t launch_diag_norms(const ClassDims& d, const MatEntry* mats, double* dpart, hipStream_t st) {
+  if (d.g_bf16) hipLaunchKernelGGL(k_diag_norms<true>, dim3(kDiagBlocks, d.nb), dim3(256), 0, st, d, mats, dpart);
+  else hipLaunchKernelGGL(k_diag_norms<false>, dim3(kDiagBlocks, d.nb), dim3(256), 0, st, d, mats, dpart);
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }
@@ -326,11 +326,11 @@ hipError_t launch_diag_cols(int nb, int n, int r, WsArr rr, WsArr part, int slab
   return hipSuccess;
 }
 
-hipError_t launch_gather_q(int nb, int n, int r, const MatPtrs& ptrs, WsArr out, hipStream_t st) {
+hipError_t launch_gather_q(int nb, int n, int r, const MatEntry* mats, WsArr out, hipStream_t st) {
   int64_t n4 = (int64_t)n * r / 4;
   int blocks = (int)((n4 + 255) / 256);
   if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(k_gather_q, dim3(blocks, nb), dim3(256), 0, st, n, r, ptrs, out);
+  hipLaunchKernelGGL(k_gather_q, dim3(blocks, nb), dim3(256), 0, st, n, r, mats, out);
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }

@@ -1,7 +1,7 @@
 // Host-callable launchers of the HIP kernels of the Orth-Dion step (defined in
 // od_kernels.hip).  Every launcher only enqueues work on `stream`; none synchronises
-// or allocates.  A launch covers the matrices of one shape class (same m, n, r),
-// `nb` of them, at most od::kMaxBatch.
+// or allocates.  A launcher takes any number of launch batches (matrices of one shape class,
+// i.e. equal m, n, r and leading dimensions); batches that need the same kernel share a launch.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -9,15 +9,17 @@
 
 namespace od {
 
-constexpr int kMaxBatchHost = 32;
-
-// Caller-owned buffers of the matrices of one shape class.
-struct MatPtrs {
-  void* X[kMaxBatchHost];
-  const void* G[kMaxBatchHost];
-  float* M[kMaxBatchHost];
-  float* Q[kMaxBatchHost];
+// Caller-owned buffers of one matrix.  The table of all matrices of a step lives in the workspace
+// (slot order); the first kernel of the step writes it from its arguments.
+struct MatEntry {
+  void* X;
+  const void* G;
+  float* M;
+  float* Q;
 };
+
+// largest rank that one workgroup factors (launch_cholinv)
+constexpr int kLeafRank = 256;
 
 enum Prec : int { PREC_F16 = 0, PREC_BF3 = 1 };   // operand format of the big contractions
 
@@ -74,105 +76,93 @@ constexpr float kMaxGramDeviation = 0.5f;
 // reciprocal condition number of the factor) that still counts as full rank
 constexpr float kMinPivotRatio = 1.0e-3f;
 
-// first kernel of a step in fast precision: clears the matrices' scale words [0..7] and flag
-// words, samples sums of squares of B (for its fp16 scale) and writes Q as pre-scaled fp16,
-// transposed [r][n]
-hipError_t launch_stats(const ClassDims& d, const MatPtrs& ptrs, float* scal, int* info, HalfArr qht, hipStream_t st);
+// One launch batch as the launchers see it: shape, the caller's buffers, its workspace arrays and
+// the choices made when the handle was created.  Choices depend on the whole matrix set (how many
+// workgroups share the chip in a launch), never on how the set is dealt into groups.
+struct BatchRef {
+  ClassDims d;
+  const MatEntry* mats;              // device table, first matrix of the batch
+  const MatEntry* host_mats;         // the same entries on the host (read while enqueuing)
+  float* scal;
+  int* info;
+  WsArr pa, pb, ra, rb, part, gram, t1[2], t2[2], w, tmp, colsq;     // t1, t2: [0] left, [1] right factor
+  HalfArr ph, pht, rh, qh, qht;
+  int splits_proj, splits_back, splits_gram[2], slabs;
+  int64_t peers;                     // matrices of this shape that would make up the work of all batches that step together with it
+  // left (P, rows m) and right (Q, rows n) side of the orthogonalisation
+  int rows(int side) const { return side == 0 ? d.m : d.n; }
+  WsArr a0(int side) const { return side == 0 ? pa : ra; }
+  WsArr a1(int side) const { return side == 0 ? pb : rb; }
+};
+typedef const BatchRef* const* BatchList;     // a list of batches; always with its length
 
-// whether launch_proj (fast precision) works on 64-row tiles for this shape class: the
-// caller sizes the number of splits accordingly
-bool proj_uses_flat_tiles(int m, int r, int nb);
-// whether launch_proj / launch_back (fast precision) take the direct-to-LDS kernel for this shape
-// class (128-row tiles, stream_tile_cols(r) columns, one workgroup per CU): the caller sizes
-// the number of splits accordingly
-bool stream_kernel_eligible(const ClassDims& d);
-int stream_tile_cols(int r);
-// P_raw partials: part[split][m][r] = (M+G)[:, k-range] * Q[k-range, :]
-hipError_t launch_proj(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal,
-                       WsArr part, int splits, HalfArr qht, hipStream_t st);
-// R partials: part[split][n][r] = (M+G)[k-range, :]^T * P[k-range, :]
-// Where back_writes_fp16_copy holds (fast precision, one split, the direct-to-LDS kernel) and
-// `rh`, `info` are given, the launch also writes R as pre-scaled fp16 and checks its range, and
-// launch_reduce_r is not needed.
-bool back_writes_fp16_copy(const ClassDims& d, Prec prec, int splits);
-hipError_t launch_back(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal,
-                       WsArr p, WsArr part, int splits, HalfArr pht, hipStream_t st, HalfArr rh = HalfArr{nullptr, 0},
-                       int* info = nullptr);
+// First kernel of a step: writes the table of the caller's buffers, clears the matrices' scale words
+// [0..7] and flag words; in fast precision also samples sums of squares of B (for its fp16 scale)
+// and writes Q as pre-scaled fp16, transposed [r][n].
+hipError_t launch_begin(BatchList b, int n, Prec prec, hipStream_t st);
+
+// the tile rows and columns of the projection / back-projection for this shape, and the workgroups
+// of its kernel that fit the chip at a time: what the number of splits is chosen from
+void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, int* rows, int* cols, int* slots);
+void back_tiling(const ClassDims& d, Prec prec, int* rows, int* cols, int* slots);
+// P_raw = (M + G) Q, split over n: partial sums in `part`, or with one split straight in `pa`
+hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st);
+// pa = sum of the projection's partials (batches with one split have nothing to add)
+hipError_t launch_proj_reduce(BatchList b, int n, hipStream_t st);
+// R = (M + G)^T P, split over m: partial sums in `part`, or with one split straight in `ra`; with
+// one split the direct-to-LDS kernel also writes R as pre-scaled fp16 and checks its range
+hipError_t launch_back(BatchList b, int n, Prec prec, hipStream_t st);
+// ra = sum of the partials; in fast precision also R as pre-scaled fp16 (rh)
+hipError_t launch_back_reduce(BatchList b, int n, Prec prec, hipStream_t st);
+
+// The orthogonalisation of P_raw (side 0) or R (side 1) by CholeskyQR2, in pieces:
+// orth_gram: Gram matrix of a0 in the batch's slices of the class array `gram` (r <= 32: partial sums
+// left in `part` for the first pass)
+hipError_t launch_orth_gram(BatchList b, int n, int side, Prec prec, hipStream_t st);
+// second pass: a1 = a0 W1, Gram of a1, T2 = I + Phi(E), Phi^T (fast) or W2 = I - Phi(E) (exact), max |E|;
+// r <= 32: with the factorisation of the first pass in front
+hipError_t launch_orth_second(BatchList b, int n, int side, Prec prec, hipStream_t st);
+// r <= 256: Cholesky factor of I + E for the matrices whose deviation is above kFirstOrderDeviation
+hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st);
+// result = a1 - a1 Phi(E) (fast), a1 W2 (exact), for a flagged matrix the full product a1 W2, to a0 or (side 1)
+// the callers' Q, with the fp16 copies of fast precision.  `which`: 0 everything, 1 only the
+// first-order correction of the well-conditioned matrices, 2 only the full product of the flagged ones.
+hipError_t launch_orth_result(BatchList b, int n, int side, Prec prec, int which, hipStream_t st);
+
+// Gram partials of a plain array: part[split][r][r] = A^T A over a row range, six-product operands
+hipError_t launch_gram_plain(int nb, int rows, int r, WsArr a, WsArr part, int splits, hipStream_t st);
 // out[i] = sum_s part[s * count + i], i < count, per matrix
 hipError_t launch_reduce(int nb, WsArr part, int splits, int64_t count, WsArr out, hipStream_t st, Pred pred = Pred{nullptr, 0, 0.f, 0});
-// the same for R (n x r), also written as pre-scaled fp16 [n][r]; with one split `part` may be
-// `out` itself (the back-projection wrote R in place): then only the fp16 copy is written
-hipError_t launch_reduce_r(const ClassDims& d, WsArr part, int splits, WsArr out, HalfArr rh, const float* scal, int* info, hipStream_t st);
-
-// Gram partials: part[split][r][r] = A[k-range, :]^T A[k-range, :], A is rows x r (ld r)
-// Operand format (`mode`): kGramBF2 / kGramBF3 two- / three-way split bf16 (3 / 6 products,
-// 16 / 24 bits), kGramH2 two-term scaled fp16 (3 products, 22 bits).  kGramH2 needs the
-// operand's scale: `side` 0 = P_raw, 1 = R (scale derived from the sampled scale of B in
-// `scal`, shape in `d`), 2 = a nearly orthonormal factor (fixed scale, d and scal unused).
-enum : int { kGramBF2 = 0, kGramBF3 = 1, kGramH2 = 2 };
-hipError_t launch_gram(int nb, int rows, int r, WsArr a, WsArr part, int splits, int mode, hipStream_t st,
-                       const ClassDims* d = nullptr, const float* scal = nullptr, int side = -1);
-// out = A * W, A rows x r, W r x r upper triangular (both ld r); the result goes to the
-// callers' Q buffers when q_ptrs is given, else to the workspace array `out`.
-// With hn.base / ht.base non-null the result is also stored as fp16 scaled by 2^10, in
-// natural [rows][r] and transposed [r][rows] layout.
-hipError_t launch_apply(int nb, int rows, int r, WsArr a, WsArr w, WsArr out, const MatPtrs* q_ptrs, HalfArr hn,
-                        HalfArr ht, int exact, hipStream_t st, Pred pred = Pred{nullptr, 0, 0.f, 0});
-// out = A - A * Phi with Phi upper triangular and small (the first-order second pass of
-// CholeskyQR2): A enters in fp32, the correction is a single fp16 product.  `phit` is Phi^T as
-// fp16 scaled by 2^13, [r][r] per matrix (written by launch_corr).  Outputs as above.
-hipError_t launch_apply_correction(int nb, int rows, int r, WsArr a, HalfArr phit, WsArr out, const MatPtrs* q_ptrs,
-                                   HalfArr hn, HalfArr ht, hipStream_t st, Pred pred = Pred{nullptr, 0, 0.f, 0});
 
 // Cholesky factor and its inverse of the SPD r x r matrices `gram` (ld r): gram = T^T T,
 // W = T^-1, both upper triangular with zeros below the diagonal.  The matrices need not belong
 // to one shape class: the work depends on r only, so one call serves every matrix of that
-// rank.  For r <= 256 one workgroup per matrix does everything; above, the factorisation is
-// blocked, `gram` is destroyed and `tmp` is r x r scratch.  A non-positive or non-finite pivot
-// writes its 1-based column to info[mat * kInfoPerMat + info_slot] (first failure wins); the
-// factors of such a matrix are unspecified (they may hold NaN).
-// With `splits` > 1 (r <= 256 only) `gram` holds that many partial sums per matrix, `split_stride`
-// elements apart, which the factorisation adds up itself.
-hipError_t launch_cholinv(int nb, int r, WsArr gram, WsArr t, WsArr w, WsArr tmp, int* info, int info_slot,
-                          hipStream_t st, Pred pred = Pred{nullptr, 0, 0.f, 0}, int splits = 1, int64_t split_stride = 0);
+// rank (`nb` of them).  For r <= 256 one workgroup per matrix does everything, and jobs of
+// different ranks share a launch; above, the factorisation is blocked, `gram` is destroyed and
+// `tmp` is r x r scratch.  A non-positive or non-finite pivot writes its 1-based column to
+// info[mat * kInfoPerMat + info_slot] (first failure wins); the factors of such a matrix are
+// unspecified (they may hold NaN).  With `splits` > 1 (r <= 256 only) `gram` holds that many partial
+// sums per matrix, `split_stride` elements apart, which the factorisation adds up itself.
+struct CholJob {
+  int nb, r;
+  WsArr gram, t, w, tmp;
+  int* info;
+  int info_slot;
+  Pred pred;
+  int splits;
+  int64_t split_stride;
+};
+hipError_t launch_cholinv(const CholJob* jobs, int njobs, hipStream_t st);
 
-// r <= 32: Cholesky factor and inverse of `gram`, A1 = A0 W1 and the Gram partials of A1
-// (`splits` of them, r x r each, in `part`) in one launch; T1 and W1 are written as by
-// launch_cholinv, a bad pivot is reported the same way.
-// `gram` holds `gram_splits` partial sums per matrix, r * r elements apart (launch_small_gram).
-hipError_t launch_small_first_pass(int nb, int rows, int r, WsArr a0, WsArr gram, int gram_splits, WsArr t1, WsArr w1, WsArr a1,
-                                   WsArr part, int splits, int* info, int info_slot, hipStream_t st);
-// r <= 32: Gram partials of A0 in plain fp32, part[split][r][r]
-hipError_t launch_small_gram(int nb, int rows, int r, WsArr a0, WsArr part, int splits, hipStream_t st);
-
-// First-order second pass: from the Gram partials of a nearly orthonormal matrix writes
-// T2 = I + Phi(E), and either W2 = I - Phi(E) (fp32) or, with phit.base non-null, Phi(E)^T as
-// fp16 scaled by 2^13 ([r][r], stride phit.stride) instead; max |E| into scal[mat][scal_slot]
-// (must be zeroed); a deviation above kMaxGramDeviation (or NaN) is a breakdown:
-// info[mat][info_slot] = r unless already set.
-// Also reads the diagonal of the first pass's factor `t1`: a ratio of its smallest to its
-// largest entry below kMinPivotRatio reports the matrix as numerically rank deficient.
-hipError_t launch_corr(int nb, int r, WsArr part, int splits, WsArr t1, WsArr t2, WsArr w2, HalfArr phit, float* scal,
-                       int scal_slot, int* info, int info_slot, hipStream_t st);
-
-// scal[mat][1] = power-of-two scale for R from trace(gram) = ||R||_F^2 (rows n, cols r)
-hipError_t launch_scale_from_trace(int nb, int n, int r, WsArr gram, float* scal, hipStream_t st);
-
-// ColNorm: Q[:, c] = R[:, c] / ||R[:, c]||; also writes the scale of R.  `part` holds
-// slabs x r partial sums per matrix, `colsq` r reciprocal lengths per matrix.
-hipError_t launch_colnorm(int nb, int n, int r, WsArr rr, const MatPtrs& ptrs, WsArr part, int slabs, WsArr colsq,
-                          float* scal, int* info, HalfArr qh, hipStream_t st);
+// ColNorm: Q[:, c] = R[:, c] / ||R[:, c]||; `part` holds slabs x r partial sums per matrix, `colsq` r
+// reciprocal lengths per matrix.
+hipError_t launch_colnorm(BatchList b, int n, Prec prec, hipStream_t st);
 
 // M_new = a (M+G) - b P R^T ;  X_new = X - lr P Q^T   (one pass over M, G, X)
 // A matrix whose info words report a breakdown keeps its X and gets M_new = a (M + G): its
-// factors are unspecified and must not reach the caller's state.
-hipError_t launch_efx(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal, const int* info, WsArr p,
-                      WsArr rr, float a_coef, float b_coef, float lr, hipStream_t st);
-
-// the same pass from the pre-scaled fp16 factors (fast precision); also checks every entry of
-// B against its sampled fp16 scale and sets the warning bits of `info`
-hipError_t launch_efx_h(const ClassDims& d, const MatPtrs& ptrs, const float* scal, int* info, HalfArr ph, HalfArr rh,
-                        HalfArr qh, float a_coef, float b_coef, float lr, hipStream_t st);
+// factors are unspecified and must not reach the caller's state.  Fast precision also checks every
+// entry of B against its sampled fp16 scale and sets the warning bits of `info`.
+hipError_t launch_efx(BatchList b, int n, Prec prec, float a_coef, float b_coef, float lr, hipStream_t st);
 
 // ---- optional diagnostics (od_diag.hip) ----
 constexpr int kDiagPerMat = 8;     // floats reported per matrix
@@ -181,11 +171,11 @@ constexpr int kDaccPerMat = 8;     // fp64 accumulators per matrix: [3] ||R||^2,
 constexpr int kDiagBlocks = 512;   // workgroups (partial triples of 4 doubles) per matrix of the norm pass
 
 // dpart[mat][kDiagBlocks][4] = partial sums of squares of M, G, M + G
-hipError_t launch_diag_norms(const ClassDims& d, const MatPtrs& ptrs, double* dpart, hipStream_t st);
+hipError_t launch_diag_norms(const ClassDims& d, const MatEntry* mats, double* dpart, hipStream_t st);
 // column lengths of R (n x r, ld r) -> dacc[mat][3..5]; `part` needs slabs * r floats per matrix
 hipError_t launch_diag_cols(int nb, int n, int r, WsArr rr, WsArr part, int slabs, double* dacc, hipStream_t st);
 // out[mat] = callers' Q (n x r)
-hipError_t launch_gather_q(int nb, int n, int r, const MatPtrs& ptrs, WsArr out, hipStream_t st);
+hipError_t launch_gather_q(int nb, int n, int r, const MatEntry* mats, WsArr out, hipStream_t st);
 // dacc[mat][7] = largest eigenvalue of the symmetric PSD r x r matrix `gram` by power iteration with
 // squared powers; tmp1, tmp2: r x r scratch per matrix, xbuf: 2 r floats per matrix (used for r > 512)
 hipError_t launch_power(int nb, int r, WsArr gram, WsArr tmp1, WsArr tmp2, WsArr xbuf, double* dacc, hipStream_t st);
@@ -195,11 +185,8 @@ hipError_t launch_diag_final(int nb, int r, const double* dpart, const double* d
 // q_new (n x r_new) = leading min(r_old, r_new) columns of q_old, then columns of pad (n x (r_new - r_old))
 hipError_t launch_resize_q(const float* q_old, int64_t n, int r_old, float* q_new, int r_new, const float* pad, hipStream_t st);
 
-// The next launch_proj / launch_back / launch_efx / launch_efx_h of this thread records the
-// start and stop time stamps of its kernel in the two events (one shot).
+// The next launch_proj / launch_back / launch_efx of this thread records the start time stamp of its
+// first and the stop time stamp of its last kernel in the two events (one shot).
 void time_next_launch(hipEvent_t start, hipEvent_t stop);
-
-hipError_t launch_fill_int(int* p, int64_t count, int value, hipStream_t st);
-hipError_t launch_fill_f32(float* p, int64_t count, float value, hipStream_t st);
 
 }  // namespace od

@@ -7,17 +7,76 @@
 
 #include <hip/hip_ext.h>
 
-#include <cstdio>
-#include <cstdlib>
-#include <cstring>
-
 #include "od_chol.h"
 #include "od_dma.h"
 #include "od_gemm.h"
 
 namespace od {
 
-static_assert(kMaxBatchHost == kMaxBatch, "batch limit");
+// ------------------------------------------------------------------------------------
+// One launch for several batches.  A step over matrices of different shapes is a chain of short
+// kernels, each a few microseconds of launch and latency; batches that take the same kernel share
+// its launch, one segment of the grid each (five small matrices of four shapes and ranks: 503 -> 250 us;
+// 126 matrices of three shapes, r = 192: 1950 -> 1715 us).
+// The grid is one-dimensional; a segment starts at a multiple of 8 workgroups, so that the XCD a
+// workgroup lands on (round robin by its index) follows from its index in the segment.
+// A launch of a single segment takes its arguments as One<A> and an ordinary three-dimensional
+// grid: indexing a table of segments costs a second round of argument loads before a workgroup can
+// start (0.4 us per kernel in a chain of short ones).
+// ------------------------------------------------------------------------------------
+constexpr int kMaxSeg = 8;
+struct SegGrid { int x, y, z; };              // the segment's own grid, x fastest
+template <class A>
+struct Segs {
+  int n;
+  int first[kMaxSeg];                         // first workgroup of segment i
+  SegGrid grid[kMaxSeg];
+  A seg[kMaxSeg];
+};
+template <class A>
+struct One {
+  A seg[1];
+};
+struct SegBlock {
+  int flat, x, y, z;                          // position in the segment
+  SegGrid grid;
+};
+// The segment of this workgroup, or -1 for the padding between segments.
+template <class A>
+OD_DEV int seg_locate(const Segs<A>& g, SegBlock& b) {
+  const int bid = (int)blockIdx.x;
+  int s = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxSeg; ++i)
+    if (i < g.n && bid >= g.first[i]) s = i;
+  b.grid = g.grid[s];
+  b.flat = bid - g.first[s];
+  const int plane = b.grid.x * b.grid.y;
+  if (b.flat >= plane * b.grid.z) return -1;
+  b.z = 0;
+  int rest = b.flat;
+  if (b.grid.z > 1) { b.z = rest / plane; rest -= b.z * plane; }
+  b.y = 0;
+  if (b.grid.y > 1) { b.y = rest / b.grid.x; rest -= b.y * b.grid.x; }
+  b.x = rest;
+  return s;
+}
+template <class A>
+OD_DEV int seg_locate(const One<A>&, SegBlock& b) {
+  b.grid = SegGrid{(int)gridDim.x, (int)gridDim.y, (int)gridDim.z};
+  b.x = (int)blockIdx.x;
+  b.y = (int)blockIdx.y;
+  b.z = (int)blockIdx.z;
+  b.flat = b.x + b.grid.x * (b.y + b.grid.y * b.z);
+  return 0;
+}
+#define OD_SEGMENT(Args)                      \
+  SegBlock blk;                               \
+  const int seg_ = seg_locate(segs, blk);     \
+  if (seg_ < 0) return;                       \
+  const Args& a_ = segs.seg[seg_]
+// The caller's buffers of matrix z: from the table, or from the arguments when the batch has one matrix
+#define OD_MATRIX(z) (a_.d.nb == 1 ? a_.only : a_.mats[z])
 
 // ------------------------------------------------------------------------------------
 // tile shapes
@@ -47,10 +106,10 @@ OD_DEV int split_begin(int K, int splits, int KT, int s, int* kend) {
 }
 
 template <class GSrc>
-OD_DEV SrcSum<GSrc> make_b_source(const ClassDims& d, const MatPtrs& ptrs, int z) {
+OD_DEV SrcSum<GSrc> make_b_source(const ClassDims& d, const MatEntry& e) {
   SrcSum<GSrc> s;
-  s.m = SrcF32{ptrs.M[z], d.m, d.n, d.ldm};
-  s.g = GSrc{reinterpret_cast<decltype(GSrc::p)>(ptrs.G[z]), d.m, d.n, d.ldg};
+  s.m = SrcF32{e.M, d.m, d.n, d.ldm};
+  s.g = GSrc{reinterpret_cast<decltype(GSrc::p)>(e.G), d.m, d.n, d.ldg};
   return s;
 }
 
@@ -65,15 +124,15 @@ OD_DEV float pow2_scale_for_rms(float ms) {
 constexpr int kStatRows = 32;      // sampled rows per matrix, one workgroup each
 
 template <class GSrc>
-OD_DEV void stats_block(const ClassDims& d, const MatPtrs& ptrs, float* scal, int z) {
+OD_DEV void stats_block(const ClassDims& d, const MatEntry& e, float* scal, int z, int row_index) {
   const int tid = threadIdx.x;
-  SrcSum<GSrc> b = make_b_source<GSrc>(d, ptrs, z);
+  SrcSum<GSrc> b = make_b_source<GSrc>(d, e);
   const int nrows = d.m < kStatRows ? d.m : kStatRows;
   float acc = 0.f;
   const int groups = d.n / 8;
-  if ((int)blockIdx.x < nrows)
+  if (row_index < nrows)
   for (int idx = tid; idx < groups; idx += 256) {
-    int s = blockIdx.x, c = idx * 8;
+    int s = row_index, c = idx * 8;
     int row = (int)(((int64_t)s * d.m) / nrows);
     float x[8];
     SrcSum<GSrc>::unpack8(b.load8(row, c), x);
@@ -87,15 +146,14 @@ OD_DEV void stats_block(const ClassDims& d, const MatPtrs& ptrs, float* scal, in
     if (tid < w) red[tid] += red[tid + w];
     __syncthreads();
   }
-  if (tid == 0) scal[z * kScalPerMat + kScalSample + blockIdx.x] = red[0];
+  if (tid == 0) scal[z * kScalPerMat + kScalSample + row_index] = red[0];
 }
 
 // Q (n x r fp32, the caller's state) -> pre-scaled fp16, transposed to [r][n]
-OD_DEV void prep_q_block(const ClassDims& d, const MatPtrs& ptrs, HalfArr qht, int z, int bx, int by) {
+OD_DEV void prep_q_block(const ClassDims& d, const float* q, HalfArr qht, int z, int bx, int by) {
   __shared__ uint16_t tile[64][66];
   const int tid = threadIdx.x;
   const int k0 = bx * 64, c0 = by * 64;       // k over n, c over r
-  const float* q = ptrs.Q[z];
   uint16_t* out = qht.base + (int64_t)z * qht.stride;
   for (int idx = tid; idx < 64 * 16; idx += 256) {            // 64 rows (k) x 16 groups of 4 columns
     const int kk = idx / 16, cg = (idx % 16) * 4;
@@ -118,21 +176,38 @@ OD_DEV void prep_q_block(const ClassDims& d, const MatPtrs& ptrs, HalfArr qht, i
   }
 }
 
-// First kernel of a step in fast precision, one launch for three small jobs: workgroups
-// 0 .. kStatRows-1 of a matrix sample the scale of B (the first of them also clears the
-// matrix's flag and scale words), the others convert Q.
-template <class GSrc>
-__global__ __launch_bounds__(256) void k_prologue(ClassDims d, MatPtrs ptrs, float* scal, int* info, HalfArr qht) {
-  const int z = blockIdx.y, bx = blockIdx.x;
-  if (bx < kStatRows) {
-    if (bx == 0) {
-      if (threadIdx.x < kScalSample) scal[z * kScalPerMat + threadIdx.x] = 0.f;
-      if (threadIdx.x < kInfoPerMat) info[z * kInfoPerMat + threadIdx.x] = 0;
+// First kernel of a step.  The caller's buffers arrive as kernel arguments, kMatChunk matrices at a
+// time, and go to the table in the workspace that every later kernel reads (those can then take any
+// number of matrices).  Workgroup 0 of a matrix writes its entry and clears its flag and scale words;
+// in fast precision workgroups 0 .. kStatRows-1 also sample the scale of B and the others convert Q.
+constexpr int kMatChunk = 64;
+struct BeginArgs {
+  ClassDims d;
+  MatEntry* table;      // entries of this segment's matrices
+  int chunk0;           // first of them in the launch's chunk
+  float* scal;
+  int* info;
+  HalfArr qht;
+};
+struct MatChunk { MatEntry e[kMatChunk]; };
+
+template <class GSrc, bool FAST, class SegsT>
+__global__ __launch_bounds__(256) void k_begin(SegsT segs, MatChunk chunk) {
+  OD_SEGMENT(BeginArgs);
+  const int z = blk.z, bx = blk.x;
+  const MatEntry e = chunk.e[a_.chunk0 + z];
+  if (bx == 0) {
+    if (threadIdx.x == 0) a_.table[z] = e;
+    if (threadIdx.x < kScalSample) a_.scal[z * kScalPerMat + threadIdx.x] = 0.f;
+    if (threadIdx.x < kInfoPerMat) a_.info[z * kInfoPerMat + threadIdx.x] = 0;
+  }
+  if constexpr (FAST) {
+    if (bx < kStatRows) {
+      stats_block<GSrc>(a_.d, e, a_.scal, z, bx);
+    } else {
+      const int t = bx - kStatRows, tiles_k = (a_.d.n + 63) / 64;
+      prep_q_block(a_.d, e.Q, a_.qht, z, t % tiles_k, t / tiles_k);
     }
-    stats_block<GSrc>(d, ptrs, scal, z);
-  } else {
-    const int t = bx - kStatRows, tiles_k = (d.n + 63) / 64;
-    prep_q_block(d, ptrs, qht, z, t % tiles_k, t / tiles_k);
   }
 }
 
@@ -163,16 +238,35 @@ OD_DEV float r_scale(const ClassDims& d, const float* scal, int z) {
 template <class T, int PF>
 constexpr int min_waves_per_simd() { return ((PF > 1 && T::FM * T::FN >= 8) || T::FM * T::FN >= 16) ? 1 : 2; }
 
-template <class T, class Num, class GSrc, int PF>
-__global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_proj(ClassDims d, MatPtrs ptrs, const float* scal, WsArr part, int splits, HalfArr qht, int rotate) {
+// Arguments of the projection and the back-projection (one segment).
+struct StreamArgs {
+  ClassDims d;
+  const MatEntry* mats;
+  MatEntry only;        // the one matrix of a batch of one
+  const float* scal;
+  int* info;
+  WsArr factor;         // back-projection, exact precision: P in fp32
+  HalfArr fh;           // fast precision: the factor operand as fp16, [r][contracted dimension]
+  WsArr part;
+  HalfArr rh;           // direct-to-LDS back-projection with one split: fp16 copy of R
+  int splits, rotate;
+};
+
+template <class T, class Num, class GSrc, int PF, class SegsT>
+__global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_proj(SegsT segs) {
   extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(StreamArgs);
+  const ClassDims& d = a_.d;
+  const float* scal = a_.scal;
+  const int splits = a_.splits, rotate = a_.rotate;
   const int tiles_n = (d.r + T::NT - 1) / T::NT;
   // the column tiles of one row panel read the same part of B: keep them on one XCD
-  const int bid = tiles_n > 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int bid = tiles_n > 1 ? xcd_contiguous(blk.x, blk.grid.x) : blk.x;
   const int tn = bid % tiles_n, tm = bid / tiles_n;
-  const int split = blockIdx.y, z = blockIdx.z;
-  SrcSum<GSrc> a = make_b_source<GSrc>(d, ptrs, z);
-  SrcF32 b{ptrs.Q[z], d.n, d.r, d.r};
+  const int split = blk.y, z = blk.z;
+  const MatEntry mat = OD_MATRIX(z);
+  SrcSum<GSrc> a = make_b_source<GSrc>(d, mat);
+  SrcF32 b{mat.Q, d.n, d.r, d.r};
   int kend;
   const int kbeg = split_begin(d.n, splits, T::KT, split, &kend);
   const float sa = Num::F16 ? b_scale(d, scal, z) : 1.f;
@@ -181,7 +275,7 @@ __global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_p
   zero_acc<T>(acc);
   if constexpr (Num::F16) {
     // Q as pre-scaled fp16, transposed to [r][n] so that k is contiguous
-    SrcH16 bh{qht.base + (int64_t)z * qht.stride, d.r, d.n, d.n};
+    SrcH16 bh{a_.fh.base + (int64_t)z * a_.fh.stride, d.r, d.n, d.n};
     // Row panels of one matrix read the same columns of B at the same time, and with a row
     // stride that is a multiple of the memory-channel interleave they all land on the same
     // channels: start every panel at a different k step then.
@@ -193,7 +287,7 @@ __global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_p
     gemm_mainloop<T, Num, KC, SrcSum<GSrc>, KS, SrcF32>(a, b, tm * T::MT, tn * T::NT, kbeg, kend, sa, sb, lds, acc);
   }
   const float inv = 1.f / (sa * sb);
-  float* out = part.base + (int64_t)z * part.stride + (int64_t)split * d.m * d.r;
+  float* out = a_.part.base + (int64_t)z * a_.part.stride + (int64_t)split * d.m * d.r;
   for_each_acc<T>(acc, tm * T::MT, tn * T::NT, [&](int row, int col, float v) {
     if (row < d.m && col < d.r) out[(int64_t)row * d.r + col] = v * inv;
   });
@@ -202,16 +296,21 @@ __global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_p
 // ------------------------------------------------------------------------------------
 // R = B^T P  (split over m)                                         Alg. 1 line 3
 // ------------------------------------------------------------------------------------
-template <class T, class Num, class GSrc, int PF>
-__global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_back(ClassDims d, MatPtrs ptrs, const float* scal, WsArr p, WsArr part, int splits, HalfArr pht) {
+template <class T, class Num, class GSrc, int PF, class SegsT>
+__global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_back(SegsT segs) {
   extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(StreamArgs);
+  const ClassDims& d = a_.d;
+  const float* scal = a_.scal;
+  const int splits = a_.splits;
   const int tiles_n = (d.r + T::NT - 1) / T::NT;
   // as in the projection: the column tiles of one panel of B share an XCD's L2
-  const int bid = tiles_n > 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int bid = tiles_n > 1 ? xcd_contiguous(blk.x, blk.grid.x) : blk.x;
   const int tn = bid % tiles_n, tm = bid / tiles_n;
-  const int split = blockIdx.y, z = blockIdx.z;
-  SrcSum<GSrc> a = make_b_source<GSrc>(d, ptrs, z);      // read as [k = row i][operand row = column j]
-  SrcF32 b{p.base + (int64_t)z * p.stride, d.m, d.r, d.r};
+  const int split = blk.y, z = blk.z;
+  const MatEntry mat = OD_MATRIX(z);
+  SrcSum<GSrc> a = make_b_source<GSrc>(d, mat);           // read as [k = row i][operand row = column j]
+  SrcF32 b{a_.factor.base + (int64_t)z * a_.factor.stride, d.m, d.r, d.r};
   int kend;
   const int kbeg = split_begin(d.m, splits, T::KT, split, &kend);
   const float sa = Num::F16 ? b_scale(d, scal, z) : 1.f;
@@ -219,7 +318,7 @@ __global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_b
   f32x16 acc[T::FM][T::FN];
   zero_acc<T>(acc);
   if constexpr (Num::F16) {
-    SrcH16 bh{pht.base + (int64_t)z * pht.stride, d.r, d.m, d.m};      // P^T as fp16, [r][m]
+    SrcH16 bh{a_.fh.base + (int64_t)z * a_.fh.stride, d.r, d.m, d.m};  // P^T as fp16, [r][m]
     if constexpr (PF > 1)
       gemm_mainloop_deep<T, Num, KS, SrcSum<GSrc>, KC, SrcH16, PF>(a, bh, tm * T::MT, tn * T::NT, kbeg, kend, sa, sb, lds, acc);
     else
@@ -228,7 +327,7 @@ __global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_b
     gemm_mainloop<T, Num, KS, SrcSum<GSrc>, KS, SrcF32>(a, b, tm * T::MT, tn * T::NT, kbeg, kend, sa, sb, lds, acc);
   }
   const float inv = 1.f / (sa * sb);
-  float* out = part.base + (int64_t)z * part.stride + (int64_t)split * d.n * d.r;
+  float* out = a_.part.base + (int64_t)z * a_.part.stride + (int64_t)split * d.n * d.r;
   for_each_acc<T>(acc, tm * T::MT, tn * T::NT, [&](int row, int col, float v) {
     if (row < d.n && col < d.r) out[(int64_t)row * d.r + col] = v * inv;
   });
@@ -237,13 +336,22 @@ __global__ __launch_bounds__(T::THREADS, (min_waves_per_simd<T, PF>())) void k_b
 // ------------------------------------------------------------------------------------
 // deterministic second stage of the split contractions
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_reduce(WsArr part, int splits, int64_t count, WsArr out, Pred pred) {
-  const int z = blockIdx.y;
-  if (!pred_on(pred, z)) return;
-  const float* src = part.base + (int64_t)z * part.stride;
-  float* dst = out.base + (int64_t)z * out.stride;
+struct ReduceArgs {
+  WsArr part, out;
+  int64_t count;
+  int splits;
+  Pred pred;
+};
+template <class SegsT>
+__global__ __launch_bounds__(256) void k_reduce(SegsT segs) {
+  OD_SEGMENT(ReduceArgs);
+  const int z = blk.z, splits = a_.splits;
+  if (!pred_on(a_.pred, z)) return;
+  const int64_t count = a_.count;
+  const float* src = a_.part.base + (int64_t)z * a_.part.stride;
+  float* dst = a_.out.base + (int64_t)z * a_.out.stride;
   const int64_t n4 = count / 4;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blk.x * 256 + threadIdx.x; i < n4; i += (int64_t)blk.grid.x * 256) {
     f32x4 s = reinterpret_cast<const f32x4*>(src)[i];
 #pragma unroll 8
     for (int k = 1; k < splits; ++k) {       // unrolled: the loads of eight partials are in flight together
@@ -255,15 +363,27 @@ __global__ __launch_bounds__(256) void k_reduce(WsArr part, int splits, int64_t 
 }
 
 // the same for R, which is also stored as pre-scaled fp16 for the error-feedback kernel
-__global__ __launch_bounds__(256) void k_reduce_r(ClassDims d, WsArr part, int splits, WsArr out, HalfArr rh, const float* scal, int* info) {
-  const int z = blockIdx.y;
-  const float* src = part.base + (int64_t)z * part.stride;
-  float* dst = out.base + (int64_t)z * out.stride;
-  uint16_t* dh = rh.base + (int64_t)z * rh.stride;
+struct ReduceRArgs {
+  ClassDims d;
+  WsArr part, out;
+  int splits;
+  HalfArr rh;
+  const float* scal;
+  int* info;
+};
+template <class SegsT>
+__global__ __launch_bounds__(256) void k_reduce_r(SegsT segs) {
+  OD_SEGMENT(ReduceRArgs);
+  const int z = blk.z, splits = a_.splits;
+  const ClassDims& d = a_.d;
+  int* info = a_.info;
+  const float* src = a_.part.base + (int64_t)z * a_.part.stride;
+  float* dst = a_.out.base + (int64_t)z * a_.out.stride;
+  uint16_t* dh = a_.rh.base + (int64_t)z * a_.rh.stride;
   const int64_t count = (int64_t)d.n * d.r, n4 = count / 4;
-  const float sr = r_scale(d, scal, z);
+  const float sr = r_scale(d, a_.scal, z);
   float rmax = 0.f;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blk.x * 256 + threadIdx.x; i < n4; i += (int64_t)blk.grid.x * 256) {
     f32x4 s = reinterpret_cast<const f32x4*>(src)[i];
 #pragma unroll 8
     for (int k = 1; k < splits; ++k) s += reinterpret_cast<const f32x4*>(src + (int64_t)k * count)[i];
@@ -292,10 +412,18 @@ OD_DEV float gram_operand_scale(const ClassDims& d, const float* scal, int side,
   return ldexpf(sb, 6 - ilogbf(ratio) / 2);
 }
 
-template <class T, class Num>
-__global__ __launch_bounds__(T::THREADS) void k_gram(int rows, int r, WsArr a, WsArr part, int splits, ClassDims d, const float* scal, int side) {
+struct GramArgs {
+  ClassDims d;            // for the operand scale of sides 0 and 1
+  const float* scal;
+  int rows, r, splits, side;
+  WsArr a, part;
+};
+template <class T, class Num, class SegsT>
+__global__ __launch_bounds__(T::THREADS) void k_gram(SegsT segs) {
   static_assert(T::MT == T::NT, "the tile grid of a symmetric result must be symmetric");
   extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(GramArgs);
+  const int rows = a_.rows, r = a_.r, splits = a_.splits;
   const int tiles = (r + T::NT - 1) / T::NT;
   // The result is symmetric: only the tiles (tm, tn) with tm <= tn are computed, row by row
   // of the tile grid, and an off-diagonal tile is stored a second time, transposed.
@@ -303,20 +431,19 @@ __global__ __launch_bounds__(T::THREADS) void k_gram(int rows, int r, WsArr a, W
   // by their flattened index; each XCD gets one contiguous range of the order (matrix, split,
   // tile), so those tiles run under one L2 and A comes from HBM once.  (Taken per matrix, 20
   // workgroups spread over all XCDs: the counters showed three times the input fetched.)
-  const int per_z = (int)gridDim.x * (int)gridDim.y;
-  const int flat = xcd_contiguous((int)blockIdx.x + (int)gridDim.x * ((int)blockIdx.y + (int)gridDim.y * (int)blockIdx.z),
-                                  per_z * (int)gridDim.z);
+  const int per_z = blk.grid.x * blk.grid.y;
+  const int flat = xcd_contiguous(blk.flat, per_z * blk.grid.z);
   const int z = flat / per_z, logical = flat - z * per_z;
-  int tm = 0, tn = logical % (int)gridDim.x;
+  int tm = 0, tn = logical % blk.grid.x;
   while (tn >= tiles - tm) { tn -= tiles - tm; ++tm; }
   tn += tm;
-  const int split = logical / (int)gridDim.x;
-  SrcF32 s{a.base + (int64_t)z * a.stride, rows, r, r};
+  const int split = logical / blk.grid.x;
+  SrcF32 s{a_.a.base + (int64_t)z * a_.a.stride, rows, r, r};
   int kend;
   const int kbeg = split_begin(rows, splits, T::KT, split, &kend);
   f32x16 acc[T::FM][T::FN];
   zero_acc<T>(acc);
-  const float sc = Num::F16 ? gram_operand_scale(d, scal, side, z) : 1.f;
+  const float sc = Num::F16 ? gram_operand_scale(a_.d, a_.scal, a_.side, z) : 1.f;
   gemm_mainloop_deep<T, Num, KSF, SrcF32, KSF, SrcF32, 3>(s, s, tm * T::MT, tn * T::NT, kbeg, kend, sc, sc, lds, acc);
   if constexpr (Num::F16) {
     const float inv = 1.f / (sc * sc);
@@ -327,7 +454,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gram(int rows, int r, WsArr a, W
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[fm][fn][v] *= inv;
   }
-  float* out = part.base + (int64_t)z * part.stride + (int64_t)split * r * r;
+  float* out = a_.part.base + (int64_t)z * a_.part.stride + (int64_t)split * r * r;
   for_each_acc<T>(acc, tm * T::MT, tn * T::NT, [&](int row, int col, float v) {
     if (row < r && col < r) out[(int64_t)row * r + col] = v;
   });
@@ -363,18 +490,27 @@ __global__ __launch_bounds__(T::THREADS) void k_gram(int rows, int r, WsArr a, W
 // enough, and A itself enters in full fp32 precision.
 // ------------------------------------------------------------------------------------
 constexpr float kPhiScale = 8192.f;
-template <class T, class Num, bool DEEP, bool CORR>
-__global__ __launch_bounds__(T::THREADS) void k_apply(int rows, int r, WsArr a, WsArr w, HalfArr wh, WsArr out, MatPtrs ptrs,
-                                                      int to_q, HalfArr hn, HalfArr ht, Pred pred) {
+struct ApplyArgs {
+  int rows, r;
+  WsArr a, w, out;
+  HalfArr wh, hn, ht;
+  const MatEntry* q_mats;       // the result goes to these matrices' Q, or to `out` when null
+  float* only_q;                // Q of the one matrix of a batch of one
+  Pred pred;
+};
+template <class T, class Num, bool DEEP, bool CORR, class SegsT>
+__global__ __launch_bounds__(T::THREADS) void k_apply(SegsT segs) {
   extern __shared__ __align__(16) char lds[];
-  if (!pred_on(pred, blockIdx.z)) return;
+  OD_SEGMENT(ApplyArgs);
+  const int rows = a_.rows, r = a_.r, z = blk.z;
+  const HalfArr &hn = a_.hn, &ht = a_.ht, &wh = a_.wh;
+  if (!pred_on(a_.pred, z)) return;
   const int tiles_n = (r + T::NT - 1) / T::NT;
   // the column tiles of one row panel of A share an XCD's L2
-  const int bid = tiles_n > 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int bid = tiles_n > 1 ? xcd_contiguous(blk.x, blk.grid.x) : blk.x;
   const int tn = bid % tiles_n, tm = bid / tiles_n;
-  const int z = blockIdx.z;
-  SrcF32 sa{a.base + (int64_t)z * a.stride, rows, r, r};
-  SrcF32 sw{w.base + (int64_t)z * w.stride, r, r, r};
+  SrcF32 sa{a_.a.base + (int64_t)z * a_.a.stride, rows, r, r};
+  SrcF32 sw{a_.w.base + (int64_t)z * a_.w.stride, r, r, r};
   int kend = (tn + 1) * T::NT;          // W[k][j] = 0 for k > j
   if (kend > r) kend = r;
   f32x16 acc[T::FM][T::FN];
@@ -405,7 +541,7 @@ __global__ __launch_bounds__(T::THREADS) void k_apply(int rows, int r, WsArr a, 
           acc[fm][fn][v] = a1 - inv * acc[fm][fn][v];
         }
   }
-  float* dst = to_q ? ptrs.Q[z] : out.base + (int64_t)z * out.stride;
+  float* dst = a_.only_q != nullptr ? a_.only_q : a_.q_mats != nullptr ? a_.q_mats[z].Q : a_.out.base + (int64_t)z * a_.out.stride;
   for_each_acc<T>(acc, tm * T::MT, tn * T::NT, [&](int row, int col, float v) {
     if (row < rows && col < r) dst[(int64_t)row * r + col] = v;
   });
@@ -477,12 +613,24 @@ OD_DEV void small_gram_store(float* S, const f32x16& acc, int r, float* out, int
 }
 
 // r <= 32: Gram partials A^T A of `splits` row ranges, one thread per row, in plain fp32.
-__global__ __launch_bounds__(kSmallRows) void k_small_gram(int rows, int r, WsArr a0, WsArr part, int splits) {
+struct SmallArgs {
+  int rows, r, splits;
+  WsArr a0, a1;
+  WsArr gram;                   // `splits` Gram partials of a0, r x r each
+  WsArr part;                   // the same of a1
+  WsArr t1, w1;
+  int* info;
+  int info_slot;
+};
+template <class SegsT>
+__global__ __launch_bounds__(kSmallRows) void k_small_gram(SegsT segs) {
   __shared__ __align__(16) float S[kSmallRows * kSmallPitch];
-  const int z = blockIdx.y, split = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  OD_SEGMENT(SmallArgs);
+  const int rows = a_.rows, r = a_.r, splits = a_.splits;
+  const int z = blk.z, split = blk.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int kend;
   const int kbeg = split_begin(rows, splits, 8, split, &kend);
-  const float* A = a0.base + (int64_t)z * a0.stride;
+  const float* A = a_.a0.base + (int64_t)z * a_.a0.stride;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -498,17 +646,18 @@ __global__ __launch_bounds__(kSmallRows) void k_small_gram(int rows, int r, WsAr
     acc = small_gram_rows(S, wave, lane, acc);
     __syncthreads();
   }
-  small_gram_store(S, acc, r, part.base + (int64_t)z * part.stride + (int64_t)split * r * r, tid);
+  small_gram_store(S, acc, r, a_.gram.base + (int64_t)z * a_.gram.stride + (int64_t)split * r * r, tid);
 }
 
-__global__ __launch_bounds__(kSmallRows) void k_small_first_pass(int rows, int r, WsArr a0, WsArr gram, int gram_splits, WsArr t1,
-                                                                WsArr w1, WsArr a1, WsArr part, int splits, int* info,
-                                                                int info_slot) {
+template <class SegsT>
+__global__ __launch_bounds__(kSmallRows) void k_small_first_pass(SegsT segs) {
   __shared__ __align__(16) float Wl[32 * kSmallPitch];           // W[k][j]
   __shared__ __align__(16) float S[kSmallRows * kSmallPitch];    // the rows of a1 of one pass
-  const int z = blockIdx.y, split = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  OD_SEGMENT(SmallArgs);
+  const int rows = a_.rows, r = a_.r, splits = a_.splits, gram_splits = a_.splits;
+  const int z = blk.z, split = blk.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (wave == 0) {
-    const float* G = gram.base + (int64_t)z * gram.stride;
+    const float* G = a_.gram.base + (int64_t)z * a_.gram.stride;
     const int c = lane & 31, h = lane >> 5;
     // accumulator layout (lane = column c, registers = rows) read through the mirrored element
     // of the symmetric matrix: four consecutive entries of row c
@@ -526,13 +675,13 @@ __global__ __launch_bounds__(kSmallRows) void k_small_first_pass(int rows, int r
       for (int e = 0; e < 4; ++e) d[4 * q + e] = (c < r && gi < r) ? v4[e] : ((gi + e == c) ? 1.f : 0.f);
     }
     const int bad = diag_tile_factor(d, zt, lane);
-    if (bad != 0 && lane == 0) atomicCAS(&info[z * kInfoPerMat + info_slot], 0, bad);
+    if (bad != 0 && lane == 0) atomicCAS(&a_.info[z * kInfoPerMat + a_.info_slot], 0, bad);
     // zt = M with W = M^T: lane c holds row c of W
 #pragma unroll
     for (int v = 0; v < 16; ++v) Wl[c * kSmallPitch + acc_row(v, lane)] = zt[v];
     if (split == 0 && c < r) {
-      float* tp = t1.base + (int64_t)z * t1.stride;
-      float* wp = w1.base + (int64_t)z * w1.stride;
+      float* tp = a_.t1.base + (int64_t)z * a_.t1.stride;
+      float* wp = a_.w1.base + (int64_t)z * a_.w1.stride;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int gi = 8 * q + 4 * h;
@@ -547,8 +696,8 @@ __global__ __launch_bounds__(kSmallRows) void k_small_first_pass(int rows, int r
   }
   int kend;
   const int kbeg = split_begin(rows, splits, 8, split, &kend);
-  const float* A = a0.base + (int64_t)z * a0.stride;
-  float* O = a1.base + (int64_t)z * a1.stride;
+  const float* A = a_.a0.base + (int64_t)z * a_.a0.stride;
+  float* O = a_.a1.base + (int64_t)z * a_.a1.stride;
   // Gram of the produced rows, 64 per wave and pass; the four tiles are summed at the end
   f32x16 gacc;
 #pragma unroll
@@ -598,7 +747,7 @@ __global__ __launch_bounds__(kSmallRows) void k_small_first_pass(int rows, int r
     __syncthreads();
   }
   if (first) __syncthreads();          // a workgroup without rows still meets the others' barrier count
-  small_gram_store(S, gacc, r, part.base + (int64_t)z * part.stride + (int64_t)split * r * r, tid);
+  small_gram_store(S, gacc, r, a_.part.base + (int64_t)z * a_.part.stride + (int64_t)split * r * r, tid);
 }
 
 // ------------------------------------------------------------------------------------
@@ -655,6 +804,14 @@ OD_DEV void sgemm_tile(const SgemmArgs& g, int bx, int bz, char* lds) {
   });
 }
 
+// diagonal block `blk` of every matrix of a segment's batch; ranks up to 256: the whole factorisation
+template <class SegsT>
+__global__ __launch_bounds__(kCholThreads) void k_chol256(SegsT segs) {
+  extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(CholArgs);
+  chol256_block(a_, blk.x, lds);
+}
+
 template <class T, class Num, class DirA>
 __global__ __launch_bounds__(T::THREADS) void k_sgemm(SgemmArgs g) {
   extern __shared__ __align__(16) char lds[];
@@ -699,18 +856,35 @@ constexpr int kLeaf = kCholMax;   // diagonal block of the blocked factorisation
 // triangle + half the diagonal, and the inverse factor I - Phi(E) + O(E^2).  Writes
 // T2 = I + Phi(E), W2 = I - Phi(E) and the largest |E| entry (scal[mat][scal_slot]).
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_corr(int r, WsArr part, int splits, WsArr t1, WsArr t2, WsArr w2, HalfArr phit, float* scal,
-                                              int scal_slot, int* info, int info_slot) {
-  const int z = blockIdx.y;
-  const float* src = part.base + (int64_t)z * part.stride;
-  float* tp = t2.base + (int64_t)z * t2.stride;
-  float* wp = w2.base + (int64_t)z * w2.stride;
+// Fast precision (phit.base non-null) writes Phi(E)^T as fp16 scaled by 2^13 ([r][r]) instead of W2.  A
+// deviation above kMaxGramDeviation (or NaN) is a breakdown: info[mat][info_slot] = r unless already
+// set; so is a ratio of the smallest to the largest diagonal entry of t1 below kMinPivotRatio.
+struct CorrArgs {
+  int r, splits;
+  WsArr part, t1, t2, w2;
+  HalfArr phit;
+  float* scal;
+  int scal_slot;
+  int* info;
+  int info_slot;
+};
+template <class SegsT>
+__global__ __launch_bounds__(256) void k_corr(SegsT segs) {
+  OD_SEGMENT(CorrArgs);
+  const int r = a_.r, splits = a_.splits, scal_slot = a_.scal_slot, info_slot = a_.info_slot;
+  const HalfArr& phit = a_.phit;
+  float* scal = a_.scal;
+  int* info = a_.info;
+  const int z = blk.z;
+  const float* src = a_.part.base + (int64_t)z * a_.part.stride;
+  float* tp = a_.t2.base + (int64_t)z * a_.t2.stride;
+  float* wp = a_.w2.base + (int64_t)z * a_.w2.stride;
   const int64_t count = (int64_t)r * r;
   float emax = 0.f;
   // four consecutive entries of one row per thread (r is a multiple of 8)
-  for (int64_t i4 = (int64_t)blockIdx.x * 256 + threadIdx.x; i4 < count / 4; i4 += (int64_t)gridDim.x * 256) {
-    const int64_t idx = i4 * 4;
-    const int i = (int)(idx / r), j0 = (int)(idx % r);
+  for (int64_t i4 = (int64_t)blk.x * 256 + threadIdx.x; i4 < count / 4; i4 += (int64_t)blk.grid.x * 256) {
+    const int i = r <= 32768 ? (int)i4 * 4 / r : (int)(i4 * 4 / r);       // the 32-bit division where it is enough
+    const int j0 = (int)(i4 * 4 - (int64_t)i * r);
     f32x4 g = reinterpret_cast<const f32x4*>(src)[i4];
 #pragma unroll 8
     for (int sp = 1; sp < splits; ++sp) g += reinterpret_cast<const f32x4*>(src + (int64_t)sp * count)[i4];
@@ -760,8 +934,8 @@ __global__ __launch_bounds__(256) void k_corr(int r, WsArr part, int splits, WsA
   // condition number from below.  Beyond about 1 / sqrt(rounding of the Gram matrix) the small
   // pivots are rounding noise - CholeskyQR would return an orthonormal basis of that noise -
   // so such a matrix is reported as rank deficient whatever deviation the noise happened to leave.
-  if (blockIdx.x == 0) {
-    const float* t = t1.base + (int64_t)z * t1.stride;
+  if (blk.x == 0) {
+    const float* t = a_.t1.base + (int64_t)z * a_.t1.stride;
     float lo = 3.0e38f, hi = 0.f;
     for (int i = threadIdx.x; i < r; i += 256) {
       const float d = t[(int64_t)i * r + i];
@@ -798,33 +972,21 @@ __global__ __launch_bounds__(256) void k_zero_pair(WsArr a, WsArr b, int64_t cou
     pb[i] = zero;
   }
 }
-__global__ __launch_bounds__(256) void k_fill_f32(float* p, int64_t count, float v) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) p[i] = v;
-}
-__global__ __launch_bounds__(256) void k_fill_i32(int* p, int64_t count, int v) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) p[i] = v;
-}
-
-
-__global__ __launch_bounds__(256) void k_scale_from_trace(int n, int r, WsArr gram, float* scal) {
-  const int z = blockIdx.x, tid = threadIdx.x;
-  const float* g = gram.base + (int64_t)z * gram.stride;
-  float acc = 0.f;
-  for (int i = tid; i < r; i += 256) acc += g[(int64_t)i * r + i];
-  __shared__ float red[256];
-  red[tid] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  if (tid == 0) scal[z * kScalPerMat + 1] = pow2_scale_for_rms(red[0] / ((float)n * (float)r));
-}
-
 // ColNorm stage 1: partial column sums of squares over a slab of rows (deterministic)
-__global__ __launch_bounds__(256) void k_colsq_partial(int n, int r, WsArr rr, WsArr part, int slabs) {
-  const int z = blockIdx.z, slab = blockIdx.y;
-  const int c = blockIdx.x * 256 + threadIdx.x;
+struct ColnormArgs {
+  int n, r, slabs;
+  WsArr rr, part, colsq;
+  int* info;
+  const MatEntry* mats;
+  HalfArr qh;
+};
+template <class SegsT>
+__global__ __launch_bounds__(256) void k_colsq_partial(SegsT segs) {
+  OD_SEGMENT(ColnormArgs);
+  const int n = a_.n, r = a_.r, slabs = a_.slabs;
+  const WsArr &rr = a_.rr, &part = a_.part;
+  const int z = blk.z, slab = blk.y;
+  const int c = blk.x * 256 + threadIdx.x;
   const int per = (n + slabs - 1) / slabs;
   const int r0 = slab * per, r1 = (r0 + per) < n ? (r0 + per) : n;
   if (c >= r) return;
@@ -836,38 +998,33 @@ __global__ __launch_bounds__(256) void k_colsq_partial(int n, int r, WsArr rr, W
   }
   part.base[(int64_t)z * part.stride + (int64_t)slab * r + c] = acc;
 }
-// stage 2: column lengths, the scale of R, and the zero-column flag
-__global__ __launch_bounds__(256) void k_colsq_final(int n, int r, WsArr part, int slabs, WsArr colsq, float* scal, int* info) {
-  const int z = blockIdx.x, tid = threadIdx.x;
-  float tot = 0.f;
-  for (int c = tid; c < r; c += 256) {
-    float s = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < slabs; ++k) s += part.base[(int64_t)z * part.stride + (int64_t)k * r + c];
-    tot += s;
-    float len = sqrtf(s);
-    float inv = 0.f;
-    if (len > 1e-30f && len < 3.0e38f) inv = 1.f / len;
-    else atomicCAS(&info[z * kInfoPerMat + 2], 0, c + 1);
-    colsq.base[(int64_t)z * colsq.stride + c] = inv;
-  }
-  __shared__ float red[256];
-  red[tid] = tot;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  if (tid == 0) scal[z * kScalPerMat + 1] = pow2_scale_for_rms(red[0] / ((float)n * (float)r));
+// stage 2: reciprocal column lengths and the zero-column flag
+template <class SegsT>
+__global__ __launch_bounds__(256) void k_colsq_final(SegsT segs) {
+  OD_SEGMENT(ColnormArgs);
+  const int z = blk.z, r = a_.r, c = blk.x * 256 + threadIdx.x;
+  if (c >= r) return;
+  const float* p = a_.part.base + (int64_t)z * a_.part.stride + c;
+  float s = 0.f;
+#pragma unroll 16
+  for (int k = 0; k < a_.slabs; ++k) s += p[(int64_t)k * r];
+  const float len = sqrtf(s);
+  float inv = 0.f;
+  if (len > 1e-30f && len < 3.0e38f) inv = 1.f / len;
+  else atomicCAS(&a_.info[z * kInfoPerMat + 2], 0, c + 1);
+  a_.colsq.base[(int64_t)z * a_.colsq.stride + c] = inv;
 }
 // stage 3: Q = R * diag(1/len)
-__global__ __launch_bounds__(256) void k_colnorm_apply(int n, int r, WsArr rr, WsArr colsq, MatPtrs ptrs, HalfArr qh) {
-  const int z = blockIdx.y;
-  const float* src = rr.base + (int64_t)z * rr.stride;
-  const float* inv = colsq.base + (int64_t)z * colsq.stride;
-  float* q = ptrs.Q[z];
+template <class SegsT>
+__global__ __launch_bounds__(256) void k_colnorm_apply(SegsT segs) {
+  OD_SEGMENT(ColnormArgs);
+  const int n = a_.n, r = a_.r, z = blk.z;
+  const HalfArr& qh = a_.qh;
+  const float* src = a_.rr.base + (int64_t)z * a_.rr.stride;
+  const float* inv = a_.colsq.base + (int64_t)z * a_.colsq.stride;
+  float* q = a_.mats[z].Q;
   const int64_t n4 = (int64_t)n * r / 4;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blk.x * 256 + threadIdx.x; i < n4; i += (int64_t)blk.grid.x * 256) {
     int c = (int)((i * 4) % r);
     f32x4 v = reinterpret_cast<const f32x4*>(src)[i];
     f32x4 s = *reinterpret_cast<const f32x4*>(inv + c);
@@ -909,24 +1066,38 @@ OD_DEV void report_b_range(const ClassDims& d, const float* scal, int* info, int
   if (warn != 0) atomicOr(&info[z * kInfoPerMat + kWarnSlot], warn);
 }
 
-template <class T, class Num, bool XBF, bool GBF>
-__global__ __launch_bounds__(T::THREADS) void k_efx(ClassDims d, MatPtrs ptrs, const float* scal, const int* info, WsArr p, WsArr rr,
-                                                    float a_coef, float b_coef, float lr) {
+// Arguments of the error-feedback pass (one segment): fp32 factors (exact) or their fp16 copies.
+struct EfxArgs {
+  ClassDims d;
+  const MatEntry* mats;
+  MatEntry only;
+  const float* scal;
+  int* info;
+  WsArr p, rr;
+  HalfArr ph, rh, qh;
+};
+struct EfxCoef { float a, b, lr; };
+
+template <class T, class Num, bool XBF, bool GBF, class SegsT>
+__global__ __launch_bounds__(T::THREADS) void k_efx(SegsT segs, EfxCoef coef) {
   extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(EfxArgs);
+  const ClassDims& d = a_.d;
+  const int* info = a_.info;
+  const float a_coef = coef.a;
   const int tiles_i = (d.m + T::NT - 1) / T::NT;
-  const int ti = blockIdx.x % tiles_i, tj = blockIdx.x / tiles_i;
-  const int z = blockIdx.z;
-  SrcF32 sp{p.base + (int64_t)z * p.stride, d.m, d.r, d.r};
-  SrcF32 sr{rr.base + (int64_t)z * rr.stride, d.n, d.r, d.r};
-  SrcF32 sq{ptrs.Q[z], d.n, d.r, d.r};
-  const float s_r = Num::F16 ? scal[z * kScalPerMat + 1] : 1.f;
-  const float s_u = Num::F16 ? kUnitScale : 1.f;
+  const int ti = blk.x % tiles_i, tj = blk.x / tiles_i;
+  const int z = blk.z;
+  const MatEntry mat = OD_MATRIX(z);
+  SrcF32 sp{a_.p.base + (int64_t)z * a_.p.stride, d.m, d.r, d.r};
+  SrcF32 sr{a_.rr.base + (int64_t)z * a_.rr.stride, d.n, d.r, d.r};
+  SrcF32 sq{mat.Q, d.n, d.r, d.r};
   f32x16 acc_r[T::FM][T::FN], acc_q[T::FM][T::FN];
   zero_acc<T>(acc_r);
   zero_acc<T>(acc_q);
-  gemm_mainloop<T, Num, KC, SrcF32, KC, SrcF32>(sr, sp, tj * T::MT, ti * T::NT, 0, d.r, s_r, s_u, lds, acc_r);
-  gemm_mainloop<T, Num, KC, SrcF32, KC, SrcF32>(sq, sp, tj * T::MT, ti * T::NT, 0, d.r, s_u, s_u, lds, acc_q);
-  const float cr = b_coef / (s_r * s_u), cq = lr / (s_u * s_u);
+  gemm_mainloop<T, Num, KC, SrcF32, KC, SrcF32>(sr, sp, tj * T::MT, ti * T::NT, 0, d.r, 1.f, 1.f, lds, acc_r);
+  gemm_mainloop<T, Num, KC, SrcF32, KC, SrcF32>(sq, sp, tj * T::MT, ti * T::NT, 0, d.r, 1.f, 1.f, lds, acc_q);
+  const float cr = coef.b, cq = coef.lr;
   if (matrix_flagged(info, z)) {        // unspecified factors (possibly NaN) never reach X and M
     zero_acc<T>(acc_r);
     zero_acc<T>(acc_q);
@@ -934,7 +1105,7 @@ __global__ __launch_bounds__(T::THREADS) void k_efx(ClassDims d, MatPtrs ptrs, c
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / T::WN, wn = wave % T::WN;
-  float* Mz = ptrs.M[z];
+  float* Mz = mat.M;
 #pragma unroll
   for (int fn = 0; fn < T::FN; ++fn) {
     const int i = ti * T::NT + wn * T::WTN + fn * 32 + (lane & 31);
@@ -946,10 +1117,10 @@ __global__ __launch_bounds__(T::THREADS) void k_efx(ClassDims d, MatPtrs ptrs, c
         if (i < d.m && j < d.n) {
           float g[4], x[4];
           if constexpr (GBF) {
-            u32x2 gv = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(ptrs.G[z]) + (int64_t)i * d.ldg + j);
+            u32x2 gv = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(mat.G) + (int64_t)i * d.ldg + j);
             g[0] = bf16_lo(gv[0]); g[1] = bf16_hi(gv[0]); g[2] = bf16_lo(gv[1]); g[3] = bf16_hi(gv[1]);
           } else {
-            f32x4 gv = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(ptrs.G[z]) + (int64_t)i * d.ldg + j);
+            f32x4 gv = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(mat.G) + (int64_t)i * d.ldg + j);
             g[0] = gv[0]; g[1] = gv[1]; g[2] = gv[2]; g[3] = gv[3];
           }
           f32x4* mp = reinterpret_cast<f32x4*>(Mz + (int64_t)i * d.ldm + j);
@@ -958,7 +1129,7 @@ __global__ __launch_bounds__(T::THREADS) void k_efx(ClassDims d, MatPtrs ptrs, c
           for (int e = 0; e < 4; ++e) mo[e] = a_coef * (mv[e] + g[e]) - cr * acc_r[fm][fn][4 * vq + e];
           *mp = mo;
           if constexpr (XBF) {
-            u32x2* xp = reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(ptrs.X[z]) + (int64_t)i * d.ldx + j);
+            u32x2* xp = reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(mat.X) + (int64_t)i * d.ldx + j);
             u32x2 xv = *xp;
             x[0] = bf16_lo(xv[0]); x[1] = bf16_hi(xv[0]); x[2] = bf16_lo(xv[1]); x[3] = bf16_hi(xv[1]);
 #pragma unroll
@@ -968,7 +1139,7 @@ __global__ __launch_bounds__(T::THREADS) void k_efx(ClassDims d, MatPtrs ptrs, c
             xo[1] = pack_bf16_rne(x[2], x[3]);
             *xp = xo;
           } else {
-            f32x4* xp = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(ptrs.X[z]) + (int64_t)i * d.ldx + j);
+            f32x4* xp = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(mat.X) + (int64_t)i * d.ldx + j);
             f32x4 xv = *xp;
 #pragma unroll
             for (int e = 0; e < 4; ++e) xv[e] -= cq * acc_q[fm][fn][4 * vq + e];
@@ -1008,17 +1179,24 @@ OD_DEV void st_stream(V* p, V v) {
   else *p = v;
 }
 
-template <bool XBF, bool GBF, bool STREAM>
-__global__ __launch_bounds__(512, 4) void k_efx_h(ClassDims d, MatPtrs ptrs, const float* scal, int* info, HalfArr ph, HalfArr rh,
-                                               HalfArr qh, float a_coef, float b_coef, float lr) {
+template <bool XBF, bool GBF, bool STREAM, class SegsT>
+__global__ __launch_bounds__(512, 4) void k_efx_h(SegsT segs, EfxCoef coef) {
   constexpr int TJ = 128, TI = 128, KT = 32, PITCH = KT * 2 + 16, PLANE = 128 * PITCH, BUF = 3 * PLANE;
   extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(EfxArgs);
+  const ClassDims& d = a_.d;
+  const float* scal = a_.scal;
+  int* info = a_.info;
+  const HalfArr &ph = a_.ph, &rh = a_.rh, &qh = a_.qh;
+  const float a_coef = coef.a, b_coef = coef.b, lr = coef.lr;
+  const int z = blk.z;
+  const MatEntry mat = OD_MATRIX(z);
   const int tiles_i = (d.m + TI - 1) / TI;
-  int ti = blockIdx.x % tiles_i, tj = blockIdx.x / tiles_i;
+  int ti = blk.x % tiles_i, tj = blk.x / tiles_i;
   if (d.col_fast) {
     const int tiles_jj = (d.n + TJ - 1) / TJ;
-    tj = blockIdx.x % tiles_jj;
-    ti = blockIdx.x / tiles_jj;
+    tj = blk.x % tiles_jj;
+    ti = blk.x / tiles_jj;
   }
   if (d.r > 256) {
     // Long K loops re-read the panels of P, R and Q often enough to matter: bands of eight tile
@@ -1027,14 +1205,13 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(ClassDims d, MatPtrs ptrs, con
     // into its L2 serves eight of them (measured -4 to -5 %; at r = 256 the plain order is 2 us
     // faster).
     const int tiles_j = (d.n + TJ - 1) / TJ;
-    const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int logical = xcd_contiguous(blk.x, blk.grid.x);
     const int band = logical / (tiles_i * 8);
     const int in_band = logical - band * tiles_i * 8;
     const int bw = min(8, tiles_j - band * 8);
     ti = in_band / bw;
     tj = band * 8 + in_band % bw;
   }
-  const int z = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wi = wave & 3, wj = wave >> 2, c = lane & 31;
   SrcH16 sp{ph.base + (int64_t)z * ph.stride, d.m, d.r, d.r};
@@ -1091,9 +1268,9 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(ClassDims d, MatPtrs ptrs, con
   // ---- epilogue: this lane's 16 rows x 2 adjacent columns, in two halves of 8 rows; within a
   // half every load is issued before the first store
   const int j0 = tj * TJ + 64 * wj + 2 * c;
-  float* __restrict__ Mz = ptrs.M[z];
-  const char* __restrict__ Gz = reinterpret_cast<const char*>(ptrs.G[z]);
-  char* __restrict__ Xz = reinterpret_cast<char*>(ptrs.X[z]);
+  float* __restrict__ Mz = mat.M;
+  const char* __restrict__ Gz = reinterpret_cast<const char*>(mat.G);
+  char* __restrict__ Xz = reinterpret_cast<char*>(mat.X);
   constexpr int GE = GBF ? 2 : 4, XE = XBF ? 2 : 4;
   const float s_r = r_scale(d, scal, z);
   const float cr = b_coef / (s_r * kUnitScale), cq = lr / (kUnitScale * kUnitScale);
@@ -1159,31 +1336,37 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(ClassDims d, MatPtrs ptrs, con
 // (G, X) row segments, as in k_efx_h.  Two workgroups per CU (72 KB of LDS each): one streams
 // M, G, X while the other multiplies.
 // ------------------------------------------------------------------------------------
-template <bool XBF, bool GBF, bool STREAM, int WI>
-__global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(ClassDims d, MatPtrs ptrs, const float* scal, int* info, HalfArr ph,
-                                                                     HalfArr rh, HalfArr qh, float a_coef, float b_coef, float lr) {
+template <bool XBF, bool GBF, bool STREAM, int WI, class SegsT>
+__global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT segs, EfxCoef coef) {
   constexpr int TI = 64 * WI, TJ = 128, KT = 32, ROWB = KT * 2, ST = 3, NW = 2 * WI;
   constexpr int PLANE = 128 * ROWB, STAGE = 2 * PLANE + TI * ROWB;       // R | Q | P
   constexpr int CPW = (16 + TI / 16) / NW;                    // 1 KB chunks per wave and stage
   extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(EfxArgs);
+  const ClassDims& d = a_.d;
+  const float* scal = a_.scal;
+  int* info = a_.info;
+  const HalfArr &ph = a_.ph, &rh = a_.rh, &qh = a_.qh;
+  const float a_coef = coef.a, b_coef = coef.b, lr = coef.lr;
+  const int z = blk.z;
+  const MatEntry mat = OD_MATRIX(z);
   const int tiles_i = (d.m + TI - 1) / TI;
-  int ti = blockIdx.x % tiles_i, tj = blockIdx.x / tiles_i;
+  int ti = blk.x % tiles_i, tj = blk.x / tiles_i;
   if (d.col_fast) {
     const int tiles_jj = (d.n + TJ - 1) / TJ;
-    tj = blockIdx.x % tiles_jj;
-    ti = blockIdx.x / tiles_jj;
+    tj = blk.x % tiles_jj;
+    ti = blk.x / tiles_jj;
   }
   if (d.r > 256) {
     // bands of eight tile columns, one contiguous range of that order per XCD (see k_efx_h)
     const int tiles_j = (d.n + TJ - 1) / TJ;
-    const int logical = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int logical = xcd_contiguous(blk.x, blk.grid.x);
     const int band = logical / (tiles_i * 8);
     const int in_band = logical - band * tiles_i * 8;
     const int bw = min(8, tiles_j - band * 8);
     ti = in_band / bw;
     tj = band * 8 + in_band % bw;
   }
-  const int z = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, c = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wi = wave % WI, wj = wave / WI;
@@ -1263,9 +1446,9 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(ClassDims
   // ---- epilogue: 2 row blocks x 16 rows x 2 adjacent columns per lane, in four parts of 8
   // rows; within a part every load is issued before the first store
   const int j0 = tj * TJ + 64 * wj + 2 * c;
-  float* __restrict__ Mz = ptrs.M[z];
-  const char* __restrict__ Gz = reinterpret_cast<const char*>(ptrs.G[z]);
-  char* __restrict__ Xz = reinterpret_cast<char*>(ptrs.X[z]);
+  float* __restrict__ Mz = mat.M;
+  const char* __restrict__ Gz = reinterpret_cast<const char*>(mat.G);
+  char* __restrict__ Xz = reinterpret_cast<char*>(mat.X);
   constexpr int GE = GBF ? 2 : 4, XE = XBF ? 2 : 4;
   const float s_r = r_scale(d, scal, z);
   const float cr = b_coef / (s_r * kUnitScale), cq = lr / (kUnitScale * kUnitScale);
@@ -1344,9 +1527,8 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(ClassDims
 //     rows a half-wave touches fall into different banks.
 // One barrier per step.  Waits count loads: per step and wave kCB factor loads, then kNR raw loads.
 // ------------------------------------------------------------------------------------
-template <bool TRANS, int NT, int SB>
-__global__ __launch_bounds__(512, 1) void k_stream_d(ClassDims d, MatPtrs ptrs, const float* scal, WsArr part, int splits, HalfArr fh, HalfArr rh,
-                                                  int* info, int rotate) {
+template <bool TRANS, int NT, int SB, class SegsT>
+__global__ __launch_bounds__(512, 1) void k_stream_d(SegsT segs) {
   constexpr int MT = 128, KT = 32, ROWB = 64, SR = 3;
   constexpr int FN = NT / 128;                                // 32-column accumulator blocks per wave
   constexpr int B_STAGE = NT * ROWB, RAW_M = MT * KT * 4, RAW_G = MT * KT * 2, RAW_STAGE = RAW_M + RAW_G;
@@ -1354,17 +1536,22 @@ __global__ __launch_bounds__(512, 1) void k_stream_d(ClassDims d, MatPtrs ptrs, 
   constexpr int OFF_RAW = SB * B_STAGE, OFF_A = OFF_RAW + SR * RAW_STAGE;
   constexpr int kCB = NT / 16 / 8, kNR = 3;                   // 1 KB chunks per wave: factor stage, raw stage (2 of M, 1 of G)
   extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(StreamArgs);
+  const ClassDims& d = a_.d;
+  const float* scal = a_.scal;
+  int* info = a_.info;
+  const HalfArr &fh = a_.fh, &rh = a_.rh;
+  const int splits = a_.splits, rotate = a_.rotate;
   const int Mdim = TRANS ? d.n : d.m, Kdim = TRANS ? d.m : d.n;
   const int tiles_n = (d.r + NT - 1) / NT;
   // Workgroups go to the 8 XCDs round robin by their flattened index.  Each XCD gets one
   // contiguous range of the order (matrix, split, row panel, column tile): the workgroups that
   // run side by side under one L2 then read the same k range of the same factor operand (and
   // the column tiles of a row panel the same raw tile), instead of 16 different ones.
-  const int per_z = (int)gridDim.x * (int)gridDim.y;
-  const int logical = xcd_contiguous((int)blockIdx.x + (int)gridDim.x * ((int)blockIdx.y + (int)gridDim.y * (int)blockIdx.z),
-                                     per_z * (int)gridDim.z);
+  const int per_z = blk.grid.x * blk.grid.y;
+  const int logical = xcd_contiguous(blk.flat, per_z * blk.grid.z);
   const int z = logical / per_z, in_z = logical - z * per_z;
-  const int split = in_z / (int)gridDim.x, bid = in_z - split * (int)gridDim.x;
+  const int split = in_z / blk.grid.x, bid = in_z - split * blk.grid.x;
   const int tn = bid % tiles_n, tm = bid / tiles_n;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1383,8 +1570,9 @@ __global__ __launch_bounds__(512, 1) void k_stream_d(ClassDims d, MatPtrs ptrs, 
   };
   const float sa = b_scale(d, scal, z);
   const uint32_t lds0 = lds_offset_of(lds);
-  const float* Mz = ptrs.M[z];
-  const uint16_t* Gz = reinterpret_cast<const uint16_t*>(ptrs.G[z]);
+  const MatEntry mat = OD_MATRIX(z);
+  const float* Mz = mat.M;
+  const uint16_t* Gz = reinterpret_cast<const uint16_t*>(mat.G);
   const uint16_t* Fz = fh.base + (int64_t)z * fh.stride;      // [r][Kdim]
 
   // ---- factor operand: chunk = 16 rows (output columns) x 64 bytes
@@ -1537,7 +1725,7 @@ __global__ __launch_bounds__(512, 1) void k_stream_d(ClassDims d, MatPtrs ptrs, 
     }
   }
   const float inv = 1.f / (sa * kUnitScale);
-  float* out = part.base + (int64_t)z * part.stride + (int64_t)split * Mdim * d.r;
+  float* out = a_.part.base + (int64_t)z * a_.part.stride + (int64_t)split * Mdim * d.r;
 #pragma unroll
   for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
@@ -1580,33 +1768,17 @@ __global__ __launch_bounds__(512, 1) void k_stream_d(ClassDims d, MatPtrs ptrs, 
     hipError_t e_ = hipGetLastError();          \
     if (e_ != hipSuccess) return e_;            \
   } while (0)
+#define OD_RETURN_IF(expr)                      \
+  do {                                          \
+    const hipError_t e_ = (expr);               \
+    if (e_ != hipSuccess) return e_;            \
+  } while (0)
 
-// One-shot timing of the next streaming kernel (projection, back-projection, error feedback):
-// the events receive the start and stop time stamps of the dispatch itself, without the
-// gaps around separately recorded events.
+// One-shot timing of the next streaming phase (projection, back-projection, error feedback): the
+// events receive the start time stamp of its first dispatch and the stop time stamp of its last
+// one, without the gaps around separately recorded events.
 static thread_local hipEvent_t g_time_start = nullptr, g_time_stop = nullptr;
 void time_next_launch(hipEvent_t start, hipEvent_t stop) { g_time_start = start; g_time_stop = stop; }
-
-template <class K, class... Args>
-static void launch_timed(K kernel, dim3 grid, dim3 block, int lds, hipStream_t st, Args... args) {
-  if (g_time_start != nullptr) {
-    hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, st, g_time_start, g_time_stop, 0u, args...);
-    g_time_start = nullptr;
-    g_time_stop = nullptr;
-  } else {
-    hipLaunchKernelGGL(kernel, grid, block, lds, st, args...);
-  }
-}
-
-// Development switch: ORTHDION_KERNELS="efx=old,..." selects the previous kernel of a phase,
-// so that two generations can be timed in one process.  Unset in normal use.
-static bool kernel_choice(const char* phase, const char* value) {
-  const char* env = std::getenv("ORTHDION_KERNELS");
-  if (env == nullptr) return false;
-  char key[64];
-  std::snprintf(key, sizeof(key), "%s=%s", phase, value);
-  return std::strstr(env, key) != nullptr;
-}
 
 template <class K>
 static hipError_t allow_lds(K kernel, int bytes) {
@@ -1614,213 +1786,539 @@ static hipError_t allow_lds(K kernel, int bytes) {
   return hipSuccess;
 }
 
-hipError_t launch_fill_int(int* p, int64_t count, int value, hipStream_t st) {
-  if (count <= 0) return hipSuccess;
-  int blocks = (int)((count + 255) / 256);
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(k_fill_i32, dim3(blocks), dim3(256), 0, st, p, count, value);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
-hipError_t launch_fill_f32(float* p, int64_t count, float v, hipStream_t st) {
-  if (count <= 0) return hipSuccess;
-  int blocks = (int)((count + 255) / 256);
-  if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(k_fill_f32, dim3(blocks), dim3(256), 0, st, p, count, v);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
-hipError_t launch_stats(const ClassDims& d, const MatPtrs& ptrs, float* scal, int* info, HalfArr qht, hipStream_t st) {
-  const dim3 grid(kStatRows + ((d.n + 63) / 64) * ((d.r + 63) / 64), d.nb);
-  if (d.g_bf16) hipLaunchKernelGGL(k_prologue<SrcBF16>, grid, dim3(256), 0, st, d, ptrs, scal, info, qht);
-  else hipLaunchKernelGGL(k_prologue<SrcF32>, grid, dim3(256), 0, st, d, ptrs, scal, info, qht);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
-template <class T, class Num, class GSrc, int PF = 1>
-static hipError_t proj_t(const ClassDims& d, const MatPtrs& ptrs, const float* scal, WsArr part, int splits, HalfArr qht, hipStream_t st) {
-  constexpr int lds = T::template lds_bytes<Num>();
-  hipError_t e = allow_lds(k_proj<T, Num, GSrc, PF>, lds);
-  if (e != hipSuccess) return e;
-  dim3 grid(((d.m + T::MT - 1) / T::MT) * ((d.r + T::NT - 1) / T::NT), splits, d.nb);
-  // one matrix whose rows are a multiple of 32 KB apart (in M): measured 10-20 % faster with
-  // rotated k order at 8192 columns; with several matrices in flight the order does not matter
-  const int rotate = (d.nb == 1 && (d.ldm * (int64_t)sizeof(float)) % 32768 == 0) ? 1 : 0;
-  launch_timed(k_proj<T, Num, GSrc, PF>, grid, dim3(T::THREADS), lds, st, d, ptrs, scal, part, splits, qht, rotate);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-// Few wide tiles need many splits to fill the chip; 64-row tiles get there with half of them,
-// i.e. half the partial sums to write and to add up.  With enough tiles the wide one wins.
-bool proj_uses_flat_tiles(int m, int r, int nb) {
-  return r > 128 && (int64_t)((m + 127) / 128) * ((r + 255) / 256) * nb < 256;
-}
-template <class GSrc>
-static hipError_t proj_g(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal, WsArr part, int splits, HalfArr qht, hipStream_t st) {
-  if (prec == PREC_BF3) {
-    // small problems: 64-deep steps halve the number of round trips of a loop that is all latency
-    if ((int64_t)((d.m + 127) / 128) * ((d.r + 127) / 128) * splits * d.nb < 256)
-      return proj_t<TileSmall, NumBF<3>, GSrc>(d, ptrs, scal, part, splits, qht, st);
-    return proj_t<TileSquare, NumBF<3>, GSrc>(d, ptrs, scal, part, splits, qht, st);
+// The segments of one launch.
+template <class A>
+struct SegList {
+  Segs<A> g;
+  int total;
+  SegList() : g{}, total(0) {}
+  bool full() const { return g.n == kMaxSeg; }
+  void add(const A& a, int x, int y, int z) {
+    g.first[g.n] = total;
+    g.grid[g.n] = SegGrid{x, y, z};
+    g.seg[g.n] = a;
+    total += (x * y * z + 7) / 8 * 8;         // segments start at multiples of 8 workgroups (see above)
+    ++g.n;
   }
-  if (d.r <= 64) return proj_t<TileNarrow, NumF16, GSrc>(d, ptrs, scal, part, splits, qht, st);
-  if (d.r <= 128) return proj_t<TileSquare, NumF16, GSrc>(d, ptrs, scal, part, splits, qht, st);
-  if (proj_uses_flat_tiles(d.m, d.r, d.nb)) {
-    // long enough K loops per column tile pay for a second register stage
-    if (d.r > 256) return proj_t<TileFlat, NumF16, GSrc, 2>(d, ptrs, scal, part, splits, qht, st);
-    return proj_t<TileFlat, NumF16, GSrc>(d, ptrs, scal, part, splits, qht, st);
+  // enqueues what was added, with `single` for one segment and `multi` for several; `timed` bit 0 / 1:
+  // the first / last launch of a timed phase
+  template <class K1, class K2, class... Extra>
+  hipError_t launch(K1 single, K2 multi, int threads, int lds, hipStream_t st, int timed, Extra... extra) {
+    if (g.n == 0) return hipSuccess;
+    hipEvent_t e0 = (timed & 1) ? g_time_start : nullptr, e1 = (timed & 2) ? g_time_stop : nullptr;
+    if (timed & 2) g_time_start = g_time_stop = nullptr;
+    if (g.n == 1) {
+      OD_RETURN_IF(allow_lds(single, lds));
+      const One<A> one = {{g.seg[0]}};
+      const dim3 grid(g.grid[0].x, g.grid[0].y, g.grid[0].z);
+      if (e0 != nullptr || e1 != nullptr) hipExtLaunchKernelGGL(single, grid, dim3(threads), (uint32_t)lds, st, e0, e1, 0u, one, extra...);
+      else hipLaunchKernelGGL(single, grid, dim3(threads), lds, st, one, extra...);
+    } else {
+      OD_RETURN_IF(allow_lds(multi, lds));
+      if (e0 != nullptr || e1 != nullptr) hipExtLaunchKernelGGL(multi, dim3(total), dim3(threads), (uint32_t)lds, st, e0, e1, 0u, g, extra...);
+      else hipLaunchKernelGGL(multi, dim3(total), dim3(threads), lds, st, g, extra...);
+    }
+    g.n = 0;
+    total = 0;
+    OD_CHECK_LAUNCH();
+    return hipSuccess;
   }
-  return proj_t<TileWide, NumF16, GSrc>(d, ptrs, scal, part, splits, qht, st);
-}
-template <bool TRANS, int NT>
-static hipError_t stream_d_t(const ClassDims& d, const MatPtrs& ptrs, const float* scal, WsArr part, int splits, HalfArr fh, hipStream_t st,
-                             HalfArr rh = HalfArr{nullptr, 0}, int* info = nullptr) {
-  constexpr int SB = NT == 512 ? 2 : 3;
-  constexpr int lds = SB * NT * 64 + 3 * (128 * 32 * 6) + 2 * (TRANS ? 32 * 320 : 128 * 64);
-  hipError_t e = allow_lds(k_stream_d<TRANS, NT, SB>, lds);
-  if (e != hipSuccess) return e;
-  const int Mdim = TRANS ? d.n : d.m;
-  dim3 grid(((Mdim + 127) / 128) * ((d.r + NT - 1) / NT), splits, d.nb);
-  // rotated k order for the projection of a single matrix at 8192 columns (see the kernel): 120 ->
-  // 102 us at r = 256.  With several matrices in flight the order does not matter, and the
-  // 512-column tiles of the larger ranks are not waiting for memory (no gain measured there).
-  const int rotate = (!TRANS && NT == 256 && d.nb == 1 && (d.ldm * (int64_t)sizeof(float)) % 32768 == 0) ? 1 : 0;
-  launch_timed(k_stream_d<TRANS, NT, SB>, grid, dim3(512), lds, st, d, ptrs, scal, part, splits, fh, rh, info, rotate);
-  OD_CHECK_LAUNCH();
+};
+
+// Calls one(variant, members, count, timed) for groups of at most kMaxSeg batches that take the same
+// kernel; variant(batch) < 0 leaves a batch out.
+template <class V, class F>
+static hipError_t by_variant(BatchList b, int n, V variant, F one) {
+  constexpr int kMany = 256;                  // batches looked at together
+  for (int base = 0; base < n; base += kMany) {
+    const int cnt = n - base < kMany ? n - base : kMany;
+    int var[kMany], left = 0;
+    for (int i = 0; i < cnt; ++i) {
+      var[i] = variant(*b[base + i]);
+      left += var[i] >= 0;
+    }
+    bool first = base == 0;
+    for (int i = 0; i < cnt && left > 0; ++i) {
+      if (var[i] < 0) continue;
+      const int v = var[i];
+      const BatchRef* group[kMaxSeg];
+      int k = 0;
+      for (int j = i; j < cnt && k < kMaxSeg; ++j)
+        if (var[j] == v) { group[k++] = b[base + j]; var[j] = -1; }
+      left -= k;
+      const bool last = left == 0 && base + cnt == n;
+      OD_RETURN_IF(one(v, group, k, (first ? 1 : 0) | (last ? 2 : 0)));
+      first = false;
+      if (left > 0) --i;                      // more of the same variant may remain behind this position
+    }
+  }
   return hipSuccess;
 }
+
+static int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+static int copy_blocks(int64_t count4, int most) {
+  const int64_t blocks = (count4 + 255) / 256;
+  return blocks < 1 ? 1 : blocks > most ? most : (int)blocks;
+}
+
+hipError_t launch_begin(BatchList b, int n, Prec prec, hipStream_t st) {
+  const bool fast = prec == PREC_F16;
+  SegList<BeginArgs> segs;
+  MatChunk chunk = {};
+  int used = 0;
+  auto flush = [&]() -> hipError_t {
+    used = 0;
+    if (!fast) return segs.launch(k_begin<SrcF32, false, One<BeginArgs>>, k_begin<SrcF32, false, Segs<BeginArgs>>, 256, 0, st, 0, chunk);
+    return b[0]->d.g_bf16 ? segs.launch(k_begin<SrcBF16, true, One<BeginArgs>>, k_begin<SrcBF16, true, Segs<BeginArgs>>, 256, 0, st, 0, chunk) : segs.launch(k_begin<SrcF32, true, One<BeginArgs>>, k_begin<SrcF32, true, Segs<BeginArgs>>, 256, 0, st, 0, chunk);
+  };
+  for (int i = 0; i < n; ++i) {
+    const BatchRef& r = *b[i];
+    const int per_mat = fast ? kStatRows + ceil_div(r.d.n, 64) * ceil_div(r.d.r, 64) : 1;
+    for (int z = 0; z < r.d.nb;) {
+      if (used == kMatChunk || segs.full()) OD_RETURN_IF(flush());
+      const int take = r.d.nb - z < kMatChunk - used ? r.d.nb - z : kMatChunk - used;
+      for (int k = 0; k < take; ++k) chunk.e[used + k] = r.host_mats[z + k];
+      BeginArgs a = {};
+      a.d = r.d;
+      a.table = const_cast<MatEntry*>(r.mats) + z;
+      a.chunk0 = used;
+      a.scal = r.scal + (int64_t)z * kScalPerMat;
+      a.info = r.info + (int64_t)z * kInfoPerMat;
+      a.qht = HalfArr{r.qht.base + (int64_t)z * r.qht.stride, r.qht.stride};
+      segs.add(a, per_mat, 1, take);
+      used += take;
+      z += take;
+    }
+  }
+  return flush();
+}
+
+// ---- projection and back-projection -------------------------------------------------
 // shapes the direct-to-LDS contraction takes (fast precision only): bf16 gradients, a rank
 // that fills its 256- or 512-column tiles reasonably, at least one whole 32-deep step
-bool stream_kernel_eligible(const ClassDims& d) {
-  return d.g_bf16 && d.r >= 192 && d.m >= 32 && d.n >= 32 && !kernel_choice("stream", "old");
-}
-int stream_tile_cols(int r) { return r <= 256 ? 256 : 512; }
+static bool stream_kernel_eligible(const ClassDims& d) { return d.g_bf16 && d.r >= 192 && d.m >= 32 && d.n >= 32; }
+static int stream_tile_cols(int r) { return r <= 256 ? 256 : 512; }
+// Few wide tiles need many splits to fill the chip; 64-row tiles get there with half of them,
+// i.e. half the partial sums to write and to add up.  With enough tiles the wide one wins.
+// `peers`: matrices of this shape that would fill the launch the batch is part of.
+static bool proj_uses_flat_tiles(int m, int r, int64_t peers) { return r > 128 && (int64_t)ceil_div(m, 128) * ceil_div(r, 256) * peers < 256; }
 
-hipError_t launch_proj(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal, WsArr part, int splits, HalfArr qht, hipStream_t st) {
-  if (prec == PREC_F16 && stream_kernel_eligible(d))
-    return stream_tile_cols(d.r) == 256 ? stream_d_t<false, 256>(d, ptrs, scal, part, splits, qht, st)
-                                        : stream_d_t<false, 512>(d, ptrs, scal, part, splits, qht, st);
-  return d.g_bf16 ? proj_g<SrcBF16>(d, ptrs, prec, scal, part, splits, qht, st) : proj_g<SrcF32>(d, ptrs, prec, scal, part, splits, qht, st);
+void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, int* rows, int* cols, int* slots) {
+  *rows = 128;
+  *cols = d.r <= 64 ? 64 : (d.r <= 128 ? 128 : 256);
+  *slots = 512;                                // two workgroups per CU
+  if (prec != PREC_F16) return;
+  if (stream_kernel_eligible(d)) {             // one 8-wave workgroup per CU
+    *cols = stream_tile_cols(d.r);
+    *slots = 256;
+  } else if (proj_uses_flat_tiles(d.m, d.r, peers)) {
+    *rows = 64;
+  }
+}
+void back_tiling(const ClassDims& d, Prec prec, int* rows, int* cols, int* slots) {
+  *rows = 128;
+  *cols = d.r <= 64 ? 64 : (d.r <= 128 ? 128 : 256);
+  *slots = 512;
+  if (prec == PREC_F16 && stream_kernel_eligible(d)) {
+    *cols = stream_tile_cols(d.r);
+    *slots = 256;
+  }
+}
+
+enum ProjVariant : int { PV_STREAM256, PV_STREAM512, PV_NARROW, PV_SQUARE, PV_FLAT, PV_FLAT2, PV_WIDE, PV_HUGE, PV_EXACT_SMALL, PV_EXACT };
+
+static StreamArgs stream_args(const BatchRef& r, bool back) {
+  StreamArgs a = {};
+  a.d = r.d;
+  a.mats = r.mats;
+  a.only = r.host_mats[0];
+  a.scal = r.scal;
+  a.info = r.info;
+  a.factor = r.pa;
+  a.fh = back ? r.pht : r.qht;
+  a.splits = back ? r.splits_back : r.splits_proj;
+  a.part = a.splits == 1 ? (back ? r.ra : r.pa) : r.part;
+  return a;
+}
+// one matrix whose rows are a multiple of 32 KB apart (in M): measured 10-20 % faster with
+// rotated k order at 8192 columns; with several matrices in flight the order does not matter
+static bool rows_share_channels(const BatchRef& r) { return r.peers == 1 && (r.d.ldm * (int64_t)sizeof(float)) % 32768 == 0; }
+
+template <class T, class Num, class GSrc, int PF = 1>
+static hipError_t proj_t(BatchList b, int n, hipStream_t st, int timed) {
+  SegList<StreamArgs> segs;
+  for (int i = 0; i < n; ++i) {
+    StreamArgs a = stream_args(*b[i], false);
+    a.rotate = rows_share_channels(*b[i]) ? 1 : 0;
+    segs.add(a, ceil_div(a.d.m, T::MT) * ceil_div(a.d.r, T::NT), a.splits, a.d.nb);
+  }
+  return segs.launch(k_proj<T, Num, GSrc, PF, One<StreamArgs>>, k_proj<T, Num, GSrc, PF, Segs<StreamArgs>>, T::THREADS, T::template lds_bytes<Num>(), st, timed);
+}
+template <bool TRANS, int NT>
+static hipError_t stream_d_t(BatchList b, int n, hipStream_t st, int timed) {
+  constexpr int SB = NT == 512 ? 2 : 3;
+  constexpr int lds = SB * NT * 64 + 3 * (128 * 32 * 6) + 2 * (TRANS ? 32 * 320 : 128 * 64);
+  SegList<StreamArgs> segs;
+  for (int i = 0; i < n; ++i) {
+    StreamArgs a = stream_args(*b[i], TRANS);
+    if (TRANS && a.splits == 1) a.rh = b[i]->rh;
+    // rotated k order for the projection of a single matrix at 8192 columns (see the kernel): 120 ->
+    // 102 us at r = 256.  With several matrices in flight the order does not matter, and the
+    // 512-column tiles of the larger ranks are not waiting for memory (no gain measured there).
+    a.rotate = !TRANS && NT == 256 && rows_share_channels(*b[i]) ? 1 : 0;
+    segs.add(a, ceil_div(TRANS ? a.d.n : a.d.m, 128) * ceil_div(a.d.r, NT), a.splits, a.d.nb);
+  }
+  return segs.launch(k_stream_d<TRANS, NT, SB, One<StreamArgs>>, k_stream_d<TRANS, NT, SB, Segs<StreamArgs>>, 512, lds, st, timed);
+}
+template <class GSrc>
+static hipError_t proj_v(int v, BatchList b, int n, hipStream_t st, int timed) {
+  switch (v) {
+    case PV_NARROW: return proj_t<TileNarrow, NumF16, GSrc>(b, n, st, timed);
+    case PV_SQUARE: return proj_t<TileSquare, NumF16, GSrc>(b, n, st, timed);
+    case PV_FLAT: return proj_t<TileFlat, NumF16, GSrc>(b, n, st, timed);
+    case PV_FLAT2: return proj_t<TileFlat, NumF16, GSrc, 2>(b, n, st, timed);
+    case PV_WIDE: return proj_t<TileWide, NumF16, GSrc>(b, n, st, timed);
+    case PV_EXACT_SMALL: return proj_t<TileSmall, NumBF<3>, GSrc>(b, n, st, timed);
+    default: return proj_t<TileSquare, NumBF<3>, GSrc>(b, n, st, timed);
+  }
+}
+hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st) {
+  const auto variant = [&](const BatchRef& r) -> int {
+    const ClassDims& d = r.d;
+    if (prec == PREC_BF3)
+      // small problems: 64-deep steps halve the number of round trips of a loop that is all latency
+      return (int64_t)ceil_div(d.m, 128) * ceil_div(d.r, 128) * r.splits_proj * r.peers < 256 ? PV_EXACT_SMALL : PV_EXACT;
+    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
+    if (d.r <= 64) return PV_NARROW;
+    if (d.r <= 128) return PV_SQUARE;
+    // long enough K loops per column tile pay for a second register stage
+    if (proj_uses_flat_tiles(d.m, d.r, r.peers)) return d.r > 256 ? PV_FLAT2 : PV_FLAT;
+    return PV_WIDE;
+  };
+  return by_variant(b, n, variant, [&](int v, BatchList g, int k, int timed) -> hipError_t {
+    if (v == PV_STREAM256) return stream_d_t<false, 256>(g, k, st, timed);
+    if (v == PV_STREAM512) return stream_d_t<false, 512>(g, k, st, timed);
+    return g[0]->d.g_bf16 ? proj_v<SrcBF16>(v, g, k, st, timed) : proj_v<SrcF32>(v, g, k, st, timed);
+  });
 }
 
 template <class T, class Num, class GSrc, int PF = 1>
-static hipError_t back_t(const ClassDims& d, const MatPtrs& ptrs, const float* scal, WsArr p, WsArr part, int splits, HalfArr pht, hipStream_t st) {
-  constexpr int lds = T::template lds_bytes<Num>();
-  hipError_t e = allow_lds(k_back<T, Num, GSrc, PF>, lds);
-  if (e != hipSuccess) return e;
-  dim3 grid(((d.n + T::MT - 1) / T::MT) * ((d.r + T::NT - 1) / T::NT), splits, d.nb);
-  launch_timed(k_back<T, Num, GSrc, PF>, grid, dim3(T::THREADS), lds, st, d, ptrs, scal, p, part, splits, pht);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
+static hipError_t back_t(BatchList b, int n, hipStream_t st, int timed) {
+  SegList<StreamArgs> segs;
+  for (int i = 0; i < n; ++i) {
+    const StreamArgs a = stream_args(*b[i], true);
+    segs.add(a, ceil_div(a.d.n, T::MT) * ceil_div(a.d.r, T::NT), a.splits, a.d.nb);
+  }
+  return segs.launch(k_back<T, Num, GSrc, PF, One<StreamArgs>>, k_back<T, Num, GSrc, PF, Segs<StreamArgs>>, T::THREADS, T::template lds_bytes<Num>(), st, timed);
 }
 template <class GSrc>
-static hipError_t back_g(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal, WsArr p, WsArr part, int splits, HalfArr pht, hipStream_t st) {
-  if (prec == PREC_BF3) {
-    if ((int64_t)((d.n + 127) / 128) * ((d.r + 127) / 128) * splits * d.nb < 256)
-      return back_t<TileSmall, NumBF<3>, GSrc>(d, ptrs, scal, p, part, splits, pht, st);
-    return back_t<TileSquare, NumBF<3>, GSrc>(d, ptrs, scal, p, part, splits, pht, st);
+static hipError_t back_v(int v, BatchList b, int n, hipStream_t st, int timed) {
+  switch (v) {
+    case PV_NARROW: return back_t<TileNarrow, NumF16, GSrc>(b, n, st, timed);
+    case PV_SQUARE: return back_t<TileSquare, NumF16, GSrc>(b, n, st, timed);
+    case PV_HUGE: return back_t<TileHuge, NumF16, GSrc, 2>(b, n, st, timed);
+    case PV_WIDE: return back_t<TileWide, NumF16, GSrc>(b, n, st, timed);
+    case PV_EXACT_SMALL: return back_t<TileSmall, NumBF<3>, GSrc>(b, n, st, timed);
+    default: return back_t<TileSquare, NumBF<3>, GSrc>(b, n, st, timed);
   }
-  if (d.r <= 64) return back_t<TileNarrow, NumF16, GSrc>(d, ptrs, scal, p, part, splits, pht, st);
-  if (d.r <= 128) return back_t<TileSquare, NumF16, GSrc>(d, ptrs, scal, p, part, splits, pht, st);
-  // several column tiles per row panel: 256 x 256 tiles halve the operand traffic per product
-  // and run one workgroup per CU with two register stages of loads in flight
-  if (d.r > 256) return back_t<TileHuge, NumF16, GSrc, 2>(d, ptrs, scal, p, part, splits, pht, st);
-  return back_t<TileWide, NumF16, GSrc>(d, ptrs, scal, p, part, splits, pht, st);
 }
-bool back_writes_fp16_copy(const ClassDims& d, Prec prec, int splits) { return prec == PREC_F16 && splits == 1 && stream_kernel_eligible(d); }
+hipError_t launch_back(BatchList b, int n, Prec prec, hipStream_t st) {
+  const auto variant = [&](const BatchRef& r) -> int {
+    const ClassDims& d = r.d;
+    if (prec == PREC_BF3)
+      return (int64_t)ceil_div(d.n, 128) * ceil_div(d.r, 128) * r.splits_back * r.peers < 256 ? PV_EXACT_SMALL : PV_EXACT;
+    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
+    if (d.r <= 64) return PV_NARROW;
+    if (d.r <= 128) return PV_SQUARE;
+    // several column tiles per row panel: 256 x 256 tiles halve the operand traffic per product
+    // and run one workgroup per CU with two register stages of loads in flight
+    return d.r > 256 ? PV_HUGE : PV_WIDE;
+  };
+  return by_variant(b, n, variant, [&](int v, BatchList g, int k, int timed) -> hipError_t {
+    if (v == PV_STREAM256) return stream_d_t<true, 256>(g, k, st, timed);
+    if (v == PV_STREAM512) return stream_d_t<true, 512>(g, k, st, timed);
+    return g[0]->d.g_bf16 ? back_v<SrcBF16>(v, g, k, st, timed) : back_v<SrcF32>(v, g, k, st, timed);
+  });
+}
 
-hipError_t launch_back(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal, WsArr p, WsArr part, int splits, HalfArr pht, hipStream_t st,
-                       HalfArr rh, int* info) {
-  if (prec == PREC_F16 && stream_kernel_eligible(d)) {
-    const HalfArr none{nullptr, 0};
-    const bool copy = back_writes_fp16_copy(d, prec, splits) && rh.base != nullptr && info != nullptr;
-    return stream_tile_cols(d.r) == 256 ? stream_d_t<true, 256>(d, ptrs, scal, part, splits, pht, st, copy ? rh : none, info)
-                                        : stream_d_t<true, 512>(d, ptrs, scal, part, splits, pht, st, copy ? rh : none, info);
-  }
-  return d.g_bf16 ? back_g<SrcBF16>(d, ptrs, prec, scal, p, part, splits, pht, st) : back_g<SrcF32>(d, ptrs, prec, scal, p, part, splits, pht, st);
+// ---- ordered sums of partials ----------------------------------------------------------
+static void add_reduce(SegList<ReduceArgs>& segs, int nb, WsArr part, int splits, int64_t count, WsArr out, Pred pred) {
+  ReduceArgs a = {};
+  a.part = part;
+  a.out = out;
+  a.count = count;
+  a.splits = splits;
+  a.pred = pred;
+  segs.add(a, copy_blocks(count / 4, 2048), 1, nb);
 }
+static const Pred kAlways = {nullptr, 0, 0.f, 0};
 
 hipError_t launch_reduce(int nb, WsArr part, int splits, int64_t count, WsArr out, hipStream_t st, Pred pred) {
-  int64_t n4 = count / 4;
-  int blocks = (int)((n4 + 255) / 256);
-  if (blocks > 2048) blocks = 2048;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_reduce, dim3(blocks, nb), dim3(256), 0, st, part, splits, count, out, pred);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
+  SegList<ReduceArgs> segs;
+  add_reduce(segs, nb, part, splits, count, out, pred);
+  return segs.launch(k_reduce<One<ReduceArgs>>, k_reduce<Segs<ReduceArgs>>, 256, 0, st, 0);
+}
+hipError_t launch_proj_reduce(BatchList b, int n, hipStream_t st) {
+  return by_variant(b, n, [](const BatchRef& r) { return r.splits_proj > 1 ? 0 : -1; }, [&](int, BatchList g, int k, int) {
+    SegList<ReduceArgs> segs;
+    for (int i = 0; i < k; ++i) add_reduce(segs, g[i]->d.nb, g[i]->part, g[i]->splits_proj, (int64_t)g[i]->d.m * g[i]->d.r, g[i]->pa, kAlways);
+    return segs.launch(k_reduce<One<ReduceArgs>>, k_reduce<Segs<ReduceArgs>>, 256, 0, st, 0);
+  });
+}
+hipError_t launch_back_reduce(BatchList b, int n, Prec prec, hipStream_t st) {
+  const auto variant = [&](const BatchRef& r) -> int {
+    if (prec != PREC_F16) return r.splits_back > 1 ? 0 : -1;
+    return r.splits_back == 1 && stream_kernel_eligible(r.d) ? -1 : 1;      // that kernel has written the fp16 copy itself
+  };
+  return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
+    if (v == 0) {
+      SegList<ReduceArgs> segs;
+      for (int i = 0; i < k; ++i) add_reduce(segs, g[i]->d.nb, g[i]->part, g[i]->splits_back, (int64_t)g[i]->d.n * g[i]->d.r, g[i]->ra, kAlways);
+      return segs.launch(k_reduce<One<ReduceArgs>>, k_reduce<Segs<ReduceArgs>>, 256, 0, st, 0);
+    }
+    SegList<ReduceRArgs> segs;
+    for (int i = 0; i < k; ++i) {
+      const BatchRef& r = *g[i];
+      ReduceRArgs a = {};
+      a.d = r.d;
+      a.part = r.splits_back == 1 ? r.ra : r.part;
+      a.out = r.ra;
+      a.splits = r.splits_back;
+      a.rh = r.rh;
+      a.scal = r.scal;
+      a.info = r.info;
+      segs.add(a, copy_blocks((int64_t)r.d.n * r.d.r / 4, 2048), 1, r.d.nb);
+    }
+    return segs.launch(k_reduce_r<One<ReduceRArgs>>, k_reduce_r<Segs<ReduceRArgs>>, 256, 0, st, 0);
+  });
 }
 
-hipError_t launch_reduce_r(const ClassDims& d, WsArr part, int splits, WsArr out, HalfArr rh, const float* scal, int* info, hipStream_t st) {
-  int64_t n4 = (int64_t)d.n * d.r / 4;
-  int blocks = (int)((n4 + 255) / 256);
-  if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(k_reduce_r, dim3(blocks, d.nb), dim3(256), 0, st, d, part, splits, out, rh, scal, info);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
+// ---- orthogonalisation ------------------------------------------------------------------
+// Ranks of one 32 x 32 tile take the first CholeskyQR pass in a single launch, factorisation included.
+static bool small_rank(const BatchRef& r) { return r.d.r <= 32; }
 
+// Gram partials of a0 (`first`, into gram_out or with several splits `part`) or a1 (into `part`)
 template <class T, class Num>
-static hipError_t gram_tt(int nb, int rows, int r, WsArr a, WsArr part, int splits, hipStream_t st, const ClassDims& d, const float* scal, int side) {
-  constexpr int lds = T::template lds_bytes<Num>();
-  hipError_t e = allow_lds(k_gram<T, Num>, lds);
-  if (e != hipSuccess) return e;
-  int tiles = (r + T::NT - 1) / T::NT;
-  hipLaunchKernelGGL((k_gram<T, Num>), dim3(tiles * (tiles + 1) / 2, splits, nb), dim3(T::THREADS), lds, st, rows, r, a, part, splits, d, scal, side);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-template <class Num>
-static hipError_t gram_t(int nb, int rows, int r, WsArr a, WsArr part, int splits, hipStream_t st, const ClassDims& d, const float* scal, int side) {
-  // few large tiles leave most of the chip idle: use small ones until the grid fills it
-  const int big = ((r + 127) / 128) * ((r + 127) / 128) * splits * nb;
-  if (big < 512) return gram_tt<TileSmall, Num>(nb, rows, r, a, part, splits, st, d, scal, side);
-  return gram_tt<TileSquare, Num>(nb, rows, r, a, part, splits, st, d, scal, side);
-}
-hipError_t launch_gram(int nb, int rows, int r, WsArr a, WsArr part, int splits, int mode, hipStream_t st, const ClassDims* d,
-                       const float* scal, int side) {
-  const ClassDims none = {};
-  if (mode == kGramH2) {
-    if (side != 2 && (d == nullptr || scal == nullptr)) return hipErrorInvalidValue;
-    return gram_t<NumH2>(nb, rows, r, a, part, splits, st, d ? *d : none, scal, side);
+static hipError_t gram_tt(BatchList b, int n, int side, bool first, hipStream_t st) {
+  SegList<GramArgs> segs;
+  for (int i = 0; i < n; ++i) {
+    const BatchRef& r = *b[i];
+    GramArgs a = {};
+    a.d = r.d;
+    a.scal = r.scal;
+    a.rows = r.rows(side);
+    a.r = r.d.r;
+    a.splits = r.splits_gram[side];
+    a.side = first ? side : 2;
+    a.a = first ? r.a0(side) : r.a1(side);
+    a.part = first && a.splits == 1 ? r.gram : r.part;       // a single split is the Gram matrix itself
+    const int tiles = ceil_div(a.r, T::NT);
+    segs.add(a, tiles * (tiles + 1) / 2, a.splits, r.d.nb);
   }
-  return mode == kGramBF3 ? gram_t<NumBF<3>>(nb, rows, r, a, part, splits, st, none, nullptr, -1)
-                          : gram_t<NumBF<2>>(nb, rows, r, a, part, splits, st, none, nullptr, -1);
+  return segs.launch(k_gram<T, Num, One<GramArgs>>, k_gram<T, Num, Segs<GramArgs>>, T::THREADS, T::template lds_bytes<Num>(), st, 0);
 }
+static hipError_t gram_pass(BatchList b, int n, int side, bool first, Prec prec, hipStream_t st) {
+  const auto variant = [&](const BatchRef& r) -> int {
+    if (small_rank(r)) return -1;
+    // few large tiles leave most of the chip idle: use small ones until the grid fills it
+    const int64_t t = ceil_div(r.d.r, 128);
+    return t * t * r.splits_gram[side] * r.peers < 512 ? 0 : 1;
+  };
+  return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
+    // fast precision has the sampled scale of B at hand: two-term fp16 operands (half the
+    // matrix-core work of the three-way bf16 split at 22 instead of 24 bits)
+    if (prec == PREC_F16) return v == 0 ? gram_tt<TileSmall, NumH2>(g, k, side, first, st) : gram_tt<TileSquare, NumH2>(g, k, side, first, st);
+    return v == 0 ? gram_tt<TileSmall, NumBF<3>>(g, k, side, first, st) : gram_tt<TileSquare, NumBF<3>>(g, k, side, first, st);
+  });
+}
+hipError_t launch_gram_plain(int nb, int rows, int r, WsArr a, WsArr part, int splits, hipStream_t st) {
+  GramArgs ga = {};
+  ga.rows = rows;
+  ga.r = r;
+  ga.splits = splits;
+  ga.side = -1;
+  ga.a = a;
+  ga.part = part;
+  SegList<GramArgs> segs;
+  const int t = ceil_div(r, 128);
+  const int tiles = (int64_t)t * t * splits * nb < 512 ? ceil_div(r, 64) : t;
+  segs.add(ga, tiles * (tiles + 1) / 2, splits, nb);
+  return tiles == t && r > 64 ? segs.launch(k_gram<TileSquare, NumBF<3>, One<GramArgs>>, k_gram<TileSquare, NumBF<3>, Segs<GramArgs>>, TileSquare::THREADS, TileSquare::lds_bytes<NumBF<3>>(), st, 0)
+                              : segs.launch(k_gram<TileSmall, NumBF<3>, One<GramArgs>>, k_gram<TileSmall, NumBF<3>, Segs<GramArgs>>, TileSmall::THREADS, TileSmall::lds_bytes<NumBF<3>>(), st, 0);
+}
+
+static hipError_t small_pass(BatchList b, int n, int side, bool first_pass, hipStream_t st) {
+  return by_variant(b, n, [](const BatchRef& r) { return small_rank(r) ? 0 : -1; }, [&](int, BatchList g, int k, int) -> hipError_t {
+    SegList<SmallArgs> segs;
+    for (int i = 0; i < k; ++i) {
+      const BatchRef& r = *g[i];
+      SmallArgs a = {};
+      a.rows = r.rows(side);
+      a.r = r.d.r;
+      a.splits = r.splits_gram[side];
+      a.a0 = r.a0(side);
+      a.a1 = r.a1(side);
+      a.gram = r.part;
+      a.part = WsArr{r.part.base + (int64_t)a.splits * a.r * a.r, r.part.stride};
+      a.t1 = r.t1[side];
+      a.w1 = r.w;
+      a.info = r.info;
+      a.info_slot = side;
+      segs.add(a, a.splits, 1, r.d.nb);
+    }
+    return first_pass ? segs.launch(k_small_first_pass<One<SmallArgs>>, k_small_first_pass<Segs<SmallArgs>>, kSmallRows, 0, st, 0) : segs.launch(k_small_gram<One<SmallArgs>>, k_small_gram<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
+  });
+}
+
+hipError_t launch_orth_gram(BatchList b, int n, int side, Prec prec, hipStream_t st) {
+  OD_RETURN_IF(small_pass(b, n, side, false, st));
+  OD_RETURN_IF(gram_pass(b, n, side, true, prec, st));
+  // ordered reduction of the split partial sums on many workgroups: the factorisation runs on
+  // one workgroup per matrix and should not spend its time summing
+  return by_variant(b, n, [&](const BatchRef& r) { return !small_rank(r) && r.splits_gram[side] > 1 ? 0 : -1; }, [&](int, BatchList g, int k, int) {
+    SegList<ReduceArgs> segs;
+    for (int i = 0; i < k; ++i) add_reduce(segs, g[i]->d.nb, g[i]->part, g[i]->splits_gram[side], (int64_t)g[i]->d.r * g[i]->d.r, g[i]->gram, kAlways);
+    return segs.launch(k_reduce<One<ReduceArgs>>, k_reduce<Segs<ReduceArgs>>, 256, 0, st, 0);
+  });
+}
+
+// ---- triangular products
+enum ApplyKind : int { APPLY_W, APPLY_FULL, APPLY_CORRECTION };     // a0 W1 -> a1; a1 W2 -> result; a1 - a1 Phi -> result
+static Pred deviation(const BatchRef& r, int side, int want) { return Pred{r.scal, 2 + side, kFirstOrderDeviation, want}; }
 
 template <class T, class Num, bool DEEP, bool CORR>
-static hipError_t apply_tt(int nb, int rows, int r, WsArr a, WsArr w, HalfArr wh, WsArr out, const MatPtrs* ptrs, HalfArr hn, HalfArr ht, hipStream_t st, Pred pred) {
-  constexpr int lds = T::template lds_bytes<Num>();
-  hipError_t e = allow_lds(k_apply<T, Num, DEEP, CORR>, lds);
-  if (e != hipSuccess) return e;
-  MatPtrs none = {};
-  dim3 grid(((rows + T::MT - 1) / T::MT) * ((r + T::NT - 1) / T::NT), 1, nb);
-  hipLaunchKernelGGL((k_apply<T, Num, DEEP, CORR>), grid, dim3(T::THREADS), lds, st, rows, r, a, w, wh, out, ptrs ? *ptrs : none, ptrs ? 1 : 0, hn, ht, pred);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
+static hipError_t apply_tt(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
+  SegList<ApplyArgs> segs;
+  for (int i = 0; i < n; ++i) {
+    const BatchRef& r = *b[i];
+    ApplyArgs a = {};
+    a.rows = r.rows(side);
+    a.r = r.d.r;
+    a.w = r.w;
+    a.pred = kAlways;
+    if (kind == APPLY_W) {
+      a.a = r.a0(side);
+      a.out = r.a1(side);
+    } else {
+      a.a = r.a1(side);
+      a.out = r.a0(side);
+      a.q_mats = side == 1 ? r.mats : nullptr;
+      if (side == 1 && r.d.nb == 1) a.only_q = r.host_mats[0].Q;
+      if (prec == PREC_F16) {
+        a.wh = HalfArr{reinterpret_cast<uint16_t*>(r.tmp.base), 2 * r.tmp.stride};      // Phi^T (see k_corr)
+        a.pred = deviation(r, side, kind == APPLY_FULL ? 1 : 0);
+        a.hn = side == 0 ? r.ph : r.qh;
+        if (side == 0) a.ht = r.pht;
+      }
+    }
+    segs.add(a, ceil_div(a.rows, T::MT) * ceil_div(a.r, T::NT), 1, r.d.nb);
+  }
+  return segs.launch(k_apply<T, Num, DEEP, CORR, One<ApplyArgs>>, k_apply<T, Num, DEEP, CORR, Segs<ApplyArgs>>, T::THREADS, T::template lds_bytes<Num>(), st, 0);
 }
 template <class Num, bool CORR>
-static hipError_t apply_t(int nb, int rows, int r, WsArr a, WsArr w, HalfArr wh, WsArr out, const MatPtrs* ptrs, HalfArr hn, HalfArr ht, hipStream_t st, Pred pred) {
-  const int big = ((rows + 127) / 128) * ((r + 127) / 128) * nb;
-  if (big < 512) return apply_tt<TileSmall, Num, true, CORR>(nb, rows, r, a, w, wh, out, ptrs, hn, ht, st, pred);
-  // 128 columns per tile: the loop of a column tile ends at its last row of W (upper triangular),
-  // so narrower tiles skip more of the zero half than 256-column ones would (measured -10 %)
-  // one operand part leaves LDS room for 64-deep steps at two workgroups per CU (measured -13 to
-  // -23 %); with two parts the deeper tile halves the occupancy and loses
-  if constexpr (Num::PARTS == 1) return apply_tt<TileSquareDeepK, Num, false, CORR>(nb, rows, r, a, w, wh, out, ptrs, hn, ht, st, pred);
-  else return apply_tt<TileSquare, Num, false, CORR>(nb, rows, r, a, w, wh, out, ptrs, hn, ht, st, pred);
+static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
+  const auto variant = [&](const BatchRef& r) -> int {
+    if (kind == APPLY_W && small_rank(r)) return -1;
+    return (int64_t)ceil_div(r.rows(side), 128) * ceil_div(r.d.r, 128) * r.peers < 512 ? 0 : 1;
+  };
+  return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
+    if (v == 0) return apply_tt<TileSmall, Num, true, CORR>(g, k, side, kind, prec, st);
+    // 128 columns per tile: the loop of a column tile ends at its last row of W (upper triangular),
+    // so narrower tiles skip more of the zero half than 256-column ones would (measured -10 %)
+    // one operand part leaves LDS room for 64-deep steps at two workgroups per CU (measured -13 to
+    // -23 %); with two parts the deeper tile halves the occupancy and loses
+    if constexpr (Num::PARTS == 1) return apply_tt<TileSquareDeepK, Num, false, CORR>(g, k, side, kind, prec, st);
+    else return apply_tt<TileSquare, Num, false, CORR>(g, k, side, kind, prec, st);
+  });
 }
-hipError_t launch_apply(int nb, int rows, int r, WsArr a, WsArr w, WsArr out, const MatPtrs* q_ptrs, HalfArr hn, HalfArr ht, int exact, hipStream_t st, Pred pred) {
-  const HalfArr none{nullptr, 0};
-  return exact ? apply_t<NumBF<3>, false>(nb, rows, r, a, w, none, out, q_ptrs, hn, ht, st, pred) : apply_t<NumBF<2>, false>(nb, rows, r, a, w, none, out, q_ptrs, hn, ht, st, pred);
-}
-hipError_t launch_apply_correction(int nb, int rows, int r, WsArr a, HalfArr phit, WsArr out, const MatPtrs* q_ptrs, HalfArr hn, HalfArr ht, hipStream_t st, Pred pred) {
-  const WsArr unused{nullptr, 0};
-  return apply_t<NumF16, true>(nb, rows, r, a, unused, phit, out, q_ptrs, hn, ht, st, pred);
+static hipError_t apply_product(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
+  return prec == PREC_BF3 ? apply_t<NumBF<3>, false>(b, n, side, kind, prec, st) : apply_t<NumBF<2>, false>(b, n, side, kind, prec, st);
 }
 
+// Gram partials of a1 (the second pass's input): behind those of a0 for small ranks
+static WsArr second_partials(const BatchRef& r, int side) {
+  WsArr p = r.part;
+  if (small_rank(r)) p.base += (int64_t)r.splits_gram[side] * r.d.r * r.d.r;
+  return p;
+}
+
+hipError_t launch_orth_second(BatchList b, int n, int side, Prec prec, hipStream_t st) {
+  OD_RETURN_IF(small_pass(b, n, side, true, st));
+  OD_RETURN_IF(apply_product(b, n, side, APPLY_W, prec, st));
+  OD_RETURN_IF(gram_pass(b, n, side, false, prec, st));
+  const auto all = [](const BatchRef&) { return 0; };
+  OD_RETURN_IF(by_variant(b, n, all, [&](int, BatchList g, int k, int) {
+    SegList<CorrArgs> segs;
+    for (int i = 0; i < k; ++i) {
+      const BatchRef& r = *g[i];
+      CorrArgs a = {};
+      a.r = r.d.r;
+      a.splits = r.splits_gram[side];
+      a.part = second_partials(r, side);
+      a.t1 = r.t1[side];
+      a.t2 = r.t2[side];
+      a.w2 = r.w;
+      // fast precision: Phi^T as fp16 operand words lives in the r x r scratch the factorisation no
+      // longer needs; exact precision: W2 = I - Phi(E)
+      if (prec == PREC_F16) a.phit = HalfArr{reinterpret_cast<uint16_t*>(r.tmp.base), 2 * r.tmp.stride};
+      a.scal = r.scal;
+      a.scal_slot = 2 + side;
+      a.info = r.info;
+      a.info_slot = side;
+      segs.add(a, copy_blocks((int64_t)a.r * a.r / 4, 1024), 1, r.d.nb);
+    }
+    return segs.launch(k_corr<One<CorrArgs>>, k_corr<Segs<CorrArgs>>, 256, 0, st, 0);
+  }));
+  // ranks above 256: the summed Gram matrix of a flagged matrix goes to the class array for the
+  // class-wide guard
+  return by_variant(b, n, [](const BatchRef& r) { return r.d.r > kCholMax ? 0 : -1; }, [&](int, BatchList g, int k, int) {
+    SegList<ReduceArgs> segs;
+    for (int i = 0; i < k; ++i)
+      add_reduce(segs, g[i]->d.nb, g[i]->part, g[i]->splits_gram[side], (int64_t)g[i]->d.r * g[i]->d.r, g[i]->gram, deviation(*g[i], side, 1));
+    return segs.launch(k_reduce<One<ReduceArgs>>, k_reduce<Segs<ReduceArgs>>, 256, 0, st, 0);
+  });
+}
+
+static hipError_t launch_leaf(const CholArgs* args, const int* counts, int n, hipStream_t st) {
+  SegList<CholArgs> segs;
+  for (int i = 0; i < n; ++i) {
+    segs.add(args[i], counts[i], 1, 1);
+    if (segs.full() || i + 1 == n) OD_RETURN_IF(segs.launch(k_chol256<One<CholArgs>>, k_chol256<Segs<CholArgs>>, kCholThreads, kCholLds, st, 0));
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st) {
+  return by_variant(b, n, [](const BatchRef& r) { return r.d.r <= kCholMax ? 0 : -1; }, [&](int, BatchList g, int k, int) {
+    CholArgs args[kMaxSeg];
+    int counts[kMaxSeg];
+    for (int i = 0; i < k; ++i) {
+      const BatchRef& r = *g[i];
+      CholArgs ca = {};
+      ca.t = r.t2[side];
+      ca.w = r.w;
+      ca.r = r.d.r;
+      ca.info = r.info;
+      ca.info_slot = side;
+      ca.src = second_partials(r, side);
+      ca.splits = r.splits_gram[side];
+      ca.split_stride = (int64_t)r.d.r * r.d.r;
+      ca.pred = deviation(r, side, 1);
+      args[i] = ca;
+      counts[i] = r.d.nb;
+    }
+    return launch_leaf(args, counts, k, st);
+  });
+}
+
+hipError_t launch_orth_result(BatchList b, int n, int side, Prec prec, int which, hipStream_t st) {
+  if (prec == PREC_BF3) return apply_product(b, n, side, APPLY_FULL, prec, st);
+  if (which != 2) OD_RETURN_IF((apply_t<NumF16, true>(b, n, side, APPLY_CORRECTION, prec, st)));
+  if (which != 1) OD_RETURN_IF(apply_product(b, n, side, APPLY_FULL, prec, st));
+  return hipSuccess;
+}
+
+// ---- Cholesky --------------------------------------------------------------------------
 template <class T, class Num, class DirA>
 static hipError_t sgemm_tt(int nb, const SgemmArgs& g, hipStream_t st) {
   constexpr int lds = T::template lds_bytes<Num>();
@@ -1867,22 +2365,17 @@ static hipError_t sgemm_pair(int nb, const SgemmArgs& g1, const SgemmArgs& g2, h
   return sgemm_pair_tt<TileSquare>(nb, g1, g2, st);
 }
 
-hipError_t launch_cholinv(int nb, int r, WsArr gram, WsArr t, WsArr w, WsArr tmp, int* info, int info_slot,
-                          hipStream_t st, Pred pred, int splits, int64_t split_stride) {
-  hipError_t e = allow_lds(k_chol256, kCholLds);
-  if (e != hipSuccess) return e;
+// ranks above 256: blocked factorisation of one class
+static hipError_t blocked_cholinv(const CholJob& job, hipStream_t st) {
+  const int nb = job.nb, r = job.r;
+  const WsArr gram = job.gram, t = job.t, w = job.w, tmp = job.tmp;
+  const Pred pred = job.pred;
+  hipError_t e;
   const int nblk = (r + kLeaf - 1) / kLeaf;
   CholArgs ca = {};
-  ca.t = t; ca.w = w; ca.r = r; ca.info = info; ca.info_slot = info_slot;
+  ca.t = t; ca.w = w; ca.r = r; ca.info = job.info; ca.info_slot = job.info_slot;
   ca.src = gram; ca.splits = 1; ca.split_stride = 0;
   ca.pred = pred;
-  if (nblk == 1) {
-    ca.splits = splits; ca.split_stride = split_stride;
-    ca.blk = 0;
-    hipLaunchKernelGGL(k_chol256, dim3(nb), dim3(kCholThreads), kCholLds, st, ca);
-    OD_CHECK_LAUNCH();
-    return hipSuccess;
-  }
   // lower block triangles of T and W are never written below; clear them once
   {
     const int64_t count = (int64_t)r * r;          // a multiple of 64
@@ -1905,8 +2398,7 @@ hipError_t launch_cholinv(int nb, int r, WsArr gram, WsArr t, WsArr w, WsArr tmp
   for (int p = 0; p < nblk; ++p) {
     if (p == 0) {
       ca.blk = 0;
-      hipLaunchKernelGGL(k_chol256, dim3(nb), dim3(kCholThreads), kCholLds, st, ca);
-      OD_CHECK_LAUNCH();
+      OD_RETURN_IF(launch_leaf(&ca, &nb, 1, st));
     }
     const int o = p * kLeaf, o1 = (p + 1) * kLeaf, rest = r > o1 ? r - o1 : 0;
     const int bw = r - o < kLeaf ? r - o : kLeaf;       // width of block column p
@@ -1963,133 +2455,118 @@ hipError_t launch_cholinv(int nb, int r, WsArr gram, WsArr t, WsArr w, WsArr tmp
   return hipSuccess;
 }
 
-hipError_t launch_small_gram(int nb, int rows, int r, WsArr a0, WsArr part, int splits, hipStream_t st) {
-  if (r > 32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_small_gram, dim3(splits, nb), dim3(kSmallRows), 0, st, rows, r, a0, part, splits);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
+hipError_t launch_cholinv(const CholJob* jobs, int njobs, hipStream_t st) {
+  CholArgs args[kMaxSeg];
+  int counts[kMaxSeg], k = 0;
+  for (int i = 0; i < njobs; ++i) {
+    const CholJob& j = jobs[i];
+    if (j.r > kLeaf) {
+      OD_RETURN_IF(blocked_cholinv(j, st));
+      continue;
+    }
+    CholArgs ca = {};
+    ca.t = j.t; ca.w = j.w; ca.r = j.r; ca.info = j.info; ca.info_slot = j.info_slot;
+    ca.src = j.gram; ca.splits = j.splits; ca.split_stride = j.split_stride;
+    ca.pred = j.pred;
+    args[k] = ca;
+    counts[k++] = j.nb;
+    if (k == kMaxSeg) {
+      OD_RETURN_IF(launch_leaf(args, counts, k, st));
+      k = 0;
+    }
+  }
+  return k > 0 ? launch_leaf(args, counts, k, st) : hipSuccess;
 }
 
-hipError_t launch_small_first_pass(int nb, int rows, int r, WsArr a0, WsArr gram, int gram_splits, WsArr t1, WsArr w1, WsArr a1,
-                                   WsArr part, int splits, int* info, int info_slot, hipStream_t st) {
-  if (r > 32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_small_first_pass, dim3(splits, nb), dim3(kSmallRows), 0, st, rows, r, a0, gram, gram_splits, t1, w1, a1,
-                     part, splits, info, info_slot);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
+hipError_t launch_colnorm(BatchList b, int n, Prec prec, hipStream_t st) {
+  const auto all = [](const BatchRef&) { return 0; };
+  return by_variant(b, n, all, [&](int, BatchList g, int k, int) -> hipError_t {
+    SegList<ColnormArgs> sum, fin, app;
+    for (int i = 0; i < k; ++i) {
+      const BatchRef& r = *g[i];
+      ColnormArgs a = {};
+      a.n = r.d.n;
+      a.r = r.d.r;
+      a.slabs = r.slabs;
+      a.rr = r.ra;
+      a.part = r.part;
+      a.colsq = r.colsq;
+      a.info = r.info;
+      a.mats = r.mats;
+      if (prec == PREC_F16) a.qh = r.qh;
+      sum.add(a, ceil_div(a.r, 256), a.slabs, r.d.nb);
+      fin.add(a, ceil_div(a.r, 256), 1, r.d.nb);
+      app.add(a, copy_blocks((int64_t)a.n * a.r / 4, 2048), 1, r.d.nb);
+    }
+    OD_RETURN_IF(sum.launch(k_colsq_partial<One<ColnormArgs>>, k_colsq_partial<Segs<ColnormArgs>>, 256, 0, st, 0));
+    OD_RETURN_IF(fin.launch(k_colsq_final<One<ColnormArgs>>, k_colsq_final<Segs<ColnormArgs>>, 256, 0, st, 0));
+    return app.launch(k_colnorm_apply<One<ColnormArgs>>, k_colnorm_apply<Segs<ColnormArgs>>, 256, 0, st, 0);
+  });
 }
 
-hipError_t launch_corr(int nb, int r, WsArr part, int splits, WsArr t1, WsArr t2, WsArr w2, HalfArr phit, float* scal, int scal_slot,
-                       int* info, int info_slot, hipStream_t st) {
-  int64_t count = (int64_t)r * r;
-  int blocks = (int)((count / 4 + 255) / 256);
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(k_corr, dim3(blocks, nb), dim3(256), 0, st, r, part, splits, t1, t2, w2, phit, scal, scal_slot, info, info_slot);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
-hipError_t launch_scale_from_trace(int nb, int n, int r, WsArr gram, float* scal, hipStream_t st) {
-  hipLaunchKernelGGL(k_scale_from_trace, dim3(nb), dim3(256), 0, st, n, r, gram, scal);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
-hipError_t launch_colnorm(int nb, int n, int r, WsArr rr, const MatPtrs& ptrs, WsArr part, int slabs, WsArr colsq,
-                          float* scal, int* info, HalfArr qh, hipStream_t st) {
-  hipLaunchKernelGGL(k_colsq_partial, dim3((r + 255) / 256, slabs, nb), dim3(256), 0, st, n, r, rr, part, slabs);
-  OD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_colsq_final, dim3(nb), dim3(256), 0, st, n, r, part, slabs, colsq, scal, info);
-  OD_CHECK_LAUNCH();
-  int64_t n4 = (int64_t)n * r / 4;
-  int blocks = (int)((n4 + 255) / 256);
-  if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(k_colnorm_apply, dim3(blocks, nb), dim3(256), 0, st, n, r, rr, colsq, ptrs, qh);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
-template <class T, class Num, bool XBF, bool GBF>
-static hipError_t efx_tt(const ClassDims& d, const MatPtrs& ptrs, const float* scal, const int* info, WsArr p, WsArr rr, float a_coef,
-                         float b_coef, float lr, hipStream_t st) {
-  constexpr int lds = T::template lds_bytes<Num>();
-  hipError_t e = allow_lds(k_efx<T, Num, XBF, GBF>, lds);
-  if (e != hipSuccess) return e;
-  dim3 grid(((d.m + T::NT - 1) / T::NT) * ((d.n + T::MT - 1) / T::MT), 1, d.nb);
-  launch_timed(k_efx<T, Num, XBF, GBF>, grid, dim3(T::THREADS), lds, st, d, ptrs, scal, info, p, rr, a_coef, b_coef, lr);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-template <class Num, bool XBF, bool GBF>
-static hipError_t efx_t(const ClassDims& d, const MatPtrs& ptrs, const float* scal, const int* info, WsArr p, WsArr rr, float a_coef,
-                        float b_coef, float lr, hipStream_t st) {
-  // small problems: more, smaller tiles (the kernel is a few microseconds of latency per tile)
-  if ((int64_t)((d.m + 127) / 128) * ((d.n + 127) / 128) * d.nb < 256)
-    return efx_tt<TileSmall, Num, XBF, GBF>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st);
-  return efx_tt<TileSquare, Num, XBF, GBF>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st);
-}
-template <class Num>
-static hipError_t efx_n(const ClassDims& d, const MatPtrs& ptrs, const float* scal, const int* info, WsArr p, WsArr rr, float a_coef,
-                        float b_coef, float lr, hipStream_t st) {
-  if (d.x_bf16) return d.g_bf16 ? efx_t<Num, true, true>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st)
-                                : efx_t<Num, true, false>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st);
-  return d.g_bf16 ? efx_t<Num, false, true>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st)
-                  : efx_t<Num, false, false>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st);
-}
-template <bool XBF, bool GBF>
-static hipError_t efx_h_t(const ClassDims& d_in, const MatPtrs& ptrs, const float* scal, int* info, HalfArr ph, HalfArr rh, HalfArr qh,
-                          float a_coef, float b_coef, float lr, hipStream_t st) {
-  ClassDims d = d_in;
+// ---- error feedback and update -----------------------------------------------------------
+static EfxArgs efx_args(const BatchRef& r) {
+  EfxArgs a = {};
+  a.d = r.d;
+  a.mats = r.mats;
+  a.only = r.host_mats[0];
+  a.scal = r.scal;
+  a.info = r.info;
+  a.p = r.pa;
+  a.rr = r.ra;
+  a.ph = r.ph;
+  a.rh = r.rh;
+  a.qh = r.qh;
   // up to r = 256 (above, the XCD-aware band order takes over) consecutive workgroups walk along a
   // row of tiles, i.e. through consecutive addresses of M, G, X, instead of down a column of tiles
   // whose rows lie a whole leading dimension apart: 8192 x 8192: 172 -> 156 us at r = 16, 233 ->
   // 224 us at r = 256; no difference at 4096 x 4096
-  d.col_fast = d.r <= 256 ? 1 : 0;
-  dim3 grid(((d.m + 127) / 128) * ((d.n + 127) / 128), 1, d.nb);
-  const bool stream = d.r > 256 || (int64_t)d.m * d.n * d.nb >= ((int64_t)48 << 20);
-  // ranks that are whole 32-deep steps take the direct-to-LDS kernel
-  if (d.r % 32 == 0 && d.r >= 64 && !kernel_choice("efx", "old")) {
+  a.d.col_fast = r.d.r <= 256 ? 1 : 0;
+  return a;
+}
+enum EfxVariant : int { EV_EXACT_SMALL, EV_EXACT, EV_H, EV_H_STREAM, EV_D, EV_D_STREAM, EV_TALL, EV_TALL_STREAM };
+
+template <class K1, class K2>
+static hipError_t efx_launch(K1 single, K2 multi, BatchList b, int n, int tile_i, int tile_j, int threads, int lds, EfxCoef coef, hipStream_t st, int timed) {
+  SegList<EfxArgs> segs;
+  for (int i = 0; i < n; ++i) segs.add(efx_args(*b[i]), ceil_div(b[i]->d.m, tile_i) * ceil_div(b[i]->d.n, tile_j), 1, b[i]->d.nb);
+  return segs.launch(single, multi, threads, lds, st, timed, coef);
+}
+template <bool XBF, bool GBF>
+static hipError_t efx_v(int v, BatchList b, int n, EfxCoef c, hipStream_t st, int timed) {
+  typedef NumBF<3> Num;
+  constexpr int lds_h = 2 * 3 * 128 * 80, lds_d = 3 * 3 * 128 * 64, lds_tall = 3 * (2 * 128 + 256) * 64;
+  switch (v) {
+    case EV_EXACT_SMALL: return efx_launch(k_efx<TileSmall, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSmall, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 64, 64, TileSmall::THREADS, TileSmall::lds_bytes<Num>(), c, st, timed);
+    case EV_EXACT: return efx_launch(k_efx<TileSquare, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSquare, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 128, 128, TileSquare::THREADS, TileSquare::lds_bytes<Num>(), c, st, timed);
+    case EV_H: return efx_launch(k_efx_h<XBF, GBF, false, One<EfxArgs>>, k_efx_h<XBF, GBF, false, Segs<EfxArgs>>, b, n, 128, 128, 512, lds_h, c, st, timed);
+    case EV_H_STREAM: return efx_launch(k_efx_h<XBF, GBF, true, One<EfxArgs>>, k_efx_h<XBF, GBF, true, Segs<EfxArgs>>, b, n, 128, 128, 512, lds_h, c, st, timed);
+    case EV_D: return efx_launch(k_efx_d<XBF, GBF, false, 2, One<EfxArgs>>, k_efx_d<XBF, GBF, false, 2, Segs<EfxArgs>>, b, n, 128, 128, 256, lds_d, c, st, timed);
+    case EV_D_STREAM: return efx_launch(k_efx_d<XBF, GBF, true, 2, One<EfxArgs>>, k_efx_d<XBF, GBF, true, 2, Segs<EfxArgs>>, b, n, 128, 128, 256, lds_d, c, st, timed);
+    case EV_TALL: return efx_launch(k_efx_d<XBF, GBF, false, 4, One<EfxArgs>>, k_efx_d<XBF, GBF, false, 4, Segs<EfxArgs>>, b, n, 256, 128, 512, lds_tall, c, st, timed);
+    default: return efx_launch(k_efx_d<XBF, GBF, true, 4, One<EfxArgs>>, k_efx_d<XBF, GBF, true, 4, Segs<EfxArgs>>, b, n, 256, 128, 512, lds_tall, c, st, timed);
+  }
+}
+hipError_t launch_efx(BatchList b, int n, Prec prec, float a_coef, float b_coef, float lr, hipStream_t st) {
+  const EfxCoef coef = {a_coef, b_coef, lr};
+  const auto variant = [&](const BatchRef& r) -> int {
+    const ClassDims& d = r.d;
+    // small problems: more, smaller tiles (the kernel is a few microseconds of latency per tile)
+    if (prec == PREC_BF3) return (int64_t)ceil_div(d.m, 128) * ceil_div(d.n, 128) * r.peers < 256 ? EV_EXACT_SMALL : EV_EXACT;
+    // nontemporal stores also for sets far beyond the Infinity Cache at any rank: they leave no dirty
+    // lines behind for the next kernel to wait on (measured on 8192 x 8192: the step is 2-7 % faster)
+    const int stream = d.r > 256 || (int64_t)d.m * d.n * r.peers >= ((int64_t)48 << 20) ? 1 : 0;
+    // ranks that are whole 32-deep steps take the direct-to-LDS kernel
+    if (d.r % 32 != 0 || d.r < 64) return EV_H + stream;
     // r > 256: 256-row tiles (one 8-wave workgroup per CU) while they still fill the chip twice:
     // a third less operand traffic into LDS per product than 128-row tiles
-    const int64_t tall = (int64_t)((d.m + 255) / 256) * ((d.n + 127) / 128) * d.nb;
-    if (d.r > 256 && tall >= 512 && !kernel_choice("efx", "dma128")) {
-      constexpr int lds_t = 3 * (2 * 128 + 256) * 64;
-      hipError_t e = stream ? allow_lds(k_efx_d<XBF, GBF, true, 4>, lds_t) : allow_lds(k_efx_d<XBF, GBF, false, 4>, lds_t);
-      if (e != hipSuccess) return e;
-      const dim3 tgrid(((d.m + 255) / 256) * ((d.n + 127) / 128), 1, d.nb);
-      if (stream) launch_timed(k_efx_d<XBF, GBF, true, 4>, tgrid, dim3(512), lds_t, st, d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr);
-      else launch_timed(k_efx_d<XBF, GBF, false, 4>, tgrid, dim3(512), lds_t, st, d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr);
-      OD_CHECK_LAUNCH();
-      return hipSuccess;
-    }
-    constexpr int lds_d = 3 * 3 * 128 * 64;
-    hipError_t e = stream ? allow_lds(k_efx_d<XBF, GBF, true, 2>, lds_d) : allow_lds(k_efx_d<XBF, GBF, false, 2>, lds_d);
-    if (e != hipSuccess) return e;
-    if (stream) launch_timed(k_efx_d<XBF, GBF, true, 2>, grid, dim3(256), lds_d, st, d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr);
-    else launch_timed(k_efx_d<XBF, GBF, false, 2>, grid, dim3(256), lds_d, st, d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr);
-    OD_CHECK_LAUNCH();
-    return hipSuccess;
-  }
-  constexpr int lds = 2 * 3 * 128 * 80;
-  // also for sets far beyond the Infinity Cache at any rank: nontemporal stores leave no dirty
-  // lines behind for the next kernel to wait on (measured on 8192 x 8192: the step is 2-7 % faster)
-  if (d.r > 256 || (int64_t)d.m * d.n * d.nb >= ((int64_t)48 << 20)) launch_timed(k_efx_h<XBF, GBF, true>, grid, dim3(512), lds, st, d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr);
-  else launch_timed(k_efx_h<XBF, GBF, false>, grid, dim3(512), lds, st, d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr);
-  OD_CHECK_LAUNCH();
-  return hipSuccess;
-}
-hipError_t launch_efx_h(const ClassDims& d, const MatPtrs& ptrs, const float* scal, int* info, HalfArr ph, HalfArr rh,
-                        HalfArr qh, float a_coef, float b_coef, float lr, hipStream_t st) {
-  if (d.x_bf16) return d.g_bf16 ? efx_h_t<true, true>(d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr, st)
-                                : efx_h_t<true, false>(d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr, st);
-  return d.g_bf16 ? efx_h_t<false, true>(d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr, st)
-                  : efx_h_t<false, false>(d, ptrs, scal, info, ph, rh, qh, a_coef, b_coef, lr, st);
-}
-
-hipError_t launch_efx(const ClassDims& d, const MatPtrs& ptrs, Prec prec, const float* scal, const int* info, WsArr p, WsArr rr,
-                      float a_coef, float b_coef, float lr, hipStream_t st) {
-  return prec == PREC_BF3 ? efx_n<NumBF<3>>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st)
-                          : efx_n<NumF16>(d, ptrs, scal, info, p, rr, a_coef, b_coef, lr, st);
+    const int64_t tall = (int64_t)ceil_div(d.m, 256) * ceil_div(d.n, 128) * r.peers;
+    return (d.r > 256 && tall >= 512 ? EV_TALL : EV_D) + stream;
+  };
+  return by_variant(b, n, variant, [&](int v, BatchList g, int k, int timed) -> hipError_t {
+    if (g[0]->d.x_bf16) return g[0]->d.g_bf16 ? efx_v<true, true>(v, g, k, coef, st, timed) : efx_v<true, false>(v, g, k, coef, st, timed);
+    return g[0]->d.g_bf16 ? efx_v<false, true>(v, g, k, coef, st, timed) : efx_v<false, false>(v, g, k, coef, st, timed);
+  });
 }
 
 }  // namespace od

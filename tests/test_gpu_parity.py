@@ -103,6 +103,33 @@ def test_more_matrices_than_one_launch_batch():
     _free_running(w)
 
 
+@pytest.mark.parametrize("x_dtype,variant", [("bf16", "qr"), ("f32", "qr"), ("bf16", "colnorm")])
+def test_batches_of_many_shapes_and_ranks_share_their_launches(x_dtype, variant):
+    """More shapes than one launch has segments (ten of rank 16, so that one kernel serves them
+    all), ranks of every kernel family, batches of one and of several matrices, one batch with more
+    matrices than the first kernel takes at a time: every matrix must come out as if alone."""
+    shapes = [(64 + 8 * i, 136 - 8 * i) for i in range(10)] + [(296, 328), (408, 272), (296, 328), (328, 288), (272, 280)]
+    ranks = [16] * 10 + [40, 72, 40, 200, 264]
+    shapes += [(72, 40)] * 66
+    ranks += [8] * 66
+    nmat = len(shapes)
+    streams = [synth.power_law_stream(m, n, 1500 + 3 * i, out_dtype=x_dtype) for i, (m, n) in enumerate(shapes)]
+    states = [synth.initial_state(m, n, ranks[i], 1500 + 3 * i, x_dtype, 1e-3) for i, (m, n) in enumerate(shapes)]
+    gpu = GpuRun(shapes, ranks, x_dtype, states, variant=variant, mu=0.95, lr=0.01)
+    orc = OrthDionOracle(mu=0.95, lr=0.01, variant=variant, ef="dion", x_bf16=(x_dtype == "bf16"))
+    cur = [(s.X, s.M.astype(np.float64), s.Q.astype(np.float64)) for s in states]
+    for t in range(2):
+        grads = [st.gradient(t) for st in streams]
+        assert gpu.step(grads) == [0] * nmat
+        for i in range(nmat):
+            x, mom, q = cur[i]
+            o = orc.step(x, grads[i], mom, q)
+            res = compare_step(gpu.fetch(i), o, x, 0.01)
+            for key in ("M", "Q", "P", "R", "D"):
+                assert res[key] <= TOL[x_dtype], (t, i, shapes[i], ranks[i], key, res[key])
+            cur[i] = (o["X_bits"] if x_dtype == "bf16" else o["X"], o["M"], o["Q"])
+
+
 def test_teacher_forced_single_steps_bf16():
     """Per-step error with the oracle restarted from the GPU's own state each step."""
     import torch
