@@ -149,17 +149,15 @@ struct NumBF {
 // ---------------------------------------------------------------------------------
 // Global-memory sources of operand tiles.  A source is a row-major matrix view with
 // R rows, C columns and leading dimension ld (elements).  load8(r, c) returns the 8
-// consecutive elements (r, c..c+7), load4(r, c) the 4 elements (r, c..c+3); positions
-// outside the view read as zero.  C is a multiple of 8, so a group of 8 (or 4) aligned
-// columns is either wholly inside or wholly outside.  load8u / load4u / load1u are the same
-// reads without the bounds check, for tiles known to lie inside the view: a checked load is
-// a branch, and past a branch the compiler waits for every outstanding load, not just the
-// oldest, which defeats a multi-stage prefetch.
+// consecutive elements (r, c..c+7); positions outside the view read as zero.  R and C are
+// multiples of 8, so an aligned group of 8 (or 4) is either wholly inside or wholly outside.
+// load8u / load4u / load1u (8, 4, 1 elements) check nothing: a checked load is a branch, and
+// past a branch the compiler waits for every outstanding load, not just the oldest, which
+// defeats a multi-stage prefetch.  The tile loaders clamp the address instead.
 // ---------------------------------------------------------------------------------
 struct SrcF32 {
   static constexpr bool PACKED = false;
   static constexpr bool HAS_LOAD1 = true;
-  OD_DEV float load1(int r, int c) const { return (r < R && c < C) ? p[(int64_t)r * ld + c] : 0.f; }
   const float* p;
   int R, C;
   int64_t ld;
@@ -184,10 +182,6 @@ struct SrcF32 {
       v.b = v.a;
     }
     return v;
-  }
-  OD_DEV Raw4 load4(int r, int c) const {
-    if (r < R && c < C) return *reinterpret_cast<const f32x4*>(p + (int64_t)r * ld + c);
-    return f32x4{0.f, 0.f, 0.f, 0.f};
   }
   OD_DEV static void unpack8(const Raw8& v, float* x) {
 #pragma unroll
@@ -214,10 +208,6 @@ struct SrcBF16 {
   OD_DEV Raw8 load8(int r, int c) const {
     if (r < R && c < C) return *reinterpret_cast<const u32x4*>(p + (int64_t)r * ld + c);
     return u32x4{0u, 0u, 0u, 0u};
-  }
-  OD_DEV Raw4 load4(int r, int c) const {
-    if (r < R && c < C) return *reinterpret_cast<const u32x2*>(p + (int64_t)r * ld + c);
-    return u32x2{0u, 0u};
   }
   OD_DEV static void unpack8(const Raw8& v, float* x) {
 #pragma unroll
@@ -247,7 +237,6 @@ struct SrcH16 {
     if (r < R && c < C) return *reinterpret_cast<const u32x4*>(p + (int64_t)r * ld + c);
     return u32x4{0u, 0u, 0u, 0u};
   }
-  OD_DEV Raw4 load4(int, int) const { return u32x2{0u, 0u}; }
   OD_DEV static void unpack8(const Raw8&, float* x) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = 0.f;
@@ -280,7 +269,6 @@ struct SrcSum {
   OD_DEV Raw8 load8u(int r, int c) const { return Raw8{m.load8u(r, c), g.load8u(r, c)}; }
   OD_DEV Raw4 load4u(int r, int c) const { return Raw4{m.load4u(r, c), g.load4u(r, c)}; }
   OD_DEV Raw8 load8(int r, int c) const { return Raw8{m.load8(r, c), g.load8(r, c)}; }
-  OD_DEV Raw4 load4(int r, int c) const { return Raw4{m.load4(r, c), g.load4(r, c)}; }
   OD_DEV static void unpack8(const Raw8& v, float* x) {
     float y[8];
     SrcF32::unpack8(v.a, x);

@@ -31,15 +31,21 @@ struct Tile {
   static constexpr int lds_bytes() { return 2 * Num::PARTS * (PLANE_A + PLANE_B); }
 };
 
+OD_DEV u32x4 keep_if(bool in, const u32x4& w) { return in ? w : u32x4{0u, 0u, 0u, 0u}; }
+
 template <class Src, int ROWS, int KT, int PITCH, int THREADS>
 struct LoadKC {
   static constexpr int KG = KT / 8, ITEMS = ROWS * KG, PER = (ITEMS + THREADS - 1) / THREADS;
   typename Src::Raw8 raw[PER];
+  bool in[PER];                  // whether the item lies inside the source (load())
   OD_DEV void load(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       int item = tid + p * THREADS;
-      if (ITEMS % THREADS == 0 || item < ITEMS) raw[p] = s.load8(row0 + item / KG, k0 + (item % KG) * 8);
+      if (ITEMS % THREADS != 0) item %= ITEMS;         // surplus threads repeat a valid item; store() skips them
+      const int row = row0 + item / KG, k = k0 + (item % KG) * 8;
+      in[p] = row < s.rows() && k < s.cols();
+      raw[p] = s.load8u(in[p] ? row : 0, in[p] ? k : 0);
     }
   }
   // the tile rows and every k below kpad lie inside the source
@@ -51,6 +57,7 @@ struct LoadKC {
       int item = tid + p * THREADS;
       if (ITEMS % THREADS != 0) item %= ITEMS;         // surplus threads repeat a valid item; store() skips them
       raw[p] = s.load8u(row0 + item / KG, k0 + (item % KG) * 8);
+      in[p] = true;
     }
   }
   template <class Num>
@@ -62,14 +69,14 @@ struct LoadKC {
         char* dst = lds + (item / KG) * PITCH + (item % KG) * 16;
         if constexpr (Src::PACKED) {
           static_assert(Num::PARTS == 1, "packed operands have one part");
-          *reinterpret_cast<u32x4*>(dst) = raw[p];
+          *reinterpret_cast<u32x4*>(dst) = keep_if(in[p], raw[p]);
         } else {
           float x[8];
           Src::unpack8(raw[p], x);
           u32x4 w[Num::PARTS];
           Num::pack(x, scale, w);
 #pragma unroll
-          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = w[s];
+          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(in[p], w[s]);
         }
       }
     }
@@ -80,15 +87,17 @@ template <class Src, int ROWS, int KT, int PITCH, int THREADS>
 struct LoadKS {
   static constexpr int RQ = ROWS / 4, KG = KT / 8, ITEMS = RQ * KG, PER = (ITEMS + THREADS - 1) / THREADS;
   typename Src::Raw4 raw[PER][8];
+  bool in[PER];
   OD_DEV void load(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       int item = tid + p * THREADS;
-      if (ITEMS % THREADS == 0 || item < ITEMS) {
-        int rq = item % RQ, kg = item / RQ;
+      if (ITEMS % THREADS != 0) item %= ITEMS;
+      const int row = row0 + (item % RQ) * 4, k = k0 + item / RQ * 8;
+      in[p] = k < s.rows() && row < s.cols();
+      const int kc = in[p] ? k : 0, rc = in[p] ? row : 0;
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load4(k0 + kg * 8 + kk, row0 + rq * 4);
-      }
+      for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load4u(kc + kk, rc);
     }
   }
   OD_DEV static bool interior(const Src& s, int row0, int kpad) { return kpad <= s.rows() && row0 + ROWS <= s.cols(); }
@@ -100,6 +109,7 @@ struct LoadKS {
       int rq = item % RQ, kg = item / RQ;
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load4u(k0 + kg * 8 + kk, row0 + rq * 4);
+      in[p] = true;
     }
   }
   template <class Num>
@@ -121,7 +131,7 @@ struct LoadKS {
           Num::pack(col, scale, w);
           char* dst = lds + (rq * 4 + j) * PITCH + kg * 16;
 #pragma unroll
-          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = w[s];
+          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(in[p], w[s]);
         }
       }
     }
@@ -135,15 +145,17 @@ template <class Src, int ROWS, int KT, int PITCH, int THREADS>
 struct LoadKS1 {
   static constexpr int KG = KT / 8, ITEMS = ROWS * KG, PER = (ITEMS + THREADS - 1) / THREADS;
   float raw[PER][8];
+  bool in[PER];
   OD_DEV void load(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       int item = tid + p * THREADS;
-      if (ITEMS % THREADS == 0 || item < ITEMS) {
-        int row = item % ROWS, kg = item / ROWS;
+      if (ITEMS % THREADS != 0) item %= ITEMS;
+      const int row = row0 + item % ROWS, k = k0 + item / ROWS * 8;
+      in[p] = k < s.rows() && row < s.cols();
+      const int kc = in[p] ? k : 0, rc = in[p] ? row : 0;
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load1(k0 + kg * 8 + kk, row0 + row);
-      }
+      for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load1u(kc + kk, rc);
     }
   }
   OD_DEV static bool interior(const Src& s, int row0, int kpad) { return kpad <= s.rows() && row0 + ROWS <= s.cols(); }
@@ -155,6 +167,7 @@ struct LoadKS1 {
       int row = item % ROWS, kg = item / ROWS;
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load1u(k0 + kg * 8 + kk, row0 + row);
+      in[p] = true;
     }
   }
   template <class Num>
@@ -168,7 +181,7 @@ struct LoadKS1 {
         Num::pack(raw[p], scale, w);
         char* dst = lds + row * PITCH + kg * 16;
 #pragma unroll
-        for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = w[s];
+        for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(in[p], w[s]);
       }
     }
   }
@@ -281,7 +294,7 @@ OD_DEV void gemm_mainloop_deep(const SrcA& a, const SrcB& b, int m0, int n0, int
   auto k_of = [&](int i) { const int c = i + rot; return kbeg + (c >= nsteps ? c - nsteps : c) * T::KT; };
   LA la[PF];
   LB lb[PF];
-  // (small tiles are chosen for short K loops on small grids: they keep the simple loop only)
+  // (small tiles are chosen for short K loops on small grids: they keep the clamped loop only)
   if (T::MT * T::NT >= 128 * 128 && nsteps >= 2 * PF && LA::interior(a, m0, kbeg + nsteps * T::KT) &&
       LB::interior(b, n0, kbeg + nsteps * T::KT)) {
     // Both tiles lie inside their sources for every step: loads without bounds checks, and a
@@ -328,33 +341,40 @@ OD_DEV void gemm_mainloop_deep(const SrcA& a, const SrcB& b, int m0, int n0, int
     }
     return;
   }
+  // 16 accumulator tiles leave no registers for clamped addresses in several stages
+  if constexpr (T::FM * T::FN >= 16) {
+    gemm_mainloop<T, Num, DirA, SrcA, DirB, SrcB>(a, b, m0, n0, kbeg, kend, scaleA, scaleB, lds, acc, rot);
+    return;
+  }
+  // Anything else: the same straight line with clamped addresses, and with steps past the last one
+  // reading the last again (a load under a condition would make the wait before every store to LDS
+  // one for all loads).  The only branch leaves the loop.  (Five small matrices of
+  // ranks 24 to 72: 253 -> 245 us; 126 matrices of rank 192: 1719 -> 1674 us.)
+  const int last = nsteps - 1;
 #pragma unroll
   for (int p = 0; p < PF; ++p) {
-    if (p < nsteps) {
-      la[p].load(a, m0, k_of(p), tid);
-      lb[p].load(b, n0, k_of(p), tid);
-    }
+    la[p].load(a, m0, k_of(p < last ? p : last), tid);
+    lb[p].load(b, n0, k_of(p < last ? p : last), tid);
   }
   la[0].template store<Num>(lds, T::PLANE_A, scaleA, tid);
   lb[0].template store<Num>(lds + OFF_B, T::PLANE_B, scaleB, tid);
   __syncthreads();
-  for (int i0 = 0; i0 < nsteps; i0 += PF) {
+  for (int i0 = 0;; i0 += PF) {
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
-      const int i = i0 + j;                    // step i lives in register stage j
-      if (i < nsteps) {
-        const int buf = i & 1;
-        if (i + PF < nsteps) {                 // stage j went to LDS one step ago: refill it
-          la[j].load(a, m0, k_of(i + PF), tid);
-          lb[j].load(b, n0, k_of(i + PF), tid);
-        }
-        mma_step<T, Num>(lds + buf * BUF, lds + buf * BUF + OFF_B, acc, wm, wn, lane);
-        if (i + 1 < nsteps) {
-          la[(j + 1) % PF].template store<Num>(lds + (buf ^ 1) * BUF, T::PLANE_A, scaleA, tid);
-          lb[(j + 1) % PF].template store<Num>(lds + (buf ^ 1) * BUF + OFF_B, T::PLANE_B, scaleB, tid);
-        }
+      const int i = i0 + j, buf = i & 1;       // step i lives in register stage j
+      const int next = i + PF < last ? i + PF : last;
+      la[j].load(a, m0, k_of(next), tid);      // stage j went to LDS one step ago: refill it
+      lb[j].load(b, n0, k_of(next), tid);
+      __builtin_amdgcn_sched_barrier(0);
+      mma_step<T, Num>(lds + buf * BUF, lds + buf * BUF + OFF_B, acc, wm, wn, lane);
+      if (i == last) {
         __syncthreads();
+        return;
       }
+      la[(j + 1) % PF].template store<Num>(lds + (buf ^ 1) * BUF, T::PLANE_A, scaleA, tid);
+      lb[(j + 1) % PF].template store<Num>(lds + (buf ^ 1) * BUF + OFF_B, T::PLANE_B, scaleB, tid);
+      __syncthreads();
     }
   }
 }
