@@ -1,11 +1,11 @@
 // Cholesky factorisation and triangular inverse of one SPD block of up to 256 x 256 in a
-// single workgroup (8 waves):  G = T^T T with T upper triangular, W = T^-1.
+// single workgroup (12 waves):  G = T^T T with T upper triangular, W = T^-1.
 //
 // Used by the CholeskyQR orthogonalisation (orth() of Alg. 1 lines 2 and 4): T is the
 // triangular factor of the thin QR, W turns the triangular solve into a product.
 //
-// Layout of the computation (8 waves: wave 3 runs the serial chain of diagonal tiles, the
-// other seven are workers)
+// Layout of the computation (12 waves: wave 3 runs the serial chain of diagonal tiles, the
+// other eleven are workers)
 //   * The block is cut into 32 x 32 tiles; the tiles (I, K) with I < K are kept as
 //     matrix-core accumulators (16 registers per lane: register v of lane l is row
 //     8 (v / 4) + 4 (l / 32) + v % 4, column l % 32), spread over the workers so that every
@@ -15,6 +15,8 @@
 //     (wave-uniform) arithmetic; the new rows are a 4 x 4 product inside each lane; the
 //     rank-4 trailing update of the tile is two fp32 matrix-core products (32x32x2).  The
 //     same operations applied to an identity tile give the inverse of the tile's factor.
+//     Only the inverse (fp32) and the factor are left in LDS; a worker without a tile in (b) writes both
+//     out and splits the inverse for (c).
 //     (b): the owner of tile (J, K) forms T(J, K) = W_JJ^T S(J, K) on the matrix cores (the
 //     accumulator tile serves directly as the k-side operand), writes it out, publishes it
 //     to LDS already split into three bf16 terms in the operand's register order, and
@@ -43,10 +45,13 @@ constexpr int kCholMax = kLeafRank;    // largest block one workgroup factors
 constexpr int kCT = 32;                // tile size
 constexpr int kCNT = kCholMax / kCT;   // 8 tiles per side
 constexpr int kCTiles = kCNT * (kCNT + 1) / 2;   // 36
-constexpr int kCholThreads = 512;      // 8 waves: two per SIMD
-constexpr int kCholDiagWave = 3;       // the serial chain; the other seven are workers
-constexpr int kCWorkers = 7;
-constexpr int kCSlots = 4;             // off-diagonal tiles per worker: 28 over 7 workers, four each
+// Three waves per SIMD.  What a step waits for is the latency of one wave's tiles, one after the other, so
+// more waves with fewer tiles each.  Rank 256: 57 us with two waves per SIMD and four tiles per worker, 53 with
+// the chain below, 48 with three waves, the worker that finishes a diagonal tile and the loads shared out.
+constexpr int kCholThreads = 768;
+constexpr int kCholDiagWave = 3;       // the serial chain; the other eleven are workers
+constexpr int kCWorkers = 11;
+constexpr int kCSlots = 3;             // off-diagonal tiles per worker: 28 over 11 workers
 constexpr int kCPitch = 36;            // floats per row of an fp32 LDS tile (16-byte aligned, conflict free)
 constexpr int kCTileF = kCT * kCPitch; // floats per fp32 LDS tile
 constexpr int kPPitch = 80;            // bytes per row of a pre-split operand tile (32 bf16 + pad)
@@ -57,7 +62,8 @@ constexpr int kCholOffPanel = 2 * kCTileF * 4;
 constexpr int kCholOffVPanel = kCholOffPanel + kCNT * kPTile;
 constexpr int kCholOffSync = kCholOffVPanel + kCNT * kPTile;   // published[8] | s_ready[8] (ints)
 constexpr int kCholOffStash = kCholOffSync + 2 * kCNT * 4;      // two fp32 tile images: S(J, J+1) for the diagonal wave
-constexpr int kCholLds = kCholOffStash + 2 * 4096;
+constexpr int kCholOffFactor = kCholOffStash + 2 * 4096;        // two fp32 tile images: T(J, J) for its way out
+constexpr int kCholLds = kCholOffFactor + 2 * 4096;
 constexpr int kCholSpinLimit = 1 << 22;  // bound of every wait below (never reached: the producers do not wait)
 
 struct CholArgs {
@@ -74,17 +80,20 @@ struct CholArgs {
 
 // tile (I, K), I < K, of slot s of worker u, four bits per slot, 15 = no tile (kept in scalar
 // registers: a table in memory would cost a dependent load per use).  Tile (I, K) belongs
-// to worker (I + K) mod 7: four tiles each, and in every step the panel tiles (one row and one
-// column of tiles, sums I + K that span eight consecutive values) go to seven different
-// workers but for one pair.
-OD_DEV uint64_t own_rows(int u) {
-  return u == 0 ? 0x3210ull : u == 1 ? 0x3210ull : u == 2 ? 0x4320ull : u == 3 ? 0x4310ull : u == 4 ? 0x5410ull : u == 5 ? 0x5210ull
-       : u == 6 ? 0x6210ull : 0xffffull;
+// to worker (I + K) mod 11, but (3, 4) to worker 1: at most three tiles each, in every step the panel
+// tiles (one row and one column of tiles, eight consecutive sums I + K) go to seven different workers, and
+// worker 2J mod 11 has none in step J.
+OD_DEV uint32_t own_rows(int u) {
+  return u == 0 ? 0xff54u : u == 1 ? 0xf350u : u == 2 ? 0xff60u : u == 3 ? 0xff10u : u == 4 ? 0xff10u : u == 5 ? 0xf210u
+       : u == 6 ? 0xf210u : u == 7 ? 0xf210u : u == 8 ? 0xf321u : u == 9 ? 0xf432u : u == 10 ? 0xff43u : 0xffffu;
 }
-OD_DEV uint64_t own_cols(int u) {
-  return u == 0 ? 0x4567ull : u == 1 ? 0x5671ull : u == 2 ? 0x5672ull : u == 3 ? 0x6723ull : u == 4 ? 0x6734ull : u == 5 ? 0x7345ull
-       : u == 6 ? 0x7456ull : 0xffffull;
+OD_DEV uint32_t own_cols(int u) {
+  return u == 0 ? 0xff67u : u == 1 ? 0xf471u : u == 2 ? 0xff72u : u == 3 ? 0xff23u : u == 4 ? 0xff34u : u == 5 ? 0xf345u
+       : u == 6 ? 0xf456u : u == 7 ? 0xf567u : u == 8 ? 0xf567u : u == 9 ? 0xf567u : u == 10 ? 0xff67u : 0xffffu;
 }
+// worker of a wave: waves 7 and 11 share the diagonal wave's SIMD and get the workers whose tiles are
+// finished first
+OD_DEV int worker_of(int wave) { return (int)(0x4a023651987ull >> (4 * (wave - (wave > kCholDiagWave ? 1 : 0)))) & 15; }
 
 // A diagonal tile waiting in LDS in accumulator layout: plane q holds registers 4q .. 4q+3
 // of every lane (16 bytes per lane, conflict free).
@@ -202,12 +211,10 @@ OD_DEV bool lds_wait_ge(int* word, int target) {
 // inverse of its transpose (M = L^-1, lower triangular), both in accumulator layout.
 // Returns the 1-based index of the first bad pivot within the tile, or 0.
 // ---------------------------------------------------------------------------------------
-// value of `x` held by the lanes of half `hh`, in both halves
-OD_DEV float half_bcast(float x, int hh) {
-  const uint32_t u = __float_as_uint(x);
-  // swaps lanes 32..63 of the first operand with lanes 0..31 of the second:
-  // [0] = the lower half's values in both halves, [1] = the upper half's
-  auto pr = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+// The rows a and b, valid in the lanes of half `hh`: a in the lower lane half, b in the upper one.
+OD_DEV float half_pair(float a, float b, int hh) {
+  // swaps lanes 32..63 of the first operand with lanes 0..31 of the second
+  auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float(hh ? pr[1] : pr[0]);
 }
 
@@ -216,93 +223,88 @@ OD_DEV f32x16 mfma_f32_k2(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-OD_DEV int diag_tile_factor(f32x16& d_io, f32x16& zt_out, int lane) {
+// `nv`: valid rows (a multiple of 8); the tile is the identity beyond them.
+//
+// One serial chain, eight groups of four pivots long, that every later tile waits for: per group the two
+// products that update `d`, ten readlanes, four reciprocal square roots with two operations each
+// between them.  A wave issues one instruction in 4 cycles at best, so what counts besides is their number:
+// rows come by forward substitution (no inverse of the 4 x 4 block), are computed in the lane half that
+// holds them only (one lane swap makes the operand of two rows), columns left of the diagonal are not
+// masked before the end (they only ever meet each other), and bad pivots are found at the end.  Alone on its
+// SIMD a tile took 8900 cycles and takes 7400, hand-over included.
+OD_DEV int diag_tile_factor(f32x16& d_io, f32x16& zt_out, int lane, int nv) {
   const int c = lane & 31, h = lane >> 5;
-  int bad = 0;
   // `d` and `zt` are only ever changed by the matrix-core updates; the finished rows are
   // collected on the side (a finished row of `d` / `zt` itself is never read again)
   f32x16 d = d_io, zt;
   float tfin[16], zfin[16];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) zt[v] = (acc_row(v, lane) == c) ? 1.f : 0.f;
+  for (int v = 0; v < 16; ++v) tfin[v] = zfin[v] = zt[v] = (acc_row(v, lane) == c) ? 1.f : 0.f;
 #pragma unroll
   for (int g = 0; g < 8; ++g) {
     const int q = g >> 1, hh = g & 1, src_lane = 32 * hh + 4 * g;
+    if (hh == 0 && 8 * q >= nv) break;
     // 4 x 4 diagonal block (upper part), wave-uniform
     const float d00 = lane_bcast(d[4 * q + 0], src_lane + 0), d01 = lane_bcast(d[4 * q + 0], src_lane + 1);
     const float d02 = lane_bcast(d[4 * q + 0], src_lane + 2), d03 = lane_bcast(d[4 * q + 0], src_lane + 3);
     const float d11 = lane_bcast(d[4 * q + 1], src_lane + 1), d12 = lane_bcast(d[4 * q + 1], src_lane + 2);
     const float d13 = lane_bcast(d[4 * q + 1], src_lane + 3), d22 = lane_bcast(d[4 * q + 2], src_lane + 2);
     const float d23 = lane_bcast(d[4 * q + 2], src_lane + 3), d33 = lane_bcast(d[4 * q + 3], src_lane + 3);
-    // rows 4g .. 4g+3 of both tiles, made available to both lane halves
-    float s[4], zz[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      s[e] = half_bcast(d[4 * q + e], hh);
-      zz[e] = half_bcast(zt[4 * q + e], hh);
-    }
-    // pivots: a non-positive or non-finite one is only recorded (the outputs of such a matrix
-    // are unspecified); the hardware reciprocal square root (1 ulp) is accurate enough here,
-    // since the inverse below is built from the same rounded values
-    const float p0 = d00;
-    const float i00 = __builtin_amdgcn_rsqf(p0);
-    const float t01 = d01 * i00, t02 = d02 * i00, t03 = d03 * i00;
-    const float p1 = d11 - t01 * t01;
-    const float i11 = __builtin_amdgcn_rsqf(p1);
-    const float t12 = (d12 - t01 * t02) * i11, t13 = (d13 - t01 * t03) * i11;
-    const float p2 = d22 - t02 * t02 - t12 * t12;
-    const float i22 = __builtin_amdgcn_rsqf(p2);
-    const float t23 = (d23 - t02 * t03 - t12 * t13) * i22;
-    const float p3 = d33 - t03 * t03 - t13 * t13 - t23 * t23;
-    const float i33 = __builtin_amdgcn_rsqf(p3);
-    // one test per group on the critical path (a NaN or an infinite pivot makes the sum fail
-    // the upper bound; fminf alone would skip a NaN); which of the four it was is worked out
-    // only when the test fails
-    const float pmin = fminf(fminf(p0, p1), fminf(p2, p3)), psum = (p0 + p1) + (p2 + p3);
-    if (bad == 0 && !(pmin > 0.f && psum < 3.0e38f)) {
-      if (!(p0 > 0.f) || !(p0 < 3.0e38f)) bad = 4 * g + 1;
-      else if (!(p1 > 0.f) || !(p1 < 3.0e38f)) bad = 4 * g + 2;
-      else if (!(p2 > 0.f) || !(p2 < 3.0e38f)) bad = 4 * g + 3;
-      else bad = 4 * g + 4;
-    }
-    // inverse of the 4 x 4 upper factor
-    const float w01 = -(t01 * i11) * i00, w12 = -(t12 * i22) * i11, w23 = -(t23 * i33) * i22;
-    const float w02 = -(t01 * w12 + t02 * i22) * i00, w13 = -(t12 * w23 + t13 * i33) * i11;
-    const float w03 = -(t01 * w13 + t02 * w23 + t03 * i33) * i00;
-    // new rows of the factor and of the inverse: (W4^T s)_a = sum_{b <= a} W4[b][a] s_b
+    // pivots: the hardware reciprocal square root (1 ulp) is accurate enough here, since the
+    // inverse is built from the same rounded values.  A non-positive or non-finite pivot leaves a NaN.
+    // New rows of the factor: t_e = (s_e - sum_{b < e} t4[b][e] t_b) / t4[e][e]
     float tn[4], zn[4];
-    tn[0] = i00 * s[0];
-    tn[1] = w01 * s[0] + i11 * s[1];
-    tn[2] = w02 * s[0] + w12 * s[1] + i22 * s[2];
-    tn[3] = w03 * s[0] + w13 * s[1] + w23 * s[2] + i33 * s[3];
-    zn[0] = i00 * zz[0];
-    zn[1] = w01 * zz[0] + i11 * zz[1];
-    zn[2] = w02 * zz[0] + w12 * zz[1] + i22 * zz[2];
-    zn[3] = w03 * zz[0] + w13 * zz[1] + w23 * zz[2] + i33 * zz[3];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (c < 4 * g + e) tn[e] = 0.f;                // row 4g+e of an upper factor starts at its diagonal
+    const float i00 = __builtin_amdgcn_rsqf(d00);
+    const float t01 = d01 * i00, t02 = d02 * i00, t03 = d03 * i00;
+    const float i11 = __builtin_amdgcn_rsqf(d11 - t01 * t01);
+    tn[0] = d[4 * q] * i00;
+    const float t12 = (d12 - t01 * t02) * i11, t13 = (d13 - t01 * t03) * i11;
+    const float i22 = __builtin_amdgcn_rsqf(d22 - t02 * t02 - t12 * t12);
+    tn[1] = (d[4 * q + 1] - t01 * tn[0]) * i11;
+    const float t23 = (d23 - t02 * t03 - t12 * t13) * i22;
+    const float i33 = __builtin_amdgcn_rsqf(d33 - t03 * t03 - t13 * t13 - t23 * t23);
+    tn[2] = (d[4 * q + 2] - t02 * tn[0] - t12 * tn[1]) * i22;
+    tn[3] = (d[4 * q + 3] - t03 * tn[0] - t13 * tn[1] - t23 * tn[2]) * i33;
+    // rank-4 update of the tile, -T_g^T T_g, as two k = 2 products: the lower lane half
+    // carries rows 4g, 4g+2 and the upper half rows 4g+1, 4g+3
+    float t01v, t23v;
     if (g < 7) {
-      // rank-4 update of both tiles, -T_g^T T_g and -T_g^T Z_g, as two k = 2 products each:
-      // the lower lane half carries rows 4g, 4g+2 and the upper half rows 4g+1, 4g+3
-      const float t01v = h ? tn[1] : tn[0], t23v = h ? tn[3] : tn[2];
-      const float z01v = h ? zn[1] : zn[0], z23v = h ? zn[3] : zn[2];
+      t01v = half_pair(tn[0], tn[1], hh);
+      t23v = half_pair(tn[2], tn[3], hh);
       d = mfma_f32_k2(-t01v, t01v, d);
-      zt = mfma_f32_k2(-t01v, z01v, zt);
       d = mfma_f32_k2(-t23v, t23v, d);
-      zt = mfma_f32_k2(-t23v, z23v, zt);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // the same for the inverse, -T_g^T Z_g, while those products run
+    zn[0] = zt[4 * q] * i00;
+    zn[1] = (zt[4 * q + 1] - t01 * zn[0]) * i11;
+    zn[2] = (zt[4 * q + 2] - t02 * zn[0] - t12 * zn[1]) * i22;
+    zn[3] = (zt[4 * q + 3] - t03 * zn[0] - t13 * zn[1] - t23 * zn[2]) * i33;
+    if (g < 7) {
+      zt = mfma_f32_k2(-t01v, half_pair(zn[0], zn[1], hh), zt);
+      zt = mfma_f32_k2(-t23v, half_pair(zn[2], zn[3], hh), zt);
     }
     // the rows of this group are final (register 4q + e of lane half hh; the other half's
     // turn for these registers comes with the next group)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      if (hh == 0) { tfin[4 * q + e] = tn[e]; zfin[4 * q + e] = zn[e]; }
-      else if (h == 1) { tfin[4 * q + e] = tn[e]; zfin[4 * q + e] = zn[e]; }
+      if (hh == 0 || h == 1) { tfin[4 * q + e] = tn[e]; zfin[4 * q + e] = zn[e]; }
     }
+    __builtin_amdgcn_sched_barrier(0);
   }
+  // column c starts at its diagonal, whose entry tells whether the pivot was a positive number
+  // below 3e38 (the root of that here); the first column where it was not is the breakdown
+  bool ok = true;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) { d_io[v] = tfin[v]; zt_out[v] = zfin[v]; }
-  return bad;
+  for (int v = 0; v < 16; ++v) {
+    const int row = acc_row(v, lane);
+    if (row == c) ok = tfin[v] > 0.f && tfin[v] < 1.7320508e19f;
+    d_io[v] = c < row ? 0.f : tfin[v];
+    zt_out[v] = zfin[v];
+  }
+  const uint64_t failed = __ballot(!ok);
+  const uint32_t columns = (uint32_t)failed | (uint32_t)(failed >> 32);
+  return columns != 0u ? __ffs((int)columns) : 0;
 }
 
 // The factorisation of block `a.blk` of matrix `z` by one workgroup of kCholThreads threads;
@@ -321,8 +323,8 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
   if (a.pred.scal != nullptr && (a.pred.scal[z * kScalPerMat + a.pred.slot] > a.pred.thr) != (a.pred.want != 0)) return;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool diag_wave = wave == kCholDiagWave;
-  const int worker = diag_wave ? kCWorkers : (wave < kCholDiagWave ? wave : wave - 1);
-  const uint64_t ownI = own_rows(worker), ownK = own_cols(worker);
+  const int worker = diag_wave ? kCWorkers : worker_of(wave);
+  const uint32_t ownI = own_rows(worker), ownK = own_cols(worker);
   const int r = a.r;
   const int o = a.blk * kCholMax;
   const int nb = (r - o) < kCholMax ? (r - o) : kCholMax;     // order of this block
@@ -333,20 +335,6 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
   float* wg = a.w.base + (int64_t)z * a.w.stride + off;
   const int col = lane & 31, half = lane >> 5;
   if (tid < 2 * kCNT) published[tid] = 0;
-
-  // ---- tiles strictly below the diagonal of T and W are zero and written by nobody else:
-  // one tile per iteration (256 threads x 16 bytes = one 32 x 32 tile)
-  if (tid < 256) {
-    for (int I = 1; I < nt; ++I)
-      for (int K = 0; K < I; ++K) {
-        const int gi = I * kCT + (tid >> 3), gj = K * kCT + (tid & 7) * 4;
-        if (gi < nb && gj < nb) {
-          const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-          *reinterpret_cast<f32x4*>(tg + (int64_t)gi * r + gj) = zero;
-          *reinterpret_cast<f32x4*>(wg + (int64_t)gi * r + gj) = zero;
-        }
-      }
-  }
 
   // ---- load: every tile is read straight into accumulator layout through the transposed
   // element (the matrix is symmetric): lane column c needs rows 8q + 4h + {0..3} of its
@@ -372,6 +360,10 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
     }
     return t;
   };
+  // the diagonal tiles: (0, 0) is factored at once by the diagonal wave (below), worker u brings tile
+  // (u + 1, u + 1), which waits in LDS for its updates
+  f32x16 waiting;
+  if (!diag_wave && worker + 1 < nt) waiting = load_tile(worker + 1, worker + 1);
   f32x16 acc[kCSlots];
 #pragma unroll
   for (int s = 0; s < kCSlots; ++s) {
@@ -384,17 +376,29 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
   }
 
   // ================================ factorisation ================================
-  // (a) tile (J, J): factor, invert, write T_JJ and W_JJ, publish W_JJ^T
+  char* factor = lds_raw + kCholOffFactor;                               // buffer J & 1
+  // (a) tile (J, J): factor, invert, leave T_JJ and W_JJ^T in LDS
   auto do_diag = [&](int J, f32x16 d) {
     f32x16 zt;
-    const int bad = diag_tile_factor(d, zt, lane);
-    if (bad != 0 && lane == 0) atomicCAS(&a.info[z * kInfoPerMat + a.info_slot], 0, o + J * kCT + bad);
     const int nv = (nb - J * kCT) < kCT ? (nb - J * kCT) : kCT;   // valid rows / cols of this tile
+    const int bad = diag_tile_factor(d, zt, lane, nv);
     // zt = M = V(J, J) with W_JJ = M^T:  Wt[i][k] = M[i][k]
     float* wt = Wt + (J & 1) * kCTileF;
 #pragma unroll
     for (int v = 0; v < 16; ++v) wt[acc_row(v, lane) * kCPitch + col] = zt[v];
+    store_dtile(factor + (J & 1) * 4096, d, lane);
+    if (bad != 0 && lane == 0) atomicCAS(&a.info[z * kInfoPerMat + a.info_slot], 0, o + J * kCT + bad);
+  };
+  // ... and by a worker: V(J, J) split for (c), W_JJ and T_JJ written out
+  auto finish_diag = [&](int J) {
+    const int nv = (nb - J * kCT) < kCT ? (nb - J * kCT) : kCT;
+    const float* wt = Wt + (J & 1) * kCTileF;
+    f32x16 zt;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) zt[v] = wt[acc_row(v, lane) * kCPitch + col];
     store_presplit(vpanel + J * kPTile, zt, lane);
+    lds_signal_add(published + J, lane);
+    const f32x16 d = load_dtile(factor + (J & 1) * 4096, lane);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       // global W_JJ[c][rows] (row c of W = column c of M), 4 consecutive entries
@@ -446,6 +450,9 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) res[v] = row_tile ? (res[v] + res2[v]) : -(res[v] + res2[v]);
     if (row_tile) {
+      // published first: the other workers wait for this tile, nobody waits for the rest
+      store_presplit(panel + K * kPTile, res, lane);
+      lds_signal_add(published + J, lane);
       // block orders are multiples of 8, so rows 8q .. 8q+7 are valid or not together
       if (K * kCT + col < nb) {
         float* tp = tg + (int64_t)(J * kCT + 4 * half) * r + K * kCT + col;
@@ -457,7 +464,6 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
           }
         }
       }
-      store_presplit(panel + K * kPTile, res, lane);
 #pragma unroll
       for (int v = 0; v < 16; ++v) tile[v] = 0.f;       // from now on the sum S'(K, J)
       // the waiting diagonal tile (K, K) -= T(J, K)^T T(J, K), operands read back from the panel
@@ -468,7 +474,6 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
         lds_product(dt, panel + K * kPTile, panel + K * kPTile, true);
         store_dtile(dk, dt, lane);
       }
-      lds_signal_add(published + J, lane);
     } else {
       store_presplit(vpanel + I * kPTile, res, lane);
       lds_signal_add(published + J, lane);
@@ -486,15 +491,28 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
   };
 
   if (diag_wave) {
-    // the diagonal tiles: (0, 0) is factored at once, the others wait in LDS for their updates
-    for (int I = 1; I < nt; ++I) store_dtile(vpanel + I * kPTile, load_tile(I, I), lane);
     do_diag(0, load_tile(0, 0));
   } else {
+    if (worker + 1 < nt) store_dtile(vpanel + (worker + 1) * kPTile, waiting, lane);
     // tile (0, 1) as loaded is what the diagonal wave needs first
 #pragma unroll
     for (int s = 0; s < kCSlots; ++s) {
       const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
       if (I == 0 && K == 1 && K < nt) store_dtile(stash, acc[s], lane);     // made visible by the barrier below
+    }
+    // tiles strictly below the diagonal of T and W are zero and written by nobody else: one tile
+    // per iteration (waves 4 to 7, 16 bytes per lane = one 32 x 32 tile), beside the first factorisation
+    if (wave >= 4 && wave < 8) {
+      const int t = tid - 256;
+      for (int I = 1; I < nt; ++I)
+        for (int K = 0; K < I; ++K) {
+          const int gi = I * kCT + (t >> 3), gj = K * kCT + (t & 7) * 4;
+          if (gi < nb && gj < nb) {
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4*>(tg + (int64_t)gi * r + gj) = zero;
+            *reinterpret_cast<f32x4*>(wg + (int64_t)gi * r + gj) = zero;
+          }
+        }
     }
   }
   lds_barrier();
@@ -552,9 +570,10 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
         const bool row_tile = I == J && K > J + 1 && K < nt, col_tile = K == J && I < J;
         if (row_tile || col_tile) panel_tile(acc[s], mrow, J, I, K, row_tile);
       }
-      // ---- (c) once all nt - 1 tiles of the step are published:
+      if (worker == (2 * J) % kCWorkers) finish_diag(J);
+      // ---- (c) once all nt tiles of the step are published:
       // S(I, K) -= T(J, I)^T T(J, K) for J < I < K;  S'(K, I) += T(J, K)^T V(J, I) for I <= J < K
-      if (!lds_wait_ge(published + J, nt - 1)) expired = true;
+      if (!lds_wait_ge(published + J, nt)) expired = true;
 #pragma unroll
       for (int s = 0; s < kCSlots; ++s) {
         const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;

@@ -83,6 +83,7 @@ OD_DEV int seg_locate(const One<A>&, SegBlock& b) {
 // ------------------------------------------------------------------------------------
 typedef Tile<128, 256, 32, 2, 2> TileWide;     // r > 128: wave tile 64 x 128
 typedef Tile<128, 128, 32, 2, 2> TileSquare;   // wave tile 64 x 64
+typedef Tile<128, 128, 32, 4, 2> TileSquare8;  // the same on eight waves (wave tile 32 x 64): half the registers
 typedef Tile<128, 64, 32, 4, 1> TileNarrow;    // r <= 64: wave tile 32 x 64
 typedef Tile<64, 256, 32, 2, 2> TileFlat;      // projection, r > 128: twice the row panels, half the splits (wave tile 32 x 128)
 typedef Tile<256, 256, 32, 2, 2> TileHuge;    // back-projection, r > 256: wave tile 128 x 128, one workgroup per CU
@@ -674,7 +675,7 @@ __global__ __launch_bounds__(kSmallRows) void k_small_first_pass(SegsT segs) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) d[4 * q + e] = (c < r && gi < r) ? v4[e] : ((gi + e == c) ? 1.f : 0.f);
     }
-    const int bad = diag_tile_factor(d, zt, lane);
+    const int bad = diag_tile_factor(d, zt, lane, r);
     if (bad != 0 && lane == 0) atomicCAS(&a_.info[z * kInfoPerMat + a_.info_slot], 0, bad);
     // zt = M with W = M^T: lane c holds row c of W
 #pragma unroll
@@ -778,7 +779,8 @@ OD_DEV SrcF32 sub_view(const float* base, int r, int row0, int col0, int rows, i
   return SrcF32{base + (int64_t)row0 * r + col0, R, C, r};
 }
 
-template <class T, class Num, class DirA>
+// DEEP: three register stages of loads in flight
+template <class T, class Num, class DirA, bool DEEP = true>
 OD_DEV void sgemm_tile(const SgemmArgs& g, int bx, int bz, char* lds) {
   const int tiles_n = (g.Nc + T::NT - 1) / T::NT;
   const int tn = bx % tiles_n, tm = bx / tiles_n;
@@ -793,7 +795,8 @@ OD_DEV void sgemm_tile(const SgemmArgs& g, int bx, int bz, char* lds) {
   SrcF32 sb = sub_view(bp, g.r, g.b_k0 + o, g.b_c0 + o, g.Kc, g.Nc);
   f32x16 acc[T::FM][T::FN];
   zero_acc<T>(acc);
-  gemm_mainloop_deep<T, Num, DirA, SrcF32, KSF, SrcF32, 3>(sa, sb, tm * T::MT, tn * T::NT, 0, g.Kc, 1.f, 1.f, lds, acc);
+  if constexpr (DEEP) gemm_mainloop_deep<T, Num, DirA, SrcF32, KSF, SrcF32, 3>(sa, sb, tm * T::MT, tn * T::NT, 0, g.Kc, 1.f, 1.f, lds, acc);
+  else gemm_mainloop<T, Num, DirA, SrcF32, KSF, SrcF32>(sa, sb, tm * T::MT, tn * T::NT, 0, g.Kc, 1.f, 1.f, lds, acc);
   const int cr = g.c_r0 + o, cc = g.c_c0 + o;
   for_each_acc<T>(acc, tm * T::MT, tn * T::NT, [&](int row, int col, float v) {
     if (row < g.Mc && col < g.Nc && cr + row < g.r && cc + col < g.r) {
@@ -832,7 +835,8 @@ __global__ __launch_bounds__(T::THREADS) void k_sgemm_pair(SgemmArgs g1, SgemmAr
 // block (whose own update has already been applied) while the others apply the rest of the
 // current block's trailing update (g1, g2) and finish block column p of the inverse (g3).
 // The products run on the first T::THREADS threads of their workgroups; the surplus waves end
-// at once (a barrier counts only the waves that are still alive).
+// at once (a barrier counts only the waves that are still alive).  They have the time of a factorisation, so
+// one register stage is enough (the registers are those of three waves per SIMD).
 template <class T>
 __global__ __launch_bounds__(kCholThreads) void k_chol_ahead(CholArgs ca, SgemmArgs g1, SgemmArgs g2, SgemmArgs g3, int tiles1, int tiles2) {
   extern __shared__ __align__(16) char lds[];
@@ -843,9 +847,9 @@ __global__ __launch_bounds__(kCholThreads) void k_chol_ahead(CholArgs ca, SgemmA
   }
   if ((int)threadIdx.x >= T::THREADS) return;
   const int bx = (int)blockIdx.x - 1;
-  if (bx < tiles1) sgemm_tile<T, Num, KSF>(g1, bx, blockIdx.z, lds);
-  else if (bx < tiles1 + tiles2) sgemm_tile<T, Num, KSF>(g2, bx - tiles1, blockIdx.z, lds);
-  else sgemm_tile<T, Num, KC>(g3, bx - tiles1 - tiles2, blockIdx.z, lds);
+  if (bx < tiles1) sgemm_tile<T, Num, KSF, false>(g1, bx, blockIdx.z, lds);
+  else if (bx < tiles1 + tiles2) sgemm_tile<T, Num, KSF, false>(g2, bx - tiles1, blockIdx.z, lds);
+  else sgemm_tile<T, Num, KC, false>(g3, bx - tiles1 - tiles2, blockIdx.z, lds);
 }
 
 constexpr int kLeaf = kCholMax;   // diagonal block of the blocked factorisation
@@ -2444,7 +2448,7 @@ static hipError_t blocked_cholinv(const CholJob& job, hipStream_t st) {
       const int t1 = tiles_of(right, T::MT), t2 = tiles_of(below, T::MT), t3 = tiles_of(wcol, T::MT);
       hipLaunchKernelGGL(k_chol_ahead<T>, dim3(1 + t1 + t2 + t3, 1, nb), dim3(kCholThreads), lds, st, ca, right, below, wcol, t1, t2);
     } else {
-      typedef TileSquare T;
+      typedef TileSquare8 T;
       constexpr int lds = T::lds_bytes<NumBF<3>>() > kCholLds ? T::lds_bytes<NumBF<3>>() : kCholLds;
       if ((e = allow_lds(k_chol_ahead<T>, lds)) != hipSuccess) return e;
       const int t1 = tiles_of(right, T::MT), t2 = tiles_of(below, T::MT), t3 = tiles_of(wcol, T::MT);

@@ -472,3 +472,23 @@ def test_phase_profile_counts_and_leaves_results_alone():
     for a, b in zip(*runs):
         for key in ("X", "M", "Q"):
             assert a[key].tobytes() == b[key].tobytes(), key
+
+
+@pytest.mark.parametrize("r", [40, 104, 168, 200, 232, 256])
+def test_leaf_factorisation_at_every_tile_count(r):
+    """Cholesky factor and inverse of one workgroup with two to eight 32 x 32 tiles per side, the last
+    one whole or partly filled: P^T P = I, upper-triangular factors with a positive diagonal that reproduce
+    B Q_prev.  Bounds as in the r = 96 test: a Gram matrix in 24-bit operands leaves about 1e-6."""
+    w = synth.Workload("leaf", ((576, 320),), r=r, x_dtype="bf16", steps=1)
+    stream, st = synth.make_stream(w, 0), synth.make_state(w, 0)
+    g = stream.gradient(0)
+    gpu = GpuRun(w.shapes, w.r, "bf16", [st], precision="exact")
+    assert gpu.step([g]) == [0]
+    f = gpu.fetch(0)
+    b = st.M.astype(np.float64) + bf16_bits_to_f64(g)
+    for factor, t1, t2, source in (("P", "T_P1", "T_P2", b @ st.Q.astype(np.float64)), ("Q", "T_Q1", "T_Q2", f["R"].astype(np.float64))):
+        q = f[factor].astype(np.float64)
+        assert np.max(np.abs(q.T @ q - np.eye(r))) < 5e-6
+        t = f[t2].astype(np.float64) @ f[t1].astype(np.float64)
+        assert np.all(np.diag(t) > 0) and np.all(np.tril(f[t1], -1) == 0) and np.all(np.tril(f[t2], -1) == 0)
+        assert rel_fro(q @ t, source) < 1e-5
