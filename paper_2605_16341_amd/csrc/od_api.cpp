@@ -55,6 +55,7 @@ struct Batch {
   int slot_base;                     // first row of this batch in the scal / info tables
   int rank_class;
   int cluster;                       // batches of one cluster share their launches
+  bool small;                        // orthogonalisation by the three kernels for ranks up to 32
   int64_t peers;                     // matrices of this shape that make up the same work as the cluster
 };
 
@@ -63,6 +64,7 @@ struct Batch {
 // matrices: the class owns the r x r arrays, every batch a contiguous range of slices.
 struct RankClass {
   int r, count, slot_base;
+  bool small;                        // see Batch
   int group;                         // which of the two groups a large set of one rank is dealt into
   int64_t st_rr;
   std::vector<int> batches;
@@ -300,6 +302,16 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       b.peers = (int64_t)(cluster_elems[b.cluster] / ((double)b.d.m * b.d.n));
       if (b.peers < (int64_t)b.members.size()) b.peers = (int64_t)b.members.size();
     }
+    // Ranks up to 32 have three kernels of their own per orthogonalisation instead of eight (one matrix of
+    // 8192 x 8192, r = 16: 376 -> 352 us).  Where a cluster runs the eight anyway for a larger rank, its small
+    // ranks join them (five matrices of ranks 24 to 72: 262 -> 201 us).  One choice per rank: the factorisations
+    // are launched by rank.
+    std::vector<int> widest(cluster_elems.size(), 0);
+    for (const Batch& b : h->batches) widest[b.cluster] = std::max(widest[b.cluster], b.d.r);
+    bool beside[33] = {};                // ranks that share a cluster with a larger one than 32
+    for (const Batch& b : h->batches)
+      if (b.d.r <= 32 && widest[b.cluster] > 32) beside[b.d.r] = true;
+    for (Batch& b : h->batches) b.small = b.d.r <= 32 && !beside[b.d.r];
   }
 
   // workspace plan
@@ -337,6 +349,7 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     if (found < 0) {
       RankClass rc = {};
       rc.r = b.d.r;
+      rc.small = b.small;
       rc.group = group_of[bi];
       rc.st_rr = ((int64_t)b.d.r * b.d.r + 63) / 64 * 64;
       h->classes.push_back(rc);
@@ -406,9 +419,9 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     const int64_t gt = gt1 * (gt1 + 1) / 2;
     for (int side = 0; side < 2; ++side) {
       const int64_t rows = side == 0 ? m : n;
-      // r <= 32: one 32 x 32 tile, one thread per row: 256-row slabs (k_small_gram, k_small_first_pass);
+      // small ranks: one 32 x 32 tile, one thread per row: 256-row slabs (k_small_gram, k_small_first_pass);
       // else two workgroups of the Gram kernel fit one CU
-      int sg = r <= 32 ? pick_splits(1, b.peers, rows, 256) : pick_splits_by_rounds(gt, b.peers, rows, 256, 512);
+      int sg = b.small ? pick_splits(1, b.peers, rows, 256) : pick_splits_by_rounds(gt, b.peers, rows, 256, 512);
       if (sg > 32) sg = 32;
       b.splits_gram[side] = sg;
     }
@@ -416,9 +429,8 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     if (b.slabs > 256) b.slabs = 256;
     int64_t part = (int64_t)b.splits_proj * m * r;
     if ((int64_t)b.splits_back * n * r > part) part = (int64_t)b.splits_back * n * r;
-    // r <= 32: the Gram partials of both CholeskyQR passes live side by side
     for (int sg : b.splits_gram)
-      if ((int64_t)sg * r * r * (r <= 32 ? 2 : 1) > part) part = (int64_t)sg * r * r * (r <= 32 ? 2 : 1);
+      if ((int64_t)sg * r * r > part) part = (int64_t)sg * r * r;
     if ((int64_t)b.slabs * r > part) part = (int64_t)b.slabs * r;
     // strides rounded so that every matrix slice stays 256-byte aligned
     auto rnd = [](int64_t e) { return (e + 63) / 64 * 64; };
@@ -476,14 +488,14 @@ extern "C" int orthdion_set_variant(orthdion_handle h, orthdion_variant v) {
 // do not depend on the number of rows, can be launched once for every matrix of a rank.
 
 // Cholesky factor and inverse of the first pass for every matrix of a unit; side 0: left factor.
-// (Ranks up to 32 factor inside the first kernel of the second pass.)
+// (Small ranks factor inside the first kernel of the second pass.)
 static int unit_cholinv(const orthdion_ctx* h, const Unit& u, char* ws, int side, int* info_all, hipStream_t st) {
   for (size_t i = 0; i < u.classes.size();) {
     od::CholJob jobs[8];
     int n = 0;
     for (; i < u.classes.size() && n < 8; ++i) {
       const RankClass& c = h->classes[u.classes[i]];
-      if (c.r <= 32) continue;
+      if (c.small) continue;
       od::CholJob& j = jobs[n++];
       j = od::CholJob{};
       j.nb = c.count;
@@ -589,6 +601,7 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     v.splits_proj = b.splits_proj; v.splits_back = b.splits_back;
     v.splits_gram[0] = b.splits_gram[0]; v.splits_gram[1] = b.splits_gram[1];
     v.slabs = b.slabs;
+    v.small = b.small;
     v.peers = b.peers;
   }
 

@@ -88,6 +88,7 @@ struct BatchRef {
   WsArr pa, pb, ra, rb, part, gram, t1[2], t2[2], w, tmp, colsq;     // t1, t2: [0] left, [1] right factor
   HalfArr ph, pht, rh, qh, qht;
   int splits_proj, splits_back, splits_gram[2], slabs;
+  bool small;                        // orthogonalised by the kernels for ranks up to 32
   int64_t peers;                     // matrices of this shape that would make up the work of all batches that step together with it
   // left (P, rows m) and right (Q, rows n) side of the orthogonalisation
   int rows(int side) const { return side == 0 ? d.m : d.n; }
@@ -116,17 +117,18 @@ hipError_t launch_back(BatchList b, int n, Prec prec, hipStream_t st);
 hipError_t launch_back_reduce(BatchList b, int n, Prec prec, hipStream_t st);
 
 // The orthogonalisation of P_raw (side 0) or R (side 1) by CholeskyQR2, in pieces:
-// orth_gram: Gram matrix of a0 in the batch's slices of the class array `gram` (r <= 32: partial sums
-// left in `part` for the first pass)
+// orth_gram: Gram matrix of a0 in the batch's slices of the class array `gram` (small batches: partial sums
+// for the second pass)
 hipError_t launch_orth_gram(BatchList b, int n, int side, Prec prec, hipStream_t st);
 // second pass: a1 = a0 W1, Gram of a1, T2 = I + Phi(E), Phi^T (fast) or W2 = I - Phi(E) (exact), max |E|;
-// r <= 32: with the factorisation of the first pass in front
+// small batches: the factorisation of the first pass, a1 and its Gram partials
 hipError_t launch_orth_second(BatchList b, int n, int side, Prec prec, hipStream_t st);
 // r <= 256: Cholesky factor of I + E for the matrices whose deviation is above kFirstOrderDeviation
 hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st);
 // result = a1 - a1 Phi(E) (fast), a1 W2 (exact), for a flagged matrix the full product a1 W2, to a0 or (side 1)
 // the callers' Q, with the fp16 copies of fast precision.  `which`: 0 everything, 1 only the
 // first-order correction of the well-conditioned matrices, 2 only the full product of the flagged ones.
+// small batches: the whole rest of the second pass.
 hipError_t launch_orth_result(BatchList b, int n, int side, Prec prec, int which, hipStream_t st);
 
 // Gram partials of a plain array: part[split][r][r] = A^T A over a row range, six-product operands

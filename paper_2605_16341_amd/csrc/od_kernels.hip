@@ -580,12 +580,14 @@ __global__ __launch_bounds__(T::THREADS) void k_apply(SegsT segs) {
 
 // ------------------------------------------------------------------------------------
 // r <= 32: the first CholeskyQR pass in one launch.  At this size every kernel of the pass is
-// a few microseconds of latency, so three of them become one: every workgroup factors the
-// (reduced) Gram matrix for itself in its first wave (one 32 x 32 tile, padded with the
+// a few microseconds of latency, so three of them become one: every workgroup adds the partials of
+// the Gram matrix and factors it for itself in its first wave (one 32 x 32 tile, padded with the
 // identity), applies W = T^-1 to its share of the rows in plain fp32 and leaves the Gram
 // partial of the rows it has just produced for the second pass.  Workgroup 0 of a matrix also
-// writes T1 and W1.  One thread per row; `part` receives `splits` partial sums of r x r.
+// writes T1.  One thread per row; `part` receives `splits` partial sums of r x r.
 // ------------------------------------------------------------------------------------
+// (second launch bound: up to 256 registers, which keeps the matrix-core accumulators in ordinary ones; in the
+// others every group of pivots copied them back and forth)
 constexpr int kSmallRows = 256, kSmallPitch = 36;
 
 // Sum of a^T a over the 64 rows a wave owns of the tile S ([rows][kSmallPitch], 32 columns) on
@@ -613,18 +615,74 @@ OD_DEV void small_gram_store(float* S, const f32x16& acc, int r, float* out, int
   if (gi < r && gj < r) *reinterpret_cast<f32x4*>(out + (int64_t)gi * r + gj) = g;
 }
 
+// The r x r sum of `splits` Gram partials (r * r apart, added in order) into `S` ([row][kSmallPitch],
+// 32 x 32, the identity beyond r): one thread per four entries, so that all partials are in flight
+// together; a single wave that added them row block by row block spent 8 round trips to memory on it.
+OD_DEV void small_sum_partials(const float* G, int splits, int r, float* S, int tid) {
+  const int gi = tid >> 3, gj = 4 * (tid & 7);
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (gi < r && gj < r) {
+    const f32x4* p = reinterpret_cast<const f32x4*>(G + gi * r + gj);
+    const int step = r * r / 4;
+#pragma unroll 16
+    for (int sp = 0; sp < splits; ++sp) v += p[(int64_t)sp * step];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = gi == gj + e ? 1.f : 0.f;
+  }
+  *reinterpret_cast<f32x4*>(S + gi * kSmallPitch + gj) = v;
+}
+// ... and from there to accumulator layout (lane = column c, registers = rows), read through the
+// mirrored element of the symmetric matrix
+OD_DEV f32x16 small_acc_tile(const float* S, int lane) {
+  const int c = lane & 31, h = lane >> 5;
+  f32x16 d;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const f32x4 v4 = *reinterpret_cast<const f32x4*>(S + c * kSmallPitch + 8 * q + 4 * h);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d[4 * q + e] = v4[e];
+  }
+  return d;
+}
+// o = x W for the row x in `xs` (LDS), W upper triangular in `Wl` (zero below the diagonal): column
+// block jb takes k <= 4 jb + 3.  Four k per turn of a loop that stays rolled: unrolled, all 144 reads of W
+// were issued ahead of the arithmetic and a quarter of them spilled to scratch memory.
+OD_DEV void small_row_product(const float* xs, const float* Wl, int r, f32x4* o) {
+#pragma unroll
+  for (int jb = 0; jb < 8; ++jb) o[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int kb = 0; kb < r / 4; ++kb) {
+    const f32x4 x4 = *reinterpret_cast<const f32x4*>(xs + 4 * kb);
+#pragma unroll
+    for (int jb = 0; jb < 8; ++jb) {
+      if (jb >= kb) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 w4 = *reinterpret_cast<const f32x4*>(Wl + (4 * kb + i) * kSmallPitch + 4 * jb);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[jb][e] = fmaf(x4[i], w4[e], o[jb][e]);
+        }
+      }
+    }
+  }
+}
+
 // r <= 32: Gram partials A^T A of `splits` row ranges, one thread per row, in plain fp32.
 struct SmallArgs {
-  int rows, r, splits;
+  int rows, r, splits, side;
   WsArr a0, a1;
   WsArr gram;                   // `splits` Gram partials of a0, r x r each
   WsArr part;                   // the same of a1
-  WsArr t1, w1;
+  WsArr t1, t2;
+  const MatEntry* q_mats;       // the result goes to these matrices' Q, or to a0 when null
+  float* only_q;                // Q of the one matrix of a batch of one
+  HalfArr hn, ht;               // fp16 copies of the result ([rows][r] and [r][rows]), or null
+  float* scal;
   int* info;
-  int info_slot;
 };
 template <class SegsT>
-__global__ __launch_bounds__(kSmallRows) void k_small_gram(SegsT segs) {
+__global__ __launch_bounds__(kSmallRows, 2) void k_small_gram(SegsT segs) {
   __shared__ __align__(16) float S[kSmallRows * kSmallPitch];
   OD_SEGMENT(SmallArgs);
   const int rows = a_.rows, r = a_.r, splits = a_.splits;
@@ -651,46 +709,31 @@ __global__ __launch_bounds__(kSmallRows) void k_small_gram(SegsT segs) {
 }
 
 template <class SegsT>
-__global__ __launch_bounds__(kSmallRows) void k_small_first_pass(SegsT segs) {
+__global__ __launch_bounds__(kSmallRows, 2) void k_small_first_pass(SegsT segs) {
   __shared__ __align__(16) float Wl[32 * kSmallPitch];           // W[k][j]
   __shared__ __align__(16) float S[kSmallRows * kSmallPitch];    // the rows of a1 of one pass
   OD_SEGMENT(SmallArgs);
-  const int rows = a_.rows, r = a_.r, splits = a_.splits, gram_splits = a_.splits;
+  const int rows = a_.rows, r = a_.r, splits = a_.splits;
   const int z = blk.z, split = blk.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // (Wl holds the sum until the factorisation replaces it by W)
+  small_sum_partials(a_.gram.base + (int64_t)z * a_.gram.stride, splits, r, Wl, tid);
+  __syncthreads();
   if (wave == 0) {
-    const float* G = a_.gram.base + (int64_t)z * a_.gram.stride;
     const int c = lane & 31, h = lane >> 5;
-    // accumulator layout (lane = column c, registers = rows) read through the mirrored element
-    // of the symmetric matrix: four consecutive entries of row c
-    f32x16 d, zt;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int gi = 8 * q + 4 * h;
-      f32x4 v4 = {0.f, 0.f, 0.f, 0.f};
-      if (c < r && gi < r) {
-        // `gram_splits` partial sums, r * r apart, added in order
-#pragma unroll 8
-        for (int sp = 0; sp < gram_splits; ++sp) v4 += *reinterpret_cast<const f32x4*>(G + (int64_t)sp * r * r + (int64_t)c * r + gi);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) d[4 * q + e] = (c < r && gi < r) ? v4[e] : ((gi + e == c) ? 1.f : 0.f);
-    }
+    f32x16 d = small_acc_tile(Wl, lane), zt;
     const int bad = diag_tile_factor(d, zt, lane, r);
-    if (bad != 0 && lane == 0) atomicCAS(&a_.info[z * kInfoPerMat + a_.info_slot], 0, bad);
+    if (bad != 0 && lane == 0) atomicCAS(&a_.info[z * kInfoPerMat + a_.side], 0, bad);
     // zt = M with W = M^T: lane c holds row c of W
 #pragma unroll
     for (int v = 0; v < 16; ++v) Wl[c * kSmallPitch + acc_row(v, lane)] = zt[v];
     if (split == 0 && c < r) {
       float* tp = a_.t1.base + (int64_t)z * a_.t1.stride;
-      float* wp = a_.w1.base + (int64_t)z * a_.w1.stride;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int gi = 8 * q + 4 * h;
         if (gi < r) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) tp[(int64_t)(gi + e) * r + c] = d[4 * q + e];
-          const f32x4 v4 = {zt[4 * q], zt[4 * q + 1], zt[4 * q + 2], zt[4 * q + 3]};
-          *reinterpret_cast<f32x4*>(wp + (int64_t)c * r + gi) = v4;
         }
       }
     }
@@ -717,27 +760,8 @@ __global__ __launch_bounds__(kSmallRows) void k_small_first_pass(SegsT segs) {
     }
     // the first rows are requested before the wait for the factorisation
     if (first) { __syncthreads(); first = false; }
-    // o = x W, W upper triangular: column block jb takes k <= 4 jb + 3.  Four k per turn of a
-    // loop that stays rolled: unrolled, all 144 reads of W were issued ahead of the arithmetic
-    // and a quarter of them spilled to scratch memory.
     f32x4 o[8];
-#pragma unroll
-    for (int jb = 0; jb < 8; ++jb) o[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int kb = 0; kb < 8; ++kb) {
-      const f32x4 x4 = *reinterpret_cast<const f32x4*>(xs + 4 * kb);
-#pragma unroll
-      for (int jb = 0; jb < 8; ++jb) {
-        if (jb >= kb) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const f32x4 w4 = *reinterpret_cast<const f32x4*>(Wl + (4 * kb + i) * kSmallPitch + 4 * jb);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[jb][e] = fmaf(x4[i], w4[e], o[jb][e]);
-          }
-        }
-      }
-    }
+    small_row_product(xs, Wl, r, o);
 #pragma unroll
     for (int jb = 0; jb < 8; ++jb) {
       if (valid && 4 * jb < r) *reinterpret_cast<f32x4*>(O + (int64_t)row * r + 4 * jb) = o[jb];
@@ -749,6 +773,116 @@ __global__ __launch_bounds__(kSmallRows) void k_small_first_pass(SegsT segs) {
   }
   if (first) __syncthreads();          // a workgroup without rows still meets the others' barrier count
   small_gram_store(S, gacc, r, a_.part.base + (int64_t)z * a_.part.stride + (int64_t)split * r * r, tid);
+}
+
+// r <= 32, second pass (see k_corr and k_apply for the general form): every workgroup adds the Gram
+// partials of a1 (I + E), takes T2 = I + Phi(E) and W2 = I - Phi(E), or the Cholesky factor and its inverse where
+// the deviation is too large for the first-order form, and applies W2 to its rows in plain fp32.  Workgroup 0 of
+// a matrix also writes T2 and the flags.  One launch in place of four (sum, guard, two triangular products; 22 us of
+// launches and latency at 8192 rows, r = 16, against 10).
+template <class SegsT>
+__global__ __launch_bounds__(kSmallRows, 2) void k_small_result(SegsT segs) {
+  __shared__ __align__(16) float Wl[32 * kSmallPitch];           // I + E, then W2[k][j]
+  __shared__ __align__(16) float S[kSmallRows * kSmallPitch];    // the rows of a1 of one pass
+  OD_SEGMENT(SmallArgs);
+  const int rows = a_.rows, r = a_.r, side = a_.side;
+  const int z = blk.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = blk.x * kSmallRows + tid;
+  const bool valid = row < rows;
+  float* xs = S + tid * kSmallPitch;
+  {
+    const float* A = a_.a1.base + (int64_t)z * a_.a1.stride + (int64_t)row * r;
+#pragma unroll
+    for (int j4 = 0; j4 < 8; ++j4) {
+      f32x4 v4 = {0.f, 0.f, 0.f, 0.f};
+      if (valid && 4 * j4 < r) v4 = *reinterpret_cast<const f32x4*>(A + 4 * j4);
+      *reinterpret_cast<f32x4*>(xs + 4 * j4) = v4;
+    }
+  }
+  small_sum_partials(a_.part.base + (int64_t)z * a_.part.stride, a_.splits, r, Wl, tid);
+  __syncthreads();
+  if (wave == 0) {
+    const int c = lane & 31;
+    f32x16 d = small_acc_tile(Wl, lane), zt;
+    // largest deviation, a NaN counting as a huge one
+    float dev = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float e = fabsf(acc_row(v, lane) == c ? d[v] - 1.f : d[v]);
+      dev = e <= dev ? dev : e == e ? e : 3.0e38f;
+    }
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) dev = fmaxf(dev, __shfl_xor(dev, w));
+    int* flag = &a_.info[z * kInfoPerMat + side];
+    if (dev > kFirstOrderDeviation) {
+      const int bad = diag_tile_factor(d, zt, lane, r);
+      if (blk.x == 0 && lane == 0) {
+        if (dev > kMaxGramDeviation) atomicCAS(flag, 0, r);
+        if (bad != 0) atomicCAS(flag, 0, bad);
+      }
+    } else {
+      // d = column c, rows i of the symmetric E; zt[v] = W2[c][i]
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int i = acc_row(v, lane);
+        const float e = i == c ? d[v] - 1.f : d[v], phi = i == c ? 0.5f * e : e, id = i == c ? 1.f : 0.f;
+        d[v] = i <= c ? id + phi : 0.f;
+        zt[v] = i >= c ? id - phi : 0.f;
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) Wl[c * kSmallPitch + acc_row(v, lane)] = zt[v];
+    if (blk.x == 0) {
+      if (c < r) {
+        float* tp = a_.t2.base + (int64_t)z * a_.t2.stride;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int i = acc_row(v, lane);
+          if (i < r) tp[(int64_t)i * r + c] = d[v];
+        }
+      }
+      // numerical rank from the diagonal of the first pass's factor (see k_corr)
+      const float* t = a_.t1.base + (int64_t)z * a_.t1.stride;
+      const float dg = t[(int64_t)(c < r ? c : 0) * (r + 1)];
+      float lo = dg == dg ? dg : 0.f, hi = dg > 0.f ? dg : 0.f;
+#pragma unroll
+      for (int w = 16; w > 0; w >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, w));
+        hi = fmaxf(hi, __shfl_xor(hi, w));
+      }
+      if (lane == 0) {
+        a_.scal[z * kScalPerMat + 2 + side] = dev;
+        if (!(lo > kMinPivotRatio * hi)) atomicCAS(flag, 0, r);
+      }
+    }
+  }
+  __syncthreads();
+  f32x4 o[8];
+  small_row_product(xs, Wl, r, o);
+  float* dst = a_.only_q != nullptr ? a_.only_q : a_.q_mats != nullptr ? a_.q_mats[z].Q : a_.a0.base + (int64_t)z * a_.a0.stride;
+  if (valid) {
+#pragma unroll
+    for (int jb = 0; jb < 8; ++jb)
+      if (4 * jb < r) *reinterpret_cast<f32x4*>(dst + (int64_t)row * r + 4 * jb) = o[jb];
+    if (a_.hn.base != nullptr) {
+      uint16_t* hn = a_.hn.base + (int64_t)z * a_.hn.stride + (int64_t)row * r;
+#pragma unroll
+      for (int jb = 0; jb < 8; ++jb)
+        if (4 * jb < r)
+          *reinterpret_cast<u32x2*>(hn + 4 * jb) = u32x2{pack_f16_sat(o[jb][0] * kUnitScale, o[jb][1] * kUnitScale),
+                                                         pack_f16_sat(o[jb][2] * kUnitScale, o[jb][3] * kUnitScale)};
+    }
+    if (a_.ht.base != nullptr) {       // adjacent lanes hold adjacent rows: whole segments of every column
+      uint16_t* ht = a_.ht.base + (int64_t)z * a_.ht.stride + row;
+#pragma unroll
+      for (int jb = 0; jb < 8; ++jb)
+        if (4 * jb < r) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            ht[(int64_t)(4 * jb + e) * rows] = __builtin_bit_cast(uint16_t, (_Float16)__builtin_amdgcn_fmed3f(o[jb][e] * kUnitScale, -65504.f, 65504.f));
+        }
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -2099,7 +2233,6 @@ hipError_t launch_back_reduce(BatchList b, int n, Prec prec, hipStream_t st) {
 
 // ---- orthogonalisation ------------------------------------------------------------------
 // Ranks of one 32 x 32 tile take the first CholeskyQR pass in a single launch, factorisation included.
-static bool small_rank(const BatchRef& r) { return r.d.r <= 32; }
 
 // Gram partials of a0 (`first`, into gram_out or with several splits `part`) or a1 (into `part`)
 template <class T, class Num>
@@ -2123,7 +2256,7 @@ static hipError_t gram_tt(BatchList b, int n, int side, bool first, hipStream_t 
 }
 static hipError_t gram_pass(BatchList b, int n, int side, bool first, Prec prec, hipStream_t st) {
   const auto variant = [&](const BatchRef& r) -> int {
-    if (small_rank(r)) return -1;
+    if (r.small) return -1;
     // few large tiles leave most of the chip idle: use small ones until the grid fills it
     const int64_t t = ceil_div(r.d.r, 128);
     return t * t * r.splits_gram[side] * r.peers < 512 ? 0 : 1;
@@ -2151,8 +2284,20 @@ hipError_t launch_gram_plain(int nb, int rows, int r, WsArr a, WsArr part, int s
                               : segs.launch(k_gram<TileSmall, NumBF<3>, One<GramArgs>>, k_gram<TileSmall, NumBF<3>, Segs<GramArgs>>, TileSmall::THREADS, TileSmall::lds_bytes<NumBF<3>>(), st, 0);
 }
 
-static hipError_t small_pass(BatchList b, int n, int side, bool first_pass, hipStream_t st) {
-  return by_variant(b, n, [](const BatchRef& r) { return small_rank(r) ? 0 : -1; }, [&](int, BatchList g, int k, int) -> hipError_t {
+// Gram partials of a0 (pass 0) and of a1 (pass 1) for small ranks.  The first pass reads the former while it
+// writes the latter, so they lie in the array of the result's fp16 copy, which holds them from two row ranges
+// (of 256 rows and more) on.
+static WsArr small_partials(const BatchRef& r, int side, int pass) {
+  if (pass == 1) return r.part;
+  if (r.splits_gram[side] == 1) return r.gram;
+  const HalfArr& h = side == 0 ? r.ph : r.qh;
+  return WsArr{reinterpret_cast<float*>(h.base), h.stride / 2};
+}
+
+// The three kernels of an orthogonalisation of rank up to 32.
+enum SmallStage : int { SMALL_GRAM, SMALL_FIRST, SMALL_RESULT };
+static hipError_t small_pass(BatchList b, int n, int side, SmallStage stage, Prec prec, hipStream_t st) {
+  return by_variant(b, n, [](const BatchRef& r) { return r.small ? 0 : -1; }, [&](int, BatchList g, int k, int) -> hipError_t {
     SegList<SmallArgs> segs;
     for (int i = 0; i < k; ++i) {
       const BatchRef& r = *g[i];
@@ -2160,26 +2305,35 @@ static hipError_t small_pass(BatchList b, int n, int side, bool first_pass, hipS
       a.rows = r.rows(side);
       a.r = r.d.r;
       a.splits = r.splits_gram[side];
+      a.side = side;
       a.a0 = r.a0(side);
       a.a1 = r.a1(side);
-      a.gram = r.part;
-      a.part = WsArr{r.part.base + (int64_t)a.splits * a.r * a.r, r.part.stride};
+      a.gram = small_partials(r, side, 0);
+      a.part = small_partials(r, side, 1);
       a.t1 = r.t1[side];
-      a.w1 = r.w;
+      a.t2 = r.t2[side];
+      a.scal = r.scal;
       a.info = r.info;
-      a.info_slot = side;
-      segs.add(a, a.splits, 1, r.d.nb);
+      if (side == 1) a.q_mats = r.mats;
+      if (side == 1 && r.d.nb == 1) a.only_q = r.host_mats[0].Q;
+      if (prec == PREC_F16) {
+        a.hn = side == 0 ? r.ph : r.qh;
+        if (side == 0) a.ht = r.pht;
+      }
+      segs.add(a, stage == SMALL_RESULT ? ceil_div(a.rows, kSmallRows) : a.splits, 1, r.d.nb);
     }
-    return first_pass ? segs.launch(k_small_first_pass<One<SmallArgs>>, k_small_first_pass<Segs<SmallArgs>>, kSmallRows, 0, st, 0) : segs.launch(k_small_gram<One<SmallArgs>>, k_small_gram<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
+    if (stage == SMALL_GRAM) return segs.launch(k_small_gram<One<SmallArgs>>, k_small_gram<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
+    if (stage == SMALL_FIRST) return segs.launch(k_small_first_pass<One<SmallArgs>>, k_small_first_pass<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
+    return segs.launch(k_small_result<One<SmallArgs>>, k_small_result<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
   });
 }
 
 hipError_t launch_orth_gram(BatchList b, int n, int side, Prec prec, hipStream_t st) {
-  OD_RETURN_IF(small_pass(b, n, side, false, st));
+  OD_RETURN_IF(small_pass(b, n, side, SMALL_GRAM, prec, st));
   OD_RETURN_IF(gram_pass(b, n, side, true, prec, st));
   // ordered reduction of the split partial sums on many workgroups: the factorisation runs on
   // one workgroup per matrix and should not spend its time summing
-  return by_variant(b, n, [&](const BatchRef& r) { return !small_rank(r) && r.splits_gram[side] > 1 ? 0 : -1; }, [&](int, BatchList g, int k, int) {
+  return by_variant(b, n, [&](const BatchRef& r) { return !r.small && r.splits_gram[side] > 1 ? 0 : -1; }, [&](int, BatchList g, int k, int) {
     SegList<ReduceArgs> segs;
     for (int i = 0; i < k; ++i) add_reduce(segs, g[i]->d.nb, g[i]->part, g[i]->splits_gram[side], (int64_t)g[i]->d.r * g[i]->d.r, g[i]->gram, kAlways);
     return segs.launch(k_reduce<One<ReduceArgs>>, k_reduce<Segs<ReduceArgs>>, 256, 0, st, 0);
@@ -2222,7 +2376,7 @@ static hipError_t apply_tt(BatchList b, int n, int side, ApplyKind kind, Prec pr
 template <class Num, bool CORR>
 static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
   const auto variant = [&](const BatchRef& r) -> int {
-    if (kind == APPLY_W && small_rank(r)) return -1;
+    if (r.small) return -1;
     return (int64_t)ceil_div(r.rows(side), 128) * ceil_div(r.d.r, 128) * r.peers < 512 ? 0 : 1;
   };
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
@@ -2239,26 +2393,18 @@ static hipError_t apply_product(BatchList b, int n, int side, ApplyKind kind, Pr
   return prec == PREC_BF3 ? apply_t<NumBF<3>, false>(b, n, side, kind, prec, st) : apply_t<NumBF<2>, false>(b, n, side, kind, prec, st);
 }
 
-// Gram partials of a1 (the second pass's input): behind those of a0 for small ranks
-static WsArr second_partials(const BatchRef& r, int side) {
-  WsArr p = r.part;
-  if (small_rank(r)) p.base += (int64_t)r.splits_gram[side] * r.d.r * r.d.r;
-  return p;
-}
-
 hipError_t launch_orth_second(BatchList b, int n, int side, Prec prec, hipStream_t st) {
-  OD_RETURN_IF(small_pass(b, n, side, true, st));
+  OD_RETURN_IF(small_pass(b, n, side, SMALL_FIRST, prec, st));
   OD_RETURN_IF(apply_product(b, n, side, APPLY_W, prec, st));
   OD_RETURN_IF(gram_pass(b, n, side, false, prec, st));
-  const auto all = [](const BatchRef&) { return 0; };
-  OD_RETURN_IF(by_variant(b, n, all, [&](int, BatchList g, int k, int) {
+  OD_RETURN_IF(by_variant(b, n, [](const BatchRef& r) { return r.small ? -1 : 0; }, [&](int, BatchList g, int k, int) {
     SegList<CorrArgs> segs;
     for (int i = 0; i < k; ++i) {
       const BatchRef& r = *g[i];
       CorrArgs a = {};
       a.r = r.d.r;
       a.splits = r.splits_gram[side];
-      a.part = second_partials(r, side);
+      a.part = r.part;
       a.t1 = r.t1[side];
       a.t2 = r.t2[side];
       a.w2 = r.w;
@@ -2293,7 +2439,7 @@ static hipError_t launch_leaf(const CholArgs* args, const int* counts, int n, hi
 }
 
 hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st) {
-  return by_variant(b, n, [](const BatchRef& r) { return r.d.r <= kCholMax ? 0 : -1; }, [&](int, BatchList g, int k, int) {
+  return by_variant(b, n, [](const BatchRef& r) { return r.d.r <= kCholMax && !r.small ? 0 : -1; }, [&](int, BatchList g, int k, int) {
     CholArgs args[kMaxSeg];
     int counts[kMaxSeg];
     for (int i = 0; i < k; ++i) {
@@ -2304,7 +2450,7 @@ hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st) {
       ca.r = r.d.r;
       ca.info = r.info;
       ca.info_slot = side;
-      ca.src = second_partials(r, side);
+      ca.src = r.part;
       ca.splits = r.splits_gram[side];
       ca.split_stride = (int64_t)r.d.r * r.d.r;
       ca.pred = deviation(r, side, 1);
@@ -2316,6 +2462,7 @@ hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st) {
 }
 
 hipError_t launch_orth_result(BatchList b, int n, int side, Prec prec, int which, hipStream_t st) {
+  if (which != 2) OD_RETURN_IF(small_pass(b, n, side, SMALL_RESULT, prec, st));
   if (prec == PREC_BF3) return apply_product(b, n, side, APPLY_FULL, prec, st);
   if (which != 2) OD_RETURN_IF((apply_t<NumF16, true>(b, n, side, APPLY_CORRECTION, prec, st)));
   if (which != 1) OD_RETURN_IF(apply_product(b, n, side, APPLY_FULL, prec, st));

@@ -492,3 +492,36 @@ def test_leaf_factorisation_at_every_tile_count(r):
         t = f[t2].astype(np.float64) @ f[t1].astype(np.float64)
         assert np.all(np.diag(t) > 0) and np.all(np.tril(f[t1], -1) == 0) and np.all(np.tril(f[t2], -1) == 0)
         assert rel_fro(q @ t, source) < 1e-5
+
+
+@pytest.mark.parametrize("kappa", [1e2, 1e3, 3e3])
+@pytest.mark.parametrize("precision", ["exact", "fast"])
+@pytest.mark.parametrize("r", [8, 24, 32])
+def test_ill_conditioned_small_ranks(kappa, precision, r):
+    """The kernels for ranks up to 32 take the same decisions as the general ones: first-order second
+    pass, second factorisation, or a flag."""
+    test_ill_conditioned_factors_stay_orthonormal_or_are_flagged(kappa, precision, r)
+
+
+@pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("variant", ["qr", "colnorm"])
+@pytest.mark.parametrize("ranks", [(8, 16, 32, 24), (16, 40, 24, 32)])
+def test_small_ranks_alone_and_beside_a_larger_one(ranks, variant, x_dtype):
+    """Ranks up to 32 run kernels of their own while every matrix of the launch has one, and the general
+    ones beside a larger rank; one to three row ranges of the small Gram kernels, ragged rows."""
+    shapes = ((264, 200), (1048, 72), (96, 776), (56, 40))
+    streams = [synth.power_law_stream(m, n, 1900 + i, out_dtype=x_dtype) for i, (m, n) in enumerate(shapes)]
+    states = [synth.initial_state(m, n, ranks[i], 1900 + i, x_dtype, 1e-3) for i, (m, n) in enumerate(shapes)]
+    gpu = GpuRun(shapes, list(ranks), x_dtype, states, variant=variant, mu=0.95, lr=0.01)
+    orc = OrthDionOracle(mu=0.95, lr=0.01, variant=variant, ef="dion", x_bf16=(x_dtype == "bf16"))
+    cur = [(s.X, s.M.astype(np.float64), s.Q.astype(np.float64)) for s in states]
+    for t in range(2):
+        grads = [s.gradient(t) for s in streams]
+        assert gpu.step(grads) == [0] * 4
+        for i in range(4):
+            x, mom, q = cur[i]
+            o = orc.step(x, grads[i], mom, q)
+            res = compare_step(gpu.fetch(i), o, x, 0.01)
+            for key in ("M", "Q", "P", "R", "D"):
+                assert res[key] <= TOL[x_dtype], (t, i, key, res[key])
+            cur[i] = (o["X_bits"] if x_dtype == "bf16" else o["X"], o["M"], o["Q"])
