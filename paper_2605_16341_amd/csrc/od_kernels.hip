@@ -83,11 +83,15 @@ OD_DEV int seg_locate(const One<A>&, SegBlock& b) {
 // ------------------------------------------------------------------------------------
 typedef Tile<128, 256, 32, 2, 2> TileWide;     // r > 128: wave tile 64 x 128
 typedef Tile<128, 128, 32, 2, 2> TileSquare;   // wave tile 64 x 64
-typedef Tile<128, 128, 32, 4, 2> TileSquare8;  // the same on eight waves (wave tile 32 x 64): half the registers
+// The same on eight waves (wave tile 32 x 64): half the registers, twice the waves per CU at the same LDS, so that
+// the operand conversions of one wave run beside the products of another.  A W of 96 matrices of rank 512:
+// 2.83 -> 2.52 ms, its correction 1.60 -> 1.51 ms, Gram matrices 2.43 -> 2.40 ms; 126 matrices of rank 192:
+// 1668 -> 1629 us per step; the three-part operands of a 1024-wide fp32 model: 338 -> 329 us.
+typedef Tile<128, 128, 32, 4, 2> TileSquare8;
 typedef Tile<128, 64, 32, 4, 1> TileNarrow;    // r <= 64: wave tile 32 x 64
 typedef Tile<64, 256, 32, 2, 2> TileFlat;      // projection, r > 128: twice the row panels, half the splits (wave tile 32 x 128)
 typedef Tile<256, 256, 32, 2, 2> TileHuge;    // back-projection, r > 256: wave tile 128 x 128, one workgroup per CU
-typedef Tile<128, 128, 64, 2, 2> TileSquareDeepK;   // single-part operands: half the k steps at the same LDS footprint
+typedef Tile<128, 128, 64, 4, 2> TileSquareDeepK;   // single-part operands: half the k steps at the same LDS footprint
 typedef Tile<64, 64, 64, 2, 2> TileSmall;      // wave tile 32 x 32: small problems that need many workgroups
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));    // result of the LDS transpose read
@@ -413,6 +417,10 @@ OD_DEV float gram_operand_scale(const ClassDims& d, const float* scal, int side,
   return ldexpf(sb, 6 - ilogbf(ratio) / 2);
 }
 
+// waves per SIMD the eight-wave tiles of the r-column products are meant for: two workgroups per CU
+template <class T>
+constexpr int product_waves() { return T::THREADS == 512 ? 4 : 1; }
+
 struct GramArgs {
   ClassDims d;            // for the operand scale of sides 0 and 1
   const float* scal;
@@ -420,7 +428,7 @@ struct GramArgs {
   WsArr a, part;
 };
 template <class T, class Num, class SegsT>
-__global__ __launch_bounds__(T::THREADS) void k_gram(SegsT segs) {
+__global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_gram(SegsT segs) {
   static_assert(T::MT == T::NT, "the tile grid of a symmetric result must be symmetric");
   extern __shared__ __align__(16) char lds[];
   OD_SEGMENT(GramArgs);
@@ -445,7 +453,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gram(SegsT segs) {
   f32x16 acc[T::FM][T::FN];
   zero_acc<T>(acc);
   const float sc = Num::F16 ? gram_operand_scale(a_.d, a_.scal, a_.side, z) : 1.f;
-  gemm_mainloop_deep<T, Num, KSF, SrcF32, KSF, SrcF32, 3>(s, s, tm * T::MT, tn * T::NT, kbeg, kend, sc, sc, lds, acc);
+  gemm_mainloop_deep<T, Num, KSF, SrcF32, KSF, SrcF32, (T::THREADS == 512 ? 2 : 3)>(s, s, tm * T::MT, tn * T::NT, kbeg, kend, sc, sc, lds, acc);
   if constexpr (Num::F16) {
     const float inv = 1.f / (sc * sc);
 #pragma unroll
@@ -500,7 +508,7 @@ struct ApplyArgs {
   Pred pred;
 };
 template <class T, class Num, bool DEEP, bool CORR, class SegsT>
-__global__ __launch_bounds__(T::THREADS) void k_apply(SegsT segs) {
+__global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_apply(SegsT segs) {
   extern __shared__ __align__(16) char lds[];
   OD_SEGMENT(ApplyArgs);
   const int rows = a_.rows, r = a_.r, z = blk.z;
@@ -2117,7 +2125,7 @@ static hipError_t proj_v(int v, BatchList b, int n, hipStream_t st, int timed) {
     case PV_FLAT2: return proj_t<TileFlat, NumF16, GSrc, 2>(b, n, st, timed);
     case PV_WIDE: return proj_t<TileWide, NumF16, GSrc>(b, n, st, timed);
     case PV_EXACT_SMALL: return proj_t<TileSmall, NumBF<3>, GSrc>(b, n, st, timed);
-    default: return proj_t<TileSquare, NumBF<3>, GSrc>(b, n, st, timed);
+    default: return proj_t<TileSquare8, NumBF<3>, GSrc>(b, n, st, timed);
   }
 }
 hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st) {
@@ -2157,7 +2165,7 @@ static hipError_t back_v(int v, BatchList b, int n, hipStream_t st, int timed) {
     case PV_HUGE: return back_t<TileHuge, NumF16, GSrc, 2>(b, n, st, timed);
     case PV_WIDE: return back_t<TileWide, NumF16, GSrc>(b, n, st, timed);
     case PV_EXACT_SMALL: return back_t<TileSmall, NumBF<3>, GSrc>(b, n, st, timed);
-    default: return back_t<TileSquare, NumBF<3>, GSrc>(b, n, st, timed);
+    default: return back_t<TileSquare8, NumBF<3>, GSrc>(b, n, st, timed);
   }
 }
 hipError_t launch_back(BatchList b, int n, Prec prec, hipStream_t st) {
@@ -2264,7 +2272,7 @@ static hipError_t gram_pass(BatchList b, int n, int side, bool first, Prec prec,
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
     // fast precision has the sampled scale of B at hand: two-term fp16 operands (half the
     // matrix-core work of the three-way bf16 split at 22 instead of 24 bits)
-    if (prec == PREC_F16) return v == 0 ? gram_tt<TileSmall, NumH2>(g, k, side, first, st) : gram_tt<TileSquare, NumH2>(g, k, side, first, st);
+    if (prec == PREC_F16) return v == 0 ? gram_tt<TileSmall, NumH2>(g, k, side, first, st) : gram_tt<TileSquare8, NumH2>(g, k, side, first, st);
     return v == 0 ? gram_tt<TileSmall, NumBF<3>>(g, k, side, first, st) : gram_tt<TileSquare, NumBF<3>>(g, k, side, first, st);
   });
 }
@@ -2386,7 +2394,7 @@ static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec pre
     // one operand part leaves LDS room for 64-deep steps at two workgroups per CU (measured -13 to
     // -23 %); with two parts the deeper tile halves the occupancy and loses
     if constexpr (Num::PARTS == 1) return apply_tt<TileSquareDeepK, Num, false, CORR>(g, k, side, kind, prec, st);
-    else return apply_tt<TileSquare, Num, false, CORR>(g, k, side, kind, prec, st);
+    else return apply_tt<TileSquare8, Num, false, CORR>(g, k, side, kind, prec, st);
   });
 }
 static hipError_t apply_product(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
@@ -2689,7 +2697,7 @@ static hipError_t efx_v(int v, BatchList b, int n, EfxCoef c, hipStream_t st, in
   constexpr int lds_h = 2 * 3 * 128 * 80, lds_d = 3 * 3 * 128 * 64, lds_tall = 3 * (2 * 128 + 256) * 64;
   switch (v) {
     case EV_EXACT_SMALL: return efx_launch(k_efx<TileSmall, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSmall, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 64, 64, TileSmall::THREADS, TileSmall::lds_bytes<Num>(), c, st, timed);
-    case EV_EXACT: return efx_launch(k_efx<TileSquare, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSquare, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 128, 128, TileSquare::THREADS, TileSquare::lds_bytes<Num>(), c, st, timed);
+    case EV_EXACT: return efx_launch(k_efx<TileSquare8, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSquare8, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 128, 128, TileSquare8::THREADS, TileSquare8::lds_bytes<Num>(), c, st, timed);
     case EV_H: return efx_launch(k_efx_h<XBF, GBF, false, One<EfxArgs>>, k_efx_h<XBF, GBF, false, Segs<EfxArgs>>, b, n, 128, 128, 512, lds_h, c, st, timed);
     case EV_H_STREAM: return efx_launch(k_efx_h<XBF, GBF, true, One<EfxArgs>>, k_efx_h<XBF, GBF, true, Segs<EfxArgs>>, b, n, 128, 128, 512, lds_h, c, st, timed);
     case EV_D: return efx_launch(k_efx_d<XBF, GBF, false, 2, One<EfxArgs>>, k_efx_d<XBF, GBF, false, 2, Segs<EfxArgs>>, b, n, 128, 128, 256, lds_d, c, st, timed);
