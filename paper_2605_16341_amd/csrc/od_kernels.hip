@@ -507,13 +507,10 @@ struct ApplyArgs {
   float* only_q;                // Q of the one matrix of a batch of one
   Pred pred;
 };
-template <class T, class Num, bool DEEP, bool CORR, class SegsT>
-__global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_apply(SegsT segs) {
-  extern __shared__ __align__(16) char lds[];
-  OD_SEGMENT(ApplyArgs);
+template <class T, class Num, bool DEEP, bool CORR>
+OD_DEV void apply_tile(const ApplyArgs& a_, const SegBlock& blk, char* lds) {
   const int rows = a_.rows, r = a_.r, z = blk.z;
   const HalfArr &hn = a_.hn, &ht = a_.ht, &wh = a_.wh;
-  if (!pred_on(a_.pred, z)) return;
   const int tiles_n = (r + T::NT - 1) / T::NT;
   // the column tiles of one row panel of A share an XCD's L2
   const int bid = tiles_n > 1 ? xcd_contiguous(blk.x, blk.grid.x) : blk.x;
@@ -584,6 +581,26 @@ __global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_apply(SegsT 
         }
       }
   }
+}
+
+template <class T, class Num, bool DEEP, bool CORR, class SegsT>
+__global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_apply(SegsT segs) {
+  extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(ApplyArgs);
+  if (!pred_on(a_.pred, blk.z)) return;
+  apply_tile<T, Num, DEEP, CORR>(a_, blk, lds);
+}
+// The result of the second pass in one launch: the correction where the predicate holds, the full product A W2
+// elsewhere (rare; 32-deep steps, so that it needs no more LDS).  For small grids: two launches of which one
+// returns at once cost 4 to 5 us more (five small matrices of ranks 24 to 72: 201 -> 197.5 us a step, 4096 x 4096
+// r = 256 with diagnostics 543 -> 539 us).
+typedef Tile<64, 64, 32, 2, 2> TileSmallFlat;
+template <class SegsT>
+__global__ __launch_bounds__(TileSmall::THREADS) void k_apply_result(SegsT segs) {
+  extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(ApplyArgs);
+  if (pred_on(a_.pred, blk.z)) apply_tile<TileSmall, NumF16, true, true>(a_, blk, lds);
+  else apply_tile<TileSmallFlat, NumBF<2>, false, false>(a_, blk, lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -2352,7 +2369,7 @@ hipError_t launch_orth_gram(BatchList b, int n, int side, Prec prec, hipStream_t
 enum ApplyKind : int { APPLY_W, APPLY_FULL, APPLY_CORRECTION };     // a0 W1 -> a1; a1 W2 -> result; a1 - a1 Phi -> result
 static Pred deviation(const BatchRef& r, int side, int want) { return Pred{r.scal, 2 + side, kFirstOrderDeviation, want}; }
 
-template <class T, class Num, bool DEEP, bool CORR>
+template <class T, class Num, bool DEEP, bool CORR, bool EITHER = false>
 static hipError_t apply_tt(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
   SegList<ApplyArgs> segs;
   for (int i = 0; i < n; ++i) {
@@ -2379,15 +2396,23 @@ static hipError_t apply_tt(BatchList b, int n, int side, ApplyKind kind, Prec pr
     }
     segs.add(a, ceil_div(a.rows, T::MT) * ceil_div(a.r, T::NT), 1, r.d.nb);
   }
+  if constexpr (EITHER) {
+    constexpr int corr = TileSmall::template lds_bytes<NumF16>(), full = TileSmallFlat::template lds_bytes<NumBF<2>>();
+    return segs.launch(k_apply_result<One<ApplyArgs>>, k_apply_result<Segs<ApplyArgs>>, TileSmall::THREADS, corr > full ? corr : full, st, 0);
+  }
   return segs.launch(k_apply<T, Num, DEEP, CORR, One<ApplyArgs>>, k_apply<T, Num, DEEP, CORR, Segs<ApplyArgs>>, T::THREADS, T::template lds_bytes<Num>(), st, 0);
 }
+// `merged`: small grids take the correction and the full product of a result in one launch, that of the former
 template <class Num, bool CORR>
-static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
+static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec prec, bool merged, hipStream_t st) {
   const auto variant = [&](const BatchRef& r) -> int {
     if (r.small) return -1;
-    return (int64_t)ceil_div(r.rows(side), 128) * ceil_div(r.d.r, 128) * r.peers < 512 ? 0 : 1;
+    if ((int64_t)ceil_div(r.rows(side), 128) * ceil_div(r.d.r, 128) * r.peers >= 512) return 1;
+    return merged && kind == APPLY_FULL ? -1 : 0;
   };
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
+    if constexpr (CORR)
+      if (v == 0 && merged) return apply_tt<TileSmall, Num, true, CORR, true>(g, k, side, kind, prec, st);
     if (v == 0) return apply_tt<TileSmall, Num, true, CORR>(g, k, side, kind, prec, st);
     // 128 columns per tile: the loop of a column tile ends at its last row of W (upper triangular),
     // so narrower tiles skip more of the zero half than 256-column ones would (measured -10 %)
@@ -2397,13 +2422,13 @@ static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec pre
     else return apply_tt<TileSquare8, Num, false, CORR>(g, k, side, kind, prec, st);
   });
 }
-static hipError_t apply_product(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
-  return prec == PREC_BF3 ? apply_t<NumBF<3>, false>(b, n, side, kind, prec, st) : apply_t<NumBF<2>, false>(b, n, side, kind, prec, st);
+static hipError_t apply_product(BatchList b, int n, int side, ApplyKind kind, Prec prec, bool merged, hipStream_t st) {
+  return prec == PREC_BF3 ? apply_t<NumBF<3>, false>(b, n, side, kind, prec, merged, st) : apply_t<NumBF<2>, false>(b, n, side, kind, prec, merged, st);
 }
 
 hipError_t launch_orth_second(BatchList b, int n, int side, Prec prec, hipStream_t st) {
   OD_RETURN_IF(small_pass(b, n, side, SMALL_FIRST, prec, st));
-  OD_RETURN_IF(apply_product(b, n, side, APPLY_W, prec, st));
+  OD_RETURN_IF(apply_product(b, n, side, APPLY_W, prec, false, st));
   OD_RETURN_IF(gram_pass(b, n, side, false, prec, st));
   OD_RETURN_IF(by_variant(b, n, [](const BatchRef& r) { return r.small ? -1 : 0; }, [&](int, BatchList g, int k, int) {
     SegList<CorrArgs> segs;
@@ -2471,9 +2496,9 @@ hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st) {
 
 hipError_t launch_orth_result(BatchList b, int n, int side, Prec prec, int which, hipStream_t st) {
   if (which != 2) OD_RETURN_IF(small_pass(b, n, side, SMALL_RESULT, prec, st));
-  if (prec == PREC_BF3) return apply_product(b, n, side, APPLY_FULL, prec, st);
-  if (which != 2) OD_RETURN_IF((apply_t<NumF16, true>(b, n, side, APPLY_CORRECTION, prec, st)));
-  if (which != 1) OD_RETURN_IF(apply_product(b, n, side, APPLY_FULL, prec, st));
+  if (prec == PREC_BF3) return apply_product(b, n, side, APPLY_FULL, prec, false, st);
+  if (which != 2) OD_RETURN_IF((apply_t<NumF16, true>(b, n, side, APPLY_CORRECTION, prec, which == 0, st)));
+  if (which != 1) OD_RETURN_IF(apply_product(b, n, side, APPLY_FULL, prec, which == 0, st));
   return hipSuccess;
 }
 
