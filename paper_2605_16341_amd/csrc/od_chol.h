@@ -11,8 +11,8 @@
 //     8 (v / 4) + 4 (l / 32) + v % 4, column l % 32), spread over the workers so that every
 //     row and column of tiles is shared out evenly.  The diagonal tiles wait in LDS.
 //   * Step J, (a): the diagonal wave factors tile (J, J) in place, four rows at a time.
-//     The 4 x 4 diagonal block is gathered with readlane, factored and inverted in scalar
-//     (wave-uniform) arithmetic; the new rows are a 4 x 4 product inside each lane; the
+//     The 4 x 4 diagonal block is gathered with readlane and factored in scalar (wave-uniform)
+//     arithmetic; the new rows follow by forward substitution inside each lane; the
 //     rank-4 trailing update of the tile is two fp32 matrix-core products (32x32x2).  The
 //     same operations applied to an identity tile give the inverse of the tile's factor.
 //     Only the inverse (fp32) and the factor are left in LDS; a worker without a tile in (b) writes both
