@@ -36,6 +36,8 @@ constexpr double kGroupMaxElements = 512.0 * 1024 * 1024;
 // sums, factors) should still be in the Infinity Cache when it is read.
 constexpr int kBatchMatrices = 32;
 constexpr double kBatchElements = 64.0 * 1024 * 1024;
+// In any case this many: a batch's matrices are the y or z extent of its launches, where a device takes 65536.
+constexpr int kBatchMost = 32768;
 // Batches of different shapes share their launches (a cluster) up to this many elements: below it
 // the launches of one shape leave most of the chip idle, above it every batch fills the chip by itself.
 constexpr double kClusterElements = 128.0 * 1024 * 1024;
@@ -260,7 +262,7 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     int found = -1;
     for (size_t b = 0; b < h->batches.size(); ++b) {
       const double held = (double)h->batches[b].members.size();
-      if (same_shape(h->batches[b].d, a) && (held < kBatchMatrices || (held + 1) * (double)a.m * (double)a.n <= kBatchElements)) found = (int)b;
+      if (held < kBatchMost && same_shape(h->batches[b].d, a) && (held < kBatchMatrices || (held + 1) * (double)a.m * (double)a.n <= kBatchElements)) found = (int)b;
     }
     if (found < 0) {
       Batch nb = {};

@@ -159,3 +159,22 @@ def test_groups_follow_the_size_of_the_set():
     assert groups(small, 32, 0)[0] == 1 and groups(small, 32, 2)[0] == 2
     assert groups(small, 32, 2)[1] >= groups(small, 32, 1)[1]
     assert b.load().orthdion_get_groups(None) == 0
+
+
+def test_launch_batches_stay_below_the_grid_limit():
+    """A batch's matrices are the y or z extent of its launches, which a device limits to 65536.  The P
+    arrays of a batch lie one slice behind the other, with other arrays between two batches: equal steps
+    in the layout are one batch."""
+    nmat = 70000
+    h = b.orthdion_create([(8, 8)] * nmat, 8, b.ORTHDION_F32, b.ORTHDION_F32)
+    lib, off = b.load(), ctypes.c_size_t()
+    offsets = []
+    for i in range(nmat):
+        assert lib.orthdion_workspace_layout(h, i, ctypes.byref(off), None, None, None, None, None) == b.ORTHDION_OK
+        offsets.append(off.value)
+    b.orthdion_destroy(h)
+    longest = run = 1
+    for prev, cur in zip(offsets, offsets[1:]):
+        run = run + 1 if cur - prev == 8 * 8 * 4 else 1
+        longest = max(longest, run)
+    assert 32 <= longest <= 65535, longest
