@@ -52,6 +52,8 @@ struct Batch {
   size_t off_pa, off_pb, off_ra, off_rb, off_part, off_gram, off_tp1, off_tp2, off_tq1, off_tq2, off_w,
       off_tmp, off_colsq;
   size_t off_ph, off_pht, off_rh, off_qh, off_qht;   // pre-scaled fp16 copies of the factors (uint16 arrays)
+  size_t off_dpart;                  // diagnostics: partial norms, diag_blocks times 4 doubles per matrix
+  int diag_blocks;
   int64_t st_p, st_r, st_part, st_rr, st_colsq;
   int splits_proj, splits_back, splits_gram[2], slabs;
   int slot_base;                     // first row of this batch in the scal / info tables
@@ -117,7 +119,7 @@ struct orthdion_ctx {
   std::vector<RankClass> classes;
   std::vector<Unit> units;
   std::vector<int> batch_of, slot_of;     // per matrix
-  size_t off_mats, off_scal, off_info, off_diag, off_dacc, off_dpart, ws_bytes;
+  size_t off_mats, off_scal, off_info, off_diag, off_dacc, ws_bytes;
   void* last_ws;
   bool diag_on = false, diag_valid = false;
   // optional phase timing with HIP events (host resources only)
@@ -323,7 +325,6 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
   h->off_info = off; off = align_up(off + (size_t)nmat * od::kInfoPerMat * sizeof(int));
   h->off_diag = off; off = align_up(off + (size_t)nmat * od::kDiagPerMat * sizeof(float));
   h->off_dacc = off; off = align_up(off + (size_t)nmat * od::kDaccPerMat * sizeof(double));
-  h->off_dpart = off; off = align_up(off + (size_t)nmat * od::kDiagBlocks * 4 * sizeof(double));
   // Groups: the heaviest batch first, each to the group with less work so far (m n per matrix
   // measures a batch's step).  A set with a single batch stays one group.
   std::vector<int> group_of(h->batches.size(), 0);
@@ -451,6 +452,9 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     auto take_h = [&](int64_t stride) { size_t o = off; off = align_up(off + (size_t)stride * d.nb * sizeof(uint16_t)); return o; };
     b.off_ph = take_h(b.st_p); b.off_pht = take_h(b.st_p);
     b.off_rh = take_h(b.st_r); b.off_qh = take_h(b.st_r); b.off_qht = take_h(b.st_r);
+    // one workgroup per four rows (k_diag_norms): the table stays small beside a small matrix
+    b.diag_blocks = (int)std::min<int64_t>(od::kDiagBlocks, (m + 3) / 4);
+    b.off_dpart = off; off = align_up(off + (size_t)d.nb * b.diag_blocks * 4 * sizeof(double));
   }
   h->ws_bytes = off;
   return ORTHDION_OK;
@@ -569,7 +573,6 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
   h->diag_valid = diag;
   float* diag_all = reinterpret_cast<float*>(ws + h->off_diag);
   double* dacc_all = reinterpret_cast<double*>(ws + h->off_dacc);
-  double* dpart_all = reinterpret_cast<double*>(ws + h->off_dpart);
   const bool fast = prec == od::PREC_F16;
 
   // the caller's buffers in slot order, and every batch with its workspace arrays
@@ -643,7 +646,8 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     OD_TRY(od::launch_begin(list.get(), n, prec, st));
     OD_PHASE_END(ORTHDION_PHASE_STATS);
     if (diag)
-      for (int k : cluster) OD_TRY(od::launch_diag_norms(refs[k].d, refs[k].mats, dpart_all + (size_t)h->batches[k].slot_base * od::kDiagBlocks * 4, st));
+      for (int k : cluster)
+        OD_TRY(od::launch_diag_norms(refs[k].d, refs[k].mats, reinterpret_cast<double*>(ws + h->batches[k].off_dpart), h->batches[k].diag_blocks, st));
     OD_PHASE_KERNEL(ORTHDION_PHASE_PROJ);
     OD_TRY(od::launch_proj(list.get(), n, prec, st));
     OD_PHASE_BEGIN(ORTHDION_PHASE_PROJ_REDUCE);
@@ -700,7 +704,7 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     OD_TRY(od::launch_gram_plain(d.nb, d.n, d.r, v.rb, v.part, sg, st));
     OD_TRY(od::launch_reduce(d.nb, v.part, sg, (int64_t)d.r * d.r, v.gram, st));
     OD_TRY(od::launch_power(d.nb, d.r, v.gram, v.tmp, v.w, v.part, dacc, st));
-    OD_TRY(od::launch_diag_final(d.nb, d.r, dpart_all + (size_t)slot * od::kDiagBlocks * 4, dacc, v.t1[1], v.t2[1],
+    OD_TRY(od::launch_diag_final(d.nb, d.r, reinterpret_cast<const double*>(ws + h->batches[k].off_dpart), h->batches[k].diag_blocks, dacc, v.t1[1], v.t2[1],
                                  h->cfg.variant == ORTHDION_COLNORM ? 1 : 0, diag_all + (size_t)slot * od::kDiagPerMat, st));
     return ORTHDION_OK;
   };

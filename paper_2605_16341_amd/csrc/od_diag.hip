@@ -40,8 +40,8 @@ OD_DEV double block_sum_256(double v, double* red) {
 // ------------------------------------------------------------------------------------
 // sums of squares of M_prev, G and B = M_prev + G, one partial triple per workgroup
 // ------------------------------------------------------------------------------------
-// One wave per row at a time: addresses advance without a division, and kDiagBlocks workgroups keep
-// enough loads in flight for the memory system (2048 x 5632: 44 us with a 64-bit division per four
+// One wave per row at a time, four rows per workgroup: addresses advance without a division, and up to
+// kDiagBlocks workgroups keep enough loads in flight for the memory system (2048 x 5632: 44 us with a 64-bit division per four
 // elements and 128 workgroups, 15 us like this: 4.8 TB/s, the rate of a large copy).
 template <bool GBF>
 __global__ __launch_bounds__(256) void k_diag_norms(ClassDims d, const MatEntry* mats, double* dpart) {
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void k_diag_norms(ClassDims d, const MatEntry*
   const double tg = block_sum_256(sg, red);
   const double tb = block_sum_256(sb, red);
   if (tid == 0) {
-    double* o = dpart + ((int64_t)z * kDiagBlocks + blockIdx.x) * 4;
+    double* o = dpart + ((int64_t)z * gridDim.x + blockIdx.x) * 4;
     o[0] = tm; o[1] = tg; o[2] = tb; o[3] = 0.0;
   }
 }
@@ -261,12 +261,12 @@ __global__ __launch_bounds__(256) void k_power_final(int r, WsArr xbuf, double* 
 // the reported scalars, one workgroup per matrix; QR variant: also the trace of T2 T1 (both upper
 // triangular: the sum of products of the diagonals), which is <B, P Q^T>
 // ------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_diag_final(int r, const double* dpart, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag) {
+__global__ __launch_bounds__(256) void k_diag_final(int r, const double* dpart, int blocks, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag) {
   const int z = blockIdx.x, tid = threadIdx.x;
   __shared__ double red[256];
   double sm = 0.0, sg = 0.0, sb = 0.0, tr = 0.0;
-  for (int k = tid; k < kDiagBlocks; k += 256) {
-    const double* p = dpart + ((int64_t)z * kDiagBlocks + k) * 4;
+  for (int k = tid; k < blocks; k += 256) {
+    const double* p = dpart + ((int64_t)z * blocks + k) * 4;
     sm += p[0]; sg += p[1]; sb += p[2];
   }
   if (!colnorm) {
@@ -311,9 +311,9 @@ __global__ __launch_bounds__(256) void k_resize_q(const float* q_old, int64_t n,
 // ------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------
-hipError_t launch_diag_norms(const ClassDims& d, const MatEntry* mats, double* dpart, hipStream_t st) {
-  if (d.g_bf16) hipLaunchKernelGGL(k_diag_norms<true>, dim3(kDiagBlocks, d.nb), dim3(256), 0, st, d, mats, dpart);
-  else hipLaunchKernelGGL(k_diag_norms<false>, dim3(kDiagBlocks, d.nb), dim3(256), 0, st, d, mats, dpart);
+hipError_t launch_diag_norms(const ClassDims& d, const MatEntry* mats, double* dpart, int blocks, hipStream_t st) {
+  if (d.g_bf16) hipLaunchKernelGGL(k_diag_norms<true>, dim3(blocks, d.nb), dim3(256), 0, st, d, mats, dpart);
+  else hipLaunchKernelGGL(k_diag_norms<false>, dim3(blocks, d.nb), dim3(256), 0, st, d, mats, dpart);
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }
@@ -373,8 +373,8 @@ hipError_t launch_power(int nb, int r, WsArr gram, WsArr tmp1, WsArr tmp2, WsArr
   return hipSuccess;
 }
 
-hipError_t launch_diag_final(int nb, int r, const double* dpart, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag, hipStream_t st) {
-  hipLaunchKernelGGL(k_diag_final, dim3(nb), dim3(256), 0, st, r, dpart, dacc, t1, t2, colnorm, diag);
+hipError_t launch_diag_final(int nb, int r, const double* dpart, int blocks, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag, hipStream_t st) {
+  hipLaunchKernelGGL(k_diag_final, dim3(nb), dim3(256), 0, st, r, dpart, blocks, dacc, t1, t2, colnorm, diag);
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }

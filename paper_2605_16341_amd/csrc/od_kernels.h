@@ -170,10 +170,10 @@ hipError_t launch_efx(BatchList b, int n, Prec prec, float a_coef, float b_coef,
 constexpr int kDiagPerMat = 8;     // floats reported per matrix
 constexpr int kDaccPerMat = 8;     // fp64 accumulators per matrix: [3] ||R||^2, [4] sum of column lengths of R,
                                    // [5] sum of len * log(len), [7] lambda_max
-constexpr int kDiagBlocks = 512;   // workgroups (partial triples of 4 doubles) per matrix of the norm pass
+constexpr int kDiagBlocks = 512;   // most workgroups (partial triples of 4 doubles) per matrix of the norm pass
 
-// dpart[mat][kDiagBlocks][4] = partial sums of squares of M, G, M + G
-hipError_t launch_diag_norms(const ClassDims& d, const MatEntry* mats, double* dpart, hipStream_t st);
+// dpart[mat][blocks][4] = partial sums of squares of M, G, M + G
+hipError_t launch_diag_norms(const ClassDims& d, const MatEntry* mats, double* dpart, int blocks, hipStream_t st);
 // column lengths of R (n x r, ld r) -> dacc[mat][3..5]; `part` needs slabs * r floats per matrix
 hipError_t launch_diag_cols(int nb, int n, int r, WsArr rr, WsArr part, int slabs, double* dacc, hipStream_t st);
 // out[mat] = callers' Q (n x r)
@@ -183,7 +183,7 @@ hipError_t launch_gather_q(int nb, int n, int r, const MatEntry* mats, WsArr out
 hipError_t launch_power(int nb, int r, WsArr gram, WsArr tmp1, WsArr tmp2, WsArr xbuf, double* dacc, hipStream_t st);
 // diag[mat][0..7] = ||B||, ||R||, tracking error, ||M_prev|| / ||G||, <B, P Q^T>, nu, effective rank, ||G||;
 // <B, P Q^T> is sum_i t1[i][i] t2[i][i] (QR) or the sum of the column lengths of R (colnorm)
-hipError_t launch_diag_final(int nb, int r, const double* dpart, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag, hipStream_t st);
+hipError_t launch_diag_final(int nb, int r, const double* dpart, int blocks, const double* dacc, WsArr t1, WsArr t2, int colnorm, float* diag, hipStream_t st);
 // q_new (n x r_new) = leading min(r_old, r_new) columns of q_old, then columns of pad (n x (r_new - r_old))
 hipError_t launch_resize_q(const float* q_old, int64_t n, int r_old, float* q_new, int r_new, const float* pad, hipStream_t st);
 

@@ -178,3 +178,13 @@ def test_launch_batches_stay_below_the_grid_limit():
         run = run + 1 if cur - prev == 8 * 8 * 4 else 1
         longest = max(longest, run)
     assert 32 <= longest <= 65535, longest
+
+
+@pytest.mark.parametrize("count,size,most", [(8000, 8, 69e6), (1000, 64, 22e6)])
+def test_many_small_matrices_fit_the_static_scratch(count, size, most):
+    """The tables of a matrix stay small beside its arrays, so that orthdion_step_static takes thousands
+    of small matrices (its scratch is 128 MiB).  8 x 8, r = 8: about 30 slices of 256 bytes, 8.6 KB."""
+    h = b.orthdion_create([(size, size)] * count, 8, b.ORTHDION_BF16, b.ORTHDION_BF16)
+    need = b.orthdion_workspace_bytes(h)
+    b.orthdion_destroy(h)
+    assert need <= most and need <= b.orthdion_static_scratch_bytes()

@@ -100,6 +100,12 @@ def test_diagnostics_power_iteration_tiles(count, m, n, r):
     run_case([(m, n)] * count, r, "f32", "colnorm", steps=1, seed=735)
 
 
+def test_diagnostics_norms_at_the_edges_of_their_grid():
+    """One workgroup per four rows up to 2048 rows, and two matrices of one shape whose partial sums lie
+    one behind the other: 2, 510 and 512 workgroups, the last of these with rows of a second turn."""
+    run_case([(8, 16), (2040, 24), (2056, 24), (8, 16), (2056, 24)], 8, "f32", "qr", steps=2, seed=740)
+
+
 @pytest.mark.parametrize("variant", ["qr", "colnorm"])
 def test_diagnostics_c2_shape(variant):
     w = synth.WORKLOADS["C2"]
