@@ -38,6 +38,7 @@ constexpr int kBatchMatrices = 32;
 constexpr double kBatchElements = 64.0 * 1024 * 1024;
 // In any case this many: a batch's matrices are the y or z extent of its launches, where a device takes 65536.
 constexpr int kBatchMost = 32768;
+constexpr int kLeanDiagBlocks = 128;  // see the two plans of the workspace in create_impl
 // Batches of different shapes share their launches (a cluster) up to this many elements: below it
 // the launches of one shape leave most of the chip idle, above it every batch fills the chip by itself.
 constexpr double kClusterElements = 128.0 * 1024 * 1024;
@@ -54,6 +55,7 @@ struct Batch {
   size_t off_ph, off_pht, off_rh, off_qh, off_qht;   // pre-scaled fp16 copies of the factors (uint16 arrays)
   size_t off_dpart;                  // diagnostics: partial norms, diag_blocks times 4 doubles per matrix
   int diag_blocks;
+  int alike;                         // matrices of this shape in the whole set
   int64_t st_p, st_r, st_part, st_rr, st_colsq;
   int splits_proj, splits_back, splits_gram[2], slabs;
   int slot_base;                     // first row of this batch in the scal / info tables
@@ -280,6 +282,12 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     h->batches[found].members.push_back(i);
   }
 
+  for (Batch& b : h->batches) {
+    b.alike = 0;
+    for (const Batch& o : h->batches)
+      if (same_shape(o.d, h->mats[b.members[0]])) b.alike += (int)o.members.size();
+  }
+
   // Clusters, in batch order: the ranks up to 256 together, every larger rank by itself.  They do not
   // depend on the groups below (nor does anything chosen from them), so that the groups leave the
   // results alone bit for bit.
@@ -401,61 +409,78 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     c.off_gram = take_rr(); c.off_tp1 = take_rr(); c.off_tp2 = take_rr(); c.off_tq1 = take_rr(); c.off_tq2 = take_rr();
     c.off_w = take_rr(); c.off_tmp = take_rr();
   }
-  for (Batch& b : h->batches) {
-    ClassDims& d = b.d;
-    const RankClass& rcl = h->classes[b.rank_class];
-    const int64_t m = d.m, n = d.n, r = d.r;
-    const od::Prec prec = resolve_prec(*cfg);
-    auto splits_for = [&](bool back) {
-      int rows, cols, slots;
-      if (back) od::back_tiling(d, prec, &rows, &cols, &slots);
-      else od::proj_tiling(d, prec, b.peers, &rows, &cols, &slots);
-      const int64_t out = back ? n : m, k = back ? m : n;
-      const int64_t tiles = ((out + rows - 1) / rows) * ((r + cols - 1) / cols);
-      // one 8-wave workgroup per CU is scheduled in whole rounds; two smaller ones mix
-      return slots == 256 ? pick_splits_by_rounds(tiles, b.peers, k, 256, slots) : pick_splits(tiles, b.peers, k, 128);
-    };
-    b.splits_proj = splits_for(false);
-    b.splits_back = splits_for(true);
-    // Gram tiles on and above the diagonal (the ones that are computed)
-    const int64_t gt1 = (r + 127) / 128;
-    const int64_t gt = gt1 * (gt1 + 1) / 2;
-    for (int side = 0; side < 2; ++side) {
-      const int64_t rows = side == 0 ? m : n;
-      // small ranks: one 32 x 32 tile, one thread per row: 256-row slabs (k_small_gram, k_small_first_pass);
-      // else two workgroups of the Gram kernel fit one CU
-      int sg = b.small ? pick_splits(1, b.peers, rows, 256) : pick_splits_by_rounds(gt, b.peers, rows, 256, 512);
-      if (sg > 32) sg = 32;
-      b.splits_gram[side] = sg;
+  // The arrays of the batches.  Batches that share their launches now and then take more splits than they
+  // would alone (rounds do not divide evenly), up to 30 % more workspace.  Where that would take a set out of
+  // reach of orthdion_step_static, the plan without it is used, if it fits.
+  const size_t arrays = off;
+  auto plan = [&](bool lean) {
+    off = arrays;
+    for (Batch& b : h->batches) {
+      ClassDims& d = b.d;
+      const RankClass& rcl = h->classes[b.rank_class];
+      const int64_t m = d.m, n = d.n, r = d.r;
+      const od::Prec prec = resolve_prec(*cfg);
+      auto splits_for = [&](bool back, int64_t peers) {
+        int rows, cols, slots;
+        if (back) od::back_tiling(d, prec, &rows, &cols, &slots);
+        else od::proj_tiling(d, prec, peers, &rows, &cols, &slots);
+        const int64_t out = back ? n : m, k = back ? m : n;
+        const int64_t tiles = ((out + rows - 1) / rows) * ((r + cols - 1) / cols);
+        // one 8-wave workgroup per CU is scheduled in whole rounds; two smaller ones mix
+        return slots == 256 ? pick_splits_by_rounds(tiles, peers, k, 256, slots) : pick_splits(tiles, peers, k, 128);
+      };
+      // `lean`: no more splits than in launches of the batch's own, at most kBatchMatrices matrices each
+      auto limited = [&](auto&& pick) {
+        int s = pick(b.peers);
+        if (lean)
+          for (int64_t alone : {std::min(b.alike, kBatchMatrices), b.alike % kBatchMatrices})
+            if (alone > 0) s = std::min(s, (int)pick(alone));
+        return s;
+      };
+      b.splits_proj = limited([&](int64_t peers) { return splits_for(false, peers); });
+      b.splits_back = limited([&](int64_t peers) { return splits_for(true, peers); });
+      // Gram tiles on and above the diagonal (the ones that are computed)
+      const int64_t gt1 = (r + 127) / 128;
+      const int64_t gt = gt1 * (gt1 + 1) / 2;
+      for (int side = 0; side < 2; ++side) {
+        const int64_t rows = side == 0 ? m : n;
+        // small ranks: one 32 x 32 tile, one thread per row: 256-row slabs (k_small_gram, k_small_first_pass);
+        // else two workgroups of the Gram kernel fit one CU
+        b.splits_gram[side] = limited([&](int64_t peers) {
+          return b.small ? pick_splits(1, peers, rows, 256) : pick_splits_by_rounds(gt, peers, rows, 256, 512);
+        });
+      }
+      b.slabs = (int)((n + 31) / 32);           // row slabs of the column-norm kernels: many, so the grid fills the chip
+      if (b.slabs > 256) b.slabs = 256;
+      int64_t part = (int64_t)b.splits_proj * m * r;
+      if ((int64_t)b.splits_back * n * r > part) part = (int64_t)b.splits_back * n * r;
+      for (int sg : b.splits_gram)
+        if ((int64_t)sg * r * r > part) part = (int64_t)sg * r * r;
+      if ((int64_t)b.slabs * r > part) part = (int64_t)b.slabs * r;
+      // strides rounded so that every matrix slice stays 256-byte aligned
+      auto rnd = [](int64_t e) { return (e + 63) / 64 * 64; };
+      b.st_p = rnd(m * r); b.st_r = rnd(n * r); b.st_part = rnd(part); b.st_rr = rnd(r * r); b.st_colsq = rnd(r);
+      auto take = [&](int64_t stride) { size_t o = off; off = align_up(off + (size_t)stride * d.nb * sizeof(float)); return o; };
+      b.off_pa = take(b.st_p); b.off_pb = take(b.st_p);
+      b.off_ra = take(b.st_r); b.off_rb = take(b.st_r);
+      b.off_part = take(b.st_part);
+      // this batch's slices of the class-owned r x r arrays
+      const size_t in_class = (size_t)(b.slot_base - rcl.slot_base) * (size_t)rcl.st_rr * sizeof(float);
+      b.off_gram = rcl.off_gram + in_class;
+      b.off_tp1 = rcl.off_tp1 + in_class; b.off_tp2 = rcl.off_tp2 + in_class;
+      b.off_tq1 = rcl.off_tq1 + in_class; b.off_tq2 = rcl.off_tq2 + in_class;
+      b.off_w = rcl.off_w + in_class; b.off_tmp = rcl.off_tmp + in_class;
+      b.off_colsq = take(b.st_colsq);
+      auto take_h = [&](int64_t stride) { size_t o = off; off = align_up(off + (size_t)stride * d.nb * sizeof(uint16_t)); return o; };
+      b.off_ph = take_h(b.st_p); b.off_pht = take_h(b.st_p);
+      b.off_rh = take_h(b.st_r); b.off_qh = take_h(b.st_r); b.off_qht = take_h(b.st_r);
+      // one workgroup per four rows (k_diag_norms): the table stays small beside a small matrix
+      b.diag_blocks = (int)std::min<int64_t>(lean ? kLeanDiagBlocks : od::kDiagBlocks, (m + 3) / 4);
+      b.off_dpart = off; off = align_up(off + (size_t)d.nb * b.diag_blocks * 4 * sizeof(double));
     }
-    b.slabs = (int)((n + 31) / 32);           // row slabs of the column-norm kernels: many, so the grid fills the chip
-    if (b.slabs > 256) b.slabs = 256;
-    int64_t part = (int64_t)b.splits_proj * m * r;
-    if ((int64_t)b.splits_back * n * r > part) part = (int64_t)b.splits_back * n * r;
-    for (int sg : b.splits_gram)
-      if ((int64_t)sg * r * r > part) part = (int64_t)sg * r * r;
-    if ((int64_t)b.slabs * r > part) part = (int64_t)b.slabs * r;
-    // strides rounded so that every matrix slice stays 256-byte aligned
-    auto rnd = [](int64_t e) { return (e + 63) / 64 * 64; };
-    b.st_p = rnd(m * r); b.st_r = rnd(n * r); b.st_part = rnd(part); b.st_rr = rnd(r * r); b.st_colsq = rnd(r);
-    auto take = [&](int64_t stride) { size_t o = off; off = align_up(off + (size_t)stride * d.nb * sizeof(float)); return o; };
-    b.off_pa = take(b.st_p); b.off_pb = take(b.st_p);
-    b.off_ra = take(b.st_r); b.off_rb = take(b.st_r);
-    b.off_part = take(b.st_part);
-    // this batch's slices of the class-owned r x r arrays
-    const size_t in_class = (size_t)(b.slot_base - rcl.slot_base) * (size_t)rcl.st_rr * sizeof(float);
-    b.off_gram = rcl.off_gram + in_class;
-    b.off_tp1 = rcl.off_tp1 + in_class; b.off_tp2 = rcl.off_tp2 + in_class;
-    b.off_tq1 = rcl.off_tq1 + in_class; b.off_tq2 = rcl.off_tq2 + in_class;
-    b.off_w = rcl.off_w + in_class; b.off_tmp = rcl.off_tmp + in_class;
-    b.off_colsq = take(b.st_colsq);
-    auto take_h = [&](int64_t stride) { size_t o = off; off = align_up(off + (size_t)stride * d.nb * sizeof(uint16_t)); return o; };
-    b.off_ph = take_h(b.st_p); b.off_pht = take_h(b.st_p);
-    b.off_rh = take_h(b.st_r); b.off_qh = take_h(b.st_r); b.off_qht = take_h(b.st_r);
-    // one workgroup per four rows (k_diag_norms): the table stays small beside a small matrix
-    b.diag_blocks = (int)std::min<int64_t>(od::kDiagBlocks, (m + 3) / 4);
-    b.off_dpart = off; off = align_up(off + (size_t)d.nb * b.diag_blocks * 4 * sizeof(double));
-  }
+    return off;
+  };
+  if (plan(false) > ORTHDION_STATIC_SCRATCH_BYTES && plan(true) > ORTHDION_STATIC_SCRATCH_BYTES) plan(false);
   h->ws_bytes = off;
   return ORTHDION_OK;
 }

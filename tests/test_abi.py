@@ -188,3 +188,21 @@ def test_many_small_matrices_fit_the_static_scratch(count, size, most):
     need = b.orthdion_workspace_bytes(h)
     b.orthdion_destroy(h)
     assert need <= most and need <= b.orthdion_static_scratch_bytes()
+
+
+@pytest.mark.parametrize("groups", [0, 1, 2])
+@pytest.mark.parametrize("parts,precision", [
+    # bytes with every batch in launches of its own: 116.2, 109.4, 110.6, 120.5 MB
+    ([(1880, 3216, 200, 3), (208, 856, 64, 36)], b.ORTHDION_PREC_FAST),
+    ([(728, 2896, 24, 5), (2968, 1968, 208, 5)], b.ORTHDION_PREC_FAST),
+    ([(1832, 3312, 248, 3), (1296, 768, 40, 12)], b.ORTHDION_PREC_FAST),
+    ([(2328, 2736, 224, 2), (2368, 392, 8, 2), (2000, 3352, 232, 2)], b.ORTHDION_PREC_FAST)])
+def test_sharing_launches_keeps_a_set_within_the_static_scratch(parts, precision, groups):
+    """Splits chosen for launches that several shapes share can need more workspace than splits chosen
+    shape by shape; a set that fits the scratch with the latter still fits, whatever its groups."""
+    shapes = [(m, n) for m, n, _, count in parts for _ in range(count)]
+    ranks = [r for _, _, r, count in parts for _ in range(count)]
+    h = b.orthdion_create(shapes, ranks, b.ORTHDION_BF16, b.ORTHDION_BF16, precision=precision, groups=groups)
+    need = b.orthdion_workspace_bytes(h)
+    b.orthdion_destroy(h)
+    assert need <= b.orthdion_static_scratch_bytes()
