@@ -147,15 +147,25 @@ constexpr int kPowerRowsPerWg = 16;
 OD_DEV float power_start(int i) { return 1.f + 0.5f * __sinf(0.7f * (float)i); }
 
 // out = (a / max diagonal of a)^2 for symmetric a: row i of the left and row j of the right operand
-// are both read along k.
-template <class T>
+// are both read along k.  UPPER: only the tiles on and above the diagonal are computed, and stored a second
+// time, transposed.  That is for grids that fill the chip, where the products count: what the diagnostics add
+// to a step of six matrices of r = 2048 is 3.6 ms with 128 matrix-vector products in place of the squares, 5.4 with
+// all tiles of the squares, 4.0 with half of them (one matrix 1.5, 1.06, 1.02; 24 of r = 1024 3.3, 3.1, 2.4).  A
+// grid that leaves part of the chip idle is all latency, to which the second store adds (r = 256: 5 us per step).
+template <class T, bool UPPER>
 __global__ __launch_bounds__(T::THREADS) void k_power_square(int r, WsArr a, WsArr out) {
   typedef NumBF<3> Num;
   extern __shared__ __align__(16) char lds[];
   __shared__ float red[T::THREADS / 64];
   const int z = blockIdx.z, tid = threadIdx.x;
   const int tiles = (r + T::NT - 1) / T::NT;
-  const int tn = blockIdx.x % tiles, tm = blockIdx.x / tiles;
+  int tn = blockIdx.x % tiles, tm = blockIdx.x / tiles;
+  if constexpr (UPPER) {
+    tm = 0;
+    tn = blockIdx.x;
+    while (tn >= tiles - tm) { tn -= tiles - tm; ++tm; }
+    tn += tm;
+  }
   const SrcF32 s{a.base + (int64_t)z * a.stride, r, r, r};
   float md = 0.f;
   for (int i = tid; i < r; i += T::THREADS) md = fmaxf(md, s.p[(int64_t)i * r + i]);
@@ -173,6 +183,27 @@ __global__ __launch_bounds__(T::THREADS) void k_power_square(int r, WsArr a, WsA
   for_each_acc<T>(acc, tm * T::MT, tn * T::NT, [&](int row, int col, float v) {
     if (row < r && col < r) o[(int64_t)row * r + col] = v * inv * inv;
   });
+  if (UPPER && tm != tn) {
+    // lane (c, h) holds rows 8q + 4h .. 8q + 4h + 3 of column c: four consecutive entries of row c of the
+    // transposed tile (r is a multiple of 8, so they are inside or outside together)
+    const int lane = tid & 63, wave = tid >> 6, wm = wave / T::WN, wn = wave % T::WN;
+#pragma unroll
+    for (int fm = 0; fm < T::FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < T::FN; ++fn) {
+        const int col = tn * T::NT + wn * T::WTN + fn * 32 + (lane & 31);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row0 = tm * T::MT + wm * T::WTM + fm * 32 + 8 * q + 4 * (lane >> 5);
+          if (col < r && row0 < r) {
+            f32x4 v4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v4[e] = acc[fm][fn][4 * q + e] * inv * inv;
+            *reinterpret_cast<f32x4*>(o + (int64_t)col * r + row0) = v4;
+          }
+        }
+      }
+  }
 }
 
 // y[i] = scale * sum_j g[i][j] x[j], row0 <= i < row1: four consecutive rows per wave and turn, so that
@@ -335,14 +366,14 @@ hipError_t launch_gather_q(int nb, int n, int r, const MatEntry* mats, WsArr out
   return hipSuccess;
 }
 
-template <class T>
+template <class T, bool UPPER>
 static hipError_t power_square(int nb, int r, WsArr a, WsArr out, hipStream_t st) {
   constexpr int lds = T::template lds_bytes<NumBF<3>>();
   const hipError_t e = lds > 64 * 1024
-      ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_power_square<T>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) : hipSuccess;
+      ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_power_square<T, UPPER>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) : hipSuccess;
   if (e != hipSuccess) return e;
   const int tiles = (r + T::NT - 1) / T::NT;
-  hipLaunchKernelGGL(k_power_square<T>, dim3(tiles * tiles, 1, nb), dim3(T::THREADS), lds, st, r, a, out);
+  hipLaunchKernelGGL((k_power_square<T, UPPER>), dim3(UPPER ? tiles * (tiles + 1) / 2 : tiles * tiles, 1, nb), dim3(T::THREADS), lds, st, r, a, out);
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }
@@ -353,7 +384,7 @@ hipError_t launch_power(int nb, int r, WsArr gram, WsArr tmp1, WsArr tmp2, WsArr
   const bool big = (int64_t)((r + 127) / 128) * ((r + 127) / 128) * nb >= 256;
   WsArr cur = gram, nxt = tmp1;
   for (int i = 0; i < kPowerSquarings; ++i) {
-    const hipError_t e = big ? power_square<Tile<128, 128, 32, 2, 2>>(nb, r, cur, nxt, st) : power_square<Tile<64, 64, 64, 2, 2>>(nb, r, cur, nxt, st);
+    const hipError_t e = big ? power_square<Tile<128, 128, 32, 2, 2>, true>(nb, r, cur, nxt, st) : power_square<Tile<64, 64, 64, 2, 2>, false>(nb, r, cur, nxt, st);
     if (e != hipSuccess) return e;
     cur = nxt;
     nxt = cur.base == tmp1.base ? tmp2 : tmp1;
