@@ -61,7 +61,8 @@ struct Batch {
   int slot_base;                     // first row of this batch in the scal / info tables
   int rank_class;
   int cluster;                       // batches of one cluster share their launches
-  bool small;                        // orthogonalisation by the three kernels for ranks up to 32
+  bool small;                        // orthogonalisation by the three stages for ranks up to 32
+  bool beside;                       // small, in a cluster that holds a larger rank
   int64_t peers;                     // matrices of this shape that make up the same work as the cluster
 };
 
@@ -314,16 +315,9 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       b.peers = (int64_t)(cluster_elems[b.cluster] / ((double)b.d.m * b.d.n));
       if (b.peers < (int64_t)b.members.size()) b.peers = (int64_t)b.members.size();
     }
-    // Ranks up to 32 have three kernels of their own per orthogonalisation instead of eight (one matrix of
-    // 8192 x 8192, r = 16: 376 -> 352 us).  Where a cluster runs the eight anyway for a larger rank, its small
-    // ranks join them (five matrices of ranks 24 to 72: 262 -> 201 us).  One choice per rank: the factorisations
-    // are launched by rank.
-    std::vector<int> widest(cluster_elems.size(), 0);
-    for (const Batch& b : h->batches) widest[b.cluster] = std::max(widest[b.cluster], b.d.r);
-    bool beside[33] = {};                // ranks that share a cluster with a larger one than 32
-    for (const Batch& b : h->batches)
-      if (b.d.r <= 32 && widest[b.cluster] > 32) beside[b.d.r] = true;
-    for (Batch& b : h->batches) b.small = b.d.r <= 32 && !beside[b.d.r];
+    // Ranks up to 32 have three stages of their own per orthogonalisation instead of eight kernels (one matrix of
+    // 8192 x 8192, r = 16: 376 -> 352 us), in fp32, whatever larger ranks share their launches.
+    for (Batch& b : h->batches) b.small = b.d.r <= 32;
   }
 
   // workspace plan
@@ -398,6 +392,15 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       u.clusters[k].push_back((int)bi);
     }
   }
+  // Beside a larger rank the factorisation of a small one joins that rank's instead of its own first pass, which
+  // is then no longer than the product of the larger rank that it shares a launch with (five small matrices of
+  // ranks 24 to 72: 213 -> 208 us a step).  The arithmetic is the same, so the groups may decide this.
+  for (const Unit& u : h->units)
+    for (const auto& cluster : u.clusters) {
+      int widest = 0;
+      for (int bi : cluster) widest = std::max(widest, h->batches[bi].d.r);
+      for (int bi : cluster) h->batches[bi].beside = h->batches[bi].small && widest > 32;
+    }
   int slot_base = 0;
   for (RankClass& c : h->classes) {
     c.slot_base = slot_base;
@@ -519,28 +522,49 @@ extern "C" int orthdion_set_variant(orthdion_handle h, orthdion_variant v) {
 // do not depend on the number of rows, can be launched once for every matrix of a rank.
 
 // Cholesky factor and inverse of the first pass for every matrix of a unit; side 0: left factor.
-// (Small ranks factor inside the first kernel of the second pass.)
-static int unit_cholinv(const orthdion_ctx* h, const Unit& u, char* ws, int side, int* info_all, hipStream_t st) {
-  for (size_t i = 0; i < u.classes.size();) {
-    od::CholJob jobs[8];
-    int n = 0;
-    for (; i < u.classes.size() && n < 8; ++i) {
-      const RankClass& c = h->classes[u.classes[i]];
-      if (c.small) continue;
-      od::CholJob& j = jobs[n++];
-      j = od::CholJob{};
-      j.nb = c.count;
-      j.r = c.r;
-      j.gram = WsArr{reinterpret_cast<float*>(ws + c.off_gram), c.st_rr};
-      j.t = WsArr{reinterpret_cast<float*>(ws + (side == 0 ? c.off_tp1 : c.off_tq1)), c.st_rr};
-      j.w = WsArr{reinterpret_cast<float*>(ws + c.off_w), c.st_rr};
-      j.tmp = WsArr{reinterpret_cast<float*>(ws + c.off_tmp), c.st_rr};
-      j.info = info_all + (size_t)c.slot_base * od::kInfoPerMat;
-      j.info_slot = side;
-      j.splits = 1;
-    }
-    OD_TRY(od::launch_cholinv(jobs, n, st));
+// (Small ranks by themselves factor inside their first pass.)
+static int unit_cholinv(const orthdion_ctx* h, const Unit& u, const BatchRef* refs, char* ws, int side, int* info_all, hipStream_t st) {
+  od::CholJob jobs[8];
+  int n = 0;
+  auto add = [&](const od::CholJob& j) -> hipError_t {
+    jobs[n++] = j;
+    if (n < 8) return hipSuccess;
+    n = 0;
+    return od::launch_cholinv(jobs, 8, st);
+  };
+  for (int ci : u.classes) {
+    const RankClass& c = h->classes[ci];
+    if (c.small) continue;
+    od::CholJob j = {};
+    j.nb = c.count;
+    j.r = c.r;
+    j.gram = WsArr{reinterpret_cast<float*>(ws + c.off_gram), c.st_rr};
+    j.t = WsArr{reinterpret_cast<float*>(ws + (side == 0 ? c.off_tp1 : c.off_tq1)), c.st_rr};
+    j.w = WsArr{reinterpret_cast<float*>(ws + c.off_w), c.st_rr};
+    j.tmp = WsArr{reinterpret_cast<float*>(ws + c.off_tmp), c.st_rr};
+    j.info = info_all + (size_t)c.slot_base * od::kInfoPerMat;
+    j.info_slot = side;
+    j.splits = 1;
+    OD_TRY(add(j));
   }
+  for (const auto& cluster : u.clusters)
+    for (int bi : cluster) {
+      const BatchRef& b = refs[bi];
+      if (!b.beside) continue;
+      od::CholJob j = {};
+      j.nb = b.d.nb;
+      j.r = b.d.r;
+      j.gram = od::small_partials(b, side, 0);
+      j.t = b.t1[side];
+      j.w = b.w;
+      j.tmp = b.tmp;
+      j.info = b.info;
+      j.info_slot = side;
+      j.splits = b.splits_gram[side];
+      j.split_stride = (int64_t)b.d.r * b.d.r;
+      OD_TRY(add(j));
+    }
+  OD_TRY(od::launch_cholinv(jobs, n, st));
   return ORTHDION_OK;
 }
 
@@ -632,6 +656,7 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     v.splits_gram[0] = b.splits_gram[0]; v.splits_gram[1] = b.splits_gram[1];
     v.slabs = b.slabs;
     v.small = b.small;
+    v.beside = b.beside;
     v.peers = b.peers;
   }
 
@@ -754,7 +779,7 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     bi = u.clusters[0][0];
     covers = (int)u.classes.size();
     OD_PHASE_BEGIN(ph);
-    const int rc = unit_cholinv(h, u, ws, side, info_all, st);
+    const int rc = unit_cholinv(h, u, refs.get(), ws, side, info_all, st);
     if (rc != ORTHDION_OK) return rc;
     OD_PHASE_END(ph);
     return ORTHDION_OK;

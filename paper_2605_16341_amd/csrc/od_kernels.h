@@ -88,7 +88,8 @@ struct BatchRef {
   WsArr pa, pb, ra, rb, part, gram, t1[2], t2[2], w, tmp, colsq;     // t1, t2: [0] left, [1] right factor
   HalfArr ph, pht, rh, qh, qht;
   int splits_proj, splits_back, splits_gram[2], slabs;
-  bool small;                        // orthogonalised by the kernels for ranks up to 32
+  bool small;                        // orthogonalised by the stages for ranks up to 32
+  bool beside;                       // small, but sharing launches with a larger rank: factored beside it (launch_cholinv)
   int64_t peers;                     // matrices of this shape that would make up the work of all batches that step together with it
   // left (P, rows m) and right (Q, rows n) side of the orthogonalisation
   int rows(int side) const { return side == 0 ? d.m : d.n; }
@@ -120,8 +121,10 @@ hipError_t launch_back_reduce(BatchList b, int n, Prec prec, hipStream_t st);
 // orth_gram: Gram matrix of a0 in the batch's slices of the class array `gram` (small batches: partial sums
 // for the second pass)
 hipError_t launch_orth_gram(BatchList b, int n, int side, Prec prec, hipStream_t st);
+// where the Gram partials of a0 (pass 0) or of a1 (pass 1) of a small batch lie, splits_gram[side] of r x r
+WsArr small_partials(const BatchRef& b, int side, int pass);
 // second pass: a1 = a0 W1, Gram of a1, T2 = I + Phi(E), Phi^T (fast) or W2 = I - Phi(E) (exact), max |E|;
-// small batches: the factorisation of the first pass, a1 and its Gram partials
+// small batches: the factorisation of the first pass (unless `beside`), a1 and its Gram partials
 hipError_t launch_orth_second(BatchList b, int n, int side, Prec prec, hipStream_t st);
 // r <= 256: Cholesky factor of I + E for the matrices whose deviation is above kFirstOrderDeviation
 hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st);

@@ -41,10 +41,9 @@ struct SegBlock {
   int flat, x, y, z;                          // position in the segment
   SegGrid grid;
 };
-// The segment of this workgroup, or -1 for the padding between segments.
+// The segment of workgroup `bid`, or -1 for the padding between segments.
 template <class A>
-OD_DEV int seg_locate(const Segs<A>& g, SegBlock& b) {
-  const int bid = (int)blockIdx.x;
+OD_DEV int seg_locate(const Segs<A>& g, SegBlock& b, int bid) {
   int s = 0;
 #pragma unroll
   for (int i = 1; i < kMaxSeg; ++i)
@@ -61,6 +60,8 @@ OD_DEV int seg_locate(const Segs<A>& g, SegBlock& b) {
   b.x = rest;
   return s;
 }
+template <class A>
+OD_DEV int seg_locate(const Segs<A>& g, SegBlock& b) { return seg_locate(g, b, (int)blockIdx.x); }
 template <class A>
 OD_DEV int seg_locate(const One<A>&, SegBlock& b) {
   b.grid = SegGrid{(int)gridDim.x, (int)gridDim.y, (int)gridDim.z};
@@ -427,11 +428,9 @@ struct GramArgs {
   int rows, r, splits, side;
   WsArr a, part;
 };
-template <class T, class Num, class SegsT>
-__global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_gram(SegsT segs) {
+template <class T, class Num>
+OD_DEV void gram_tile(const GramArgs& a_, const SegBlock& blk, char* lds) {
   static_assert(T::MT == T::NT, "the tile grid of a symmetric result must be symmetric");
-  extern __shared__ __align__(16) char lds[];
-  OD_SEGMENT(GramArgs);
   const int rows = a_.rows, r = a_.r, splits = a_.splits;
   const int tiles = (r + T::NT - 1) / T::NT;
   // The result is symmetric: only the tiles (tm, tn) with tm <= tn are computed, row by row
@@ -487,6 +486,12 @@ __global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_gram(SegsT s
         }
       }
   }
+}
+template <class T, class Num, class SegsT>
+__global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_gram(SegsT segs) {
+  extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(GramArgs);
+  gram_tile<T, Num>(a_, blk, lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -595,12 +600,15 @@ __global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_apply(SegsT 
 // returns at once cost 4 to 5 us more (five small matrices of ranks 24 to 72: 201 -> 197.5 us a step, 4096 x 4096
 // r = 256 with diagnostics 543 -> 539 us).
 typedef Tile<64, 64, 32, 2, 2> TileSmallFlat;
+OD_DEV void apply_result_tile(const ApplyArgs& a_, const SegBlock& blk, char* lds) {
+  if (pred_on(a_.pred, blk.z)) apply_tile<TileSmall, NumF16, true, true>(a_, blk, lds);
+  else apply_tile<TileSmallFlat, NumBF<2>, false, false>(a_, blk, lds);
+}
 template <class SegsT>
 __global__ __launch_bounds__(TileSmall::THREADS) void k_apply_result(SegsT segs) {
   extern __shared__ __align__(16) char lds[];
   OD_SEGMENT(ApplyArgs);
-  if (pred_on(a_.pred, blk.z)) apply_tile<TileSmall, NumF16, true, true>(a_, blk, lds);
-  else apply_tile<TileSmallFlat, NumBF<2>, false, false>(a_, blk, lds);
+  apply_result_tile(a_, blk, lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -613,7 +621,9 @@ __global__ __launch_bounds__(TileSmall::THREADS) void k_apply_result(SegsT segs)
 // ------------------------------------------------------------------------------------
 // (second launch bound: up to 256 registers, which keeps the matrix-core accumulators in ordinary ones; in the
 // others every group of pivots copied them back and forth)
+// LDS: S, the rows of one pass ([kSmallRows][kSmallPitch]), then Wl ([32][kSmallPitch])
 constexpr int kSmallRows = 256, kSmallPitch = 36;
+constexpr int kSmallLds = (kSmallRows + 32) * kSmallPitch * (int)sizeof(float);
 
 // Sum of a^T a over the 64 rows a wave owns of the tile S ([rows][kSmallPitch], 32 columns) on
 // the matrix cores: fp32 32x32x2 products with both operands the same register (lane (c, h)
@@ -700,16 +710,15 @@ struct SmallArgs {
   WsArr gram;                   // `splits` Gram partials of a0, r x r each
   WsArr part;                   // the same of a1
   WsArr t1, t2;
+  WsArr w;                      // W1, where the factorisation has run beside that of larger ranks (T1 is written then), or null
   const MatEntry* q_mats;       // the result goes to these matrices' Q, or to a0 when null
   float* only_q;                // Q of the one matrix of a batch of one
   HalfArr hn, ht;               // fp16 copies of the result ([rows][r] and [r][rows]), or null
   float* scal;
   int* info;
 };
-template <class SegsT>
-__global__ __launch_bounds__(kSmallRows, 2) void k_small_gram(SegsT segs) {
-  __shared__ __align__(16) float S[kSmallRows * kSmallPitch];
-  OD_SEGMENT(SmallArgs);
+OD_DEV void small_gram(const SmallArgs& a_, const SegBlock& blk, char* lds) {
+  float* S = reinterpret_cast<float*>(lds);
   const int rows = a_.rows, r = a_.r, splits = a_.splits;
   const int z = blk.z, split = blk.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int kend;
@@ -733,35 +742,43 @@ __global__ __launch_bounds__(kSmallRows, 2) void k_small_gram(SegsT segs) {
   small_gram_store(S, acc, r, a_.gram.base + (int64_t)z * a_.gram.stride + (int64_t)split * r * r, tid);
 }
 
-template <class SegsT>
-__global__ __launch_bounds__(kSmallRows, 2) void k_small_first_pass(SegsT segs) {
-  __shared__ __align__(16) float Wl[32 * kSmallPitch];           // W[k][j]
-  __shared__ __align__(16) float S[kSmallRows * kSmallPitch];    // the rows of a1 of one pass
-  OD_SEGMENT(SmallArgs);
-  const int rows = a_.rows, r = a_.r, splits = a_.splits;
-  const int z = blk.z, split = blk.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // (Wl holds the sum until the factorisation replaces it by W)
-  small_sum_partials(a_.gram.base + (int64_t)z * a_.gram.stride, splits, r, Wl, tid);
-  __syncthreads();
-  if (wave == 0) {
-    const int c = lane & 31, h = lane >> 5;
-    f32x16 d = small_acc_tile(Wl, lane), zt;
-    const int bad = diag_tile_factor(d, zt, lane, r);
-    if (bad != 0 && lane == 0) atomicCAS(&a_.info[z * kInfoPerMat + a_.side], 0, bad);
-    // zt = M with W = M^T: lane c holds row c of W
+// T1 and W = T1^-1 of the sum in `Wl`, which W replaces (one wave); workgroup 0 of a matrix writes T1
+OD_DEV void small_factor(const SmallArgs& a_, float* Wl, int z, int split, int lane) {
+  const int r = a_.r;
+  const int c = lane & 31, h = lane >> 5;
+  f32x16 d = small_acc_tile(Wl, lane), zt;
+  const int bad = diag_tile_factor(d, zt, lane, r);
+  if (bad != 0 && lane == 0) atomicCAS(&a_.info[z * kInfoPerMat + a_.side], 0, bad);
+  // zt = M with W = M^T: lane c holds row c of W
 #pragma unroll
-    for (int v = 0; v < 16; ++v) Wl[c * kSmallPitch + acc_row(v, lane)] = zt[v];
-    if (split == 0 && c < r) {
-      float* tp = a_.t1.base + (int64_t)z * a_.t1.stride;
+  for (int v = 0; v < 16; ++v) Wl[c * kSmallPitch + acc_row(v, lane)] = zt[v];
+  if (split == 0 && c < r) {
+    float* tp = a_.t1.base + (int64_t)z * a_.t1.stride;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int gi = 8 * q + 4 * h;
-        if (gi < r) {
+    for (int q = 0; q < 4; ++q) {
+      const int gi = 8 * q + 4 * h;
+      if (gi < r) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) tp[(int64_t)(gi + e) * r + c] = d[4 * q + e];
-        }
+        for (int e = 0; e < 4; ++e) tp[(int64_t)(gi + e) * r + c] = d[4 * q + e];
       }
     }
+  }
+}
+OD_DEV void small_first_pass(const SmallArgs& a_, const SegBlock& blk, char* lds) {
+  float* S = reinterpret_cast<float*>(lds);                      // the rows of a1 of one pass
+  float* Wl = S + kSmallRows * kSmallPitch;                      // W[k][j]
+  const int rows = a_.rows, r = a_.r, splits = a_.splits;
+  const int z = blk.z, split = blk.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (a_.w.base != nullptr) {
+    const int gi = tid >> 3, gj = 4 * (tid & 7);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (gi < r && gj < r) v = *reinterpret_cast<const f32x4*>(a_.w.base + (int64_t)z * a_.w.stride + gi * r + gj);
+    *reinterpret_cast<f32x4*>(Wl + gi * kSmallPitch + gj) = v;
+  } else {
+    // (Wl holds the sum until the factorisation replaces it by W)
+    small_sum_partials(a_.gram.base + (int64_t)z * a_.gram.stride, splits, r, Wl, tid);
+    __syncthreads();
+    if (wave == 0) small_factor(a_, Wl, z, split, lane);
   }
   int kend;
   const int kbeg = split_begin(rows, splits, 8, split, &kend);
@@ -805,11 +822,9 @@ __global__ __launch_bounds__(kSmallRows, 2) void k_small_first_pass(SegsT segs) 
 // the deviation is too large for the first-order form, and applies W2 to its rows in plain fp32.  Workgroup 0 of
 // a matrix also writes T2 and the flags.  One launch in place of four (sum, guard, two triangular products; 22 us of
 // launches and latency at 8192 rows, r = 16, against 10).
-template <class SegsT>
-__global__ __launch_bounds__(kSmallRows, 2) void k_small_result(SegsT segs) {
-  __shared__ __align__(16) float Wl[32 * kSmallPitch];           // I + E, then W2[k][j]
-  __shared__ __align__(16) float S[kSmallRows * kSmallPitch];    // the rows of a1 of one pass
-  OD_SEGMENT(SmallArgs);
+OD_DEV void small_result(const SmallArgs& a_, const SegBlock& blk, char* lds) {
+  float* S = reinterpret_cast<float*>(lds);                      // the rows of a1
+  float* Wl = S + kSmallRows * kSmallPitch;                      // I + E, then W2[k][j]
   const int rows = a_.rows, r = a_.r, side = a_.side;
   const int z = blk.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = blk.x * kSmallRows + tid;
@@ -908,6 +923,53 @@ __global__ __launch_bounds__(kSmallRows, 2) void k_small_result(SegsT segs) {
         }
     }
   }
+}
+
+// The three stages as kernels of their own, and beside the 64 x 64 tiles that larger ranks of the same launch take
+// in their place (Gram matrix, A W, result): workgroups from `first` on belong to the small ranks.  The small
+// ranks' arithmetic is the same either way, so a matrix does not depend on the ranks beside it.  Five matrices of
+// ranks 24 to 72 take 208 us a step with these and 243 with separate launches; 197 with the larger ranks' kernels
+// for all of them, which have 16 bits in A W where the small ranks have 24.
+enum SmallStage : int { SMALL_GRAM, SMALL_FIRST, SMALL_RESULT };
+template <int STAGE>
+OD_DEV void small_stage(const SmallArgs& a_, const SegBlock& blk, char* lds) {
+  if constexpr (STAGE == SMALL_GRAM) small_gram(a_, blk, lds);
+  else if constexpr (STAGE == SMALL_FIRST) small_first_pass(a_, blk, lds);
+  else small_result(a_, blk, lds);
+}
+template <int STAGE, class SegsT>
+__global__ __launch_bounds__(kSmallRows, 2) void k_small(SegsT segs) {
+  extern __shared__ __align__(16) char lds[];
+  OD_SEGMENT(SmallArgs);
+  small_stage<STAGE>(a_, blk, lds);
+}
+#define OD_SMALL_SEGMENTS(STAGE)                                          \
+  if ((int)blockIdx.x >= first) {                                         \
+    SegBlock blk;                                                         \
+    const int seg_ = seg_locate(small, blk, (int)blockIdx.x - first);     \
+    if (seg_ >= 0) small_stage<STAGE>(small.seg[seg_], blk, lds);         \
+    return;                                                               \
+  }
+template <class Num>
+__global__ __launch_bounds__(kSmallRows, 2) void k_gram_and_small(Segs<GramArgs> segs, Segs<SmallArgs> small, int first) {
+  static_assert(TileSmall::THREADS == kSmallRows, "both kinds of workgroup have the same threads");
+  extern __shared__ __align__(16) char lds[];
+  OD_SMALL_SEGMENTS(SMALL_GRAM);
+  OD_SEGMENT(GramArgs);
+  gram_tile<TileSmall, Num>(a_, blk, lds);
+}
+template <class Num, int STAGE>
+__global__ __launch_bounds__(kSmallRows, 2) void k_apply_and_small(Segs<ApplyArgs> segs, Segs<SmallArgs> small, int first) {
+  extern __shared__ __align__(16) char lds[];
+  OD_SMALL_SEGMENTS(STAGE);
+  OD_SEGMENT(ApplyArgs);
+  apply_tile<TileSmall, Num, true, false>(a_, blk, lds);
+}
+__global__ __launch_bounds__(kSmallRows, 2) void k_apply_result_and_small(Segs<ApplyArgs> segs, Segs<SmallArgs> small, int first) {
+  extern __shared__ __align__(16) char lds[];
+  OD_SMALL_SEGMENTS(SMALL_RESULT);
+  OD_SEGMENT(ApplyArgs);
+  apply_result_tile(a_, blk, lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1988,6 +2050,15 @@ struct SegList {
   }
 };
 
+// One launch of the segments of `a` and, behind them, of `b`, with kernel(a, b, first workgroup of b).
+template <class A, class B, class K>
+static hipError_t launch_both(SegList<A>& a, SegList<B>& b, K kernel, int threads, int lds, hipStream_t st) {
+  OD_RETURN_IF(allow_lds(kernel, lds));
+  hipLaunchKernelGGL(kernel, dim3(a.total + b.total), dim3(threads), lds, st, a.g, b.g, a.total);
+  OD_CHECK_LAUNCH();
+  return hipSuccess;
+}
+
 // Calls one(variant, members, count, timed) for groups of at most kMaxSeg batches that take the same
 // kernel; variant(batch) < 0 leaves a batch out.
 template <class V, class F>
@@ -2259,9 +2330,66 @@ hipError_t launch_back_reduce(BatchList b, int n, Prec prec, hipStream_t st) {
 // ---- orthogonalisation ------------------------------------------------------------------
 // Ranks of one 32 x 32 tile take the first CholeskyQR pass in a single launch, factorisation included.
 
-// Gram partials of a0 (`first`, into gram_out or with several splits `part`) or a1 (into `part`)
+// Gram partials of a0 (pass 0) and of a1 (pass 1) for small ranks.  The first pass reads the former while it
+// writes the latter, so they lie in the array of the result's fp16 copy, which holds them from two row ranges
+// (of 256 rows and more) on.
+WsArr small_partials(const BatchRef& r, int side, int pass) {
+  if (pass == 1) return r.part;
+  if (r.splits_gram[side] == 1) return r.gram;
+  const HalfArr& h = side == 0 ? r.ph : r.qh;
+  return WsArr{reinterpret_cast<float*>(h.base), h.stride / 2};
+}
+
+// The small batches of a list that wait for a stage of theirs: with launches of larger ranks while there
+// are some, then by themselves.
+struct SmallQueue {
+  BatchList b;
+  int n, next, side;
+  Prec prec;
+  SmallQueue(BatchList b_, int n_, int side_, Prec prec_) : b(b_), n(n_), next(0), side(side_), prec(prec_) {}
+  // fills `segs` with the next of them
+  void take(SegList<SmallArgs>& segs, int stage) {
+    for (; next < n && !segs.full(); ++next) {
+      const BatchRef& r = *b[next];
+      if (!r.small) continue;
+      SmallArgs a = {};
+      a.rows = r.rows(side);
+      a.r = r.d.r;
+      a.splits = r.splits_gram[side];
+      a.side = side;
+      a.a0 = r.a0(side);
+      a.a1 = r.a1(side);
+      a.gram = small_partials(r, side, 0);
+      a.part = small_partials(r, side, 1);
+      a.t1 = r.t1[side];
+      a.t2 = r.t2[side];
+      if (r.beside) a.w = r.w;
+      a.scal = r.scal;
+      a.info = r.info;
+      if (side == 1) a.q_mats = r.mats;
+      if (side == 1 && r.d.nb == 1) a.only_q = r.host_mats[0].Q;
+      if (prec == PREC_F16) {
+        a.hn = side == 0 ? r.ph : r.qh;
+        if (side == 0) a.ht = r.pht;
+      }
+      segs.add(a, stage == SMALL_RESULT ? ceil_div(a.rows, kSmallRows) : a.splits, 1, r.d.nb);
+    }
+  }
+  template <int STAGE>
+  hipError_t rest(hipStream_t st) {
+    while (next < n) {
+      SegList<SmallArgs> segs;
+      take(segs, STAGE);
+      OD_RETURN_IF(segs.launch(k_small<STAGE, One<SmallArgs>>, k_small<STAGE, Segs<SmallArgs>>, kSmallRows, kSmallLds, st, 0));
+    }
+    return hipSuccess;
+  }
+};
+
+// Gram partials of a0 (`first`, into gram_out or with several splits `part`) or a1 (into `part`); `queue`: small
+// batches that may join, or null
 template <class T, class Num>
-static hipError_t gram_tt(BatchList b, int n, int side, bool first, hipStream_t st) {
+static hipError_t gram_tt(BatchList b, int n, int side, bool first, SmallQueue* queue, hipStream_t st) {
   SegList<GramArgs> segs;
   for (int i = 0; i < n; ++i) {
     const BatchRef& r = *b[i];
@@ -2277,9 +2405,15 @@ static hipError_t gram_tt(BatchList b, int n, int side, bool first, hipStream_t 
     const int tiles = ceil_div(a.r, T::NT);
     segs.add(a, tiles * (tiles + 1) / 2, a.splits, r.d.nb);
   }
-  return segs.launch(k_gram<T, Num, One<GramArgs>>, k_gram<T, Num, Segs<GramArgs>>, T::THREADS, T::template lds_bytes<Num>(), st, 0);
+  constexpr int lds = T::template lds_bytes<Num>();
+  if constexpr (std::is_same<T, TileSmall>::value) {
+    SegList<SmallArgs> small;
+    if (queue != nullptr) queue->take(small, SMALL_GRAM);
+    if (small.g.n > 0) return launch_both(segs, small, k_gram_and_small<Num>, T::THREADS, lds > kSmallLds ? lds : kSmallLds, st);
+  }
+  return segs.launch(k_gram<T, Num, One<GramArgs>>, k_gram<T, Num, Segs<GramArgs>>, T::THREADS, lds, st, 0);
 }
-static hipError_t gram_pass(BatchList b, int n, int side, bool first, Prec prec, hipStream_t st) {
+static hipError_t gram_pass(BatchList b, int n, int side, bool first, Prec prec, SmallQueue* queue, hipStream_t st) {
   const auto variant = [&](const BatchRef& r) -> int {
     if (r.small) return -1;
     // few large tiles leave most of the chip idle: use small ones until the grid fills it
@@ -2289,8 +2423,8 @@ static hipError_t gram_pass(BatchList b, int n, int side, bool first, Prec prec,
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
     // fast precision has the sampled scale of B at hand: two-term fp16 operands (half the
     // matrix-core work of the three-way bf16 split at 22 instead of 24 bits)
-    if (prec == PREC_F16) return v == 0 ? gram_tt<TileSmall, NumH2>(g, k, side, first, st) : gram_tt<TileSquare8, NumH2>(g, k, side, first, st);
-    return v == 0 ? gram_tt<TileSmall, NumBF<3>>(g, k, side, first, st) : gram_tt<TileSquare, NumBF<3>>(g, k, side, first, st);
+    if (prec == PREC_F16) return v == 0 ? gram_tt<TileSmall, NumH2>(g, k, side, first, queue, st) : gram_tt<TileSquare8, NumH2>(g, k, side, first, queue, st);
+    return v == 0 ? gram_tt<TileSmall, NumBF<3>>(g, k, side, first, queue, st) : gram_tt<TileSquare, NumBF<3>>(g, k, side, first, queue, st);
   });
 }
 hipError_t launch_gram_plain(int nb, int rows, int r, WsArr a, WsArr part, int splits, hipStream_t st) {
@@ -2309,53 +2443,10 @@ hipError_t launch_gram_plain(int nb, int rows, int r, WsArr a, WsArr part, int s
                               : segs.launch(k_gram<TileSmall, NumBF<3>, One<GramArgs>>, k_gram<TileSmall, NumBF<3>, Segs<GramArgs>>, TileSmall::THREADS, TileSmall::lds_bytes<NumBF<3>>(), st, 0);
 }
 
-// Gram partials of a0 (pass 0) and of a1 (pass 1) for small ranks.  The first pass reads the former while it
-// writes the latter, so they lie in the array of the result's fp16 copy, which holds them from two row ranges
-// (of 256 rows and more) on.
-static WsArr small_partials(const BatchRef& r, int side, int pass) {
-  if (pass == 1) return r.part;
-  if (r.splits_gram[side] == 1) return r.gram;
-  const HalfArr& h = side == 0 ? r.ph : r.qh;
-  return WsArr{reinterpret_cast<float*>(h.base), h.stride / 2};
-}
-
-// The three kernels of an orthogonalisation of rank up to 32.
-enum SmallStage : int { SMALL_GRAM, SMALL_FIRST, SMALL_RESULT };
-static hipError_t small_pass(BatchList b, int n, int side, SmallStage stage, Prec prec, hipStream_t st) {
-  return by_variant(b, n, [](const BatchRef& r) { return r.small ? 0 : -1; }, [&](int, BatchList g, int k, int) -> hipError_t {
-    SegList<SmallArgs> segs;
-    for (int i = 0; i < k; ++i) {
-      const BatchRef& r = *g[i];
-      SmallArgs a = {};
-      a.rows = r.rows(side);
-      a.r = r.d.r;
-      a.splits = r.splits_gram[side];
-      a.side = side;
-      a.a0 = r.a0(side);
-      a.a1 = r.a1(side);
-      a.gram = small_partials(r, side, 0);
-      a.part = small_partials(r, side, 1);
-      a.t1 = r.t1[side];
-      a.t2 = r.t2[side];
-      a.scal = r.scal;
-      a.info = r.info;
-      if (side == 1) a.q_mats = r.mats;
-      if (side == 1 && r.d.nb == 1) a.only_q = r.host_mats[0].Q;
-      if (prec == PREC_F16) {
-        a.hn = side == 0 ? r.ph : r.qh;
-        if (side == 0) a.ht = r.pht;
-      }
-      segs.add(a, stage == SMALL_RESULT ? ceil_div(a.rows, kSmallRows) : a.splits, 1, r.d.nb);
-    }
-    if (stage == SMALL_GRAM) return segs.launch(k_small_gram<One<SmallArgs>>, k_small_gram<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
-    if (stage == SMALL_FIRST) return segs.launch(k_small_first_pass<One<SmallArgs>>, k_small_first_pass<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
-    return segs.launch(k_small_result<One<SmallArgs>>, k_small_result<Segs<SmallArgs>>, kSmallRows, 0, st, 0);
-  });
-}
-
 hipError_t launch_orth_gram(BatchList b, int n, int side, Prec prec, hipStream_t st) {
-  OD_RETURN_IF(small_pass(b, n, side, SMALL_GRAM, prec, st));
-  OD_RETURN_IF(gram_pass(b, n, side, true, prec, st));
+  SmallQueue queue(b, n, side, prec);
+  OD_RETURN_IF(gram_pass(b, n, side, true, prec, &queue, st));
+  OD_RETURN_IF(queue.rest<SMALL_GRAM>(st));
   // ordered reduction of the split partial sums on many workgroups: the factorisation runs on
   // one workgroup per matrix and should not spend its time summing
   return by_variant(b, n, [&](const BatchRef& r) { return !r.small && r.splits_gram[side] > 1 ? 0 : -1; }, [&](int, BatchList g, int k, int) {
@@ -2370,7 +2461,7 @@ enum ApplyKind : int { APPLY_W, APPLY_FULL, APPLY_CORRECTION };     // a0 W1 -> 
 static Pred deviation(const BatchRef& r, int side, int want) { return Pred{r.scal, 2 + side, kFirstOrderDeviation, want}; }
 
 template <class T, class Num, bool DEEP, bool CORR, bool EITHER = false>
-static hipError_t apply_tt(BatchList b, int n, int side, ApplyKind kind, Prec prec, hipStream_t st) {
+static hipError_t apply_tt(BatchList b, int n, int side, ApplyKind kind, Prec prec, SmallQueue* queue, hipStream_t st) {
   SegList<ApplyArgs> segs;
   for (int i = 0; i < n; ++i) {
     const BatchRef& r = *b[i];
@@ -2396,15 +2487,26 @@ static hipError_t apply_tt(BatchList b, int n, int side, ApplyKind kind, Prec pr
     }
     segs.add(a, ceil_div(a.rows, T::MT) * ceil_div(a.r, T::NT), 1, r.d.nb);
   }
+  SegList<SmallArgs> small;
   if constexpr (EITHER) {
-    constexpr int corr = TileSmall::template lds_bytes<NumF16>(), full = TileSmallFlat::template lds_bytes<NumBF<2>>();
-    return segs.launch(k_apply_result<One<ApplyArgs>>, k_apply_result<Segs<ApplyArgs>>, TileSmall::THREADS, corr > full ? corr : full, st, 0);
+    constexpr int corr = TileSmall::template lds_bytes<NumF16>(), full = TileSmallFlat::template lds_bytes<NumBF<2>>(), lds = corr > full ? corr : full;
+    if (queue != nullptr) queue->take(small, SMALL_RESULT);
+    if (small.g.n > 0) return launch_both(segs, small, k_apply_result_and_small, TileSmall::THREADS, lds > kSmallLds ? lds : kSmallLds, st);
+    return segs.launch(k_apply_result<One<ApplyArgs>>, k_apply_result<Segs<ApplyArgs>>, TileSmall::THREADS, lds, st, 0);
   }
-  return segs.launch(k_apply<T, Num, DEEP, CORR, One<ApplyArgs>>, k_apply<T, Num, DEEP, CORR, Segs<ApplyArgs>>, T::THREADS, T::template lds_bytes<Num>(), st, 0);
+  constexpr int lds = T::template lds_bytes<Num>();
+  if constexpr (std::is_same<T, TileSmall>::value && !CORR) {
+    constexpr int both = lds > kSmallLds ? lds : kSmallLds;
+    if (queue != nullptr) queue->take(small, kind == APPLY_W ? SMALL_FIRST : SMALL_RESULT);
+    if (small.g.n > 0 && kind == APPLY_W) return launch_both(segs, small, k_apply_and_small<Num, SMALL_FIRST>, T::THREADS, both, st);
+    if (small.g.n > 0) return launch_both(segs, small, k_apply_and_small<Num, SMALL_RESULT>, T::THREADS, both, st);
+  }
+  return segs.launch(k_apply<T, Num, DEEP, CORR, One<ApplyArgs>>, k_apply<T, Num, DEEP, CORR, Segs<ApplyArgs>>, T::THREADS, lds, st, 0);
 }
-// `merged`: small grids take the correction and the full product of a result in one launch, that of the former
+// `merged`: small grids take the correction and the full product of a result in one launch, that of the former;
+// `queue`: small batches whose stage may join the launches of 64 x 64 tiles, or null
 template <class Num, bool CORR>
-static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec prec, bool merged, hipStream_t st) {
+static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec prec, bool merged, SmallQueue* queue, hipStream_t st) {
   const auto variant = [&](const BatchRef& r) -> int {
     if (r.small) return -1;
     if ((int64_t)ceil_div(r.rows(side), 128) * ceil_div(r.d.r, 128) * r.peers >= 512) return 1;
@@ -2412,24 +2514,25 @@ static hipError_t apply_t(BatchList b, int n, int side, ApplyKind kind, Prec pre
   };
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
     if constexpr (CORR)
-      if (v == 0 && merged) return apply_tt<TileSmall, Num, true, CORR, true>(g, k, side, kind, prec, st);
-    if (v == 0) return apply_tt<TileSmall, Num, true, CORR>(g, k, side, kind, prec, st);
+      if (v == 0 && merged) return apply_tt<TileSmall, Num, true, CORR, true>(g, k, side, kind, prec, queue, st);
+    if (v == 0) return apply_tt<TileSmall, Num, true, CORR>(g, k, side, kind, prec, queue, st);
     // 128 columns per tile: the loop of a column tile ends at its last row of W (upper triangular),
     // so narrower tiles skip more of the zero half than 256-column ones would (measured -10 %)
     // one operand part leaves LDS room for 64-deep steps at two workgroups per CU (measured -13 to
     // -23 %); with two parts the deeper tile halves the occupancy and loses
-    if constexpr (Num::PARTS == 1) return apply_tt<TileSquareDeepK, Num, false, CORR>(g, k, side, kind, prec, st);
-    else return apply_tt<TileSquare8, Num, false, CORR>(g, k, side, kind, prec, st);
+    if constexpr (Num::PARTS == 1) return apply_tt<TileSquareDeepK, Num, false, CORR>(g, k, side, kind, prec, queue, st);
+    else return apply_tt<TileSquare8, Num, false, CORR>(g, k, side, kind, prec, queue, st);
   });
 }
-static hipError_t apply_product(BatchList b, int n, int side, ApplyKind kind, Prec prec, bool merged, hipStream_t st) {
-  return prec == PREC_BF3 ? apply_t<NumBF<3>, false>(b, n, side, kind, prec, merged, st) : apply_t<NumBF<2>, false>(b, n, side, kind, prec, merged, st);
+static hipError_t apply_product(BatchList b, int n, int side, ApplyKind kind, Prec prec, bool merged, SmallQueue* queue, hipStream_t st) {
+  return prec == PREC_BF3 ? apply_t<NumBF<3>, false>(b, n, side, kind, prec, merged, queue, st) : apply_t<NumBF<2>, false>(b, n, side, kind, prec, merged, queue, st);
 }
 
 hipError_t launch_orth_second(BatchList b, int n, int side, Prec prec, hipStream_t st) {
-  OD_RETURN_IF(small_pass(b, n, side, SMALL_FIRST, prec, st));
-  OD_RETURN_IF(apply_product(b, n, side, APPLY_W, prec, false, st));
-  OD_RETURN_IF(gram_pass(b, n, side, false, prec, st));
+  SmallQueue queue(b, n, side, prec);
+  OD_RETURN_IF(apply_product(b, n, side, APPLY_W, prec, false, &queue, st));
+  OD_RETURN_IF(queue.rest<SMALL_FIRST>(st));
+  OD_RETURN_IF(gram_pass(b, n, side, false, prec, nullptr, st));
   OD_RETURN_IF(by_variant(b, n, [](const BatchRef& r) { return r.small ? -1 : 0; }, [&](int, BatchList g, int k, int) {
     SegList<CorrArgs> segs;
     for (int i = 0; i < k; ++i) {
@@ -2495,10 +2598,11 @@ hipError_t launch_orth_guard(BatchList b, int n, int side, hipStream_t st) {
 }
 
 hipError_t launch_orth_result(BatchList b, int n, int side, Prec prec, int which, hipStream_t st) {
-  if (which != 2) OD_RETURN_IF(small_pass(b, n, side, SMALL_RESULT, prec, st));
-  if (prec == PREC_BF3) return apply_product(b, n, side, APPLY_FULL, prec, false, st);
-  if (which != 2) OD_RETURN_IF((apply_t<NumF16, true>(b, n, side, APPLY_CORRECTION, prec, which == 0, st)));
-  if (which != 1) OD_RETURN_IF(apply_product(b, n, side, APPLY_FULL, prec, which == 0, st));
+  SmallQueue queue(b, n, side, prec);
+  if (prec == PREC_BF3) OD_RETURN_IF(apply_product(b, n, side, APPLY_FULL, prec, false, &queue, st));
+  else if (which != 2) OD_RETURN_IF((apply_t<NumF16, true>(b, n, side, APPLY_CORRECTION, prec, which == 0, &queue, st)));
+  if (which != 2) OD_RETURN_IF(queue.rest<SMALL_RESULT>(st));
+  if (prec != PREC_BF3 && which != 1) OD_RETURN_IF(apply_product(b, n, side, APPLY_FULL, prec, which == 0, nullptr, st));
   return hipSuccess;
 }
 

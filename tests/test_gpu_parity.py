@@ -525,3 +525,24 @@ def test_small_ranks_alone_and_beside_a_larger_one(ranks, variant, x_dtype):
             for key in ("M", "Q", "P", "R", "D"):
                 assert res[key] <= TOL[x_dtype], (t, i, key, res[key])
             cur[i] = (o["X_bits"] if x_dtype == "bf16" else o["X"], o["M"], o["Q"])
+
+
+@pytest.mark.parametrize("precision,x_dtype", [("fast", "bf16"), ("exact", "f32"), ("fast", "f32")])
+@pytest.mark.parametrize("r,count", [(8, 1), (24, 3), (32, 10)])
+def test_a_small_rank_does_not_depend_on_the_ranks_beside_it(r, count, precision, x_dtype):
+    """Ranks up to 32 keep fp32 arithmetic when a larger rank shares their launches: the bits of `count`
+    matrices of different rows (ten: more than one launch holds) are the same whether the other matrices
+    of the handle have their rank or a larger one.  The shapes and so the splits are equal on both sides."""
+    shapes = [(264 + 8 * i, 392) for i in range(count)] + [(304, 456), (552, 208)]
+    streams = [synth.power_law_stream(m, n, 2300 + i, out_dtype=x_dtype) for i, (m, n) in enumerate(shapes)]
+    runs = []
+    for others in (r, 72):
+        ranks = [r] * count + [others] * 2
+        states = [synth.initial_state(m, n, ranks[i], 2300 + i, x_dtype, 1e-3) for i, (m, n) in enumerate(shapes)]
+        gpu = GpuRun(shapes, ranks, x_dtype, states, precision=precision, mu=0.95, lr=0.01)
+        for t in range(2):
+            assert gpu.step([s.gradient(t) for s in streams]) == [0] * len(shapes)
+        runs.append([gpu.fetch(i) for i in range(count)])
+    for i, (a, b) in enumerate(zip(*runs)):
+        for key in ("P", "Q", "R", "T_P1", "T_Q1", "M", "X"):
+            assert a[key].tobytes() == b[key].tobytes(), (i, key)
