@@ -260,8 +260,8 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
   };
   double total_elems = 0.0;
   for (int i = 0; i < nmat; ++i) total_elems += (double)mats[i].m * (double)mats[i].n;
-  int groups = cfg->groups;
-  if (groups == 0) groups = (nmat >= 2 && total_elems >= kGroupMinElements && total_elems < kGroupMaxElements) ? 2 : 1;
+  const int by_default = nmat >= 2 && total_elems >= kGroupMinElements && total_elems < kGroupMaxElements ? 2 : 1;
+  const int groups = cfg->groups == 0 ? by_default : cfg->groups;
   for (int i = 0; i < nmat; ++i) {
     const orthdion_matdesc& a = mats[i];
     int found = -1;
@@ -289,13 +289,30 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       if (same_shape(o.d, h->mats[b.members[0]])) b.alike += (int)o.members.size();
   }
 
+  // Two groups: the heaviest batch first, each to the group with less work so far (m n per matrix
+  // measures a batch's step).  A set with a single batch stays one group.
+  for (Batch& b : h->batches) b.d.nb = (int)b.members.size();
+  std::vector<int> dealt(h->batches.size(), 0);
+  {
+    std::vector<int> order(h->batches.size());
+    for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
+    auto weight = [&](int k) { const ClassDims& d = h->batches[k].d; return (double)d.m * d.n * d.nb; };
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return weight(x) > weight(y); });
+    double load[2] = {0.0, 0.0};
+    for (int k : order) {
+      dealt[k] = load[1] < load[0] ? 1 : 0;
+      load[dealt[k]] += weight(k);
+    }
+  }
+
   // Clusters, in batch order: the ranks up to 256 together, every larger rank by itself.  They do not
   // depend on the groups below (nor does anything chosen from them), so that the groups leave the
   // results alone bit for bit.
   {
     struct Open { int key, id; double elems; };
     std::vector<Open> open;
-    std::vector<double> cluster_elems;
+    const auto side_of = [&](const Batch& b) { return by_default == 2 ? dealt[&b - h->batches.data()] : 0; };
+    std::vector<double> shared[2];      // elements of a cluster's batches in either group
     for (Batch& b : h->batches) {
       const int key = b.d.r <= od::kLeafRank ? 0 : b.d.r;
       const double e = (double)b.d.m * b.d.n * (double)b.members.size();
@@ -303,16 +320,21 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       while (k < open.size() && open[k].key != key) ++k;
       if (k == open.size()) open.push_back(Open{key, -1, 0.0});
       if (open[k].id < 0 || open[k].elems + e > kClusterElements) {
-        open[k].id = (int)cluster_elems.size();
+        open[k].id = (int)shared[0].size();
         open[k].elems = 0.0;
-        cluster_elems.push_back(0.0);
+        shared[0].push_back(0.0);
+        shared[1].push_back(0.0);
       }
       open[k].elems += e;
       b.cluster = open[k].id;
-      cluster_elems[b.cluster] += e;
+      shared[side_of(b)][b.cluster] += e;
     }
     for (Batch& b : h->batches) {
-      b.peers = (int64_t)(cluster_elems[b.cluster] / ((double)b.d.m * b.d.n));
+      // Where the library takes two groups, a batch shares its launches and its stream with those of its group
+      // only (the other group's run beside them): chosen for all batches of the cluster, the splits halved and one
+      // matrix of 8192 columns lost its rotated k order (8192 x 8192, r = 256 and 32: 938 us a step with launches
+      // of their own, 1030 so, 941 like this).  By the default, not by the groups of this handle: see above.
+      b.peers = (int64_t)(shared[side_of(b)][b.cluster] / ((double)b.d.m * b.d.n));
       if (b.peers < (int64_t)b.members.size()) b.peers = (int64_t)b.members.size();
     }
     // Ranks up to 32 have three stages of their own per orthogonalisation instead of eight kernels (one matrix of
@@ -327,21 +349,9 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
   h->off_info = off; off = align_up(off + (size_t)nmat * od::kInfoPerMat * sizeof(int));
   h->off_diag = off; off = align_up(off + (size_t)nmat * od::kDiagPerMat * sizeof(float));
   h->off_dacc = off; off = align_up(off + (size_t)nmat * od::kDaccPerMat * sizeof(double));
-  // Groups: the heaviest batch first, each to the group with less work so far (m n per matrix
-  // measures a batch's step).  A set with a single batch stays one group.
   std::vector<int> group_of(h->batches.size(), 0);
-  for (Batch& b : h->batches) b.d.nb = (int)b.members.size();
   if (groups == 2 && h->batches.size() >= 2) {
-    std::vector<int> order(h->batches.size());
-    for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
-    auto weight = [&](int k) { const ClassDims& d = h->batches[k].d; return (double)d.m * d.n * d.nb; };
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return weight(x) > weight(y); });
-    double load[2] = {0.0, 0.0};
-    for (int k : order) {
-      const int g = load[1] < load[0] ? 1 : 0;
-      group_of[k] = g;
-      load[g] += weight(k);
-    }
+    group_of = dealt;
     h->two_groups = true;
   }
   // rank classes in order of first appearance (one per rank and group); table rows (slots) run

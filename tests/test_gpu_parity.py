@@ -398,6 +398,30 @@ def test_two_groups_side_by_side_leave_the_bits_of_one_group(r, variant):
             assert a[key].tobytes() == b[key].tobytes(), key
 
 
+def test_groups_of_a_set_that_has_two_by_default_leave_the_bits():
+    """70 M elements, where the splits are chosen for the batches of a default group: the same choices, and
+    bits, when the caller asks for one group or for two."""
+    import torch
+    shapes, ranks = [(4096, 4096), (4096, 4096), (2048, 8192), (4096, 5120)], [24, 72, 72, 40]
+    runs = []
+    for groups in (0, 1, 2):
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(5)
+        rand = lambda *s: torch.randn(*s, device="cuda:0", generator=gen)
+        opt = binding.OrthDion(shapes, ranks, x_dtype="bf16", groups=groups)
+        assert opt.groups == (1 if groups == 1 else 2)
+        G = [0.01 * rand(*s).to(torch.bfloat16) for s in shapes]
+        X = [rand(*s).to(torch.bfloat16) for s in shapes]
+        M = [0.01 * rand(*s) for s in shapes]
+        Q = [rand(s[1], r) / s[1] ** 0.5 for s, r in zip(shapes, ranks)]
+        opt.step(X, G, M, Q)
+        torch.cuda.synchronize()
+        assert opt.info() == [0] * 4
+        runs.append(X + M + Q)
+    for other in runs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(runs[0], other))
+
+
 @pytest.mark.parametrize("shapes,r,groups", [(((256, 192), (128, 320)), 32, 0), (((640, 384), (384, 512)), 320, 0),
                                              (((1024, 640), (640, 1024)), 512, 0),
                                              (((640, 384), (384, 512), (640, 384)), 320, 2)])
