@@ -33,53 +33,63 @@ struct Tile {
 
 OD_DEV u32x4 keep_if(bool in, const u32x4& w) { return in ? w : u32x4{0u, 0u, 0u, 0u}; }
 
+// A loader's load() clamps addresses into the source (no branch, see the sources); its store() zeroes what lies
+// outside, by the flags of load() or, given the same position, by asking again.  Flags live across the
+// matrix-core work: the one-stage loop asks again (back-projection with 128 x 256 tiles and fp32 gradients: 43 to
+// 75 spilled registers with flags, none to 15 without; 4096 x 4096, r = 256: 410 -> 384 us a step), the loop of several stages has no registers left for the
+// positions instead.  loadu() is for tiles inside the source.
 template <class Src, int ROWS, int KT, int PITCH, int THREADS>
 struct LoadKC {
   static constexpr int KG = KT / 8, ITEMS = ROWS * KG, PER = (ITEMS + THREADS - 1) / THREADS;
   typename Src::Raw8 raw[PER];
-  bool in[PER];                  // whether the item lies inside the source (load())
+  bool in[PER];
+  // item of slot p: surplus threads repeat a valid one, which store() skips
+  OD_DEV static int item_of(int p, int tid) { return ITEMS % THREADS != 0 ? (tid + p * THREADS) % ITEMS : tid + p * THREADS; }
+  OD_DEV static bool inside(const Src& s, int row0, int k0, int item) { return row0 + item / KG < s.rows() && k0 + (item % KG) * 8 < s.cols(); }
   OD_DEV void load(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
-      if (ITEMS % THREADS != 0) item %= ITEMS;         // surplus threads repeat a valid item; store() skips them
-      const int row = row0 + item / KG, k = k0 + (item % KG) * 8;
-      in[p] = row < s.rows() && k < s.cols();
-      raw[p] = s.load8u(in[p] ? row : 0, in[p] ? k : 0);
+      const int item = item_of(p, tid);
+      in[p] = inside(s, row0, k0, item);
+      raw[p] = s.load8u(in[p] ? row0 + item / KG : 0, in[p] ? k0 + (item % KG) * 8 : 0);
     }
   }
   // the tile rows and every k below kpad lie inside the source
   OD_DEV static bool interior(const Src& s, int row0, int kpad) { return row0 + ROWS <= s.rows() && kpad <= s.cols(); }
-  // load() for an interior tile: no bounds checks, hence no branches
   OD_DEV void loadu(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
-      if (ITEMS % THREADS != 0) item %= ITEMS;         // surplus threads repeat a valid item; store() skips them
+      const int item = item_of(p, tid);
       raw[p] = s.load8u(row0 + item / KG, k0 + (item % KG) * 8);
       in[p] = true;
     }
   }
-  template <class Num>
-  OD_DEV void store(char* lds, int plane, float scale, int tid) const {
+  template <class Num, class Keep>
+  OD_DEV void put(char* lds, int plane, float scale, int tid, Keep keep) const {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
+      const int item = tid + p * THREADS;
       if (ITEMS % THREADS == 0 || item < ITEMS) {
         char* dst = lds + (item / KG) * PITCH + (item % KG) * 16;
         if constexpr (Src::PACKED) {
           static_assert(Num::PARTS == 1, "packed operands have one part");
-          *reinterpret_cast<u32x4*>(dst) = keep_if(in[p], raw[p]);
+          *reinterpret_cast<u32x4*>(dst) = keep_if(keep(p, item), raw[p]);
         } else {
           float x[8];
           Src::unpack8(raw[p], x);
           u32x4 w[Num::PARTS];
           Num::pack(x, scale, w);
 #pragma unroll
-          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(in[p], w[s]);
+          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(keep(p, item), w[s]);
         }
       }
     }
+  }
+  template <class Num>
+  OD_DEV void store(char* lds, int plane, float scale, int tid) const { put<Num>(lds, plane, scale, tid, [&](int p, int) { return in[p]; }); }
+  template <class Num>
+  OD_DEV void store(char* lds, int plane, float scale, int tid, const Src& s, int row0, int k0) const {
+    put<Num>(lds, plane, scale, tid, [&](int, int item) { return inside(s, row0, k0, item); });
   }
 };
 
@@ -88,14 +98,14 @@ struct LoadKS {
   static constexpr int RQ = ROWS / 4, KG = KT / 8, ITEMS = RQ * KG, PER = (ITEMS + THREADS - 1) / THREADS;
   typename Src::Raw4 raw[PER][8];
   bool in[PER];
+  OD_DEV static int item_of(int p, int tid) { return ITEMS % THREADS != 0 ? (tid + p * THREADS) % ITEMS : tid + p * THREADS; }
+  OD_DEV static bool inside(const Src& s, int row0, int k0, int item) { return k0 + item / RQ * 8 < s.rows() && row0 + (item % RQ) * 4 < s.cols(); }
   OD_DEV void load(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
-      if (ITEMS % THREADS != 0) item %= ITEMS;
-      const int row = row0 + (item % RQ) * 4, k = k0 + item / RQ * 8;
-      in[p] = k < s.rows() && row < s.cols();
-      const int kc = in[p] ? k : 0, rc = in[p] ? row : 0;
+      const int item = item_of(p, tid);
+      in[p] = inside(s, row0, k0, item);
+      const int kc = in[p] ? k0 + item / RQ * 8 : 0, rc = in[p] ? row0 + (item % RQ) * 4 : 0;
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load4u(kc + kk, rc);
     }
@@ -104,21 +114,19 @@ struct LoadKS {
   OD_DEV void loadu(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
-      if (ITEMS % THREADS != 0) item %= ITEMS;
-      int rq = item % RQ, kg = item / RQ;
+      const int item = item_of(p, tid);
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load4u(k0 + kg * 8 + kk, row0 + rq * 4);
+      for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load4u(k0 + item / RQ * 8 + kk, row0 + (item % RQ) * 4);
       in[p] = true;
     }
   }
-  template <class Num>
-  OD_DEV void store(char* lds, int plane, float scale, int tid) const {
+  template <class Num, class Keep>
+  OD_DEV void put(char* lds, int plane, float scale, int tid, Keep keep) const {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
+      const int item = tid + p * THREADS;
       if (ITEMS % THREADS == 0 || item < ITEMS) {
-        int rq = item % RQ, kg = item / RQ;
+        const int rq = item % RQ, kg = item / RQ;
         float x[8][4];
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) Src::unpack4(raw[p][kk], x[kk]);
@@ -131,10 +139,16 @@ struct LoadKS {
           Num::pack(col, scale, w);
           char* dst = lds + (rq * 4 + j) * PITCH + kg * 16;
 #pragma unroll
-          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(in[p], w[s]);
+          for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(keep(p, item), w[s]);
         }
       }
     }
+  }
+  template <class Num>
+  OD_DEV void store(char* lds, int plane, float scale, int tid) const { put<Num>(lds, plane, scale, tid, [&](int p, int) { return in[p]; }); }
+  template <class Num>
+  OD_DEV void store(char* lds, int plane, float scale, int tid, const Src& s, int row0, int k0) const {
+    put<Num>(lds, plane, scale, tid, [&](int, int item) { return inside(s, row0, k0, item); });
   }
 };
 
@@ -146,14 +160,14 @@ struct LoadKS1 {
   static constexpr int KG = KT / 8, ITEMS = ROWS * KG, PER = (ITEMS + THREADS - 1) / THREADS;
   float raw[PER][8];
   bool in[PER];
+  OD_DEV static int item_of(int p, int tid) { return ITEMS % THREADS != 0 ? (tid + p * THREADS) % ITEMS : tid + p * THREADS; }
+  OD_DEV static bool inside(const Src& s, int row0, int k0, int item) { return k0 + item / ROWS * 8 < s.rows() && row0 + item % ROWS < s.cols(); }
   OD_DEV void load(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
-      if (ITEMS % THREADS != 0) item %= ITEMS;
-      const int row = row0 + item % ROWS, k = k0 + item / ROWS * 8;
-      in[p] = k < s.rows() && row < s.cols();
-      const int kc = in[p] ? k : 0, rc = in[p] ? row : 0;
+      const int item = item_of(p, tid);
+      in[p] = inside(s, row0, k0, item);
+      const int kc = in[p] ? k0 + item / ROWS * 8 : 0, rc = in[p] ? row0 + item % ROWS : 0;
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load1u(kc + kk, rc);
     }
@@ -162,28 +176,32 @@ struct LoadKS1 {
   OD_DEV void loadu(const Src& s, int row0, int k0, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
-      if (ITEMS % THREADS != 0) item %= ITEMS;
-      int row = item % ROWS, kg = item / ROWS;
+      const int item = item_of(p, tid);
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load1u(k0 + kg * 8 + kk, row0 + row);
+      for (int kk = 0; kk < 8; ++kk) raw[p][kk] = s.load1u(k0 + item / ROWS * 8 + kk, row0 + item % ROWS);
       in[p] = true;
     }
   }
-  template <class Num>
-  OD_DEV void store(char* lds, int plane, float scale, int tid) const {
+  template <class Num, class Keep>
+  OD_DEV void put(char* lds, int plane, float scale, int tid, Keep keep) const {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
-      int item = tid + p * THREADS;
+      const int item = tid + p * THREADS;
       if (ITEMS % THREADS == 0 || item < ITEMS) {
-        int row = item % ROWS, kg = item / ROWS;
+        const int row = item % ROWS, kg = item / ROWS;
         u32x4 w[Num::PARTS];
         Num::pack(raw[p], scale, w);
         char* dst = lds + row * PITCH + kg * 16;
 #pragma unroll
-        for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(in[p], w[s]);
+        for (int s = 0; s < Num::PARTS; ++s) *reinterpret_cast<u32x4*>(dst + s * plane) = keep_if(keep(p, item), w[s]);
       }
     }
+  }
+  template <class Num>
+  OD_DEV void store(char* lds, int plane, float scale, int tid) const { put<Num>(lds, plane, scale, tid, [&](int p, int) { return in[p]; }); }
+  template <class Num>
+  OD_DEV void store(char* lds, int plane, float scale, int tid, const Src& s, int row0, int k0) const {
+    put<Num>(lds, plane, scale, tid, [&](int, int item) { return inside(s, row0, k0, item); });
   }
 };
 
@@ -253,8 +271,8 @@ OD_DEV void gemm_mainloop(const SrcA& a, const SrcB& b, int m0, int n0, int kbeg
   int cur = rot % nsteps;
   la.load(a, m0, kbeg + cur * T::KT, tid);
   lb.load(b, n0, kbeg + cur * T::KT, tid);
-  la.template store<Num>(lds, T::PLANE_A, scaleA, tid);
-  lb.template store<Num>(lds + OFF_B, T::PLANE_B, scaleB, tid);
+  la.template store<Num>(lds, T::PLANE_A, scaleA, tid, a, m0, kbeg + cur * T::KT);
+  lb.template store<Num>(lds + OFF_B, T::PLANE_B, scaleB, tid, b, n0, kbeg + cur * T::KT);
   __syncthreads();
   int buf = 0;
   for (int i = 0; i < nsteps; ++i) {
@@ -266,8 +284,8 @@ OD_DEV void gemm_mainloop(const SrcA& a, const SrcB& b, int m0, int n0, int kbeg
     }
     mma_step<T, Num>(lds + buf * BUF, lds + buf * BUF + OFF_B, acc, wm, wn, lane);
     if (more) {
-      la.template store<Num>(lds + (buf ^ 1) * BUF, T::PLANE_A, scaleA, tid);
-      lb.template store<Num>(lds + (buf ^ 1) * BUF + OFF_B, T::PLANE_B, scaleB, tid);
+      la.template store<Num>(lds + (buf ^ 1) * BUF, T::PLANE_A, scaleA, tid, a, m0, kbeg + cur * T::KT);
+      lb.template store<Num>(lds + (buf ^ 1) * BUF + OFF_B, T::PLANE_B, scaleB, tid, b, n0, kbeg + cur * T::KT);
     }
     __syncthreads();
     buf ^= 1;
