@@ -213,7 +213,7 @@ int orthdion_profile_end(orthdion_handle h, float* ms_per_phase, int32_t* count_
  * Sec. 6.3 R-norm ratio, Prop. 3.1 / Lemma 4.1 dual-norm factor nu, Lemma 4.2 inner product,
  * App. B.2 estimated effective rank).  Off by default; when on, every orthdion_step also
  * enqueues a few extra kernels (one more pass over M and G, one over R, a Gram matrix of
- * the new Q and 128 power iterations on it) that fill a table in the workspace.
+ * the new Q and its 128th power by squarings) that fill a table in the workspace.
  *   orthdion_set_diagnostics  enable != 0 switches them on for the following steps.
  *   orthdion_get_diagnostics  copies the table of the most recent step to the host array
  *                             out_host[nmat][ORTHDION_NDIAG] (matrix order of

@@ -5,7 +5,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstdlib>
 #include <memory>
 #include <new>
 #include <vector>
@@ -33,7 +32,11 @@ constexpr double kGroupMaxElements = 512.0 * 1024 * 1024;
 
 // Matrices of one shape class step in launch batches of at most this many matrices, or more while
 // they hold less than kBatchElements: what a batch's kernels leave behind for the next one (partial
-// sums, factors) should still be in the Infinity Cache when it is read.
+// sums, factors) should still be in the Infinity Cache when it is read.  Measured with half and twice the
+// elements, us a step: 100 matrices of 1024 x 1024, r = 128: 1101 | 1059 | 1112; 600 matrices of a 512-wide model,
+// r = 64: 3396 | 3369 | 3211; the 96 and 126 matrices of a 2048- and a 768-wide one within 1 %.  64 matrices instead
+// of 32 are 4 % faster on 144 and 320 matrices of a 1024-wide model, r = 128 (3262 -> 3129, 7551 -> 7229), and
+// nothing elsewhere.
 constexpr int kBatchMatrices = 32;
 constexpr double kBatchElements = 64.0 * 1024 * 1024;
 // In any case this many: a batch's matrices are the y or z extent of its launches, where a device takes 65536.
@@ -41,6 +44,10 @@ constexpr int kBatchMost = 32768;
 constexpr int kLeanDiagBlocks = 128;  // see the two plans of the workspace in create_impl
 // Batches of different shapes share their launches (a cluster) up to this many elements: below it
 // the launches of one shape leave most of the chip idle, above it every batch fills the chip by itself.
+// Measured with half and twice of it, us a step: 126 matrices of a 768-wide model, r = 192: 1806 | 1651 | 1647; 144
+// and 320 of a 1024-wide one, r = 128: 3273 | 3277 | 3163 and 7624 | 7574 | 7223; 600 of a 512-wide one, r = 64:
+// 3418 | 3358 | 3228; r = 256 and 512 of a 2048-wide one within 1 %.  So half is too little; twice is 3 to 4 %
+// better for sets of many small matrices.
 constexpr double kClusterElements = 128.0 * 1024 * 1024;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -457,7 +464,7 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       const int64_t gt = gt1 * (gt1 + 1) / 2;
       for (int side = 0; side < 2; ++side) {
         const int64_t rows = side == 0 ? m : n;
-        // small ranks: one 32 x 32 tile, one thread per row: 256-row slabs (k_small_gram, k_small_first_pass);
+        // small ranks: one 32 x 32 tile, one thread per row: 256-row slabs (small_gram, small_first_pass);
         // else two workgroups of the Gram kernel fit one CU
         b.splits_gram[side] = limited([&](int64_t peers) {
           return b.small ? pick_splits(1, peers, rows, 256) : pick_splits_by_rounds(gt, peers, rows, 256, 512);

@@ -44,7 +44,6 @@ namespace od {
 constexpr int kCholMax = kLeafRank;    // largest block one workgroup factors
 constexpr int kCT = 32;                // tile size
 constexpr int kCNT = kCholMax / kCT;   // 8 tiles per side
-constexpr int kCTiles = kCNT * (kCNT + 1) / 2;   // 36
 // Three waves per SIMD.  What a step waits for is the latency of one wave's tiles, one after the other, so
 // more waves with fewer tiles each.  Rank 256: 57 us with two waves per SIMD and four tiles per worker, 53 with
 // the chain below, 48 with three waves, the worker that finishes a diagonal tile and the loads shared out.
@@ -126,12 +125,6 @@ OD_DEV float lane_bcast(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// 1/sqrt(d) to fp32 accuracy: hardware estimate (1 ulp) plus one Newton step.
-OD_DEV float fast_rsqrt(float d) {
-  float y = __builtin_amdgcn_rsqf(d);
-  return y * fmaf(-0.5f * d * y, y, 1.5f);
-}
-
 // Three-way split bf16 operand words of 8 floats.
 OD_DEV void split3(const float* x, u32x4* parts) { NumBF<3>::pack(x, 1.f, parts); }
 
@@ -150,16 +143,6 @@ OD_DEV f32x16 mma6(const u32x4* a, const u32x4* b, f32x16 c) {
   return c;
 }
 
-// Operand of k-step kk from an fp32 LDS tile stored [row][k] with pitch kCPitch: this lane's
-// row is l % 32 and its 8 k-slots are 16 kk + 4 g + {0..3} and 16 kk + 8 + 4 g + {0..3}
-// (the rows an accumulator lane holds in registers 8 kk .. 8 kk + 7).
-OD_DEV void lds_operand(const float* tile, int lane, int kk, u32x4* parts) {
-  const float* p = tile + (lane & 31) * kCPitch + 16 * kk + 4 * (lane >> 5);
-  f32x4 lo = *reinterpret_cast<const f32x4*>(p);
-  f32x4 hi = *reinterpret_cast<const f32x4*>(p + 8);
-  float x[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  split3(x, parts);
-}
 // k-side operand of k-step kk straight from an accumulator tile.
 OD_DEV void acc_operand(const f32x16& acc, int kk, u32x4* parts) {
   float x[8];

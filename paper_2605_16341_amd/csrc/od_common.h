@@ -20,7 +20,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kMaxBatch = 32;       // matrices of one shape class per launch
 constexpr int kWave = 64;
 
 #define OD_DEV __device__ __forceinline__

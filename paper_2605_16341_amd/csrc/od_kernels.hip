@@ -86,7 +86,7 @@ typedef Tile<128, 256, 32, 2, 2> TileWide;     // r > 128: wave tile 64 x 128
 typedef Tile<128, 128, 32, 2, 2> TileSquare;   // wave tile 64 x 64
 // The same on eight waves (wave tile 32 x 64): half the registers, twice the waves per CU at the same LDS, so that
 // the operand conversions of one wave run beside the products of another.  A W of 96 matrices of rank 512:
-// 2.83 -> 2.52 ms, its correction 1.60 -> 1.51 ms, Gram matrices 2.43 -> 2.40 ms; 126 matrices of rank 192:
+// 2.44 -> 2.39 ms by the kernel trace, its correction 1.55 -> 1.50, Gram matrices 2.40 -> 2.37; 126 matrices of rank 192:
 // 1668 -> 1629 us per step; the three-part operands of a 1024-wide fp32 model: 338 -> 329 us.
 typedef Tile<128, 128, 32, 4, 2> TileSquare8;
 typedef Tile<128, 64, 32, 4, 1> TileNarrow;    // r <= 64: wave tile 32 x 64
@@ -597,7 +597,7 @@ __global__ __launch_bounds__(T::THREADS, product_waves<T>()) void k_apply(SegsT 
 }
 // The result of the second pass in one launch: the correction where the predicate holds, the full product A W2
 // elsewhere (rare; 32-deep steps, so that it needs no more LDS).  For small grids: two launches of which one
-// returns at once cost 4 to 5 us more (five small matrices of ranks 24 to 72: 201 -> 197.5 us a step, 4096 x 4096
+// returns at once cost 4 to 5 us more (five small matrices of ranks 24 to 72: 201 -> 197.5 us a step, 2048 x 5632,
 // r = 256 with diagnostics 543 -> 539 us).
 typedef Tile<64, 64, 32, 2, 2> TileSmallFlat;
 OD_DEV void apply_result_tile(const ApplyArgs& a_, const SegBlock& blk, char* lds) {
@@ -2617,16 +2617,16 @@ static hipError_t sgemm_tt(int nb, const SgemmArgs& g, hipStream_t st) {
   OD_CHECK_LAUNCH();
   return hipSuccess;
 }
-template <class Num, class DirA>
+template <class DirA>
 static hipError_t sgemm_t(int nb, const SgemmArgs& g, hipStream_t st) {
   const int big = ((g.Mc + 127) / 128) * ((g.Nc + 127) / 128) * nb * g.nq;
-  if (big < 256) return sgemm_tt<TileSmall, Num, DirA>(nb, g, st);      // one 128 x 128 tile per CU fills the chip
-  return sgemm_tt<TileSquare, Num, DirA>(nb, g, st);
+  if (big < 256) return sgemm_tt<TileSmall, NumBF<3>, DirA>(nb, g, st);      // one 128 x 128 tile per CU fills the chip
+  return sgemm_tt<TileSquare, NumBF<3>, DirA>(nb, g, st);
 }
-static hipError_t sgemm(int nb, const SgemmArgs& g, bool a_kc, int exact, hipStream_t st) {
+// six-product operands
+static hipError_t sgemm(int nb, const SgemmArgs& g, bool a_kc, hipStream_t st) {
   if (g.Mc <= 0 || g.Nc <= 0 || g.Kc <= 0 || g.nq <= 0) return hipSuccess;
-  if (exact) return a_kc ? sgemm_t<NumBF<3>, KC>(nb, g, st) : sgemm_t<NumBF<3>, KSF>(nb, g, st);
-  return a_kc ? sgemm_t<NumBF<2>, KC>(nb, g, st) : sgemm_t<NumBF<2>, KSF>(nb, g, st);
+  return a_kc ? sgemm_t<KC>(nb, g, st) : sgemm_t<KSF>(nb, g, st);
 }
 
 // g1 with A read as [k][row] (KSF) and g2 with A read as [row][k] (KC), six-product operands,
@@ -2646,8 +2646,8 @@ static hipError_t sgemm_pair_tt(int nb, const SgemmArgs& g1, const SgemmArgs& g2
 static hipError_t sgemm_pair(int nb, const SgemmArgs& g1, const SgemmArgs& g2, hipStream_t st) {
   const bool has1 = g1.Mc > 0 && g1.Nc > 0 && g1.Kc > 0, has2 = g2.Mc > 0 && g2.Nc > 0 && g2.Kc > 0;
   if (!has1 && !has2) return hipSuccess;
-  if (!has2) return sgemm(nb, g1, false, 1, st);
-  if (!has1) return sgemm(nb, g2, true, 1, st);
+  if (!has2) return sgemm(nb, g1, false, st);
+  if (!has1) return sgemm(nb, g2, true, st);
   const int big = (((g1.Mc + 127) / 128) * ((g1.Nc + 127) / 128) + ((g2.Mc + 127) / 128) * ((g2.Nc + 127) / 128)) * nb;
   if (big < 256) return sgemm_pair_tt<TileSmall>(nb, g1, g2, st);
   return sgemm_pair_tt<TileSquare>(nb, g1, g2, st);
@@ -2722,7 +2722,7 @@ static hipError_t blocked_cholinv(const CholJob& job, hipStream_t st) {
     diag.Mc = nb1; diag.Nc = nb1;
     right.b_c0 = o2; right.c_c0 = o2; right.Nc = rest - nb1;
     below.a_r0 = o2; below.c_r0 = o2; below.Mc = rest - nb1; below.Nc = nb1;
-    if ((e = sgemm(nb, diag, false, 1, st)) != hipSuccess) return e;
+    if ((e = sgemm(nb, diag, false, st)) != hipSuccess) return e;
     ca.blk = p + 1;
     const int big = (tiles_of(right, 128) + tiles_of(below, 128) + tiles_of(wcol, 128)) * nb;
     if (big < 256) {
