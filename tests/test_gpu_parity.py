@@ -570,3 +570,106 @@ def test_a_small_rank_does_not_depend_on_the_ranks_beside_it(r, count, precision
     for i, (a, b) in enumerate(zip(*runs)):
         for key in ("P", "Q", "R", "T_P1", "T_Q1", "M", "X"):
             assert a[key].tobytes() == b[key].tobytes(), (i, key)
+
+
+def _mixed_cluster(x_dtype="bf16"):
+    """Four shapes and ranks that share their launches: two of small rank, two of larger."""
+    shapes, ranks = [(264, 200), (136, 392), (328, 264), (200, 520)], [16, 32, 40, 136]
+    streams = [synth.power_law_stream(m, n, 2500 + i, out_dtype=x_dtype) for i, (m, n) in enumerate(shapes)]
+    states = [synth.initial_state(m, n, ranks[i], 2500 + i, x_dtype, 1e-3) for i, (m, n) in enumerate(shapes)]
+    return shapes, ranks, streams, states
+
+
+@pytest.mark.parametrize("variant", ["qr", "colnorm"])
+def test_a_cluster_of_mixed_ranks_replays_from_a_hip_graph(variant):
+    """Launches shared by several ranks, captured once: every replay, with eager work and synchronisation
+    in between, leaves the bits of an eager twin."""
+    import torch
+    shapes, ranks, streams, states = _mixed_cluster()
+    eager = GpuRun(shapes, ranks, "bf16", states, variant=variant)
+    twin = GpuRun(shapes, ranks, "bf16", states, variant=variant)
+    gbuf = [to_device(s.gradient(0), torch) for s in streams]
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        twin.opt.step(twin.X, gbuf, twin.M, twin.Q)
+    side.synchronize()
+    eager.step([s.gradient(0) for s in streams])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        twin.opt.step(twin.X, gbuf, twin.M, twin.Q)
+    for t in range(1, 4):
+        grads = [s.gradient(t) for s in streams]
+        for buf, g in zip(gbuf, grads):
+            buf.copy_(to_device(g, torch))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert eager.step(grads) == [0] * 4 and twin.opt.info() == [0] * 4
+        for i in range(4):
+            a, b = eager.fetch(i, with_factors=False), twin.fetch(i, with_factors=False)
+            for key in ("X", "M", "Q"):
+                assert a[key].tobytes() == b[key].tobytes(), (t, i, key)
+
+
+@pytest.mark.parametrize("broken", [0, 2])
+def test_a_broken_matrix_leaves_the_others_of_its_launches_alone(broken):
+    """B = 0 in one matrix of a cluster (a small rank, a larger one): it is flagged and keeps its X, and
+    the others have the bits of a run in which it was sound."""
+    shapes, ranks, streams, states = _mixed_cluster()
+    grads = [s.gradient(0) for s in streams]
+    sound = GpuRun(shapes, ranks, "bf16", states)
+    assert sound.step(grads) == [0] * 4
+    states[broken].M[:] = 0.0
+    zeroed = list(grads)
+    zeroed[broken] = np.zeros_like(grads[broken])
+    gpu = GpuRun(shapes, ranks, "bf16", states)
+    info = gpu.step(zeroed)
+    assert [v != 0 for v in info] == [i == broken for i in range(4)], info
+    assert gpu.fetch(broken, False)["X"].tobytes() == states[broken].X.tobytes()
+    for i in range(4):
+        if i == broken:
+            continue
+        a, b = sound.fetch(i), gpu.fetch(i)
+        for key in ("X", "M", "Q", "P", "R"):
+            assert a[key].tobytes() == b[key].tobytes(), (i, key)
+
+
+def test_leading_dimensions_larger_than_n_in_a_cluster():
+    """Padded rows in shared launches: the bits of the densely stored run, and the padding untouched."""
+    import torch
+    shapes, ranks, streams, states = _mixed_cluster()
+    dense = GpuRun(shapes, ranks, "bf16", states)
+    assert dense.step([s.gradient(0) for s in streams]) == [0] * 4
+    lds = [(n + 8, n + 24, n + 16) for _, n in shapes]
+
+    def padded(a, ld):
+        t = to_device(a, torch)
+        out = torch.full((t.shape[0], ld), 7.0, dtype=t.dtype, device=t.device)
+        out[:, :t.shape[1]] = t
+        return out
+
+    X = [padded(s.X, ld[0]) for s, ld in zip(states, lds)]
+    G = [padded(s.gradient(0), ld[1]) for s, ld in zip(streams, lds)]
+    M = [padded(s.M, ld[2]) for s, ld in zip(states, lds)]
+    Q = [to_device(s.Q, torch) for s in states]
+    h = binding.orthdion_create(shapes, ranks, binding.ORTHDION_BF16, binding.ORTHDION_BF16, lds=lds)
+    ws = torch.empty(binding.orthdion_workspace_bytes(h), dtype=torch.uint8, device="cuda:0")
+    ptr = lambda ts: [t.data_ptr() for t in ts]
+    binding.orthdion_step(h, ptr(X), ptr(G), ptr(M), ptr(Q), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert binding.orthdion_get_info(h, 4) == [0] * 4
+    for i, (_, n) in enumerate(shapes):
+        want = dense.fetch(i, False)
+        for key, t in (("X", X[i]), ("M", M[i]), ("Q", Q[i])):
+            assert to_host(t[:, :n].contiguous() if key != "Q" else t, torch).tobytes() == want[key].tobytes(), (i, key)
+            assert key == "Q" or torch.all(t[:, n:] == 7.0)
+    binding.orthdion_destroy(h)
+
+
+@pytest.mark.parametrize("shapes", [((264, 392),), ((264, 392), (520, 136))])
+@pytest.mark.parametrize("r", [136, 104])
+def test_fast_precision_with_fp32_gradients(shapes, r):
+    """fp16 operands made from fp32 gradients, one shape and two of them in a launch, tiles that reach
+    beyond the matrix on every side."""
+    w = synth.Workload(f"fast32-{len(shapes)}-{r}", shapes, r=r, x_dtype="f32", steps=2, spectrum="inverse_index", momentum_std=0.02)
+    _free_running(w, precision="fast", tol=2e-2)
