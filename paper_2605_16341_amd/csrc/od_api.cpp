@@ -452,6 +452,8 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       // `lean`: no more splits than in launches of the batch's own, at most kBatchMatrices matrices each
       auto limited = [&](auto&& pick) {
         int s = pick(b.peers);
+        // exact precision: sums no longer than in launches of the batch's own (each split is summed in fp32 by itself)
+        if (prec == od::PREC_BF3) s = std::max(s, (int)pick(std::min<int64_t>(d.nb, kBatchMatrices)));
         if (lean)
           for (int64_t alone : {std::min(b.alike, kBatchMatrices), b.alike % kBatchMatrices})
             if (alone > 0) s = std::min(s, (int)pick(alone));
