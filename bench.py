@@ -41,7 +41,7 @@ GROUPS = {
     "k_gram (first pass)": (["gram_left", "gram_right"], []),
     "cholesky chain (k_chol256, k_chol_ahead, k_sgemm_pair)": (["chol_left", "chol_right"], ["od::k_chol256", "od::k_chol_ahead", "od::k_sgemm", "od::k_zero_pair"]),
     "rest of orth (k_apply, k_gram, k_corr | ColNorm)": (["orth_left", "orth_right", "guard_left", "guard_right", "finish_left", "finish_right"],
-                                                         ["od::k_apply<", "od::k_apply_result", "od::k_small", "od::k_corr", "od::k_colsq", "od::k_colnorm"]),
+                                                         ["od::k_apply<", "od::k_apply_and_small", "od::k_apply_result", "od::k_small", "od::k_corr", "od::k_colsq", "od::k_colnorm"]),
     "k_reduce": (["proj_reduce", "back_reduce"], ["od::k_reduce"]),
     "k_prologue": (["stats"], ["od::k_prologue<", "od::k_begin<"]),
 }

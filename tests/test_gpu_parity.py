@@ -531,8 +531,8 @@ def test_ill_conditioned_small_ranks(kappa, precision, r):
 @pytest.mark.parametrize("variant", ["qr", "colnorm"])
 @pytest.mark.parametrize("ranks", [(8, 16, 32, 24), (16, 40, 24, 32)])
 def test_small_ranks_alone_and_beside_a_larger_one(ranks, variant, x_dtype):
-    """Ranks up to 32 run kernels of their own while every matrix of the launch has one, and the general
-    ones beside a larger rank; one to three row ranges of the small Gram kernels, ragged rows."""
+    """Ranks up to 32 in launches of their own, and in those of a larger rank with their factorisation in that
+    rank's; one to three row ranges of the small Gram stage, ragged rows."""
     shapes = ((264, 200), (1048, 72), (96, 776), (56, 40))
     streams = [synth.power_law_stream(m, n, 1900 + i, out_dtype=x_dtype) for i, (m, n) in enumerate(shapes)]
     states = [synth.initial_state(m, n, ranks[i], 1900 + i, x_dtype, 1e-3) for i, (m, n) in enumerate(shapes)]
