@@ -77,7 +77,8 @@ typedef enum { ORTHDION_QR = 0, ORTHDION_COLNORM = 1 } orthdion_variant;
 typedef enum { ORTHDION_EF_DION = 0, ORTHDION_EF_PAPER = 1, ORTHDION_EF_POLYAK = 2 } orthdion_ef;
 
 /* Arithmetic of the large contractions (B Q, B^T P, P R^T, P Q^T).  Accumulation is always
- * fp32; the orthogonalisations always use split-bf16 operands (>= 16 significant bits).
+ * fp32; the orthogonalisations use operands of two or three terms (>= 16 significant bits),
+ * for ranks up to 32 fp32, whatever the mode and the ranks of other matrices.
  *   ORTHDION_PREC_AUTO   FAST when X and G are both bf16, otherwise EXACT
  *   ORTHDION_PREC_FAST   fp16 matrix-core operands under a power-of-two scale (11 bits)
  *   ORTHDION_PREC_EXACT  three-way split bf16 operands, six products (24 bits) */
