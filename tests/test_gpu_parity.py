@@ -611,19 +611,20 @@ def test_a_cluster_of_mixed_ranks_replays_from_a_hip_graph(variant):
                 assert a[key].tobytes() == b[key].tobytes(), (t, i, key)
 
 
+@pytest.mark.parametrize("value", [0.0, float("nan")])
 @pytest.mark.parametrize("broken", [0, 2])
-def test_a_broken_matrix_leaves_the_others_of_its_launches_alone(broken):
-    """B = 0 in one matrix of a cluster (a small rank, a larger one): it is flagged and keeps its X, and
-    the others have the bits of a run in which it was sound."""
+def test_a_broken_matrix_leaves_the_others_of_its_launches_alone(broken, value):
+    """B all zero or NaN in one matrix of a cluster (a small rank, a larger one): it is flagged and keeps its
+    X, and the others have the bits of a run in which it was sound."""
     shapes, ranks, streams, states = _mixed_cluster()
     grads = [s.gradient(0) for s in streams]
     sound = GpuRun(shapes, ranks, "bf16", states)
     assert sound.step(grads) == [0] * 4
     states[broken].M[:] = 0.0
-    zeroed = list(grads)
-    zeroed[broken] = np.zeros_like(grads[broken])
+    bad = list(grads)
+    bad[broken] = synth.f32_to_bf16_bits(np.full(grads[broken].shape, value, dtype=np.float32))
     gpu = GpuRun(shapes, ranks, "bf16", states)
-    info = gpu.step(zeroed)
+    info = gpu.step(bad)
     assert [v != 0 for v in info] == [i == broken for i in range(4)], info
     assert gpu.fetch(broken, False)["X"].tobytes() == states[broken].X.tobytes()
     for i in range(4):
@@ -673,3 +674,28 @@ def test_fast_precision_with_fp32_gradients(shapes, r):
     beyond the matrix on every side."""
     w = synth.Workload(f"fast32-{len(shapes)}-{r}", shapes, r=r, x_dtype="f32", steps=2, spectrum="inverse_index", momentum_std=0.02)
     _free_running(w, precision="fast", tol=2e-2)
+
+
+def test_more_equal_matrices_than_a_batch_may_hold():
+    """33000 matrices of one shape: two launch batches, grids of 32768 in y and z; the first and last matrix
+    of either against the oracle."""
+    import torch
+    nmat, m, n, r = 33000, 24, 16, 8
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    rand = lambda *s: torch.randn(*s, device="cuda:0", generator=gen)
+    X, G, M, Q = 0.02 * rand(nmat, m, n), rand(nmat, m, n), 0.1 * rand(nmat, m, n), torch.linalg.qr(rand(n, r))[0].expand(nmat, n, r).contiguous()
+    probe = [0, 32767, 32768, nmat - 1]
+    before = {i: [t[i].cpu().numpy().astype(np.float64) for t in (X, G, M, Q)] for i in probe}
+    h = binding.orthdion_create([(m, n)] * nmat, r, binding.ORTHDION_F32, binding.ORTHDION_F32)
+    ws = torch.empty(binding.orthdion_workspace_bytes(h), dtype=torch.uint8, device="cuda:0")
+    ptr = lambda t: [t.data_ptr() + i * t.stride(0) * t.element_size() for i in range(nmat)]
+    binding.orthdion_step(h, ptr(X), ptr(G), ptr(M), ptr(Q), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert binding.orthdion_get_info(h, nmat) == [0] * nmat
+    orc = OrthDionOracle(mu=0.95, lr=0.01)
+    for i in probe:
+        o = orc.step(*before[i])
+        for key, t in (("X", X), ("M", M), ("Q", Q)):
+            assert rel_fro(t[i].cpu().numpy(), o[key]) <= TOL["f32"], (i, key)
+    binding.orthdion_destroy(h)
