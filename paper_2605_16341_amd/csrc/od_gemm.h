@@ -36,8 +36,8 @@ OD_DEV u32x4 keep_if(bool in, const u32x4& w) { return in ? w : u32x4{0u, 0u, 0u
 // A loader's load() clamps addresses into the source (no branch, see the sources); its store() zeroes what lies
 // outside, by the flags of load() or, given the same position, by asking again.  Flags live across the
 // matrix-core work: the one-stage loop asks again (back-projection with 128 x 256 tiles and fp32 gradients: 43 to
-// 75 spilled registers with flags, none to 15 without; 4096 x 4096, r = 256: 410 -> 384 us a step), the loop of several stages has no registers left for the
-// positions instead.  loadu() is for tiles inside the source.
+// 75 spilled registers with flags, none to 15 without; 4096 x 4096, r = 256: 410 -> 384 us a step), the loop of
+// several stages has no registers left for the positions instead.  loadu() is for tiles inside the source.
 template <class Src, int ROWS, int KT, int PITCH, int THREADS>
 struct LoadKC {
   static constexpr int KG = KT / 8, ITEMS = ROWS * KG, PER = (ITEMS + THREADS - 1) / THREADS;
@@ -52,6 +52,15 @@ struct LoadKC {
       const int item = item_of(p, tid);
       in[p] = inside(s, row0, k0, item);
       raw[p] = s.load8u(in[p] ? row0 + item / KG : 0, in[p] ? k0 + (item % KG) * 8 : 0);
+    }
+  }
+  // load() with a branch per item; outside the source it reads nothing and holds zero
+  OD_DEV void load_checked(const Src& s, int row0, int k0, int tid) {
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+      const int item = item_of(p, tid);
+      raw[p] = s.load8(row0 + item / KG, k0 + (item % KG) * 8);
+      in[p] = true;
     }
   }
   // the tile rows and every k below kpad lie inside the source
@@ -269,24 +278,40 @@ OD_DEV void gemm_mainloop(const SrcA& a, const SrcB& b, int m0, int n0, int kbeg
   // in lockstep get different rotations from their caller (see k_proj).
   const int nsteps = (kend - kbeg + T::KT - 1) / T::KT;
   int cur = rot % nsteps;
-  la.load(a, m0, kbeg + cur * T::KT, tid);
-  lb.load(b, n0, kbeg + cur * T::KT, tid);
-  la.template store<Num>(lds, T::PLANE_A, scaleA, tid, a, m0, kbeg + cur * T::KT);
-  lb.template store<Num>(lds + OFF_B, T::PLANE_B, scaleB, tid, b, n0, kbeg + cur * T::KT);
+  // One stage waits for all its loads anyway, so a branch costs it little: with both operands along k and of one
+  // part checked loads are the faster ones (projection of nine 1840 x 7384 matrices, r = 160: 350 us clamped, 328
+  // checked), with an operand across k clamped ones (their back-projection at r = 104: 239 against 253, with fp32
+  // gradients at r = 160 336 against 437), and with three parts (exact last pass of nine 1024 x 2752, r = 128: 218
+  // against 222).
+  constexpr bool kChecked = Num::PARTS == 1 && std::is_same<DirA, KC>::value && std::is_same<DirB, KC>::value;
+  auto load = [&](int k) {
+    if constexpr (kChecked) {
+      la.load_checked(a, m0, k, tid);
+      lb.load_checked(b, n0, k, tid);
+    } else {
+      la.load(a, m0, k, tid);
+      lb.load(b, n0, k, tid);
+    }
+  };
+  auto store = [&](char* to, int k) {
+    if constexpr (kChecked) {
+      la.template store<Num>(to, T::PLANE_A, scaleA, tid);
+      lb.template store<Num>(to + OFF_B, T::PLANE_B, scaleB, tid);
+    } else {
+      la.template store<Num>(to, T::PLANE_A, scaleA, tid, a, m0, k);
+      lb.template store<Num>(to + OFF_B, T::PLANE_B, scaleB, tid, b, n0, k);
+    }
+  };
+  load(kbeg + cur * T::KT);
+  store(lds, kbeg + cur * T::KT);
   __syncthreads();
   int buf = 0;
   for (int i = 0; i < nsteps; ++i) {
     const bool more = (i + 1) < nsteps;
     cur = (cur + 1 == nsteps) ? 0 : cur + 1;
-    if (more) {
-      la.load(a, m0, kbeg + cur * T::KT, tid);
-      lb.load(b, n0, kbeg + cur * T::KT, tid);
-    }
+    if (more) load(kbeg + cur * T::KT);
     mma_step<T, Num>(lds + buf * BUF, lds + buf * BUF + OFF_B, acc, wm, wn, lane);
-    if (more) {
-      la.template store<Num>(lds + (buf ^ 1) * BUF, T::PLANE_A, scaleA, tid, a, m0, kbeg + cur * T::KT);
-      lb.template store<Num>(lds + (buf ^ 1) * BUF + OFF_B, T::PLANE_B, scaleB, tid, b, n0, kbeg + cur * T::KT);
-    }
+    if (more) store(lds + (buf ^ 1) * BUF, kbeg + cur * T::KT);
     __syncthreads();
     buf ^= 1;
   }
