@@ -206,3 +206,17 @@ def test_sharing_launches_keeps_a_set_within_the_static_scratch(parts, precision
     need = b.orthdion_workspace_bytes(h)
     b.orthdion_destroy(h)
     assert need <= b.orthdion_static_scratch_bytes()
+
+
+def test_exact_precision_keeps_the_splits_of_a_narrow_matrix_beside_a_large_one():
+    """Each split of a contraction is summed in fp32 by itself, so fewer splits are longer fp32 sums: in exact
+    precision a matrix keeps its own number whatever shares its launches.  The partial sums are most of the
+    narrow matrix's workspace, so the set takes what its matrices take alone (but for rounding to 256 bytes)."""
+    def need(shapes, ranks):
+        h = b.orthdion_create(shapes, ranks, b.ORTHDION_F32, b.ORTHDION_F32)
+        got = b.orthdion_workspace_bytes(h)
+        b.orthdion_destroy(h)
+        return got
+
+    narrow, large = need([(2712, 512)], [16]), need([(9936, 6440)], [24])
+    assert need([(2712, 512), (9936, 6440)], [16, 24]) >= narrow + large - 4096
