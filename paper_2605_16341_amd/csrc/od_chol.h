@@ -4,34 +4,34 @@
 // Used by the CholeskyQR orthogonalisation (orth() of Alg. 1 lines 2 and 4): T is the
 // triangular factor of the thin QR, W turns the triangular solve into a product.
 //
-// Layout of the computation (12 waves: wave 3 runs the serial chain of diagonal tiles, the
-// other eleven are workers)
-//   * The block is cut into 32 x 32 tiles; the tiles (I, K) with I < K are kept as
-//     matrix-core accumulators (16 registers per lane: register v of lane l is row
-//     8 (v / 4) + 4 (l / 32) + v % 4, column l % 32), spread over the workers so that every
-//     row and column of tiles is shared out evenly.  The diagonal tiles wait in LDS.
-//   * Step J, (a): the diagonal wave factors tile (J, J) in place, four rows at a time.
-//     The 4 x 4 diagonal block is gathered with readlane and factored in scalar (wave-uniform)
-//     arithmetic; the new rows follow by forward substitution inside each lane; the
-//     rank-4 trailing update of the tile is two fp32 matrix-core products (32x32x2).  The
-//     same operations applied to an identity tile give the inverse of the tile's factor.
-//     Only the inverse (fp32) and the factor are left in LDS; a worker without a tile in (b) writes both
-//     out and splits the inverse for (c).
-//     (b): the owner of tile (J, K) forms T(J, K) = W_JJ^T S(J, K) on the matrix cores (the
-//     accumulator tile serves directly as the k-side operand), writes it out, publishes it
-//     to LDS already split into three bf16 terms in the operand's register order, and
-//     subtracts T(J, K)^T T(J, K) from the waiting diagonal tile (K, K).  Tile (J, J+1) goes
-//     first: as soon as it is done the diagonal wave starts on (J+1, J+1) while the workers
-//     finish (b) and do (c).
-//     (c): every remaining tile gets S(I, K) -= T(J, I)^T T(J, K) from those LDS operands.
-//   * The inverse is built alongside, right-looking, as V = W^T (lower triangular): once
-//     T(I, K) has left its accumulator the same registers collect
-//     S'(K, I) = sum_{I <= L < K} T(L, K)^T V(L, I) in the (c) phases, and in (b) of step K
-//     V(K, I) = -W_KK^T S'(K, I) is written out and published to LDS for the rows below.
-//   * Waves hand tiles over through LDS words (signal / bounded wait); the one barrier per
-//     step waits for LDS traffic only, so the global stores of finished tiles never stall
-//     the loop.  Panel and inverse products use three-way split bf16 operands (six
-//     products, 24 significant bits).
+// Layout of the computation.  The block is cut into 32 x 32 tiles, nt per side.
+//   * Two chain waves (1 and 5) run the serial chain of diagonal tiles.  One of them factors tile (J, J)
+//     four pivots at a time (chain_group) and leaves every group of four rows in LDS the moment it is done.  The
+//     other one takes tile (J, J+1) through the same elimination in fp32 (follow_group), subtracts
+//     T(J, J+1)^T T(J, J+1) from the next diagonal tile, which it holds in registers, and factors that one next.
+//   * The inverse wave (9) takes an identity tile through the elimination, one group behind the chain: V(J, J),
+//     V = W^T.  It leaves it in LDS as product operand, split into three bf16 terms.
+//   * The output wave (11) writes T(J, J) and the zero triangles.
+//   * The other eight waves are workers (the first three roles have a SIMD to themselves).  They keep the tiles (I, K),
+//     I < K, as matrix-core accumulators (16 registers per lane: register v of lane l is row
+//     8 (v / 4) + 4 (l / 32) + v % 4, column l % 32), three or four each and never two that share a row or column of
+//     tiles.  In step J a worker forms T(J, K) = V(J, J) S(J, K) or V(J, I) = -V(J, J) S'(J, I) (the accumulator
+//     serves directly as the k-side operand) and publishes it to LDS already split; then every remaining tile
+//     gets its update of the step from those operands, the one that the chain waits for first.
+//   * The inverse is built alongside, right-looking: once T(I, K) has left its accumulator the same registers
+//     collect S'(K, I) = sum_{I <= L < K} T(L, K)^T V(L, I).
+//   * Signs: the accumulators hold -S and -S', and the panel -T, so that no operand is ever negated.
+//   * Waves hand tiles over through counters in LDS (bounded waits); there is no barrier in the loop.
+//     Products of the workers use three-way split bf16 operands (six products, 24 significant bits).
+//
+// What bounds it: per step, in turn, the chain (3900 cycles), the inverse wave's lag and its hand-over (3000), a panel
+// tile and its publication (3000), the chain's next tile (1300) and its elimination (3700), of which two steps overlap;
+// in the first steps the workers' products (9 tiles per SIMD of 384 matrix-core cycles each).  Before, one wave ran the
+// chain, its factor by readlane and 32 x 32 x 2 products (7400 cycles a tile), with a barrier per step, and the loads went
+// through the mirrored element, four times over every line.  One r = 256 matrix 48 -> 38 us, r = 128 24 -> 19,
+// r = 72 14.5 -> 13; 4096 x 4096, r = 256: 356 -> 335 us a step, 8192 x 8192, r = 2048: 4350 -> 4200,
+// four 1024-wide fp32 matrices, r = 128: 333 -> 321, six ragged ones, r = 136: 514 -> 499.  Sixteen waves
+// (twelve workers) are no faster and leave no registers for another stream's kernels beside it.
 #pragma once
 
 #include <type_traits>
@@ -44,26 +44,35 @@ namespace od {
 constexpr int kCholMax = kLeafRank;    // largest block one workgroup factors
 constexpr int kCT = 32;                // tile size
 constexpr int kCNT = kCholMax / kCT;   // 8 tiles per side
-// Three waves per SIMD.  What a step waits for is the latency of one wave's tiles, one after the other, so
-// more waves with fewer tiles each.  Rank 256: 57 us with two waves per SIMD and four tiles per worker, 53 with
-// the chain below, 48 with three waves, the worker that finishes a diagonal tile and the loads shared out.
-constexpr int kCholThreads = 768;
-constexpr int kCholDiagWave = 3;       // the serial chain; the other eleven are workers
-constexpr int kCWorkers = 11;
-constexpr int kCSlots = 3;             // off-diagonal tiles per worker: 28 over 11 workers
-constexpr int kCPitch = 36;            // floats per row of an fp32 LDS tile (16-byte aligned, conflict free)
-constexpr int kCTileF = kCT * kCPitch; // floats per fp32 LDS tile
+constexpr int kCholThreads = 768;      // three waves per SIMD
+constexpr int kCWorkers = 8;
+constexpr int kCSlots = 4;             // off-diagonal tiles per worker: 28 over 8 workers
+constexpr int kCholInverseWave = 9, kCholOutWave = 11;
 constexpr int kPPitch = 80;            // bytes per row of a pre-split operand tile (32 bf16 + pad)
 constexpr int kPPlane = kCT * kPPitch; // bytes per part of a pre-split tile
 constexpr int kPTile = 3 * kPPlane;    // bytes per pre-split tile
-// LDS: Wt[2] fp32 (W_JJ^T of even / odd steps) | panel[8] pre-split T(J, K)^T | vpanel[8] pre-split V(J, I)
-constexpr int kCholOffPanel = 2 * kCTileF * 4;
+// A finished group of four rows of a diagonal tile in LDS: -t as [4][kGroupPitch] floats (columns left of the
+// group are not defined), then its 4 x 4 block: reciprocals of the diagonal, (01 02 03 12), (13 23).
+constexpr int kGroupPitch = 48, kGroupCoef = 4 * kGroupPitch, kGroupFloats = kGroupCoef + 12;
+// LDS: V(J, J) pre-split as left operand | panel[8] pre-split -T(J, K)^T | vpanel[8] pre-split V(J, I); before step I: the waiting tile (I, I) | groups of
+// even / odd steps | two tile images: S(J, J+1) for the chain | counters
+constexpr int kCholOffPanel = kPTile;
 constexpr int kCholOffVPanel = kCholOffPanel + kCNT * kPTile;
-constexpr int kCholOffSync = kCholOffVPanel + kCNT * kPTile;   // published[8] | s_ready[8] (ints)
-constexpr int kCholOffStash = kCholOffSync + 2 * kCNT * 4;      // two fp32 tile images: S(J, J+1) for the diagonal wave
-constexpr int kCholOffFactor = kCholOffStash + 2 * 4096;        // two fp32 tile images: T(J, J) for its way out
-constexpr int kCholLds = kCholOffFactor + 2 * 4096;
-constexpr int kCholSpinLimit = 1 << 22;  // bound of every wait below (never reached: the producers do not wait)
+constexpr int kCholOffGroups = kCholOffVPanel + kCNT * kPTile;
+constexpr int kCholOffStash = kCholOffGroups + 2 * 8 * kGroupFloats * 4;
+constexpr int kCholOffSync = kCholOffStash + 2 * 4096;
+struct CholSync {
+  int groups;              // groups finished by the chain, 8 per step
+  int updated;             // workers past the updates of a step, summed over the steps
+  int v_ready;             // steps whose V(J, J) is in place
+  int t_done;              // steps whose T(J, J) has been read
+  int rows[kCNT];          // panel tiles of step J published
+  int cols[kCNT];          // V tiles of step J published
+  int s_ready[kCNT];       // S(J, J+1) has its last update and is in the stash
+  int diag[kCNT];          // waiting tile (K, K): loaded, and updates so far
+};
+constexpr int kCholLds = kCholOffSync + (int)sizeof(CholSync);
+constexpr int kCholSpinLimit = 1 << 20;  // bound of every wait below (never reached)
 
 struct CholArgs {
   WsArr src;           // Gram block source: `splits` partial sums, `split_stride` elements apart
@@ -77,24 +86,21 @@ struct CholArgs {
   Pred pred;           // the matrix is skipped unless its predicate holds
 };
 
-// tile (I, K), I < K, of slot s of worker u, four bits per slot, 15 = no tile (kept in scalar
-// registers: a table in memory would cost a dependent load per use).  Tile (I, K) belongs
-// to worker (I + K) mod 11, but (3, 4) to worker 1: at most three tiles each, in every step the panel
-// tiles (one row and one column of tiles, eight consecutive sums I + K) go to seven different workers, and
-// worker 2J mod 11 has none in step J.
+// tile (I, K), I < K, of slot s of worker u, four bits per slot, 15 = no tile (kept in scalar registers: a table in
+// memory would cost a dependent load per use).  An edge colouring of the complete graph on the eight rows of tiles:
+// two tiles of a worker never share a row or column, so a step finds each worker with one tile of its panel at most.
 OD_DEV uint32_t own_rows(int u) {
-  return u == 0 ? 0xff54u : u == 1 ? 0xf350u : u == 2 ? 0xff60u : u == 3 ? 0xff10u : u == 4 ? 0xff10u : u == 5 ? 0xf210u
-       : u == 6 ? 0xf210u : u == 7 ? 0xf210u : u == 8 ? 0xf321u : u == 9 ? 0xf432u : u == 10 ? 0xff43u : 0xffffu;
+  return u == 0 ? 0xf530u : u == 1 ? 0xf610u : u == 2 ? 0x4210u : u == 3 ? 0xf210u : u == 4 ? 0x5320u : u == 5 ? 0xf431u
+       : u == 6 ? 0x4210u : u == 7 ? 0x3210u : 0xffffu;
 }
 OD_DEV uint32_t own_cols(int u) {
-  return u == 0 ? 0xff67u : u == 1 ? 0xf471u : u == 2 ? 0xff72u : u == 3 ? 0xff23u : u == 4 ? 0xff34u : u == 5 ? 0xf345u
-       : u == 6 ? 0xf456u : u == 7 ? 0xf567u : u == 8 ? 0xf567u : u == 9 ? 0xf567u : u == 10 ? 0xff67u : 0xffffu;
+  return u == 0 ? 0xf642u : u == 1 ? 0xf753u : u == 2 ? 0x6537u : u == 3 ? 0xf764u : u == 4 ? 0x7641u : u == 5 ? 0xf752u
+       : u == 6 ? 0x5376u : u == 7 ? 0x7645u : 0xffffu;
 }
-// worker of a wave: waves 7 and 11 share the diagonal wave's SIMD and get the workers whose tiles are
-// finished first
-OD_DEV int worker_of(int wave) { return (int)(0x4a023651987ull >> (4 * (wave - (wave > kCholDiagWave ? 1 : 0)))) & 15; }
+// worker of a wave (15: none)
+OD_DEV int worker_of(int wave) { return (int)(0xfffff5f274f163f0ull >> (4 * wave)) & 15; }
 
-// A diagonal tile waiting in LDS in accumulator layout: plane q holds registers 4q .. 4q+3
+// A tile in LDS in accumulator layout: plane q holds registers 4q .. 4q+3
 // of every lane (16 bytes per lane, conflict free).
 OD_DEV f32x16 load_dtile(const char* p, int lane) {
   f32x16 t;
@@ -127,13 +133,6 @@ OD_DEV float lane_bcast(float v, int lane) {
 
 // Three-way split bf16 operand words of 8 floats.
 OD_DEV void split3(const float* x, u32x4* parts) { NumBF<3>::pack(x, 1.f, parts); }
-
-OD_DEV void negate3(u32x4* parts) {
-#pragma unroll
-  for (int s = 0; s < 3; ++s)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) parts[s][i] ^= 0x80008000u;
-}
 
 OD_DEV f32x16 mma6(const u32x4* a, const u32x4* b, f32x16 c) {
 #pragma unroll
@@ -170,23 +169,27 @@ OD_DEV void load_presplit(const char* tile, int lane, int kk, u32x4* parts) {
   for (int s = 0; s < 3; ++s) parts[s] = *reinterpret_cast<const u32x4*>(p + s * kPPlane);
 }
 
-// Producer / consumer hand-off between the waves of the workgroup through LDS words.  The
-// producer's earlier LDS writes are complete before the word changes; a consumer that has
-// seen the value may read them.  Producers never wait on consumers, so every wait ends; it
-// is bounded anyway so that a wave can always run to the end of the kernel.
+// Hand-off between the waves of the workgroup through LDS words.  LDS operations of a wave are carried out in
+// order, so what it wrote before the word changes is there for whoever has seen the new value, and what it read has
+// been read; only the compiler has to be kept from moving them.  Every wait is bounded, so that a wave can
+// always run to the end of the kernel.
 OD_DEV void lds_signal_add(int* word, int lane) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  asm volatile("" ::: "memory");
   if (lane == 0) __hip_atomic_fetch_add(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  asm volatile("" ::: "memory");
 }
-// Returns false when the bound ran out (the caller reports it; the kernel still ends).
-OD_DEV bool lds_wait_ge(int* word, int target) {
-  bool seen = false;
-  for (int spins = 0; spins < kCholSpinLimit; ++spins) {
-    if (__hip_atomic_load(word, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= target) { seen = true; break; }
-    __builtin_amdgcn_s_sleep(1);
+// Returns whether the bound ran out (the caller reports it; the kernel still ends); `expired`: one has already.
+// SLEEP: for waits that nothing urgent hangs on, so that they leave LDS and issue slots to the others.
+template <bool SLEEP>
+OD_DEV bool lds_wait(const int* word, int target, bool expired) {
+  for (int spins = 0; !expired; ++spins) {
+    const int seen = __builtin_amdgcn_readfirstlane(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    if (seen >= target) break;
+    if (spins >= kCholSpinLimit) expired = true;
+    if constexpr (SLEEP) __builtin_amdgcn_s_sleep(1);
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-  return seen;
+  asm volatile("" ::: "memory");
+  return expired;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -290,24 +293,198 @@ OD_DEV int diag_tile_factor(f32x16& d_io, f32x16& zt_out, int lane, int nv) {
   return columns != 0u ? __ffs((int)columns) : 0;
 }
 
+// ---------------------------------------------------------------------------------------
+// The chain waves hold 32 x 32 tiles as 16 x 16 blocks in the layout of the 16 x 16 x 4 product: register v of lane l
+// is row 4 (l / 16) + v, column l % 16.  Rows 4 g .. 4 g + 3 are then the four registers of one 16-lane row of the
+// wave (g % 4): an element of a row reaches the lanes of that row as a DPP operand of the next instruction (no
+// readlane, no trip through scalar registers), and the rank-4 update of a block is a single product.
+// ---------------------------------------------------------------------------------------
+template <int N>
+OD_DEV float row_bcast(float x) {       // lane N of each 16-lane row
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + N, 0xf, 0xf, true));
+}
+OD_DEV f32x4 mfma_16x16x4(float a, float b, f32x4 c) {
+  // D(16x16) += A(16x4) B(4x16) in fp32: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// operand of a rank-4 update: lane row e of the result is row G of t_e
+template <int G>
+OD_DEV float gather_rows(float t0, float t1, float t2, float t3) {
+  // swaps the odd lane rows of the first operand with the even ones of the second
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(t0), __float_as_uint(t1), false, false);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(t2), __float_as_uint(t3), false, false);
+  const auto s = __builtin_amdgcn_permlane32_swap(p[G & 1], q[G & 1], false, false);
+  return __uint_as_float(s[G >> 1]);
+}
+
+// Group g of the diagonal tile with blocks d00, d01, d11 (by symmetry the fourth is not kept): factors its 4 x 4
+// diagonal block, eliminates, publishes the rows.  The hardware reciprocal square root (1 ulp) is accurate enough, since
+// everything else follows from the same rounded values.  A non-positive or non-finite pivot leaves a NaN.
+template <int g>
+OD_DEV void chain_group(f32x4& d00, f32x4& d01, f32x4& d11, int lane, float* grp, int* groups, int count) {
+  constexpr int G = g & 3, C = 4 * G;
+  constexpr bool low = g < 4;
+  const f32x4 x = low ? d00 : d11;
+  const float i0 = __builtin_amdgcn_rsqf(row_bcast<C>(x[0]));
+  const float t0 = x[0] * i0;
+  const float m01 = row_bcast<C + 1>(t0), m02 = row_bcast<C + 2>(t0), m03 = row_bcast<C + 3>(t0);
+  const float x1 = x[1] - m01 * t0;
+  const float i1 = __builtin_amdgcn_rsqf(row_bcast<C + 1>(x1));
+  const float t1 = x1 * i1;
+  const float m12 = row_bcast<C + 2>(t1), m13 = row_bcast<C + 3>(t1);
+  const float x2 = x[2] - m02 * t0 - m12 * t1;
+  const float i2 = __builtin_amdgcn_rsqf(row_bcast<C + 2>(x2));
+  const float t2 = x2 * i2;
+  const float m23 = row_bcast<C + 3>(t2);
+  const float x3 = x[3] - m03 * t0 - m13 * t1 - m23 * t2;
+  const float i3 = __builtin_amdgcn_rsqf(row_bcast<C + 3>(x3));
+  const float t3 = x3 * i3;
+  const float a = gather_rows<G>(t0, t1, t2, t3);
+  const float na = -a;
+  float* row = grp + (lane >> 4) * kGroupPitch + (lane & 15);
+  if constexpr (low) {
+    if constexpr (G < 3) d00 = mfma_16x16x4(na, a, d00);
+    __builtin_amdgcn_sched_barrier(0);          // the next group waits for that product; the rest runs beside it
+    const float u0 = d01[0] * i0;
+    const float u1 = (d01[1] - m01 * u0) * i1;
+    const float u2 = (d01[2] - m02 * u0 - m12 * u1) * i2;
+    const float u3 = (d01[3] - m03 * u0 - m13 * u1 - m23 * u2) * i3;
+    const float b = gather_rows<G>(u0, u1, u2, u3);
+    const float nb = -b;
+    if constexpr (G < 3) d01 = mfma_16x16x4(na, b, d01);
+    d11 = mfma_16x16x4(nb, b, d11);
+    row[0] = na;
+    row[16] = nb;
+  } else {
+    if constexpr (G < 3) d11 = mfma_16x16x4(na, a, d11);
+    row[16] = na;
+  }
+  asm volatile("" ::: "memory");
+  if (lane == 16 * G) {
+    *reinterpret_cast<f32x4*>(grp + kGroupCoef) = f32x4{i0, i1, i2, i3};
+    *reinterpret_cast<f32x4*>(grp + kGroupCoef + 4) = f32x4{m01, m02, m03, m12};
+    *reinterpret_cast<f32x2*>(grp + kGroupCoef + 8) = f32x2{m13, m23};
+    asm volatile("" ::: "memory");
+    __hip_atomic_store(groups, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  asm volatile("" ::: "memory");
+}
+
+// The 4 x 4 block of a group as the others read it.  (Read as whole vectors without a spare element: the register of
+// one would be given to the next load, which then waits for this one.)
+struct GroupCoef {
+  f32x4 inv, m;                // m: 01 02 03 12
+  f32x2 n;                     // 13 23
+};
+OD_DEV GroupCoef load_coef(const float* grp) {
+  return GroupCoef{*reinterpret_cast<const f32x4*>(grp + kGroupCoef), *reinterpret_cast<const f32x4*>(grp + kGroupCoef + 4),
+                   *reinterpret_cast<const f32x2*>(grp + kGroupCoef + 8)};
+}
+// rows of a group by forward substitution
+OD_DEV void solve_rows(const GroupCoef& k, float x0, float x1, float x2, float x3, float (&t)[4]) {
+  t[0] = x0 * k.inv[0];
+  t[1] = (x1 - k.m[0] * t[0]) * k.inv[1];
+  t[2] = (x2 - k.m[1] * t[0] - k.m[3] * t[1]) * k.inv[2];
+  t[3] = (x3 - k.m[2] * t[0] - k.n[0] * t[1] - k.n[1] * t[2]) * k.inv[3];
+}
+// A group as a chain wave reads it: coefficients and the rows as product operands.
+struct GroupRows {
+  GroupCoef k;
+  float a0, a1;
+};
+OD_DEV GroupRows load_group(const float* step, int g, int lane) {
+  const float* grp = step + g * kGroupFloats;
+  const float* row = grp + (lane >> 4) * kGroupPitch + (lane & 15);
+  return GroupRows{load_coef(grp), row[0], row[16]};
+}
+// Group g for the tile right of the diagonal one (s, 16 x 16 blocks [row half][column half]) and the next
+// diagonal tile (n00, n01, n11, negated).
+template <int g>
+OD_DEV void follow_group(f32x4 (&s)[2][2], f32x4& n00, f32x4& n01, f32x4& n11, const GroupRows& in) {
+  constexpr int G = g & 3, H = g >> 2;
+  float b[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    float t[4];
+    solve_rows(in.k, s[H][c][0], s[H][c][1], s[H][c][2], s[H][c][3], t);
+    b[c] = gather_rows<G>(t[0], t[1], t[2], t[3]);
+    if constexpr (G < 3) s[H][c] = mfma_16x16x4(H == 0 ? in.a0 : in.a1, b[c], s[H][c]);
+    else if constexpr (H == 0) s[1][c] = mfma_16x16x4(in.a1, b[c], s[1][c]);
+  }
+  if constexpr (g < 3) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) s[1][c] = mfma_16x16x4(in.a1, b[c], s[1][c]);
+  }
+  n00 = mfma_16x16x4(b[0], b[0], n00);
+  n01 = mfma_16x16x4(b[0], b[1], n01);
+  n11 = mfma_16x16x4(b[1], b[1], n11);
+}
+// Four groups, the next one's reads ahead of a group's arithmetic.
+template <int H>
+OD_DEV void follow_half(f32x4 (&s)[2][2], f32x4& n00, f32x4& n01, f32x4& n11, int lane, const float* step) {
+  GroupRows in0 = load_group(step, 4 * H, lane);
+  GroupRows in1 = load_group(step, 4 * H + 1, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  follow_group<4 * H>(s, n00, n01, n11, in0);
+  in0 = load_group(step, 4 * H + 2, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  follow_group<4 * H + 1>(s, n00, n01, n11, in1);
+  in1 = load_group(step, 4 * H + 3, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  follow_group<4 * H + 2>(s, n00, n01, n11, in0);
+  follow_group<4 * H + 3>(s, n00, n01, n11, in1);
+}
+
+// Group g for the identity tile: z00, z10, z11 are eliminated, f00, f10, f11 receive the finished rows.  Waits for the
+// group; what is read along with the count is valid once the count is there.
+template <int g>
+OD_DEV bool inverse_group(f32x4& z00, f32x4& z10, f32x4& z11, f32x4& f00, f32x4& f10, f32x4& f11, int lane, const float* step, const int* groups, int count, bool expired) {
+  constexpr int G = g & 3;
+  const float* grp = step + g * kGroupFloats;
+  const float* row = grp + (lane >> 4) * kGroupPitch + (lane & 15);
+  expired = lds_wait<false>(groups, count, expired);
+  const GroupCoef k = load_coef(grp);
+  const float na = row[0], nb = row[16];
+  const bool mine = (lane >> 4) == G;
+  float t[4], u[4];
+  if constexpr (g < 4) {
+    solve_rows(k, z00[0], z00[1], z00[2], z00[3], t);
+    const float b = gather_rows<G>(t[0], t[1], t[2], t[3]);
+    if constexpr (G < 3) z00 = mfma_16x16x4(na, b, z00);
+    z10 = mfma_16x16x4(nb, b, z10);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f00[e] = mine ? t[e] : f00[e];
+  } else {
+    solve_rows(k, z10[0], z10[1], z10[2], z10[3], t);
+    solve_rows(k, z11[0], z11[1], z11[2], z11[3], u);
+    if constexpr (G < 3) {
+      z10 = mfma_16x16x4(nb, gather_rows<G>(t[0], t[1], t[2], t[3]), z10);
+      z11 = mfma_16x16x4(nb, gather_rows<G>(u[0], u[1], u[2], u[3]), z11);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      f10[e] = mine ? t[e] : f10[e];
+      f11[e] = mine ? u[e] : f11[e];
+    }
+  }
+  return expired;
+}
+
 // The factorisation of block `a.blk` of matrix `z` by one workgroup of kCholThreads threads;
 // `lds_raw`: kCholLds bytes.
 OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
-  float* Wt = reinterpret_cast<float*>(lds_raw);                         // W_JJ^T, [i][k], buffer J & 1
-  char* panel = lds_raw + kCholOffPanel;                                 // T(J, K)^T pre-split, one tile per K
-  char* vpanel = lds_raw + kCholOffVPanel;                               // V(J, I) pre-split, one tile per I; before
-                                                                         // step I-1 ends: the waiting tile (I, I)
-  int* published = reinterpret_cast<int*>(lds_raw + kCholOffSync);       // tiles of step J published so far
-  int* s_ready = published + kCNT;                                       // S(J, J+1) has its last update and is in the stash
-  char* stash = lds_raw + kCholOffStash;                                 // buffer J & 1
+  char* voperand = lds_raw;
+  char* panel = lds_raw + kCholOffPanel;
+  char* vpanel = lds_raw + kCholOffVPanel;
+  float* const group_data = reinterpret_cast<float*>(lds_raw + kCholOffGroups);
+  char* stash = lds_raw + kCholOffStash;
+  CholSync& sync = *reinterpret_cast<CholSync*>(lds_raw + kCholOffSync);
 
   const int tid = threadIdx.x, lane = tid & 63;
   // uniform over the workgroup, before any barrier or LDS hand-off
   if (a.pred.scal != nullptr && (a.pred.scal[z * kScalPerMat + a.pred.slot] > a.pred.thr) != (a.pred.want != 0)) return;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool diag_wave = wave == kCholDiagWave;
-  const int worker = diag_wave ? kCWorkers : worker_of(wave);
-  const uint32_t ownI = own_rows(worker), ownK = own_cols(worker);
+  const int worker = worker_of(wave);
   const int r = a.r;
   const int o = a.blk * kCholMax;
   const int nb = (r - o) < kCholMax ? (r - o) : kCholMax;     // order of this block
@@ -316,261 +493,348 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
   const float* src = a.src.base + (int64_t)z * a.src.stride + off;
   float* tg = a.t.base + (int64_t)z * a.t.stride + off;
   float* wg = a.w.base + (int64_t)z * a.w.stride + off;
-  const int col = lane & 31, half = lane >> 5;
-  if (tid < 2 * kCNT) published[tid] = 0;
-
-  // ---- load: every tile is read straight into accumulator layout through the transposed
-  // element (the matrix is symmetric): lane column c needs rows 8q + 4h + {0..3} of its
-  // column, which are four consecutive entries of row c of the mirrored tile.  Addresses are
-  // clamped into the block, so all loads are unconditional and in flight together; identity
-  // outside the block.
-  auto load_tile = [&](int I, int K) {
-    f32x16 t;
-    const int gj = K * kCT + col, gjc = gj < nb ? gj : nb - 1;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int gi = I * kCT + 8 * q + 4 * half, gic = gi < nb ? gi : nb - 4;
-      const float* p = src + (int64_t)gjc * r + gic;
-      f32x4 v4 = *reinterpret_cast<const f32x4*>(p);
-      for (int sp = 1; sp < a.splits; ++sp) v4 += *reinterpret_cast<const f32x4*>(p + (int64_t)sp * a.split_stride);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) t[4 * q + e] = v4[e];
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int gi = I * kCT + acc_row(v, lane);
-      if (gi >= nb || gj >= nb) t[v] = (gi == gj) ? 1.f : 0.f;
-    }
-    return t;
+  if (tid < (int)(sizeof(CholSync) / sizeof(int))) reinterpret_cast<int*>(&sync)[tid] = 0;
+  lds_barrier();
+  bool expired = false;
+  auto wait = [&](const int* word, int target) { expired = lds_wait<false>(word, target, expired); };
+  auto wait_idle = [&](const int* word, int target) { expired = lds_wait<true>(word, target, expired); };
+  auto valid_rows = [&](int J) { return (nb - J * kCT) < kCT ? (nb - J * kCT) : kCT; };
+  auto step_groups = [&](int J) { return group_data + (J & 1) * 8 * kGroupFloats; };
+  // Element (row, col) of the block, the identity outside.  Lanes read along a row, so that every line of the source is
+  // fetched once.  The address is clamped into the block: the loads of a tile are unconditional and in flight together.
+  auto element = [&](int row, int col) {
+    const float* p = src + (int64_t)(row < nb ? row : nb - 1) * r + (col < nb ? col : nb - 1);
+    float v = *p;
+    for (int sp = 1; sp < a.splits; ++sp) v += p[(int64_t)sp * a.split_stride];
+    return row < nb && col < nb ? v : row == col ? 1.f : 0.f;
   };
-  // the diagonal tiles: (0, 0) is factored at once by the diagonal wave (below), worker u brings tile
-  // (u + 1, u + 1), which waits in LDS for its updates
-  f32x16 waiting;
-  if (!diag_wave && worker + 1 < nt) waiting = load_tile(worker + 1, worker + 1);
-  f32x16 acc[kCSlots];
-#pragma unroll
-  for (int s = 0; s < kCSlots; ++s) {
-    const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
-    if (K < nt) acc[s] = load_tile(I, K);
-    else {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[s][v] = 0.f;
-    }
-  }
 
-  // ================================ factorisation ================================
-  char* factor = lds_raw + kCholOffFactor;                               // buffer J & 1
-  // (a) tile (J, J): factor, invert, leave T_JJ and W_JJ^T in LDS
-  auto do_diag = [&](int J, f32x16 d) {
-    f32x16 zt;
-    const int nv = (nb - J * kCT) < kCT ? (nb - J * kCT) : kCT;   // valid rows / cols of this tile
-    const int bad = diag_tile_factor(d, zt, lane, nv);
-    // zt = M = V(J, J) with W_JJ = M^T:  Wt[i][k] = M[i][k]
-    float* wt = Wt + (J & 1) * kCTileF;
+  if (worker == 15 && wave < kCholInverseWave) {
+    // ================================ the chain ================================
+    const int self = wave >> 2, j = lane & 15, lr = lane >> 4;
+    f32x4 d00, d01, d11;
+    if (self == 0) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) wt[acc_row(v, lane) * kCPitch + col] = zt[v];
-    store_dtile(factor + (J & 1) * 4096, d, lane);
-    if (bad != 0 && lane == 0) atomicCAS(&a.info[z * kInfoPerMat + a.info_slot], 0, o + J * kCT + bad);
-  };
-  // ... and by a worker: V(J, J) split for (c), W_JJ and T_JJ written out
-  auto finish_diag = [&](int J) {
-    const int nv = (nb - J * kCT) < kCT ? (nb - J * kCT) : kCT;
-    const float* wt = Wt + (J & 1) * kCTileF;
-    f32x16 zt;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) zt[v] = wt[acc_row(v, lane) * kCPitch + col];
-    store_presplit(vpanel + J * kPTile, zt, lane);
-    lds_signal_add(published + J, lane);
-    const f32x16 d = load_dtile(factor + (J & 1) * 4096, lane);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      // global W_JJ[c][rows] (row c of W = column c of M), 4 consecutive entries
-      if (col < nv && 8 * q < nv) {
-        const f32x4 v4 = {zt[4 * q], zt[4 * q + 1], zt[4 * q + 2], zt[4 * q + 3]};
-        *reinterpret_cast<f32x4*>(wg + (int64_t)(J * kCT + col) * r + J * kCT + 8 * q + 4 * half) = v4;
+      for (int v = 0; v < 4; ++v) {
+        d00[v] = element(4 * lr + v, j);
+        d01[v] = element(4 * lr + v, 16 + j);
+        d11[v] = element(16 + 4 * lr + v, 16 + j);
       }
     }
-    if (col < nv) {
+    // 16 x 16 block (rh, ch) of a tile image
+    auto block_of = [&](const char* image, int rh, int ch) {
+      return *reinterpret_cast<const f32x4*>(image + (2 * rh + (lr >> 1)) * 1024 + (16 * ch + j + 32 * (lr & 1)) * 16);
+    };
+    for (int J = 0; J < nt; ++J) {
+      float* grp = step_groups(J);
+      if ((J & 1) == self) {
+        // the groups of step J - 2 have been read
+        if (J >= 2) wait(&sync.t_done, J - 1);
+        const int nv = valid_rows(J), base = 8 * J;
+        auto at = [&](int g) { return grp + g * kGroupFloats; };
+        chain_group<0>(d00, d01, d11, lane, at(0), &sync.groups, base + 1);
+        chain_group<1>(d00, d01, d11, lane, at(1), &sync.groups, base + 2);
+        if (nv > 8) {
+          chain_group<2>(d00, d01, d11, lane, at(2), &sync.groups, base + 3);
+          chain_group<3>(d00, d01, d11, lane, at(3), &sync.groups, base + 4);
+        }
+        if (nv > 16) {
+          chain_group<4>(d00, d01, d11, lane, at(4), &sync.groups, base + 5);
+          chain_group<5>(d00, d01, d11, lane, at(5), &sync.groups, base + 6);
+        }
+        if (nv > 24) {
+          chain_group<6>(d00, d01, d11, lane, at(6), &sync.groups, base + 7);
+          chain_group<7>(d00, d01, d11, lane, at(7), &sync.groups, base + 8);
+        }
+      } else if (J + 1 < nt) {
+        wait(&sync.diag[J + 1], 1 + J);
+        const char* image = vpanel + (J + 1) * kPTile;
+        f32x4 n00 = block_of(image, 0, 0), n01 = block_of(image, 0, 1), n11 = block_of(image, 1, 1);
+        wait(&sync.s_ready[J], 1);
+        const char* si = stash + (J & 1) * 4096;
+        f32x4 s[2][2] = {{block_of(si, 0, 0), block_of(si, 0, 1)}, {block_of(si, 1, 0), block_of(si, 1, 1)}};
+        wait(&sync.groups, 8 * J + 4);
+        follow_half<0>(s, n00, n01, n11, lane, grp);
+        wait(&sync.groups, 8 * J + 8);
+        follow_half<1>(s, n00, n01, n11, lane, grp);
+        d00 = -n00;
+        d01 = -n01;
+        d11 = -n11;
+      }
+    }
+  } else if (wave == kCholInverseWave) {
+    // ================================ V(J, J) ================================
+    const int j = lane & 15, lr = lane >> 4;
+    // in the left operand k = column 16 ch + j of V sits where the k-side operand has it in register order
+    // (lanes j and j + 1 swap halves: even lanes write the even rows of a pair, odd lanes the odd ones)
+    char* const left = voperand + (4 * lr + (j & 1)) * kPPitch + ((j >> 2) & 1) * 16 + ((j >> 3) * 4 + (j & 2)) * 2;
+    const uint32_t pick = (j & 1) ? 0x03020706u : 0x05040100u;
+    auto pair = [&](uint32_t w) { return __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xb1, 0xf, 0xf, true), w, pick); };
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) *reinterpret_cast<uint32_t*>(left + s * kPPlane + 2 * v * kPPitch + 32) = 0u;      // block (0, 1)
+    for (int J = 0; J < nt; ++J) {
+      const float* step = step_groups(J);
+      const int nv = valid_rows(J), base = 8 * J;
+      f32x4 z00, z10, z11;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        z00[v] = z11[v] = 4 * lr + v == j ? 1.f : 0.f;
+        z10[v] = 0.f;
+      }
+      f32x4 f00 = z00, f10 = z10, f11 = z11;
+      expired = inverse_group<0>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 1, expired);
+      expired = inverse_group<1>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 2, expired);
+      if (nv > 8) {
+        expired = inverse_group<2>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 3, expired);
+        expired = inverse_group<3>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 4, expired);
+      }
+      if (nv > 16) {
+        expired = inverse_group<4>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 5, expired);
+        expired = inverse_group<5>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 6, expired);
+      }
+      if (nv > 24) {
+        expired = inverse_group<6>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 7, expired);
+        expired = inverse_group<7>(z00, z10, z11, f00, f10, f11, lane, step, &sync.groups, base + 8, expired);
+      }
+      // split; the left operand of the step before has been read
+      u32x4 w0[3], w1[3];
+      {
+        const float x0[8] = {f00[0], f00[1], f00[2], f00[3], f10[0], f10[1], f10[2], f10[3]};
+        const float x1[8] = {0.f, 0.f, 0.f, 0.f, f11[0], f11[1], f11[2], f11[3]};
+        split3(x0, w0);
+        split3(x1, w1);
+      }
+      if (J > 0) {
+        wait(&sync.rows[J - 1], nt - J);
+        wait(&sync.cols[J - 1], J);
+      }
+      char* const vp = vpanel + J * kPTile + j * kPPitch + (lr & 1) * 16 + (lr >> 1) * 8;
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          *reinterpret_cast<uint32_t*>(left + s * kPPlane + 2 * v * kPPitch) = pair(w0[s][v]);
+          *reinterpret_cast<uint32_t*>(left + s * kPPlane + (16 + 2 * v) * kPPitch) = pair(w0[s][2 + v]);
+          *reinterpret_cast<uint32_t*>(left + s * kPPlane + (16 + 2 * v) * kPPitch + 32) = pair(w1[s][2 + v]);
+        }
+        *reinterpret_cast<u32x2*>(vp + s * kPPlane) = u32x2{w0[s][0], w0[s][1]};
+        *reinterpret_cast<u32x2*>(vp + s * kPPlane + 32) = u32x2{w0[s][2], w0[s][3]};
+        *reinterpret_cast<u32x2*>(vp + s * kPPlane + 16 * kPPitch) = u32x2{0u, 0u};
+        *reinterpret_cast<u32x2*>(vp + s * kPPlane + 16 * kPPitch + 32) = u32x2{w1[s][2], w1[s][3]};
+      }
+      lds_signal_add(&sync.v_ready, lane);
+      lds_signal_add(&sync.cols[J], lane);
+      // W(c, i) = V(i, c): four consecutive columns per store
+      auto put = [&](int rh, int ch, const f32x4& f) {
+        if (16 * ch + j < nv && 16 * rh + 4 * lr < nv) *reinterpret_cast<f32x4*>(wg + (int64_t)(J * kCT + 16 * ch + j) * r + J * kCT + 16 * rh + 4 * lr) = f;
+      };
+      put(0, 0, f00);
+      put(1, 0, f10);
+      put(0, 1, f32x4{0.f, 0.f, 0.f, 0.f});
+      put(1, 1, f11);
+    }
+  } else if (wave == kCholOutWave) {
+    // ================================ T(J, J), zeros ================================
+    const int col = lane & 31, half = lane >> 5;
+    for (int J = 0; J < nt; ++J) {
+      const float* step = step_groups(J);
+      const int nv = valid_rows(J);
+      wait_idle(&sync.groups, 8 * J + nv / 4);
+      // T_JJ, and whether every pivot was a positive number below 3e38 (its root is on the diagonal)
+      bool ok = true;
       float* tp = tg + (int64_t)(J * kCT + 4 * half) * r + J * kCT + col;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (8 * q < nv) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) tp[(int64_t)(8 * q + e) * r] = d[4 * q + e];
-        }
-      }
-    }
-  };
-  // tile += sign * A^T B with both operands pre-split in LDS
-  auto lds_product = [&](f32x16& tile, const char* pa, const char* pb, bool negate) {
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      u32x4 ap[3], bp[3];
-      load_presplit(pa, lane, kk, ap);
-      load_presplit(pb, lane, kk, bp);
-      if (negate) negate3(ap);
-      tile = mma6(ap, bp, tile);
-    }
-  };
-  // (b) for one owned tile of step J: T(J, K) = W_JJ^T S(J, K) (row tile) or V(J, I) = -W_JJ^T S'(J, I)
-  // (column tile), written out and published.  fp32 products (32x32x2): step (q, e) contracts
-  // over k = 8q + e (lower lane half) and 8q + 4 + e (upper half), which is exactly the row an
-  // accumulator lane keeps in register 4q + e, so the k-side operand needs no data movement
-  // and nothing is split.
-  auto panel_tile = [&](f32x16& tile, const f32x4 (&mrow)[4], int J, int I, int K, bool row_tile) {
-    const int nvr = (nb - J * kCT) < kCT ? (nb - J * kCT) : kCT;
-    // two independent accumulation chains keep the matrix core busy back to back
-    f32x16 res, res2;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { res[v] = 0.f; res2[v] = 0.f; }
-#pragma unroll
-    for (int q = 0; q < 4; q += 2)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        res = mfma_f32_k2(mrow[q][e], tile[4 * q + e], res);
-        res2 = mfma_f32_k2(mrow[q + 1][e], tile[4 * q + 4 + e], res2);
-      }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) res[v] = row_tile ? (res[v] + res2[v]) : -(res[v] + res2[v]);
-    if (row_tile) {
-      // published first: the other workers wait for this tile, nobody waits for the rest
-      store_presplit(panel + K * kPTile, res, lane);
-      lds_signal_add(published + J, lane);
-      // block orders are multiples of 8, so rows 8q .. 8q+7 are valid or not together
-      if (K * kCT + col < nb) {
-        float* tp = tg + (int64_t)(J * kCT + 4 * half) * r + K * kCT + col;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (8 * q < nvr) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) tp[(int64_t)(8 * q + e) * r] = res[4 * q + e];
+          for (int e = 0; e < 4; ++e) {
+            const int row = 8 * q + 4 * half + e;
+            const float t = -step[(2 * q + half) * kGroupFloats + e * kGroupPitch + col];
+            if (row == col) ok = t > 0.f && t < 1.7320508e19f;
+            if (col < nv) tp[(int64_t)(8 * q + e) * r] = col < row ? 0.f : t;
           }
         }
       }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) tile[v] = 0.f;       // from now on the sum S'(K, J)
-      // the waiting diagonal tile (K, K) -= T(J, K)^T T(J, K), operands read back from the panel
-      // (tile (J+1, J+1) gets this update from the diagonal wave itself, which is about to factor it)
-      if (K != J + 1) {
-        char* dk = vpanel + K * kPTile;
-        f32x16 dt = load_dtile(dk, lane);
-        lds_product(dt, panel + K * kPTile, panel + K * kPTile, true);
-        store_dtile(dk, dt, lane);
-      }
-    } else {
-      store_presplit(vpanel + I * kPTile, res, lane);
-      lds_signal_add(published + J, lane);
-      // W(I*32 + c, J*32 + i) = V(J, I)(i, c): four consecutive columns per store
-      if (I * kCT + col < nb) {
+      lds_signal_add(&sync.t_done, lane);
+      const uint64_t failed = __ballot(!ok);
+      const uint32_t columns = (uint32_t)failed | (uint32_t)(failed >> 32);
+      if (lane == 0 && columns != 0u) atomicCAS(&a.info[z * kInfoPerMat + a.info_slot], 0, o + J * kCT + __ffs((int)columns));
+      // tiles left of the diagonal of T and W
+      for (int K = 0; K < J; ++K)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          if (8 * q < nvr) {
-            const f32x4 v4 = {res[4 * q], res[4 * q + 1], res[4 * q + 2], res[4 * q + 3]};
-            *reinterpret_cast<f32x4*>(wg + (int64_t)(I * kCT + col) * r + J * kCT + 8 * q + 4 * half) = v4;
-          }
-        }
-      }
-    }
-  };
-
-  if (diag_wave) {
-    do_diag(0, load_tile(0, 0));
-  } else {
-    if (worker + 1 < nt) store_dtile(vpanel + (worker + 1) * kPTile, waiting, lane);
-    // tile (0, 1) as loaded is what the diagonal wave needs first
-#pragma unroll
-    for (int s = 0; s < kCSlots; ++s) {
-      const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
-      if (I == 0 && K == 1 && K < nt) store_dtile(stash, acc[s], lane);     // made visible by the barrier below
-    }
-    // tiles strictly below the diagonal of T and W are zero and written by nobody else: one tile
-    // per iteration (waves 4 to 7, 16 bytes per lane = one 32 x 32 tile), beside the first factorisation
-    if (wave >= 4 && wave < 8) {
-      const int t = tid - 256;
-      for (int I = 1; I < nt; ++I)
-        for (int K = 0; K < I; ++K) {
-          const int gi = I * kCT + (t >> 3), gj = K * kCT + (t & 7) * 4;
-          if (gi < nb && gj < nb) {
+          const int gi = J * kCT + 8 * q + (lane >> 3), gj = K * kCT + (lane & 7) * 4;
+          if (gi < nb) {
             const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
             *reinterpret_cast<f32x4*>(tg + (int64_t)gi * r + gj) = zero;
             *reinterpret_cast<f32x4*>(wg + (int64_t)gi * r + gj) = zero;
           }
         }
     }
-  }
-  lds_barrier();
-  bool expired = false;
-  // One loop per role (the branch is wave-uniform and both loops pass the same nt barriers): in
-  // the diagonal wave's loop the workers' accumulators are dead, so its serial chain keeps its
-  // operands in registers.
-  if (diag_wave) {
-    for (int J = 0; J < nt; ++J) {
-      // ---- the serial chain stays in this wave: T(J, J+1) = W_JJ^T S(J, J+1) from the stash,
-      // tile (J+1, J+1) -= T^T T (both fp32 products with the accumulator as k-side operand,
-      // see panel_tile), then its factorisation.  The workers form T(J, J+1) again for the panel.
-      if (J + 1 < nt) {
-        if (J > 0 && !lds_wait_ge(s_ready + J, 1)) expired = true;
-        const f32x16 sj = load_dtile(stash + (J & 1) * 4096, lane);
-        f32x16 dn = load_dtile(vpanel + (J + 1) * kPTile, lane);
-        const float* wt = Wt + (J & 1) * kCTileF;
-        f32x4 mrow[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) mrow[q] = *reinterpret_cast<const f32x4*>(wt + col * kCPitch + 8 * q + 4 * half);
-        f32x16 t1, t2;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { t1[v] = 0.f; t2[v] = 0.f; }
-#pragma unroll
-        for (int q = 0; q < 4; q += 2)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            t1 = mfma_f32_k2(mrow[q][e], sj[4 * q + e], t1);
-            t2 = mfma_f32_k2(mrow[q + 1][e], sj[4 * q + 4 + e], t2);
-          }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) t1[v] += t2[v];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) dn = mfma_f32_k2(-t1[v], t1[v], dn);
-        do_diag(J + 1, dn);
-      }
-      // the next step rewrites the panels and the other Wt buffer
-      lds_barrier();
-    }
   } else {
+    // ================================ the workers ================================
+    const int col = lane & 31, half = lane >> 5;
+    const uint32_t ownI = own_rows(worker), ownK = own_cols(worker);
+    // (a tile inside the block: one address per lane and a uniform offset per row; 64-bit addresses per
+    // element had kept the vector units busy for 20000 cycles)
+    auto load_tile = [&](int I, int K) {
+      f32x16 t;
+      if (K * kCT + kCT <= nb) {
+        const float* p = src + (int64_t)(I * kCT) * r + K * kCT;
+        const uint32_t at = (uint32_t)(4 * half * r + col);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[v] = (p + (8 * (v >> 2) + (v & 3)) * r)[at];
+        for (int sp = 1; sp < a.splits; ++sp) {
+          p += a.split_stride;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) t[v] += (p + (8 * (v >> 2) + (v & 3)) * r)[at];
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[v] = element(I * kCT + acc_row(v, lane), K * kCT + col);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) t[v] = -t[v];
+      return t;
+    };
+    // the diagonal tiles behind the first wait in LDS for their updates
+    const int waiting = kCWorkers - worker;
+    f32x16 acc[kCSlots], dt;
+    if (waiting < nt) dt = load_tile(waiting, waiting);
+#pragma unroll
+    for (int s = 0; s < kCSlots; ++s) {
+      const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
+      if (K < nt) acc[s] = load_tile(I, K);
+      else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[s][v] = 0.f;
+      }
+    }
+    if (waiting < nt) {
+      store_dtile(vpanel + waiting * kPTile, dt, lane);
+      lds_signal_add(&sync.diag[waiting], lane);
+    }
+#pragma unroll
+    for (int s = 0; s < kCSlots; ++s) {
+      const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
+      if (I == 0 && K == 1 && K < nt) {
+        store_dtile(stash, acc[s], lane);
+        lds_signal_add(&sync.s_ready[0], lane);
+      }
+    }
+    // tile += A^T B with both operands pre-split in LDS
+    auto lds_product = [&](f32x16& tile, const char* pa, const char* pb) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        u32x4 ap[3], bp[3];
+        load_presplit(pa, lane, kk, ap);
+        load_presplit(pb, lane, kk, bp);
+        tile = mma6(ap, bp, tile);
+      }
+    };
+    // the waiting diagonal tile (K, K), negated, += T(J, K)^T T(J, K); (J+1, J+1) is with the chain by now
+    auto update_diag = [&](int J, int K) {
+      wait(&sync.diag[K], 1 + J);
+      char* dk = vpanel + K * kPTile;
+      f32x16 d = load_dtile(dk, lane);
+      lds_product(d, panel + K * kPTile, panel + K * kPTile);
+      store_dtile(dk, d, lane);
+      lds_signal_add(&sync.diag[K], lane);
+    };
     for (int J = 0; J < nt; ++J) {
-      // ---- (b) row J of T and row J of V; the tile the diagonal wave waits for goes first
-      const float* wt = Wt + (J & 1) * kCTileF;
-      f32x4 mrow[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) mrow[q] = *reinterpret_cast<const f32x4*>(wt + col * kCPitch + 8 * q + 4 * half);
+      // ---- row J of T and row J of V: at most one tile per worker
+      const int nv = valid_rows(J);
+      int sel = -1, I = J, K = J;
 #pragma unroll
       for (int s = 0; s < kCSlots; ++s) {
-        const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
-        if (I == J && K == J + 1 && K < nt) panel_tile(acc[s], mrow, J, I, K, true);
+        const int Is = (int)(ownI >> (4 * s)) & 15, Ks = (int)(ownK >> (4 * s)) & 15;
+        if (Ks < nt && (Is == J || Ks == J)) { sel = s; I = Is; K = Ks; }
       }
+      f32x16 x;
+      if (sel >= 0) {
+        u32x4 b0[3], b1[3];
+        {
+          const f32x16 s = sel == 0 ? acc[0] : sel == 1 ? acc[1] : sel == 2 ? acc[2] : acc[3];
+          acc_operand(s, 0, b0);
+          acc_operand(s, 1, b1);
+        }
+        wait(&sync.v_ready, J + 1);
 #pragma unroll
-      for (int s = 0; s < kCSlots; ++s) {
-        const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
-        const bool row_tile = I == J && K > J + 1 && K < nt, col_tile = K == J && I < J;
-        if (row_tile || col_tile) panel_tile(acc[s], mrow, J, I, K, row_tile);
+        for (int v = 0; v < 16; ++v) x[v] = 0.f;
+        {
+          u32x4 a0[3], a1[3];
+          load_presplit(voperand, lane, 0, a0);
+          load_presplit(voperand, lane, 1, a1);
+          x = mma6(a0, b0, x);
+          x = mma6(a1, b1, x);
+        }
+        // the panel of the step before has been read
+        wait(&sync.updated, kCWorkers * J);
+        if (I == J) {
+          // -T(J, K): published first, the others wait for it
+          store_presplit(panel + K * kPTile, x, lane);
+          lds_signal_add(&sync.rows[J], lane);
+          // from now on the sum -S'(K, J)
+#pragma unroll
+          for (int s = 0; s < kCSlots; ++s)
+            if (sel == s) {
+#pragma unroll
+              for (int v = 0; v < 16; ++v) acc[s][v] = 0.f;
+            }
+          if (K == J + 2) update_diag(J, K);       // the chain needs this one next
+        } else {
+          store_presplit(vpanel + I * kPTile, x, lane);       // V(J, I)
+          lds_signal_add(&sync.cols[J], lane);
+        }
       }
-      if (worker == (2 * J) % kCWorkers) finish_diag(J);
-      // ---- (c) once all nt tiles of the step are published:
-      // S(I, K) -= T(J, I)^T T(J, K) for J < I < K;  S'(K, I) += T(J, K)^T V(J, I) for I <= J < K
-      if (!lds_wait_ge(published + J, nt)) expired = true;
+      // ---- updates of the step: -S(I, K) += T(J, I)^T T(J, K) for J < I < K, the one that the chain waits for
+      // first;  -S'(K, I) -= T(J, K)^T V(J, I) for I <= J < K
+      if (J + 1 < nt) {
+        wait(&sync.rows[J], nt - 1 - J);
 #pragma unroll
-      for (int s = 0; s < kCSlots; ++s) {
-        const int I = (int)(ownI >> (4 * s)) & 15, K = (int)(ownK >> (4 * s)) & 15;
-        if (K > J && K < nt) {
-          if (I > J) lds_product(acc[s], panel + I * kPTile, panel + K * kPTile, true);
-          else lds_product(acc[s], panel + K * kPTile, vpanel + I * kPTile, false);
-          // S(J+1, J+2) is final now: hand it to the diagonal wave
-          if (I == J + 1 && K == J + 2) {
+        for (int s = 0; s < kCSlots; ++s) {
+          const int Is = (int)(ownI >> (4 * s)) & 15, Ks = (int)(ownK >> (4 * s)) & 15;
+          if (Is == J + 1 && Ks == J + 2 && Ks < nt) {
+            lds_product(acc[s], panel + Is * kPTile, panel + Ks * kPTile);
             store_dtile(stash + ((J + 1) & 1) * 4096, acc[s], lane);
-            lds_signal_add(s_ready + J + 1, lane);
+            lds_signal_add(&sync.s_ready[J + 1], lane);
+          }
+        }
+#pragma unroll
+        for (int s = 0; s < kCSlots; ++s) {
+          const int Is = (int)(ownI >> (4 * s)) & 15, Ks = (int)(ownK >> (4 * s)) & 15;
+          if (Is > J && Ks < nt && !(Is == J + 1 && Ks == J + 2)) lds_product(acc[s], panel + Is * kPTile, panel + Ks * kPTile);
+        }
+        wait_idle(&sync.cols[J], J + 1);
+#pragma unroll
+        for (int s = 0; s < kCSlots; ++s) {
+          const int Is = (int)(ownI >> (4 * s)) & 15, Ks = (int)(ownK >> (4 * s)) & 15;
+          if (Is <= J && Ks > J && Ks < nt) lds_product(acc[s], panel + Ks * kPTile, vpanel + Is * kPTile);
+        }
+        if (sel >= 0 && I == J && K > J + 2) update_diag(J, K);
+        lds_signal_add(&sync.updated, lane);
+      }
+      // ---- the panel tile to memory
+      if (sel >= 0 && I == J) {
+        if (K * kCT + col < nb) {
+          float* tp = tg + (int64_t)(J * kCT + 4 * half) * r + K * kCT + col;
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tp[(int64_t)(8 * q + e) * r] = -x[4 * q + e];
+        }
+      } else if (sel >= 0) {
+        // W(I*32 + c, J*32 + i) = V(J, I)(i, c): four consecutive columns per store
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (8 * q < nv) {
+            const f32x4 v4 = {x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
+            *reinterpret_cast<f32x4*>(wg + (int64_t)(I * kCT + col) * r + J * kCT + 8 * q + 4 * half) = v4;
           }
         }
       }
-      lds_barrier();
     }
   }
   // a wait that ran out means a tile was used before its producer finished: the factors of this
