@@ -769,8 +769,10 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     const ClassDims& d = v.d;
     const int slot = h->batches[k].slot_base, sg = v.splits_gram[1];
     double* dacc = dacc_all + (size_t)slot * od::kDaccPerMat;
-    OD_TRY(od::launch_gather_q(d.nb, d.n, d.r, v.mats, v.rb, st));
-    OD_TRY(od::launch_gram_plain(d.nb, d.n, d.r, v.rb, v.part, sg, st));
+    od::WsArr q = v.rb;
+    if (d.nb == 1) q = od::WsArr{v.host_mats[0].Q, 0};      // one matrix: read where it lies
+    else OD_TRY(od::launch_gather_q(d.nb, d.n, d.r, v.mats, v.rb, st));
+    OD_TRY(od::launch_gram_plain(d.nb, d.n, d.r, q, v.part, sg, st));
     OD_TRY(od::launch_reduce(d.nb, v.part, sg, (int64_t)d.r * d.r, v.gram, st));
     OD_TRY(od::launch_power(d.nb, d.r, v.gram, v.tmp, v.w, v.part, dacc, st));
     OD_TRY(od::launch_diag_final(d.nb, d.r, reinterpret_cast<const double*>(ws + h->batches[k].off_dpart), h->batches[k].diag_blocks, dacc, v.t1[1], v.t2[1],

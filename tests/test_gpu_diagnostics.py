@@ -100,6 +100,15 @@ def test_diagnostics_power_iteration_tiles(count, m, n, r):
     run_case([(m, n)] * count, r, "f32", "colnorm", steps=1, seed=735)
 
 
+@pytest.mark.parametrize("count,m,n,r", [(1, 320, 272, 256), (3, 256, 264, 248), (2, 136, 96, 64), (1, 80, 72, 72), (1, 24, 16, 16)])
+def test_diagnostics_lanczos_sizes(count, m, n, r):
+    """nu = sigma_1(Q) by the Lanczos iteration of ranks up to 256: all of its 64-column groups, the last one short,
+    several matrices, and orders below its number of steps, where it runs into an invariant subspace.  Q of the
+    column-normalised variant has a spread of singular values, that of the other has them all equal to one."""
+    run_case([(m, n)] * count, r, "f32", "colnorm", steps=1, seed=737)
+    run_case([(m, n)] * count, r, "f32", "qr", steps=1, seed=738)
+
+
 def test_diagnostics_norms_at_the_edges_of_their_grid():
     """One workgroup per four rows up to 2048 rows, and two matrices of one shape whose partial sums lie
     one behind the other: 2, 510 and 512 workgroups, the last of these with rows of a second turn."""
