@@ -1559,11 +1559,18 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(SegsT segs, EfxCoef coef) {
 // that operand row rho of parity f is column 2 rho + f: lane c then owns the adjacent columns
 // 2c, 2c + 1 and every wave instruction of the epilogue moves whole 256-byte (M) or 128-byte
 // (G, X) row segments, as in k_efx_h.  Two workgroups per CU (72 KB of LDS each): one streams
-// M, G, X while the other multiplies.
+// M, G, X while the other multiplies.  WI = 4: 256 rows, one workgroup of eight waves per CU, five stages (four are within
+// 0.4 %).
+//
+// The epilogue is bound by latency as much as by bandwidth: four parts of 8 rows, each a round trip to memory.  Their
+// loads go out one part ahead, the first ones ahead of the last products: 8192 x 8192, r = 64, column
+// normalised: 424 -> 405 us a step, 4096 x 4096, r = 256: 335 -> 330, 126 matrices of r = 192: 1655 -> 1609.
 // ------------------------------------------------------------------------------------
+// LDS stages: what fits beside a second workgroup, or all of LDS
+constexpr int efx_stages(int wi) { return wi == 4 ? 5 : 3; }
 template <bool XBF, bool GBF, bool STREAM, int WI, class SegsT>
 __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT segs, EfxCoef coef) {
-  constexpr int TI = 64 * WI, TJ = 128, KT = 32, ROWB = KT * 2, ST = 3, NW = 2 * WI;
+  constexpr int TI = 64 * WI, TJ = 128, KT = 32, ROWB = KT * 2, ST = efx_stages(WI), NW = 2 * WI;
   constexpr int PLANE = 128 * ROWB, STAGE = 2 * PLANE + TI * ROWB;       // R | Q | P
   constexpr int CPW = (16 + TI / 16) / NW;                    // 1 KB chunks per wave and stage
   extern __shared__ __align__(16) char lds[];
@@ -1639,13 +1646,7 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
     if (s < nsteps) issue(s);
 
   const int prow = wi * 64 + c, jrow = wj * 64 + c;
-  for (int i = 0; i < nsteps; ++i) {
-    // stage i has landed when at most the loads of the one younger stage are outstanding
-    if (i + ST - 2 < nsteps) __builtin_amdgcn_s_waitcnt(vmcnt_only((ST - 2) * CPW));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if (i + ST - 1 < nsteps) issue(i + ST - 1);       // into the buffer every wave has finished reading
+  auto products = [&](int i) {
     const char* base = lds + (i % ST) * STAGE;
 #pragma unroll
     for (int kk = 0; kk < KT / 16; ++kk) {
@@ -1666,15 +1667,51 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
           acc_q[fm][f] = mfma_32x32x16<true>(fp[fm], fq[f], acc_q[fm][f]);
         }
     }
+  };
+  // the last steps, whose stages are waited for together, so that the epilogue's first loads can go out ahead of them
+  constexpr int LAST = ST - 2;
+  const int main_steps = nsteps > LAST ? nsteps - LAST : 0;
+  for (int i = 0; i < main_steps; ++i) {
+    // stage i has landed when at most the loads of the younger stages are outstanding
+    if (i + ST - 2 < nsteps) __builtin_amdgcn_s_waitcnt(vmcnt_only((ST - 2) * CPW));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (i + ST - 1 < nsteps) issue(i + ST - 1);       // into the buffer every wave has finished reading
+    products(i);
   }
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 
-  // ---- epilogue: 2 row blocks x 16 rows x 2 adjacent columns per lane, in four parts of 8
-  // rows; within a part every load is issued before the first store
-  const int j0 = tj * TJ + 64 * wj + 2 * c;
+  // ---- epilogue: 2 row blocks x 16 rows x 2 adjacent columns per lane, in four parts of 8 rows.  The loads of a part
+  // go out before the arithmetic and stores of the part before it, those of the first one before the last
+  // products.  Addresses are clamped into the matrix, stores are not made outside.
+  const int j0 = tj * TJ + 64 * wj + 2 * c, jc = min(j0, d.n - 2);
   float* __restrict__ Mz = mat.M;
   const char* __restrict__ Gz = reinterpret_cast<const char*>(mat.G);
   char* __restrict__ Xz = reinterpret_cast<char*>(mat.X);
   constexpr int GE = GBF ? 2 : 4, XE = XBF ? 2 : 4;
+  struct Part {
+    f32x2 m[8];
+    typename std::conditional<GBF, uint32_t, f32x2>::type g[8];
+    typename std::conditional<XBF, uint32_t, f32x2>::type x[8];
+  };
+  auto row_of = [&](int part, int u) { return ti * TI + 64 * wi + 32 * (part >> 1) + acc_row(8 * (part & 1) + u, lane); };
+  auto fetch = [&](int part, Part& v) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t i = min(row_of(part, u), d.m - 1);
+      v.m[u] = ld_stream<STREAM>(reinterpret_cast<const f32x2*>(Mz + i * d.ldm + jc));
+      v.g[u] = ld_stream<STREAM>(reinterpret_cast<const decltype(v.g[u] + 0)*>(Gz + (i * d.ldg + jc) * GE));
+      v.x[u] = ld_stream<STREAM>(reinterpret_cast<const decltype(v.x[u] + 0)*>(Xz + (i * d.ldx + jc) * XE));
+    }
+  };
+  Part even;
+  fetch(0, even);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int i = main_steps; i < nsteps; ++i) products(i);
+
   const float s_r = r_scale(d, scal, z);
   const float cr = b_coef / (s_r * kUnitScale), cq = lr / (kUnitScale * kUnitScale);
   if (matrix_flagged(info, z)) {        // unspecified factors (possibly NaN) never reach X and M
@@ -1686,45 +1723,53 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
         for (int v = 0; v < 16; ++v) { acc_r[fm][f][v] = 0.f; acc_q[fm][f][v] = 0.f; }
   }
   float bmax = 0.f;
-#pragma unroll
-  for (int part = 0; part < 4; ++part) {
-    const int fm = part >> 1, hv = part & 1;
-    f32x2 mv[8], gv[8], xv[8];
-    uint32_t gpk[8], xpk[8];
+  auto update = [&](int part, const Part& in) {
+    const int fm = part >> 1;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int v = 8 * hv + u;
-      const int i = ti * TI + 64 * wi + 32 * fm + acc_row(v, lane);
-      mv[u] = f32x2{0.f, 0.f};
-      gpk[u] = 0u; xpk[u] = 0u; gv[u] = f32x2{0.f, 0.f}; xv[u] = f32x2{0.f, 0.f};
-      if (i < d.m && j0 < d.n) {
-        mv[u] = ld_stream<STREAM>(reinterpret_cast<const f32x2*>(Mz + (int64_t)i * d.ldm + j0));
-        if constexpr (GBF) gpk[u] = ld_stream<STREAM>(reinterpret_cast<const uint32_t*>(Gz + ((int64_t)i * d.ldg + j0) * GE));
-        else gv[u] = ld_stream<STREAM>(reinterpret_cast<const f32x2*>(Gz + ((int64_t)i * d.ldg + j0) * GE));
-        if constexpr (XBF) xpk[u] = ld_stream<STREAM>(reinterpret_cast<const uint32_t*>(Xz + ((int64_t)i * d.ldx + j0) * XE));
-        else xv[u] = ld_stream<STREAM>(reinterpret_cast<const f32x2*>(Xz + ((int64_t)i * d.ldx + j0) * XE));
+      const int v = 8 * (part & 1) + u, i = row_of(part, u);
+      f32x2 g, x;
+      if constexpr (GBF) g = f32x2{bf16_lo(in.g[u]), bf16_hi(in.g[u])};
+      else g = in.g[u];
+      if constexpr (XBF) x = f32x2{bf16_lo(in.x[u]), bf16_hi(in.x[u])};
+      else x = in.x[u];
+      f32x2 mo, xo;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float bval = in.m[u][e] + g[e];
+        bmax = fmaxf(bmax, fabsf(bval));        // (a clamped address repeats an entry of the matrix)
+        mo[e] = a_coef * bval - cr * acc_r[fm][e][v];
+        xo[e] = x[e] - cq * acc_q[fm][e][v];
       }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int v = 8 * hv + u;
-      const int i = ti * TI + 64 * wi + 32 * fm + acc_row(v, lane);
       if (i < d.m && j0 < d.n) {
-        f32x2 g = gv[u], x = xv[u];
-        if constexpr (GBF) g = f32x2{bf16_lo(gpk[u]), bf16_hi(gpk[u])};
-        if constexpr (XBF) x = f32x2{bf16_lo(xpk[u]), bf16_hi(xpk[u])};
-        f32x2 mo, xo;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const float bval = mv[u][e] + g[e];
-          bmax = fmaxf(bmax, fabsf(bval));
-          mo[e] = a_coef * bval - cr * acc_r[fm][e][v];
-          xo[e] = x[e] - cq * acc_q[fm][e][v];
-        }
         st_stream<STREAM>(reinterpret_cast<f32x2*>(Mz + (int64_t)i * d.ldm + j0), mo);
         if constexpr (XBF) st_stream<STREAM>(reinterpret_cast<uint32_t*>(Xz + ((int64_t)i * d.ldx + j0) * XE), pack_bf16_rne(xo[0], xo[1]));
         else st_stream<STREAM>(reinterpret_cast<f32x2*>(Xz + ((int64_t)i * d.ldx + j0) * XE), xo);
       }
+    }
+  };
+  if constexpr (XBF && GBF) {
+    Part odd;
+    fetch(1, odd);
+    __builtin_amdgcn_sched_barrier(0);
+    update(0, even);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(2, even);
+    __builtin_amdgcn_sched_barrier(0);
+    update(1, odd);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(3, odd);
+    __builtin_amdgcn_sched_barrier(0);
+    update(2, even);
+    update(3, odd);
+  } else {                  // wider elements leave no registers for a second part
+    update(0, even);
+#pragma unroll
+    for (int part = 1; part < 4; ++part) {
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(part, even);
+      __builtin_amdgcn_sched_barrier(0);
+      update(part, even);
     }
   }
   report_b_range(d, scal, info, z, bmax);
@@ -2823,7 +2868,7 @@ static hipError_t efx_launch(K1 single, K2 multi, BatchList b, int n, int tile_i
 template <bool XBF, bool GBF>
 static hipError_t efx_v(int v, BatchList b, int n, EfxCoef c, hipStream_t st, int timed) {
   typedef NumBF<3> Num;
-  constexpr int lds_h = 2 * 3 * 128 * 80, lds_d = 3 * 3 * 128 * 64, lds_tall = 3 * (2 * 128 + 256) * 64;
+  constexpr int lds_h = 2 * 3 * 128 * 80, lds_d = 3 * 3 * 128 * 64, lds_tall = efx_stages(4) * (2 * 128 + 256) * 64;
   switch (v) {
     case EV_EXACT_SMALL: return efx_launch(k_efx<TileSmall, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSmall, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 64, 64, TileSmall::THREADS, TileSmall::lds_bytes<Num>(), c, st, timed);
     case EV_EXACT: return efx_launch(k_efx<TileSquare8, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSquare8, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 128, 128, TileSquare8::THREADS, TileSquare8::lds_bytes<Num>(), c, st, timed);

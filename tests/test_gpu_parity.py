@@ -676,6 +676,15 @@ def test_fast_precision_with_fp32_gradients(shapes, r):
     _free_running(w, precision="fast", tol=2e-2)
 
 
+@pytest.mark.parametrize("r", [64, 96, 128, 160])
+@pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
+def test_error_feedback_with_few_steps_per_tile(r, x_dtype):
+    """The error-feedback pass at two to five 32-deep steps, i.e. with fewer and with more of them than it keeps
+    in flight, and tiles that reach beyond the matrix on both sides (their addresses are clamped)."""
+    w = synth.Workload(f"steps-{r}-{x_dtype}", ((200, 328), (456, 168)), r=r, x_dtype=x_dtype, steps=2, spectrum="inverse_index", momentum_std=0.02)
+    _free_running(w, precision="fast", tol=2e-2)
+
+
 def test_more_equal_matrices_than_a_batch_may_hold():
     """33000 matrices of one shape: two launch batches, grids of 32768 in y and z; the first and last matrix
     of either against the oracle."""
