@@ -1777,10 +1777,10 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
 
 // ------------------------------------------------------------------------------------
 // Projection and back-projection with every global load direct to LDS (fast precision, bf16
-// gradients, r >= 128):
+// gradients, r > 64):
 //   TRANS = false   out[i][c] = sum_j (M + G)[i][j] Qt[c][j]     P_raw = B Q      (Alg. 1 line 2)
 //   TRANS = true    out[j][c] = sum_i (M + G)[i][j] Pt[c][i]     R = B^T P        (Alg. 1 line 3)
-// One workgroup (8 waves, 2 x 4) computes 128 output rows x NT columns over a K range; wave
+// One workgroup (8 waves, 2 x 4) computes 128 output rows x NT = 128, 256 or 512 columns over a K range; wave
 // tile 64 x NT / 4.  Per 32-deep step:
 //   * the factor operand (Qt / Pt: fp16 words, k contiguous) arrives by `dma16` in the swizzled
 //     layout of od_dma.h, two stages;
@@ -2173,10 +2173,17 @@ hipError_t launch_begin(BatchList b, int n, Prec prec, hipStream_t st) {
 }
 
 // ---- projection and back-projection -------------------------------------------------
-// shapes the direct-to-LDS contraction takes (fast precision only): bf16 gradients, a rank
-// that fills its 256- or 512-column tiles reasonably, at least one whole 32-deep step
-static bool stream_kernel_eligible(const ClassDims& d) { return d.g_bf16 && d.r >= 192 && d.m >= 32 && d.n >= 32; }
-static int stream_tile_cols(int r) { return r <= 256 ? 256 : 512; }
+// Shapes the direct-to-LDS contraction takes (fast precision only): bf16 gradients and at least one whole 32-deep
+// step.  Ranks above 64: up to 128 columns per tile the register kernels are 1 to 7 % slower per step (4096 x 4096,
+// r = 72 | 104 | 128: 239 | 253 | 246 us with them, 234 | 247 | 240; nine 1840 x 7384, r = 104: 1302 -> 1214;
+// 8192 x 8192, r = 96: 481 -> 457 with rotated k order), with half-filled 256-column tiles 2 to 9 % (six ragged matrices of
+// r = 136: 476 -> 437, 8192 x 8192, r = 160: 567 -> 520, 4096 x 4096, r = 184: 293 -> 286).  Below 2^18 elements and
+// r = 192 a step is a few short k loops, where the pipeline costs more than it hides: 392 x 264, r = 72 beside four smaller
+// matrices 210 against 214 us; thirty 512 x 512 of r = 128 228 -> 219.
+static bool stream_kernel_eligible(const ClassDims& d) {
+  return d.g_bf16 && d.r > 64 && d.m >= 32 && d.n >= 32 && (d.r >= 192 || (int64_t)d.m * d.n >= 1 << 18);
+}
+static int stream_tile_cols(int r) { return r <= 128 ? 128 : r <= 256 ? 256 : 512; }
 // Few wide tiles need many splits to fill the chip; 64-row tiles get there with half of them,
 // i.e. half the partial sums to write and to add up.  With enough tiles the wide one wins.
 // `peers`: matrices of this shape that would fill the launch the batch is part of.
@@ -2204,7 +2211,7 @@ void back_tiling(const ClassDims& d, Prec prec, int* rows, int* cols, int* slots
   }
 }
 
-enum ProjVariant : int { PV_STREAM256, PV_STREAM512, PV_NARROW, PV_SQUARE, PV_FLAT, PV_FLAT2, PV_WIDE, PV_HUGE, PV_EXACT_SMALL, PV_EXACT };
+enum ProjVariant : int { PV_STREAM128, PV_STREAM256, PV_STREAM512, PV_NARROW, PV_SQUARE, PV_FLAT, PV_FLAT2, PV_WIDE, PV_HUGE, PV_EXACT_SMALL, PV_EXACT };
 
 static StreamArgs stream_args(const BatchRef& r, bool back) {
   StreamArgs a = {};
@@ -2244,7 +2251,7 @@ static hipError_t stream_d_t(BatchList b, int n, hipStream_t st, int timed) {
     // rotated k order for the projection of a single matrix at 8192 columns (see the kernel): 120 ->
     // 102 us at r = 256.  With several matrices in flight the order does not matter, and the
     // 512-column tiles of the larger ranks are not waiting for memory (no gain measured there).
-    a.rotate = !TRANS && NT == 256 && rows_share_channels(*b[i]) ? 1 : 0;
+    a.rotate = !TRANS && NT <= 256 && rows_share_channels(*b[i]) ? 1 : 0;
     segs.add(a, ceil_div(TRANS ? a.d.n : a.d.m, 128) * ceil_div(a.d.r, NT), a.splits, a.d.nb);
   }
   return segs.launch(k_stream_d<TRANS, NT, SB, One<StreamArgs>>, k_stream_d<TRANS, NT, SB, Segs<StreamArgs>>, 512, lds, st, timed);
@@ -2267,7 +2274,7 @@ hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st) {
     if (prec == PREC_BF3)
       // small problems: 64-deep steps halve the number of round trips of a loop that is all latency
       return (int64_t)ceil_div(d.m, 128) * ceil_div(d.r, 128) * r.splits_proj * r.peers < 256 ? PV_EXACT_SMALL : PV_EXACT;
-    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
+    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 128 ? PV_STREAM128 : stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
     if (d.r <= 64) return PV_NARROW;
     if (d.r <= 128) return PV_SQUARE;
     // long enough K loops per column tile pay for a second register stage
@@ -2275,6 +2282,7 @@ hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st) {
     return PV_WIDE;
   };
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int timed) -> hipError_t {
+    if (v == PV_STREAM128) return stream_d_t<false, 128>(g, k, st, timed);
     if (v == PV_STREAM256) return stream_d_t<false, 256>(g, k, st, timed);
     if (v == PV_STREAM512) return stream_d_t<false, 512>(g, k, st, timed);
     return g[0]->d.g_bf16 ? proj_v<SrcBF16>(v, g, k, st, timed) : proj_v<SrcF32>(v, g, k, st, timed);
@@ -2306,7 +2314,7 @@ hipError_t launch_back(BatchList b, int n, Prec prec, hipStream_t st) {
     const ClassDims& d = r.d;
     if (prec == PREC_BF3)
       return (int64_t)ceil_div(d.n, 128) * ceil_div(d.r, 128) * r.splits_back * r.peers < 256 ? PV_EXACT_SMALL : PV_EXACT;
-    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
+    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 128 ? PV_STREAM128 : stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
     if (d.r <= 64) return PV_NARROW;
     if (d.r <= 128) return PV_SQUARE;
     // several column tiles per row panel: 256 x 256 tiles halve the operand traffic per product
@@ -2314,6 +2322,7 @@ hipError_t launch_back(BatchList b, int n, Prec prec, hipStream_t st) {
     return d.r > 256 ? PV_HUGE : PV_WIDE;
   };
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int timed) -> hipError_t {
+    if (v == PV_STREAM128) return stream_d_t<true, 128>(g, k, st, timed);
     if (v == PV_STREAM256) return stream_d_t<true, 256>(g, k, st, timed);
     if (v == PV_STREAM512) return stream_d_t<true, 512>(g, k, st, timed);
     return g[0]->d.g_bf16 ? back_v<SrcBF16>(v, g, k, st, timed) : back_v<SrcF32>(v, g, k, st, timed);

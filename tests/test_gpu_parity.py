@@ -685,6 +685,14 @@ def test_error_feedback_with_few_steps_per_tile(r, x_dtype):
     _free_running(w, precision="fast", tol=2e-2)
 
 
+@pytest.mark.parametrize("shapes,r", [(((520, 776),), 72), (((776, 520),), 128), (((1032, 264), (264, 1032)), 104), (((512, 512),), 136)])
+def test_direct_contractions_of_middle_ranks(shapes, r):
+    """The direct-to-LDS contractions at ranks that fill their column tile partly or wholly, with output rows and
+    contracted dimensions that end inside a tile, one shape and two of them in a launch."""
+    w = synth.Workload(f"direct-{r}", shapes, r=r, x_dtype="bf16", steps=2)
+    _free_running(w)
+
+
 def test_more_equal_matrices_than_a_batch_may_hold():
     """33000 matrices of one shape: two launch batches, grids of 32768 in y and z; the first and last matrix
     of either against the oracle."""
