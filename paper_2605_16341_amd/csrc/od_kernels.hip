@@ -1404,7 +1404,7 @@ OD_DEV void st_stream(V* p, V v) {
   else *p = v;
 }
 
-template <bool XBF, bool GBF, bool STREAM, class SegsT>
+template <bool XBF, bool GBF, class SegsT>
 __global__ __launch_bounds__(512, 4) void k_efx_h(SegsT segs, EfxCoef coef) {
   constexpr int TJ = 128, TI = 128, KT = 32, PITCH = KT * 2 + 16, PLANE = 128 * PITCH, BUF = 3 * PLANE;
   extern __shared__ __align__(16) char lds[];
@@ -1422,20 +1422,6 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(SegsT segs, EfxCoef coef) {
     const int tiles_jj = (d.n + TJ - 1) / TJ;
     tj = blk.x % tiles_jj;
     ti = blk.x / tiles_jj;
-  }
-  if (d.r > 256) {
-    // Long K loops re-read the panels of P, R and Q often enough to matter: bands of eight tile
-    // columns, row-major inside a band, one contiguous range of that order per XCD, so that the
-    // 64 workgroups an XCD holds at a time form an 8 x 8 block of tiles and every panel fetched
-    // into its L2 serves eight of them (measured -4 to -5 %; at r = 256 the plain order is 2 us
-    // faster).
-    const int tiles_j = (d.n + TJ - 1) / TJ;
-    const int logical = xcd_contiguous(blk.x, blk.grid.x);
-    const int band = logical / (tiles_i * 8);
-    const int in_band = logical - band * tiles_i * 8;
-    const int bw = min(8, tiles_j - band * 8);
-    ti = in_band / bw;
-    tj = band * 8 + in_band % bw;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wi = wave & 3, wj = wave >> 2, c = lane & 31;
@@ -1517,11 +1503,11 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(SegsT segs, EfxCoef coef) {
       mv[u] = f32x2{0.f, 0.f};
       gp[u] = 0u; xp[u] = 0u; gv[u] = f32x2{0.f, 0.f}; xv[u] = f32x2{0.f, 0.f};
       if (i < d.m && j0 < d.n) {
-        mv[u] = ld_stream<STREAM>(reinterpret_cast<const f32x2*>(Mz + (int64_t)i * d.ldm + j0));
-        if constexpr (GBF) gp[u] = ld_stream<STREAM>(reinterpret_cast<const uint32_t*>(Gz + ((int64_t)i * d.ldg + j0) * GE));
-        else gv[u] = ld_stream<STREAM>(reinterpret_cast<const f32x2*>(Gz + ((int64_t)i * d.ldg + j0) * GE));
-        if constexpr (XBF) xp[u] = ld_stream<STREAM>(reinterpret_cast<const uint32_t*>(Xz + ((int64_t)i * d.ldx + j0) * XE));
-        else xv[u] = ld_stream<STREAM>(reinterpret_cast<const f32x2*>(Xz + ((int64_t)i * d.ldx + j0) * XE));
+        mv[u] = *reinterpret_cast<const f32x2*>(Mz + (int64_t)i * d.ldm + j0);
+        if constexpr (GBF) gp[u] = *reinterpret_cast<const uint32_t*>(Gz + ((int64_t)i * d.ldg + j0) * GE);
+        else gv[u] = *reinterpret_cast<const f32x2*>(Gz + ((int64_t)i * d.ldg + j0) * GE);
+        if constexpr (XBF) xp[u] = *reinterpret_cast<const uint32_t*>(Xz + ((int64_t)i * d.ldx + j0) * XE);
+        else xv[u] = *reinterpret_cast<const f32x2*>(Xz + ((int64_t)i * d.ldx + j0) * XE);
       }
     }
 #pragma unroll
@@ -1540,9 +1526,9 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(SegsT segs, EfxCoef coef) {
           mo[e] = a_coef * bval - cr * acc_r[e][v];
           xo[e] = x[e] - cq * acc_q[e][v];
         }
-        st_stream<STREAM>(reinterpret_cast<f32x2*>(Mz + (int64_t)i * d.ldm + j0), mo);
-        if constexpr (XBF) st_stream<STREAM>(reinterpret_cast<uint32_t*>(Xz + ((int64_t)i * d.ldx + j0) * XE), pack_bf16_rne(xo[0], xo[1]));
-        else st_stream<STREAM>(reinterpret_cast<f32x2*>(Xz + ((int64_t)i * d.ldx + j0) * XE), xo);
+        *reinterpret_cast<f32x2*>(Mz + (int64_t)i * d.ldm + j0) = mo;
+        if constexpr (XBF) *reinterpret_cast<uint32_t*>(Xz + ((int64_t)i * d.ldx + j0) * XE) = pack_bf16_rne(xo[0], xo[1]);
+        else *reinterpret_cast<f32x2*>(Xz + ((int64_t)i * d.ldx + j0) * XE) = xo;
       }
     }
   }
@@ -1550,7 +1536,7 @@ __global__ __launch_bounds__(512, 4) void k_efx_h(SegsT segs, EfxCoef coef) {
 }
 
 // ------------------------------------------------------------------------------------
-// The same pass with direct-to-LDS operand loads (r a multiple of 32).  Tile: 128 rows i x
+// The same pass with direct-to-LDS operand loads.  Tile: 128 rows i x
 // 128 columns j, 4 waves; wave (wi, wj) owns rows 64 wi .. +63 and columns 64 wj .. +63 of BOTH
 // products: eight 32 x 32 accumulators (two row blocks x even / odd columns x {P R^T, P Q^T}),
 // six LDS operand reads for eight matrix-core products per 16-deep step (0.75 per product,
@@ -1590,7 +1576,11 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
     ti = blk.x / tiles_jj;
   }
   if (d.r > 256) {
-    // bands of eight tile columns, one contiguous range of that order per XCD (see k_efx_h)
+    // Long K loops re-read the panels of P, R and Q often enough to matter: bands of eight tile
+    // columns, row-major inside a band, one contiguous range of that order per XCD, so that the
+    // workgroups an XCD holds at a time form a block of tiles and every panel fetched
+    // into its L2 serves eight of them (measured -4 to -5 %; at r = 256 the plain order is 2 us
+    // faster).
     const int tiles_j = (d.n + TJ - 1) / TJ;
     const int logical = xcd_contiguous(blk.x, blk.grid.x);
     const int band = logical / (tiles_i * 8);
@@ -1606,6 +1596,7 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
   // ---- this lane's share of every stage: chunk = 16 LDS rows of one of the three tiles
   const uint16_t* gp[CPW];
   uint32_t loff[CPW];
+  int kgq[CPW];
   const uint32_t lds0 = lds_offset_of(lds);
 #pragma unroll
   for (int q = 0; q < CPW; ++q) {
@@ -1613,6 +1604,7 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
     const int which = chunk < 16 ? chunk >> 3 : 2, rel = chunk < 16 ? chunk & 7 : chunk - 16;
     const int row = rel * 16 + (lane >> 2), slot = lane & 3;
     const int kg = slot ^ swz32(row);
+    kgq[q] = kg;
     int grow;
     const uint16_t* base;
     if (which == 2) {
@@ -1626,11 +1618,18 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
     gp[q] = base + (int64_t)grow * d.r + kg * 8;
     loff[q] = lds0 + which * PLANE + rel * 1024;
   }
-  const int nsteps = d.r / KT;
+  // The last step of a rank that is no multiple of 32 holds fewer k: its groups of eight beyond the rank read the
+  // row's last group once more, and those of P are zeroed in LDS before the products.
+  const int nsteps = (d.r + KT - 1) / KT, tail = d.r % KT;
   auto issue = [&](int step) {
     const uint32_t boff = (uint32_t)(step % ST) * STAGE;
+    if (tail != 0 && step == nsteps - 1) {
 #pragma unroll
-    for (int q = 0; q < CPW; ++q) dma16(gp[q] + step * KT, loff[q] + boff);
+      for (int q = 0; q < CPW; ++q) dma16(gp[q] + step * KT - max(kgq[q] * 8 + 8 - tail, 0), loff[q] + boff);
+    } else {
+#pragma unroll
+      for (int q = 0; q < CPW; ++q) dma16(gp[q] + step * KT, loff[q] + boff);
+    }
   };
 
   f32x16 acc_r[2][2], acc_q[2][2];
@@ -1683,6 +1682,12 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
   __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+  if (tail != 0) {
+    char* p = lds + ((nsteps - 1) % ST) * STAGE + 2 * PLANE;
+    for (int row = tid; row < TI; row += 128 * WI)
+      for (int kg = tail / 8; kg < 4; ++kg) *reinterpret_cast<u32x4*>(p + row * ROWB + ((kg ^ swz32(row)) * 16)) = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+  }
 
   // ---- epilogue: 2 row blocks x 16 rows x 2 adjacent columns per lane, in four parts of 8 rows.  The loads of a part
   // go out before the arithmetic and stores of the part before it, those of the first one before the last
@@ -2866,7 +2871,7 @@ static EfxArgs efx_args(const BatchRef& r) {
   a.d.col_fast = r.d.r <= 256 ? 1 : 0;
   return a;
 }
-enum EfxVariant : int { EV_EXACT_SMALL, EV_EXACT, EV_H, EV_H_STREAM, EV_D, EV_D_STREAM, EV_TALL, EV_TALL_STREAM };
+enum EfxVariant : int { EV_EXACT_SMALL, EV_EXACT, EV_H, EV_D, EV_D_STREAM, EV_TALL, EV_TALL_STREAM };
 
 template <class K1, class K2>
 static hipError_t efx_launch(K1 single, K2 multi, BatchList b, int n, int tile_i, int tile_j, int threads, int lds, EfxCoef coef, hipStream_t st, int timed) {
@@ -2881,8 +2886,7 @@ static hipError_t efx_v(int v, BatchList b, int n, EfxCoef c, hipStream_t st, in
   switch (v) {
     case EV_EXACT_SMALL: return efx_launch(k_efx<TileSmall, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSmall, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 64, 64, TileSmall::THREADS, TileSmall::lds_bytes<Num>(), c, st, timed);
     case EV_EXACT: return efx_launch(k_efx<TileSquare8, Num, XBF, GBF, One<EfxArgs>>, k_efx<TileSquare8, Num, XBF, GBF, Segs<EfxArgs>>, b, n, 128, 128, TileSquare8::THREADS, TileSquare8::lds_bytes<Num>(), c, st, timed);
-    case EV_H: return efx_launch(k_efx_h<XBF, GBF, false, One<EfxArgs>>, k_efx_h<XBF, GBF, false, Segs<EfxArgs>>, b, n, 128, 128, 512, lds_h, c, st, timed);
-    case EV_H_STREAM: return efx_launch(k_efx_h<XBF, GBF, true, One<EfxArgs>>, k_efx_h<XBF, GBF, true, Segs<EfxArgs>>, b, n, 128, 128, 512, lds_h, c, st, timed);
+    case EV_H: return efx_launch(k_efx_h<XBF, GBF, One<EfxArgs>>, k_efx_h<XBF, GBF, Segs<EfxArgs>>, b, n, 128, 128, 512, lds_h, c, st, timed);
     case EV_D: return efx_launch(k_efx_d<XBF, GBF, false, 2, One<EfxArgs>>, k_efx_d<XBF, GBF, false, 2, Segs<EfxArgs>>, b, n, 128, 128, 256, lds_d, c, st, timed);
     case EV_D_STREAM: return efx_launch(k_efx_d<XBF, GBF, true, 2, One<EfxArgs>>, k_efx_d<XBF, GBF, true, 2, Segs<EfxArgs>>, b, n, 128, 128, 256, lds_d, c, st, timed);
     case EV_TALL: return efx_launch(k_efx_d<XBF, GBF, false, 4, One<EfxArgs>>, k_efx_d<XBF, GBF, false, 4, Segs<EfxArgs>>, b, n, 256, 128, 512, lds_tall, c, st, timed);
@@ -2898,8 +2902,12 @@ hipError_t launch_efx(BatchList b, int n, Prec prec, float a_coef, float b_coef,
     // nontemporal stores also for sets far beyond the Infinity Cache at any rank: they leave no dirty
     // lines behind for the next kernel to wait on (measured on 8192 x 8192: the step is 2-7 % faster)
     const int stream = d.r > 256 || (int64_t)d.m * d.n * r.peers >= ((int64_t)48 << 20) ? 1 : 0;
-    // ranks that are whole 32-deep steps take the direct-to-LDS kernel
-    if (d.r % 32 != 0 || d.r < 64) return EV_H + stream;
+    // Small sets: the kernel with eight waves per tile, which has the shorter start, unless the rank is whole 32-deep
+    // steps from 64 on (392 x 264, r = 40: 136 against 139 us a step, four 512 x 512 of r = 56 135 | 136; five matrices of
+    // ranks 24 to 72 211 in one launch, 220 with r = 72 in one of its own); above, the direct-to-LDS kernel (twenty
+    // 1024 x 1024 of r = 40 233 | 230, 4096 x 4096, r = 40 213 | 206, r = 104 246 | 238, 8192 x 8192, r = 16 349 | 343,
+    // r = 1000 2089 | 2047)
+    if ((d.r < 64 || d.r % 32 != 0) && (int64_t)d.m * d.n * r.peers < (int64_t)4 << 20) return EV_H;
     // r > 256: 256-row tiles (one 8-wave workgroup per CU) while they still fill the chip twice:
     // a third less operand traffic into LDS per product than 128-row tiles
     const int64_t tall = (int64_t)ceil_div(d.m, 256) * ceil_div(d.n, 128) * r.peers;

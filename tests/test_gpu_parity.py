@@ -685,6 +685,15 @@ def test_error_feedback_with_few_steps_per_tile(r, x_dtype):
     _free_running(w, precision="fast", tol=2e-2)
 
 
+@pytest.mark.parametrize("m,n,r", [(264, 392, 112), (2056, 2064, 8), (2056, 2064, 40), (2064, 2056, 48), (2056, 2088, 88)])
+@pytest.mark.parametrize("x_dtype", ["bf16", "f32"])
+def test_error_feedback_rank_tails(m, n, r, x_dtype):
+    """Ranks that are no multiple of the 32 columns of a step: one, two or three groups of eight in the last
+    step of the direct-to-LDS kernel, also where that is the only step; a small matrix takes the other kernel."""
+    w = synth.Workload(f"tail-{r}-{x_dtype}", ((m, n),), r=r, x_dtype=x_dtype, steps=1, spectrum="inverse_index", momentum_std=0.02)
+    _free_running(w, precision="fast", tol=2e-2)
+
+
 @pytest.mark.parametrize("shapes,r", [(((520, 776),), 72), (((776, 520),), 128), (((1032, 264), (264, 1032)), 104), (((512, 512),), 136)])
 def test_direct_contractions_of_middle_ranks(shapes, r):
     """The direct-to-LDS contractions at ranks that fill their column tile partly or wholly, with output rows and
