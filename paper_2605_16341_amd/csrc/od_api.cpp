@@ -467,9 +467,16 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       for (int side = 0; side < 2; ++side) {
         const int64_t rows = side == 0 ? m : n;
         // small ranks: one 32 x 32 tile, one thread per row: 256-row slabs (small_gram, small_first_pass);
-        // else two workgroups of the Gram kernel fit one CU
-        b.splits_gram[side] = limited([&](int64_t peers) {
-          return b.small ? pick_splits(1, peers, rows, 256) : pick_splits_by_rounds(gt, peers, rows, 256, 512);
+        // else two workgroups of the Gram kernel fit one CU.  Where that leaves few tiles, the kernel takes 64 x 64
+        // ones (gram_pass), and their short loops are split further, down to 128 rows, while the chip has idle CUs
+        // (4096 x 4096, r = 256, 14 | 25 splits: 312 | 307 us a step, 2048 x 5632 291 | 287, five small matrices of ranks
+        // 24 to 72 210 | 200; never fewer: six ragged ones of r = 136 took 444 instead of 436)
+        b.splits_gram[side] = limited([&](int64_t peers) -> int {
+          if (b.small) return pick_splits(1, peers, rows, 256);
+          const int s = pick_splits_by_rounds(gt, peers, rows, 256, 512);
+          const int64_t g64 = (r + 63) / 64;
+          const int fine = std::max(s, pick_splits_by_rounds(g64 * (g64 + 1) / 2, peers, rows, 128, 256));
+          return gt1 * gt1 * fine * peers < od::kSmallGramTiles ? fine : s;
         });
       }
       b.slabs = (int)((n + 31) / 32);           // row slabs of the column-norm kernels: many, so the grid fills the chip

@@ -20,6 +20,8 @@ struct MatEntry {
 
 // largest rank that one workgroup factors (launch_cholinv)
 constexpr int kLeafRank = 256;
+// Gram matrices: 64 x 64 tiles below this many 128 x 128 ones (of the full square, all splits and matrices together)
+constexpr int kSmallGramTiles = 512;
 
 enum Prec : int { PREC_F16 = 0, PREC_BF3 = 1 };   // operand format of the big contractions
 

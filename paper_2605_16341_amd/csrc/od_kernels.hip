@@ -2477,7 +2477,7 @@ static hipError_t gram_pass(BatchList b, int n, int side, bool first, Prec prec,
     if (r.small) return -1;
     // few large tiles leave most of the chip idle: use small ones until the grid fills it
     const int64_t t = ceil_div(r.d.r, 128);
-    return t * t * r.splits_gram[side] * r.peers < 512 ? 0 : 1;
+    return t * t * r.splits_gram[side] * r.peers < kSmallGramTiles ? 0 : 1;
   };
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
     // fast precision has the sampled scale of B at hand: two-term fp16 operands (half the
