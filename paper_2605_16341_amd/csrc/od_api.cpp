@@ -440,14 +440,19 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       const RankClass& rcl = h->classes[b.rank_class];
       const int64_t m = d.m, n = d.n, r = d.r;
       const od::Prec prec = resolve_prec(*cfg);
-      auto splits_for = [&](bool back, int64_t peers) {
+      auto splits_of = [&](bool back, int64_t peers, bool staged) {
         int rows, cols, slots;
-        if (back) od::back_tiling(d, prec, &rows, &cols, &slots);
-        else od::proj_tiling(d, prec, peers, &rows, &cols, &slots);
+        if (back) od::back_tiling(d, prec, staged, &rows, &cols, &slots);
+        else od::proj_tiling(d, prec, peers, staged, &rows, &cols, &slots);
         const int64_t out = back ? n : m, k = back ? m : n;
         const int64_t tiles = ((out + rows - 1) / rows) * ((r + cols - 1) / cols);
         // one 8-wave workgroup per CU is scheduled in whole rounds; two smaller ones mix
         return slots == 256 ? pick_splits_by_rounds(tiles, peers, k, 256, slots) : pick_splits(tiles, peers, k, 128);
+      };
+      // the lean plan takes no more splits than the register-staged kernels would
+      auto splits_for = [&](bool back, int64_t peers) {
+        const int s = splits_of(back, peers, false);
+        return lean ? std::min(s, splits_of(back, peers, true)) : s;
       };
       // `lean`: no more splits than in launches of the batch's own, at most kBatchMatrices matrices each
       auto limited = [&](auto&& pick) {
@@ -474,6 +479,7 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
         b.splits_gram[side] = limited([&](int64_t peers) -> int {
           if (b.small) return pick_splits(1, peers, rows, 256);
           const int s = pick_splits_by_rounds(gt, peers, rows, 256, 512);
+          if (lean) return s;
           const int64_t g64 = (r + 63) / 64;
           const int fine = std::max(s, pick_splits_by_rounds(g64 * (g64 + 1) / 2, peers, rows, 128, 256));
           return gt1 * gt1 * fine * peers < od::kSmallGramTiles ? fine : s;

@@ -106,9 +106,10 @@ typedef const BatchRef* const* BatchList;     // a list of batches; always with 
 hipError_t launch_begin(BatchList b, int n, Prec prec, hipStream_t st);
 
 // the tile rows and columns of the projection / back-projection for this shape, and the workgroups
-// of its kernel that fit the chip at a time: what the number of splits is chosen from
-void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, int* rows, int* cols, int* slots);
-void back_tiling(const ClassDims& d, Prec prec, int* rows, int* cols, int* slots);
+// of its kernel that fit the chip at a time: what the number of splits is chosen from.  `staged`: those of the
+// register-staged kernels for ranks below 192, whose smaller workgroups take fewer splits
+void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, bool staged, int* rows, int* cols, int* slots);
+void back_tiling(const ClassDims& d, Prec prec, bool staged, int* rows, int* cols, int* slots);
 // P_raw = (M + G) Q, split over n: partial sums in `part`, or with one split straight in `pa`
 hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st);
 // pa = sum of the projection's partials (batches with one split have nothing to add)

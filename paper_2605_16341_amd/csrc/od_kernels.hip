@@ -2194,23 +2194,23 @@ static int stream_tile_cols(int r) { return r <= 128 ? 128 : r <= 256 ? 256 : 51
 // `peers`: matrices of this shape that would fill the launch the batch is part of.
 static bool proj_uses_flat_tiles(int m, int r, int64_t peers) { return r > 128 && (int64_t)ceil_div(m, 128) * ceil_div(r, 256) * peers < 256; }
 
-void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, int* rows, int* cols, int* slots) {
+void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, bool staged, int* rows, int* cols, int* slots) {
   *rows = 128;
   *cols = d.r <= 64 ? 64 : (d.r <= 128 ? 128 : 256);
   *slots = 512;                                // two workgroups per CU
   if (prec != PREC_F16) return;
-  if (stream_kernel_eligible(d)) {             // one 8-wave workgroup per CU
+  if (stream_kernel_eligible(d) && !(staged && d.r < 192)) {       // one 8-wave workgroup per CU
     *cols = stream_tile_cols(d.r);
     *slots = 256;
   } else if (proj_uses_flat_tiles(d.m, d.r, peers)) {
     *rows = 64;
   }
 }
-void back_tiling(const ClassDims& d, Prec prec, int* rows, int* cols, int* slots) {
+void back_tiling(const ClassDims& d, Prec prec, bool staged, int* rows, int* cols, int* slots) {
   *rows = 128;
   *cols = d.r <= 64 ? 64 : (d.r <= 128 ? 128 : 256);
   *slots = 512;
-  if (prec == PREC_F16 && stream_kernel_eligible(d)) {
+  if (prec == PREC_F16 && stream_kernel_eligible(d) && !(staged && d.r < 192)) {
     *cols = stream_tile_cols(d.r);
     *slots = 256;
   }
