@@ -211,13 +211,12 @@ OD_DEV f32x16 mfma_f32_k2(float a, float b, f32x16 c) {
 
 // `nv`: valid rows (a multiple of 8); the tile is the identity beyond them.
 //
-// One serial chain, eight groups of four pivots long, that every later tile waits for: per group the two
-// products that update `d`, ten readlanes, four reciprocal square roots with two operations each
-// between them.  A wave issues one instruction in 4 cycles at best, so what counts besides is their number:
-// rows come by forward substitution (no inverse of the 4 x 4 block), are computed in the lane half that
-// holds them only (one lane swap makes the operand of two rows), columns left of the diagonal are not
-// masked before the end (they only ever meet each other), and bad pivots are found at the end.  Alone on its
-// SIMD a tile took 8900 cycles and takes 7400, hand-over included.
+// For ranks up to 32, where one wave does the whole factorisation.  One serial chain, eight groups of four pivots
+// long: per group the two products that update `d`, ten readlanes, four reciprocal square roots with two operations
+// each between them.  What counts besides is the number of instructions: rows come by forward substitution (no
+// inverse of the 4 x 4 block), are computed in the lane half that holds them only (one lane swap makes the operand of two
+// rows), columns left of the diagonal are not masked before the end (they only ever meet each other), and bad
+// pivots are found at the end.
 OD_DEV int diag_tile_factor(f32x16& d_io, f32x16& zt_out, int lane, int nv) {
   const int c = lane & 31, h = lane >> 5;
   // `d` and `zt` are only ever changed by the matrix-core updates; the finished rows are
@@ -500,25 +499,39 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
   auto wait_idle = [&](const int* word, int target) { expired = lds_wait<true>(word, target, expired); };
   auto valid_rows = [&](int J) { return (nb - J * kCT) < kCT ? (nb - J * kCT) : kCT; };
   auto step_groups = [&](int J) { return group_data + (J & 1) * 8 * kGroupFloats; };
-  // Element (row, col) of the block, the identity outside.  Lanes read along a row, so that every line of the source is
-  // fetched once.  The address is clamped into the block: the loads of a tile are unconditional and in flight together.
-  auto element = [&](int row, int col) {
-    const float* p = src + (int64_t)(row < nb ? row : nb - 1) * r + (col < nb ? col : nb - 1);
-    float v = *p;
-    for (int sp = 1; sp < a.splits; ++sp) v += p[(int64_t)sp * a.split_stride];
-    return row < nb && col < nb ? v : row == col ? 1.f : 0.f;
-  };
+  // Offset of element (row, col), clamped into the block, so that the loads of a tile are unconditional; `inside` replaces
+  // what lies beyond by the identity.  Lanes read along a row: every line of the source is fetched once.
+  auto offset = [&](int row, int col) { return (uint32_t)((row < nb ? row : nb - 1) * r + (col < nb ? col : nb - 1)); };
+  auto inside = [&](float v, int row, int col) { return row < nb && col < nb ? v : row == col ? 1.f : 0.f; };
 
   if (worker == 15 && wave < kCholInverseWave) {
     // ================================ the chain ================================
     const int self = wave >> 2, j = lane & 15, lr = lane >> 4;
     f32x4 d00, d01, d11;
     if (self == 0) {
+      uint32_t at[3][4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        d00[v] = element(4 * lr + v, j);
-        d01[v] = element(4 * lr + v, 16 + j);
-        d11[v] = element(16 + 4 * lr + v, 16 + j);
+        at[0][v] = offset(4 * lr + v, j);
+        at[1][v] = offset(4 * lr + v, 16 + j);
+        at[2][v] = offset(16 + 4 * lr + v, 16 + j);
+      }
+      d00 = d01 = d11 = f32x4{0.f, 0.f, 0.f, 0.f};
+      const float* p = src;
+      for (int sp = 0; sp < a.splits; ++sp) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          d00[v] += p[at[0][v]];
+          d01[v] += p[at[1][v]];
+          d11[v] += p[at[2][v]];
+        }
+        p += a.split_stride;
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        d00[v] = inside(d00[v], 4 * lr + v, j);
+        d01[v] = inside(d01[v], 4 * lr + v, 16 + j);
+        d11[v] = inside(d11[v], 16 + 4 * lr + v, 16 + j);
       }
     }
     // 16 x 16 block (rh, ch) of a tile image
@@ -677,23 +690,25 @@ OD_DEV void chol256_block(const CholArgs& a, int z, char* lds_raw) {
     // ================================ the workers ================================
     const int col = lane & 31, half = lane >> 5;
     const uint32_t ownI = own_rows(worker), ownK = own_cols(worker);
-    // (a tile inside the block: one address per lane and a uniform offset per row; 64-bit addresses per
-    // element had kept the vector units busy for 20000 cycles)
+    // One address per lane and a uniform offset per row (64-bit addresses per element had kept the vector units busy for
+    // 20000 cycles).  The order is a multiple of 8, so the rows of a register group are inside or outside together.
     auto load_tile = [&](int I, int K) {
       f32x16 t;
-      if (K * kCT + kCT <= nb) {
-        const float* p = src + (int64_t)(I * kCT) * r + K * kCT;
-        const uint32_t at = (uint32_t)(4 * half * r + col);
+      const float* p = src;
+      const uint32_t at = (uint32_t)(4 * half * r + (K * kCT + col < nb ? K * kCT + col : nb - 1));
 #pragma unroll
-        for (int v = 0; v < 16; ++v) t[v] = (p + (8 * (v >> 2) + (v & 3)) * r)[at];
-        for (int sp = 1; sp < a.splits; ++sp) {
-          p += a.split_stride;
+      for (int v = 0; v < 16; ++v) t[v] = 0.f;
+      for (int sp = 0; sp < a.splits; ++sp) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) t[v] += (p + (8 * (v >> 2) + (v & 3)) * r)[at];
+        for (int v = 0; v < 16; ++v) {
+          const int row8 = I * kCT + 8 * (v >> 2);
+          t[v] += (p + ((row8 < nb ? row8 : nb - 8) + (v & 3)) * r)[at];
         }
-      } else {
+        p += a.split_stride;
+      }
+      if (K * kCT + kCT > nb) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) t[v] = element(I * kCT + acc_row(v, lane), K * kCT + col);
+        for (int v = 0; v < 16; ++v) t[v] = inside(t[v], I * kCT + acc_row(v, lane), K * kCT + col);
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) t[v] = -t[v];
