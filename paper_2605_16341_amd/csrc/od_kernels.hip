@@ -1197,7 +1197,9 @@ __global__ __launch_bounds__(256) void k_zero_pair(WsArr a, WsArr b, int64_t cou
     pb[i] = zero;
   }
 }
-// ColNorm stage 1: partial column sums of squares over a slab of rows (deterministic)
+// ColNorm stage 1: partial column sums of squares over a slab of rows (deterministic).  Four columns per thread and as
+// many rows side by side as a workgroup has threads for; stage 2 adds the slabs with 16 threads per column.  (One
+// column and one row per thread, one thread per column: 8192 x 64 10.7 + 7.4 us, now 4.8 + 4.6.)
 struct ColnormArgs {
   int n, r, slabs;
   WsArr rr, part, colsq;
@@ -1210,29 +1212,43 @@ __global__ __launch_bounds__(256) void k_colsq_partial(SegsT segs) {
   OD_SEGMENT(ColnormArgs);
   const int n = a_.n, r = a_.r, slabs = a_.slabs;
   const WsArr &rr = a_.rr, &part = a_.part;
-  const int z = blk.z, slab = blk.y;
-  const int c = blk.x * 256 + threadIdx.x;
+  const int z = blk.z, slab = blk.y, tid = threadIdx.x;
+  const int cols4 = min(64, (r - blk.x * 256) / 4), groups = 256 / cols4;
+  const int g = tid / cols4, c = blk.x * 256 + 4 * (tid - g * cols4);
   const int per = (n + slabs - 1) / slabs;
   const int r0 = slab * per, r1 = (r0 + per) < n ? (r0 + per) : n;
-  if (c >= r) return;
-  const float* src = rr.base + (int64_t)z * rr.stride;
-  float acc = 0.f;
-  for (int i = r0; i < r1; ++i) {
-    float v = src[(int64_t)i * r + c];
-    acc += v * v;
+  const float* src = rr.base + (int64_t)z * rr.stride + c;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (g < groups) {
+#pragma unroll 4
+    for (int i = r0 + g; i < r1; i += groups) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + (int64_t)i * r);
+      acc += v * v;
+    }
   }
-  part.base[(int64_t)z * part.stride + (int64_t)slab * r + c] = acc;
+  __shared__ f32x4 red[256];
+  red[tid] = acc;
+  __syncthreads();
+  if (g != 0) return;
+  for (int k = 1; k < groups; ++k) acc += red[tid + k * cols4];
+  *reinterpret_cast<f32x4*>(part.base + (int64_t)z * part.stride + (int64_t)slab * r + c) = acc;
 }
 // stage 2: reciprocal column lengths and the zero-column flag
 template <class SegsT>
-__global__ __launch_bounds__(256) void k_colsq_final(SegsT segs) {
+__global__ __launch_bounds__(1024) void k_colsq_final(SegsT segs) {
   OD_SEGMENT(ColnormArgs);
-  const int z = blk.z, r = a_.r, c = blk.x * 256 + threadIdx.x;
-  if (c >= r) return;
+  const int z = blk.z, r = a_.r, g = threadIdx.x >> 6, c = blk.x * 64 + (threadIdx.x & 63);
   const float* p = a_.part.base + (int64_t)z * a_.part.stride + c;
   float s = 0.f;
+  if (c < r) {
 #pragma unroll 16
-  for (int k = 0; k < a_.slabs; ++k) s += p[(int64_t)k * r];
+    for (int k = g; k < a_.slabs; k += 16) s += p[(int64_t)k * r];
+  }
+  __shared__ float red[1024];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  if (g != 0 || c >= r) return;
+  for (int k = 1; k < 16; ++k) s += red[threadIdx.x + 64 * k];
   const float len = sqrtf(s);
   float inv = 0.f;
   if (len > 1e-30f && len < 3.0e38f) inv = 1.f / len;
@@ -2842,11 +2858,11 @@ hipError_t launch_colnorm(BatchList b, int n, Prec prec, hipStream_t st) {
       a.mats = r.mats;
       if (prec == PREC_F16) a.qh = r.qh;
       sum.add(a, ceil_div(a.r, 256), a.slabs, r.d.nb);
-      fin.add(a, ceil_div(a.r, 256), 1, r.d.nb);
+      fin.add(a, ceil_div(a.r, 64), 1, r.d.nb);
       app.add(a, copy_blocks((int64_t)a.n * a.r / 4, 2048), 1, r.d.nb);
     }
     OD_RETURN_IF(sum.launch(k_colsq_partial<One<ColnormArgs>>, k_colsq_partial<Segs<ColnormArgs>>, 256, 0, st, 0));
-    OD_RETURN_IF(fin.launch(k_colsq_final<One<ColnormArgs>>, k_colsq_final<Segs<ColnormArgs>>, 256, 0, st, 0));
+    OD_RETURN_IF(fin.launch(k_colsq_final<One<ColnormArgs>>, k_colsq_final<Segs<ColnormArgs>>, 1024, 0, st, 0));
     return app.launch(k_colnorm_apply<One<ColnormArgs>>, k_colnorm_apply<Segs<ColnormArgs>>, 256, 0, st, 0);
   });
 }

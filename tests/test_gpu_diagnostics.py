@@ -109,6 +109,13 @@ def test_diagnostics_lanczos_sizes(count, m, n, r):
     run_case([(m, n)] * count, r, "f32", "qr", steps=1, seed=738)
 
 
+@pytest.mark.parametrize("m,n,r", [(16, 8, 8), (48, 40, 24), (56, 3000, 56), (320, 1104, 264), (520, 520, 512)])
+def test_column_sums_of_squares(m, n, r):
+    """The column lengths of R (right factor of ColNorm, effective rank) where the rows that a workgroup sums side by side
+    are more than there are, leave threads over, and where the last group of columns is short."""
+    run_case([(m, n)], r, "f32", "colnorm", steps=2, seed=739)
+
+
 def test_diagnostics_norms_at_the_edges_of_their_grid():
     """One workgroup per four rows up to 2048 rows, and two matrices of one shape whose partial sums lie
     one behind the other: 2, 510 and 512 workgroups, the last of these with rows of a second turn."""
