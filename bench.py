@@ -251,8 +251,9 @@ def measure(torch, binding, synth, dev, name, variant, precision, steps, warmup,
     # the kernel the library's launchers pick for this group (same rules as od_kernels.hip)
     kname = dominant
     if fast_path and dominant == "k_efx":
-        kname = "k_efx_d" if (w.r % 32 == 0 and w.r >= 64) else "k_efx_h"
-    if fast_path and dominant in ("k_proj", "k_back") and w.x_dtype == "bf16" and w.r >= 192:
+        small = (w.r < 64 or w.r % 32) and sum(m * n for m, n in w.shapes) < 1 << 22
+        kname = "k_efx_h" if small else "k_efx_d"
+    if fast_path and dominant in ("k_proj", "k_back") and w.x_dtype == "bf16" and w.r > 64:
         kname = "k_stream_d<%s>" % ("false" if dominant == "k_proj" else "true")
     nbytes, flops = group_work(w, variant, dominant)
     hbm_frac_k = nbytes / (dom_ms * 1e-3) / 1e9 / HBM_PEAK_GBS

@@ -214,7 +214,7 @@ int orthdion_profile_end(orthdion_handle h, float* ms_per_phase, int32_t* count_
  * Sec. 6.3 R-norm ratio, Prop. 3.1 / Lemma 4.1 dual-norm factor nu, Lemma 4.2 inner product,
  * App. B.2 estimated effective rank).  Off by default; when on, every orthdion_step also
  * enqueues a few extra kernels (one more pass over M and G, one over R, a Gram matrix of
- * the new Q and its 128th power by squarings) that fill a table in the workspace.
+ * the new Q and, for r > 256, its 128th power by squarings) that fill a table in the workspace.
  *   orthdion_set_diagnostics  enable != 0 switches them on for the following steps.
  *   orthdion_get_diagnostics  copies the table of the most recent step to the host array
  *                             out_host[nmat][ORTHDION_NDIAG] (matrix order of
@@ -228,8 +228,8 @@ int orthdion_profile_end(orthdion_handle h, float* ms_per_phase, int32_t* count_
  *   RESIDUAL_RATIO  ||M_prev||_F / ||G||_F (0 when G = 0)
  *   INNER           <B, P Q^T>: trace of orth(R)'s triangular factor (QR), sum of the column
  *                   lengths of R (ColNorm)
- *   NU              sigma_1(Q_new), from power iteration on Q^T Q (a lower estimate, relative
- *                   error (lambda_2 / lambda_1)^256)
+ *   NU              sigma_1(Q_new), a lower estimate from Q^T Q: 24 Lanczos steps up to r = 256,
+ *                   power iteration beyond (relative error (lambda_2 / lambda_1)^256)
  *   ERANK           exp(-sum p_i log p_i), p_i = ||R[:, i]|| / sum_j ||R[:, j]||
  *   G_NORM          ||G||_F                                                              */
 typedef enum {

@@ -184,8 +184,8 @@ hipError_t launch_diag_norms(const ClassDims& d, const MatEntry* mats, double* d
 hipError_t launch_diag_cols(int nb, int n, int r, WsArr rr, WsArr part, int slabs, double* dacc, hipStream_t st);
 // out[mat] = callers' Q (n x r)
 hipError_t launch_gather_q(int nb, int n, int r, const MatEntry* mats, WsArr out, hipStream_t st);
-// dacc[mat][7] = largest eigenvalue of the symmetric PSD r x r matrix `gram` by power iteration with
-// squared powers; tmp1, tmp2: r x r scratch per matrix, xbuf: 2 r floats per matrix (used for r > 512)
+// dacc[mat][7] = largest eigenvalue of the symmetric PSD r x r matrix `gram`: Lanczos iteration up to r = 256, power
+// iteration with squared powers beyond; tmp1, tmp2: r x r scratch per matrix, xbuf: 2 r floats per matrix (used for r > 512)
 hipError_t launch_power(int nb, int r, WsArr gram, WsArr tmp1, WsArr tmp2, WsArr xbuf, double* dacc, hipStream_t st);
 // diag[mat][0..7] = ||B||, ||R||, tracking error, ||M_prev|| / ||G||, <B, P Q^T>, nu, effective rank, ||G||;
 // <B, P Q^T> is sum_i t1[i][i] t2[i][i] (QR) or the sum of the column lengths of R (colnorm)
