@@ -1754,14 +1754,17 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
       else g = in.g[u];
       if constexpr (XBF) x = f32x2{bf16_lo(in.x[u]), bf16_hi(in.x[u])};
       else x = in.x[u];
-      f32x2 mo, xo;
+      f32x2 bval, mo, xo;
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const float bval = in.m[u][e] + g[e];
-        bmax = fmaxf(bmax, fabsf(bval));        // (a clamped address repeats an entry of the matrix)
-        mo[e] = a_coef * bval - cr * acc_r[fm][e][v];
+        bval[e] = in.m[u][e] + g[e];
+        mo[e] = a_coef * bval[e] - cr * acc_r[fm][e][v];
         xo[e] = x[e] - cq * acc_q[fm][e][v];
       }
+      // At a clamped address the owner may have stored its new M already, which is no entry of B.  Groups of eight rows lie
+      // inside or outside together; columns follow at the end.
+      const float bm = fmaxf(fmaxf(bmax, fabsf(bval[0])), fabsf(bval[1]));
+      bmax = ti * TI + 64 * wi + 32 * fm + 8 * (v >> 2) < d.m ? bm : bmax;
       if (i < d.m && j0 < d.n) {
         st_stream<STREAM>(reinterpret_cast<f32x2*>(Mz + (int64_t)i * d.ldm + j0), mo);
         if constexpr (XBF) st_stream<STREAM>(reinterpret_cast<uint32_t*>(Xz + ((int64_t)i * d.ldx + j0) * XE), pack_bf16_rne(xo[0], xo[1]));
@@ -1793,7 +1796,7 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
       update(part, even);
     }
   }
-  report_b_range(d, scal, info, z, bmax);
+  report_b_range(d, scal, info, z, j0 < d.n ? bmax : 0.f);
 }
 
 // ------------------------------------------------------------------------------------

@@ -206,6 +206,29 @@ def test_operand_range_warnings_of_the_fast_precision():
     assert gpu.opt.warnings() == [0]
 
 
+@pytest.mark.parametrize("m,n,r,x_dtype", [(200, 312, 64, "bf16"), (200, 312, 64, "f32"), (328, 200, 96, "bf16"), (3080, 5128, 264, "bf16")])
+def test_no_range_warning_from_updated_momentum(m, n, r, x_dtype):
+    """Where a tile reaches beyond the matrix, M_new + G must not be taken for B.  G holds entries at three times the fp16
+    limit of B in rows that the sample misses, in the last row, the last column and the corner; M cancels them, so that B
+    is zero there and nothing is clipped, while M_new + G is about G."""
+    w = synth.Workload("edge", ((m, n),), r=r, x_dtype=x_dtype, steps=1)
+    stream, st = synth.make_stream(w, 0), synth.make_state(w, 0)
+    g = stream.gradient(0)
+    sampled = [i * m // 32 for i in range(32)]
+    assert m - 1 not in sampled and m - 6 not in sampled
+    to_f32 = (lambda x: bf16_bits_to_f64(x).astype(np.float32)) if x_dtype == "bf16" else (lambda x: x)
+    limit = 65504.0 * 2.0 ** np.floor(np.log2(np.sqrt(np.mean((st.M + to_f32(g))[sampled].astype(np.float64) ** 2))))
+    entry = np.array([3.0 * limit], dtype=np.float32)
+    if x_dtype == "bf16":
+        entry = synth.f32_to_bf16_bits(entry)
+    for i, j in ((m - 1, n // 2), (m - 1, n - 1), (m - 6, n - 1), (m - 6, n - 2)):
+        g[i, j] = entry[0]
+        st.M[i, j] = -to_f32(entry)[0]
+    gpu = GpuRun(w.shapes, w.r, x_dtype, [st], precision="fast", mu=w.mu, lr=w.lr)
+    assert gpu.step([g]) == [0]
+    assert gpu.opt.warnings() == [0]
+
+
 def test_leading_dimensions_larger_than_n():
     import torch
     m, n, r, ld = 128, 96, 16, 160
