@@ -70,7 +70,8 @@ struct Batch {
   int cluster;                       // batches of one cluster share their launches
   bool small;                        // orthogonalisation by the three stages for ranks up to 32
   bool beside;                       // small, in a cluster that holds a larger rank
-  int64_t peers;                     // matrices of this shape that make up the same work as the cluster
+  int64_t work;                      // elements of the cluster (of its batches in the same group)
+  int64_t peers;                     // matrices of this shape that make up the same work, rounded down
 };
 
 // All batches of one rank r.  The r x r work of the orthogonalisations (Cholesky factor and
@@ -341,8 +342,8 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       // only (the other group's run beside them): chosen for all batches of the cluster, the splits halved and one
       // matrix of 8192 columns lost its rotated k order (8192 x 8192, r = 256 and 32: 938 us a step with launches
       // of their own, 1030 so, 941 like this).  By the default, not by the groups of this handle: see above.
-      b.peers = (int64_t)(shared[side_of(b)][b.cluster] / ((double)b.d.m * b.d.n));
-      if (b.peers < (int64_t)b.members.size()) b.peers = (int64_t)b.members.size();
+      b.work = (int64_t)shared[side_of(b)][b.cluster];
+      b.peers = b.work / ((int64_t)b.d.m * b.d.n);
     }
     // Ranks up to 32 have three stages of their own per orthogonalisation instead of eight kernels (one matrix of
     // 8192 x 8192, r = 16: 376 -> 352 us), in fp32, whatever larger ranks share their launches.
@@ -689,6 +690,7 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     v.slabs = b.slabs;
     v.small = b.small;
     v.beside = b.beside;
+    v.work = b.work;
     v.peers = b.peers;
   }
 

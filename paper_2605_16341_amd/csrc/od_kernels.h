@@ -92,7 +92,8 @@ struct BatchRef {
   int splits_proj, splits_back, splits_gram[2], slabs;
   bool small;                        // orthogonalised by the stages for ranks up to 32
   bool beside;                       // small, but sharing launches with a larger rank: factored beside it (launch_cholinv)
-  int64_t peers;                     // matrices of this shape that would make up the work of all batches that step together with it
+  int64_t work;                      // elements of all batches that step together with it: the same number for all of them
+  int64_t peers;                     // matrices of this shape that would make up that work, rounded down
   // left (P, rows m) and right (Q, rows n) side of the orthogonalisation
   int rows(int side) const { return side == 0 ? d.m : d.n; }
   WsArr a0(int side) const { return side == 0 ? pa : ra; }

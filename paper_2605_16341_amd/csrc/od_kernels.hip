@@ -2920,13 +2920,15 @@ hipError_t launch_efx(BatchList b, int n, Prec prec, float a_coef, float b_coef,
     if (prec == PREC_BF3) return (int64_t)ceil_div(d.m, 128) * ceil_div(d.n, 128) * r.peers < 256 ? EV_EXACT_SMALL : EV_EXACT;
     // nontemporal stores also for sets far beyond the Infinity Cache at any rank: they leave no dirty
     // lines behind for the next kernel to wait on (measured on 8192 x 8192: the step is 2-7 % faster)
-    const int stream = d.r > 256 || (int64_t)d.m * d.n * r.peers >= ((int64_t)48 << 20) ? 1 : 0;
+    const int stream = d.r > 256 || r.work >= ((int64_t)48 << 20) ? 1 : 0;
     // Small sets: the kernel with eight waves per tile, which has the shorter start, unless the rank is whole 32-deep
     // steps from 64 on (392 x 264, r = 40: 136 against 139 us a step, four 512 x 512 of r = 56 135 | 136; five matrices of
     // ranks 24 to 72 211 in one launch, 220 with r = 72 in one of its own); above, the direct-to-LDS kernel (twenty
     // 1024 x 1024 of r = 40 233 | 230, 4096 x 4096, r = 40 213 | 206, r = 104 246 | 238, 8192 x 8192, r = 16 349 | 343,
-    // r = 1000 2089 | 2047)
-    if ((d.r < 64 || d.r % 32 != 0) && (int64_t)d.m * d.n * r.peers < (int64_t)4 << 20) return EV_H;
+    // r = 1000 2089 | 2047).  The elements of all that step together, which are the same for every batch: by m n peers, rounded
+    // down, the shapes of one set fell on both sides and took two launches (three 2768 x 496 of r = 16 beside three 232 x 192 of
+    // r = 8: 134 us, 125 in one)
+    if ((d.r < 64 || d.r % 32 != 0) && r.work < (int64_t)4 << 20) return EV_H;
     // r > 256: 256-row tiles (one 8-wave workgroup per CU) while they still fill the chip twice:
     // a third less operand traffic into LDS per product than 128-row tiles
     const int64_t tall = (int64_t)ceil_div(d.m, 256) * ceil_div(d.n, 128) * r.peers;
