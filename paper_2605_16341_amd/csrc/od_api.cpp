@@ -474,16 +474,20 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
         const int64_t rows = side == 0 ? m : n;
         // small ranks: one 32 x 32 tile, one thread per row: 256-row slabs (small_gram, small_first_pass);
         // else two workgroups of the Gram kernel fit one CU.  Where that leaves few tiles, the kernel takes 64 x 64
-        // ones (gram_pass), and their short loops are split further, down to 128 rows, while the chip has idle CUs
-        // (4096 x 4096, r = 256, 14 | 25 splits: 312 | 307 us a step, 2048 x 5632 291 | 287, five small matrices of ranks
-        // 24 to 72 210 | 200; never fewer: six ragged ones of r = 136 took 444 instead of 436)
+        // ones (gram_pass), and their short loops are split further, down to 128 rows, as long as one workgroup per CU
+        // has room (4096 x 4096, r = 256, 14 | 25 splits: 312 | 307 us a step, 2048 x 5632 291 | 287, five small matrices
+        // of ranks 24 to 72 210 | 200; without that bound 64 matrices 640 x 640 of r = 72 took 392 instead of 375); never
+        // fewer: six ragged ones of r = 136 took 444 instead of 436.  Two splits in place of one, i.e. a launch more that adds
+        // them up, pay up to some 50 matrices (48 of 320 x 320, r = 40: one 160, two 157; 64: 179, 184; 128 of 264 x 264:
+        // 290, 294).
         b.splits_gram[side] = limited([&](int64_t peers) -> int {
           if (b.small) return pick_splits(1, peers, rows, 256);
           const int s = pick_splits_by_rounds(gt, peers, rows, 256, 512);
           if (lean) return s;
-          const int64_t g64 = (r + 63) / 64;
-          const int fine = std::max(s, pick_splits_by_rounds(g64 * (g64 + 1) / 2, peers, rows, 128, 256));
-          return gt1 * gt1 * fine * peers < od::kSmallGramTiles ? fine : s;
+          const int64_t g64 = (r + 63) / 64, tiles = g64 * (g64 + 1) / 2;
+          const int64_t idle = 256 / (tiles * peers);       // splits that one workgroup per CU has room for
+          const int fine = (int)std::max<int64_t>(s, std::min<int64_t>(idle, pick_splits_by_rounds(tiles, peers, rows, 128, 256)));
+          return gt1 * gt1 * fine * peers < od::kSmallGramTiles && (s > 1 || fine > 2 || peers < 64) ? fine : s;
         });
       }
       b.slabs = (int)((n + 31) / 32);           // row slabs of the column-norm kernels: many, so the grid fills the chip

@@ -725,34 +725,43 @@ def test_direct_contractions_of_middle_ranks(shapes, r):
     _free_running(w)
 
 
+def launches_of_a_step(shapes, ranks):
+    """Number of nodes in the graph of one captured step."""
+    import ctypes
+    import torch
+    opt = binding.OrthDion(shapes, ranks, x_dtype="bf16")
+    dev = torch.device("cuda:0")
+    bufs = [[torch.zeros(m, n, dtype=dt, device=dev) for m, n in shapes] for dt in (torch.bfloat16, torch.bfloat16, torch.float32)]
+    bufs.append([torch.zeros(n, r, device=dev) for (m, n), r in zip(shapes, ranks)])
+    side = torch.cuda.Stream()
+    opt.step(*bufs, stream=side.cuda_stream)
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=side):
+        opt.step(*bufs, stream=side.cuda_stream)
+    count = ctypes.c_size_t(0)
+    hip = ctypes.CDLL("libamdhip64.so")
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    opt.close()
+    return count.value
+
+
 def test_batches_of_a_cluster_stay_in_one_launch_at_a_size_limit():
     """The kernel of the error-feedback pass is chosen by the elements that step together, 2^22 here: two shapes whose
     whole number of matrices in that work falls on different sides of the limit take as many launches as two shapes
     well above it."""
-    import ctypes
-    import torch
-
-    def launches(shapes, ranks):
-        opt = binding.OrthDion(shapes, ranks, x_dtype="bf16")
-        dev = torch.device("cuda:0")
-        bufs = [[torch.zeros(m, n, dtype=dt, device=dev) for m, n in shapes] for dt in (torch.bfloat16, torch.bfloat16, torch.float32)]
-        bufs.append([torch.zeros(n, r, device=dev) for (m, n), r in zip(shapes, ranks)])
-        side = torch.cuda.Stream()
-        opt.step(*bufs, stream=side.cuda_stream)
-        side.synchronize()
-        graph = torch.cuda.CUDAGraph(keep_graph=True)
-        with torch.cuda.graph(graph, stream=side):
-            opt.step(*bufs, stream=side.cuda_stream)
-        count = ctypes.c_size_t(0)
-        hip = ctypes.CDLL("libamdhip64.so")
-        assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
-        opt.close()
-        return count.value
-
     ranks = [16] * 3 + [8] * 3
     at_limit, above = [(2768, 496)] * 3 + [(232, 192)] * 3, [(3072, 512)] * 3 + [(232, 192)] * 3
     assert sum(m * n for m, n in at_limit) > 1 << 22 > 3 * 2768 * 496
-    assert launches(at_limit, ranks) == launches(above, ranks) > 5
+    assert launches_of_a_step(at_limit, ranks) == launches_of_a_step(above, ranks) > 5
+
+
+@pytest.mark.parametrize("size,r,count,more", [(320, 40, 96, 160)])
+def test_no_partial_sums_where_one_split_fills_the_chip(size, r, count, more):
+    """`count` matrices are added up in one piece like `more` of them are: the only launches that differ are those that
+    carry the table of 64 matrices each."""
+    few, many = (launches_of_a_step([(size, size)] * k, [r] * k) - (k + 63) // 64 for k in (count, more))
+    assert few == many
 
 
 def test_more_equal_matrices_than_a_batch_may_hold():
