@@ -108,8 +108,8 @@ int pick_splits(int64_t tiles, int64_t nb, int64_t k, int kt_min) {
 // Splits for a kernel whose workgroups run in rounds of `slots` (256 CUs times the workgroups
 // that fit one CU).  A workgroup's time is proportional to 1 / splits, so rounds / splits
 // measures the launch; the fewest splits (least partial-sum traffic) within 15 % of the best
-// are taken.
-int pick_splits_by_rounds(int64_t tiles, int64_t nb, int64_t k, int kt_min, int64_t slots) {
+// are taken; a single one, which leaves no partial sums, also within `single` of it.
+int pick_splits_by_rounds(int64_t tiles, int64_t nb, int64_t k, int kt_min, int64_t slots, double single = 1.15) {
   int64_t cap = k / kt_min;
   if (cap < 1) cap = 1;
   if (cap > 32) cap = 32;
@@ -117,7 +117,7 @@ int pick_splits_by_rounds(int64_t tiles, int64_t nb, int64_t k, int kt_min, int6
   double best = cost(1);
   for (int s = 2; s <= (int)cap; ++s) best = cost(s) < best ? cost(s) : best;
   for (int s = 1; s <= (int)cap; ++s)
-    if (cost(s) <= 1.15 * best) return s;
+    if (cost(s) <= (s == 1 ? single : 1.15) * best) return s;
   return 1;
 }
 
@@ -447,8 +447,12 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
         else od::proj_tiling(d, prec, peers, staged, &rows, &cols, &slots);
         const int64_t out = back ? n : m, k = back ? m : n;
         const int64_t tiles = ((out + rows - 1) / rows) * ((r + cols - 1) / cols);
-        // one 8-wave workgroup per CU is scheduled in whole rounds; two smaller ones mix
-        return slots == 256 ? pick_splits_by_rounds(tiles, peers, k, 256, slots) : pick_splits(tiles, peers, k, 128);
+        // One 8-wave workgroup per CU is scheduled in whole rounds; two smaller ones mix.  Below r = 192 (columns of one tile,
+        // little arithmetic) partial sums are a larger part of the traffic, and more than one split has to save a third of
+        // the rounds (us a step by the rule of the larger ranks | by this one, with the register-staged kernels: 160 matrices
+        // 512 x 512 of r = 128 687 | 625, 672; 134 of r = 72 518 | 487, 501; 66 of r = 160 457 | 435, 500; 18 of
+        // 2048 x 2048, r = 160, 805 | 806, 912)
+        return slots == 256 ? pick_splits_by_rounds(tiles, peers, k, 256, slots, r < 192 ? 1.45 : 1.15) : pick_splits(tiles, peers, k, 128);
       };
       // the lean plan takes no more splits than the register-staged kernels would
       auto splits_for = [&](bool back, int64_t peers) {

@@ -756,7 +756,7 @@ def test_batches_of_a_cluster_stay_in_one_launch_at_a_size_limit():
     assert launches_of_a_step(at_limit, ranks) == launches_of_a_step(above, ranks) > 5
 
 
-@pytest.mark.parametrize("size,r,count,more", [(320, 40, 96, 160)])
+@pytest.mark.parametrize("size,r,count,more", [(320, 40, 96, 160), (512, 72, 134, 205)])
 def test_no_partial_sums_where_one_split_fills_the_chip(size, r, count, more):
     """`count` matrices are added up in one piece like `more` of them are: the only launches that differ are those that
     carry the table of 64 matrices each."""
