@@ -70,7 +70,7 @@ struct Batch {
   int cluster;                       // batches of one cluster share their launches
   bool small;                        // orthogonalisation by the three stages for ranks up to 32
   bool beside;                       // small, in a cluster that holds a larger rank
-  int64_t work;                      // elements of the cluster (of its batches in the same group)
+  od::Work work;                     // of the cluster (its batches in the same group)
   int64_t peers;                     // matrices of this shape that make up the same work, rounded down
 };
 
@@ -320,7 +320,7 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
     struct Open { int key, id; double elems; };
     std::vector<Open> open;
     const auto side_of = [&](const Batch& b) { return by_default == 2 ? dealt[&b - h->batches.data()] : 0; };
-    std::vector<double> shared[2];      // elements of a cluster's batches in either group
+    std::vector<od::Work> shared[2];    // of a cluster's batches in either group
     for (Batch& b : h->batches) {
       const int key = b.d.r <= od::kLeafRank ? 0 : b.d.r;
       const double e = (double)b.d.m * b.d.n * (double)b.members.size();
@@ -330,20 +330,22 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       if (open[k].id < 0 || open[k].elems + e > kClusterElements) {
         open[k].id = (int)shared[0].size();
         open[k].elems = 0.0;
-        shared[0].push_back(0.0);
-        shared[1].push_back(0.0);
+        shared[0].push_back(od::Work{0, 0});
+        shared[1].push_back(od::Work{0, 0});
       }
       open[k].elems += e;
       b.cluster = open[k].id;
-      shared[side_of(b)][b.cluster] += e;
+      od::Work& w = shared[side_of(b)][b.cluster];
+      w.elements += (int64_t)e;
+      w.matrices += (int64_t)b.members.size();
     }
     for (Batch& b : h->batches) {
       // Where the library takes two groups, a batch shares its launches and its stream with those of its group
       // only (the other group's run beside them): chosen for all batches of the cluster, the splits halved and one
       // matrix of 8192 columns lost its rotated k order (8192 x 8192, r = 256 and 32: 938 us a step with launches
       // of their own, 1030 so, 941 like this).  By the default, not by the groups of this handle: see above.
-      b.work = (int64_t)shared[side_of(b)][b.cluster];
-      b.peers = b.work / ((int64_t)b.d.m * b.d.n);
+      b.work = shared[side_of(b)][b.cluster];
+      b.peers = b.work.elements / ((int64_t)b.d.m * b.d.n);
     }
     // Ranks up to 32 have three stages of their own per orthogonalisation instead of eight kernels (one matrix of
     // 8192 x 8192, r = 16: 376 -> 352 us), in fp32, whatever larger ranks share their launches.
@@ -443,8 +445,8 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
       const od::Prec prec = resolve_prec(*cfg);
       auto splits_of = [&](bool back, int64_t peers, bool staged) {
         int rows, cols, slots;
-        if (back) od::back_tiling(d, prec, staged, &rows, &cols, &slots);
-        else od::proj_tiling(d, prec, peers, staged, &rows, &cols, &slots);
+        if (back) od::back_tiling(d, prec, b.work, staged, &rows, &cols, &slots);
+        else od::proj_tiling(d, prec, peers, b.work, staged, &rows, &cols, &slots);
         const int64_t out = back ? n : m, k = back ? m : n;
         const int64_t tiles = ((out + rows - 1) / rows) * ((r + cols - 1) / cols);
         // One 8-wave workgroup per CU is scheduled in whole rounds; two smaller ones mix.  Below r = 192 (columns of one tile,

@@ -78,6 +78,11 @@ constexpr float kMaxGramDeviation = 0.5f;
 // reciprocal condition number of the factor) that still counts as full rank
 constexpr float kMinPivotRatio = 1.0e-3f;
 
+// What steps together in shared launches.
+struct Work {
+  int64_t elements, matrices;
+};
+
 // One launch batch as the launchers see it: shape, the caller's buffers, its workspace arrays and
 // the choices made when the handle was created.  Choices depend on the whole matrix set (how many
 // workgroups share the chip in a launch), never on how the set is dealt into groups.
@@ -92,7 +97,7 @@ struct BatchRef {
   int splits_proj, splits_back, splits_gram[2], slabs;
   bool small;                        // orthogonalised by the stages for ranks up to 32
   bool beside;                       // small, but sharing launches with a larger rank: factored beside it (launch_cholinv)
-  int64_t work;                      // elements of all batches that step together with it: the same number for all of them
+  Work work;                         // of all batches that step together with it: the same for all of them
   int64_t peers;                     // matrices of this shape that would make up that work, rounded down
   // left (P, rows m) and right (Q, rows n) side of the orthogonalisation
   int rows(int side) const { return side == 0 ? d.m : d.n; }
@@ -109,8 +114,8 @@ hipError_t launch_begin(BatchList b, int n, Prec prec, hipStream_t st);
 // the tile rows and columns of the projection / back-projection for this shape, and the workgroups
 // of its kernel that fit the chip at a time: what the number of splits is chosen from.  `staged`: those of the
 // register-staged kernels for ranks below 192, whose smaller workgroups take fewer splits
-void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, bool staged, int* rows, int* cols, int* slots);
-void back_tiling(const ClassDims& d, Prec prec, bool staged, int* rows, int* cols, int* slots);
+void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, const Work& work, bool staged, int* rows, int* cols, int* slots);
+void back_tiling(const ClassDims& d, Prec prec, const Work& work, bool staged, int* rows, int* cols, int* slots);
 // P_raw = (M + G) Q, split over n: partial sums in `part`, or with one split straight in `pa`
 hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st);
 // pa = sum of the projection's partials (batches with one split have nothing to add)

@@ -2197,15 +2197,20 @@ hipError_t launch_begin(BatchList b, int n, Prec prec, hipStream_t st) {
 }
 
 // ---- projection and back-projection -------------------------------------------------
-// Shapes the direct-to-LDS contraction takes (fast precision only): bf16 gradients and at least one whole 32-deep
+// What the direct-to-LDS contraction takes (fast precision only): bf16 gradients and at least one whole 32-deep
 // step.  Ranks above 64: up to 128 columns per tile the register kernels are 1 to 7 % slower per step (4096 x 4096,
 // r = 72 | 104 | 128: 239 | 253 | 246 us with them, 234 | 247 | 240; nine 1840 x 7384, r = 104: 1302 -> 1214;
 // 8192 x 8192, r = 96: 481 -> 457 with rotated k order), with half-filled 256-column tiles 2 to 9 % (six ragged matrices of
-// r = 136: 476 -> 437, 8192 x 8192, r = 160: 567 -> 520, 4096 x 4096, r = 184: 293 -> 286).  Below 2^18 elements and
-// r = 192 a step is a few short k loops, where the pipeline costs more than it hides: 392 x 264, r = 72 beside four smaller
-// matrices 210 against 214 us; thirty 512 x 512 of r = 128 228 -> 219.
-static bool stream_kernel_eligible(const ClassDims& d) {
-  return d.g_bf16 && d.r > 64 && d.m >= 32 && d.n >= 32 && (d.r >= 192 || (int64_t)d.m * d.n >= 1 << 18);
+// r = 136: 476 -> 437, 8192 x 8192, r = 160: 567 -> 520, 4096 x 4096, r = 184: 293 -> 286).  Below r = 192 only from
+// 2^21 elements on, of all that step together, or 2^20 in matrices of 2^19 each: less is a few short k loops, where the
+// pipeline costs what it hides (register | direct, r = 72 and 128: 384 x 384 137 | 142 and 150 | 154, eight of them 149 | 152
+// and 164 | 165, 640 x 640 142 | 146 and 154 | 157, four of them 152 | 155 and 167 | 168, 1024 x 1024 153 | 152 and
+// 167 | 165; ten 448 x 512 158 | 158 and 175 | 173, forty 221 | 209 and 260 | 237).  By the whole work and not the size of one
+// matrix, so that one set does not take two kernels where it could share a launch (four of 256 x 384 to 512 x 640, ranks 72 to
+// 128: 191 | 196, 216 with both).
+static bool stream_kernel_eligible(const ClassDims& d, const Work& work) {
+  if (!d.g_bf16 || d.r <= 64 || d.m < 32 || d.n < 32) return false;
+  return d.r >= 192 || work.elements >= 1 << 21 || (work.elements >= 1 << 20 && work.elements >= work.matrices << 19);
 }
 static int stream_tile_cols(int r) { return r <= 128 ? 128 : r <= 256 ? 256 : 512; }
 // Few wide tiles need many splits to fill the chip; 64-row tiles get there with half of them,
@@ -2213,23 +2218,23 @@ static int stream_tile_cols(int r) { return r <= 128 ? 128 : r <= 256 ? 256 : 51
 // `peers`: matrices of this shape that would fill the launch the batch is part of.
 static bool proj_uses_flat_tiles(int m, int r, int64_t peers) { return r > 128 && (int64_t)ceil_div(m, 128) * ceil_div(r, 256) * peers < 256; }
 
-void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, bool staged, int* rows, int* cols, int* slots) {
+void proj_tiling(const ClassDims& d, Prec prec, int64_t peers, const Work& work, bool staged, int* rows, int* cols, int* slots) {
   *rows = 128;
   *cols = d.r <= 64 ? 64 : (d.r <= 128 ? 128 : 256);
   *slots = 512;                                // two workgroups per CU
   if (prec != PREC_F16) return;
-  if (stream_kernel_eligible(d) && !(staged && d.r < 192)) {       // one 8-wave workgroup per CU
+  if (stream_kernel_eligible(d, work) && !(staged && d.r < 192)) {       // one 8-wave workgroup per CU
     *cols = stream_tile_cols(d.r);
     *slots = 256;
   } else if (proj_uses_flat_tiles(d.m, d.r, peers)) {
     *rows = 64;
   }
 }
-void back_tiling(const ClassDims& d, Prec prec, bool staged, int* rows, int* cols, int* slots) {
+void back_tiling(const ClassDims& d, Prec prec, const Work& work, bool staged, int* rows, int* cols, int* slots) {
   *rows = 128;
   *cols = d.r <= 64 ? 64 : (d.r <= 128 ? 128 : 256);
   *slots = 512;
-  if (prec == PREC_F16 && stream_kernel_eligible(d) && !(staged && d.r < 192)) {
+  if (prec == PREC_F16 && stream_kernel_eligible(d, work) && !(staged && d.r < 192)) {
     *cols = stream_tile_cols(d.r);
     *slots = 256;
   }
@@ -2298,7 +2303,7 @@ hipError_t launch_proj(BatchList b, int n, Prec prec, hipStream_t st) {
     if (prec == PREC_BF3)
       // small problems: 64-deep steps halve the number of round trips of a loop that is all latency
       return (int64_t)ceil_div(d.m, 128) * ceil_div(d.r, 128) * r.splits_proj * r.peers < 256 ? PV_EXACT_SMALL : PV_EXACT;
-    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 128 ? PV_STREAM128 : stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
+    if (stream_kernel_eligible(d, r.work)) return stream_tile_cols(d.r) == 128 ? PV_STREAM128 : stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
     if (d.r <= 64) return PV_NARROW;
     if (d.r <= 128) return PV_SQUARE;
     // long enough K loops per column tile pay for a second register stage
@@ -2338,7 +2343,7 @@ hipError_t launch_back(BatchList b, int n, Prec prec, hipStream_t st) {
     const ClassDims& d = r.d;
     if (prec == PREC_BF3)
       return (int64_t)ceil_div(d.n, 128) * ceil_div(d.r, 128) * r.splits_back * r.peers < 256 ? PV_EXACT_SMALL : PV_EXACT;
-    if (stream_kernel_eligible(d)) return stream_tile_cols(d.r) == 128 ? PV_STREAM128 : stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
+    if (stream_kernel_eligible(d, r.work)) return stream_tile_cols(d.r) == 128 ? PV_STREAM128 : stream_tile_cols(d.r) == 256 ? PV_STREAM256 : PV_STREAM512;
     if (d.r <= 64) return PV_NARROW;
     if (d.r <= 128) return PV_SQUARE;
     // several column tiles per row panel: 256 x 256 tiles halve the operand traffic per product
@@ -2380,7 +2385,7 @@ hipError_t launch_proj_reduce(BatchList b, int n, hipStream_t st) {
 hipError_t launch_back_reduce(BatchList b, int n, Prec prec, hipStream_t st) {
   const auto variant = [&](const BatchRef& r) -> int {
     if (prec != PREC_F16) return r.splits_back > 1 ? 0 : -1;
-    return r.splits_back == 1 && stream_kernel_eligible(r.d) ? -1 : 1;      // that kernel has written the fp16 copy itself
+    return r.splits_back == 1 && stream_kernel_eligible(r.d, r.work) ? -1 : 1;      // that kernel has written the fp16 copy itself
   };
   return by_variant(b, n, variant, [&](int v, BatchList g, int k, int) -> hipError_t {
     if (v == 0) {
@@ -2920,7 +2925,7 @@ hipError_t launch_efx(BatchList b, int n, Prec prec, float a_coef, float b_coef,
     if (prec == PREC_BF3) return (int64_t)ceil_div(d.m, 128) * ceil_div(d.n, 128) * r.peers < 256 ? EV_EXACT_SMALL : EV_EXACT;
     // nontemporal stores also for sets far beyond the Infinity Cache at any rank: they leave no dirty
     // lines behind for the next kernel to wait on (measured on 8192 x 8192: the step is 2-7 % faster)
-    const int stream = d.r > 256 || r.work >= ((int64_t)48 << 20) ? 1 : 0;
+    const int stream = d.r > 256 || r.work.elements >= ((int64_t)48 << 20) ? 1 : 0;
     // Small sets: the kernel with eight waves per tile, which has the shorter start, unless the rank is whole 32-deep
     // steps from 64 on (392 x 264, r = 40: 136 against 139 us a step, four 512 x 512 of r = 56 135 | 136; five matrices of
     // ranks 24 to 72 211 in one launch, 220 with r = 72 in one of its own); above, the direct-to-LDS kernel (twenty
@@ -2928,7 +2933,7 @@ hipError_t launch_efx(BatchList b, int n, Prec prec, float a_coef, float b_coef,
     // r = 1000 2089 | 2047).  The elements of all that step together, which are the same for every batch: by m n peers, rounded
     // down, the shapes of one set fell on both sides and took two launches (three 2768 x 496 of r = 16 beside three 232 x 192 of
     // r = 8: 134 us, 125 in one)
-    if ((d.r < 64 || d.r % 32 != 0) && r.work < (int64_t)4 << 20) return EV_H;
+    if ((d.r < 64 || d.r % 32 != 0) && r.work.elements < (int64_t)4 << 20) return EV_H;
     // r > 256: 256-row tiles (one 8-wave workgroup per CU) while they still fill the chip twice:
     // a third less operand traffic into LDS per product than 128-row tiles
     const int64_t tall = (int64_t)ceil_div(d.m, 256) * ceil_div(d.n, 128) * r.peers;

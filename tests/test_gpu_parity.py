@@ -717,10 +717,12 @@ def test_error_feedback_rank_tails(m, n, r, x_dtype):
     _free_running(w, precision="fast", tol=2e-2)
 
 
-@pytest.mark.parametrize("shapes,r", [(((520, 776),), 72), (((776, 520),), 128), (((1032, 264), (264, 1032)), 104), (((512, 512),), 136)])
+@pytest.mark.parametrize("shapes,r", [(((520, 776),) * 6, 72), (((776, 520),) * 6, 128), (((1032, 264), (264, 1032)) * 4, 104), (((512, 512),) * 8, 136),
+                                      (((200, 168),) * 64, 72), (((136, 232),) * 68, 72), (((1032, 1160),), 104), (((520, 776),), 72), (((776, 520),), 128)])
 def test_direct_contractions_of_middle_ranks(shapes, r):
     """The direct-to-LDS contractions at ranks that fill their column tile partly or wholly, with output rows and
-    contracted dimensions that end inside a tile, one shape and two of them in a launch."""
+    contracted dimensions that end inside a tile, one shape and two of them in a launch, many matrices of less than a
+    tile; and the register-staged ones, which a single one of them takes."""
     w = synth.Workload(f"direct-{r}", shapes, r=r, x_dtype="bf16", steps=2)
     _free_running(w)
 
@@ -746,14 +748,15 @@ def launches_of_a_step(shapes, ranks):
     return count.value
 
 
-def test_batches_of_a_cluster_stay_in_one_launch_at_a_size_limit():
-    """The kernel of the error-feedback pass is chosen by the elements that step together, 2^22 here: two shapes whose
-    whole number of matrices in that work falls on different sides of the limit take as many launches as two shapes
-    well above it."""
-    ranks = [16] * 3 + [8] * 3
-    at_limit, above = [(2768, 496)] * 3 + [(232, 192)] * 3, [(3072, 512)] * 3 + [(232, 192)] * 3
-    assert sum(m * n for m, n in at_limit) > 1 << 22 > 3 * 2768 * 496
-    assert launches_of_a_step(at_limit, ranks) == launches_of_a_step(above, ranks) > 5
+@pytest.mark.parametrize("at_limit,elsewhere,ranks", [
+    # error feedback, 2^22 elements: three matrices of 1.4 M would make up less than the sum, 95 of 45 K more than 2^22
+    ([(2768, 496)] * 3 + [(232, 192)] * 3, [(3072, 512)] * 3 + [(232, 192)] * 3, [16] * 3 + [8] * 3),
+    # contractions of middle ranks, 2^21 elements: matrices above and below 2^18
+    ([(512, 640), (640, 512), (256, 384), (392, 264)], [(384, 512), (512, 384), (256, 384), (392, 264)], [72, 104, 80, 128])])
+def test_batches_of_a_cluster_stay_in_one_launch_at_a_size_limit(at_limit, elsewhere, ranks):
+    """Kernels are chosen by the elements that step together, not by those of one matrix or of a whole number of
+    matrices: shapes on both sides of a limit take as many launches as shapes on one side."""
+    assert launches_of_a_step(at_limit, ranks) == launches_of_a_step(elsewhere, ranks) > 5
 
 
 @pytest.mark.parametrize("size,r,count,more", [(320, 40, 96, 160), (512, 72, 134, 205)])
