@@ -521,10 +521,10 @@ def test_phase_profile_counts_and_leaves_results_alone():
             assert a[key].tobytes() == b[key].tobytes(), key
 
 
-@pytest.mark.parametrize("r", [40, 104, 168, 200, 232, 256])
+@pytest.mark.parametrize("r", [40, 48, 56, 88, 104, 112, 168, 200, 232, 240, 248, 256])
 def test_leaf_factorisation_at_every_tile_count(r):
     """Cholesky factor and inverse of one workgroup with two to eight 32 x 32 tiles per side, the last
-    one whole or partly filled: P^T P = I, upper-triangular factors with a positive diagonal that reproduce
+    one with 8, 16, 24 or all 32 rows: P^T P = I, upper-triangular factors with a positive diagonal that reproduce
     B Q_prev.  Bounds as in the r = 96 test: a Gram matrix in 24-bit operands leaves about 1e-6."""
     w = synth.Workload("leaf", ((576, 320),), r=r, x_dtype="bf16", steps=1)
     stream, st = synth.make_stream(w, 0), synth.make_state(w, 0)
