@@ -485,16 +485,18 @@ static int create_impl(orthdion_handle* out, const orthdion_matdesc* mats, int32
         // of ranks 24 to 72 210 | 200; without that bound 64 matrices 640 x 640 of r = 72 took 392 instead of 375); never
         // fewer: six ragged ones of r = 136 took 444 instead of 436.  Two splits in place of one, i.e. a launch more that adds
         // them up, pay up to some 50 matrices (48 of 320 x 320, r = 40: one 160, two 157; 64: 179, 184; 128 of 264 x 264:
-        // 290, 294).
-        b.splits_gram[side] = limited([&](int64_t peers) -> int {
-          if (b.small) return pick_splits(1, peers, rows, 256);
-          const int s = pick_splits_by_rounds(gt, peers, rows, 256, 512);
-          if (lean) return s;
-          const int64_t g64 = (r + 63) / 64, tiles = g64 * (g64 + 1) / 2;
-          const int64_t idle = 256 / (tiles * peers);       // splits that one workgroup per CU has room for
-          const int fine = (int)std::max<int64_t>(s, std::min<int64_t>(idle, pick_splits_by_rounds(tiles, peers, rows, 128, 256)));
-          return gt1 * gt1 * fine * peers < od::kSmallGramTiles && (s > 1 || fine > 2 || peers < 64) ? fine : s;
-        });
+        // 290, 294), in exact precision, whose loops take longer, as long as there is room (64 and 100 of 256 x 256, r = 40:
+        // one 172 and 237, two 164 and 228).
+        const int s = limited([&](int64_t peers) { return b.small ? pick_splits(1, peers, rows, 256) : pick_splits_by_rounds(gt, peers, rows, 256, 512); });
+        b.splits_gram[side] = s;
+        if (b.small || lean) continue;
+        // By what steps together, also in exact precision: 32 matrices alone, which its least splits are taken from, leave
+        // CUs idle that many do not (fp32, with finer splits for the former | so: 300 matrices 256 x 256 of r = 40 585 | 513,
+        // 500 of 384 x 384 1560 | 1382, 1000 of 256 x 256, r = 96, 2060 | 1960).
+        const int64_t g64 = (r + 63) / 64, tiles = g64 * (g64 + 1) / 2;
+        const int64_t idle = 256 / (tiles * b.peers);       // splits that one workgroup per CU has room for
+        const int fine = (int)std::max<int64_t>(s, std::min<int64_t>(idle, pick_splits_by_rounds(tiles, b.peers, rows, 128, 256)));
+        if (gt1 * gt1 * fine * b.peers < od::kSmallGramTiles && (s > 1 || fine > 2 || b.peers < 64 || prec == od::PREC_BF3)) b.splits_gram[side] = fine;
       }
       b.slabs = (int)((n + 31) / 32);           // row slabs of the column-norm kernels: many, so the grid fills the chip
       if (b.slabs > 256) b.slabs = 256;

@@ -727,13 +727,14 @@ def test_direct_contractions_of_middle_ranks(shapes, r):
     _free_running(w)
 
 
-def launches_of_a_step(shapes, ranks):
+def launches_of_a_step(shapes, ranks, x_dtype="bf16"):
     """Number of nodes in the graph of one captured step."""
     import ctypes
     import torch
-    opt = binding.OrthDion(shapes, ranks, x_dtype="bf16")
+    opt = binding.OrthDion(shapes, ranks, x_dtype=x_dtype)
     dev = torch.device("cuda:0")
-    bufs = [[torch.zeros(m, n, dtype=dt, device=dev) for m, n in shapes] for dt in (torch.bfloat16, torch.bfloat16, torch.float32)]
+    store = torch.bfloat16 if x_dtype == "bf16" else torch.float32
+    bufs = [[torch.zeros(m, n, dtype=dt, device=dev) for m, n in shapes] for dt in (store, store, torch.float32)]
     bufs.append([torch.zeros(n, r, device=dev) for (m, n), r in zip(shapes, ranks)])
     side = torch.cuda.Stream()
     opt.step(*bufs, stream=side.cuda_stream)
@@ -765,6 +766,13 @@ def test_no_partial_sums_where_one_split_fills_the_chip(size, r, count, more):
     carry the table of 64 matrices each."""
     few, many = (launches_of_a_step([(size, size)] * k, [r] * k) - (k + 63) // 64 for k in (count, more))
     assert few == many
+
+
+def test_finer_gram_splits_of_exact_precision_by_what_steps_together():
+    """The least splits of exact precision are those of 32 matrices; the finer ones for idle CUs do not join them.  At 128
+    columns 32 matrices would leave CUs idle, at 136 not: 100 of them take the same launches."""
+    at_128, at_136 = (launches_of_a_step([(256, 256)] * 100, [r] * 100, "f32") for r in (128, 136))
+    assert at_128 == at_136
 
 
 def test_more_equal_matrices_than_a_batch_may_hold():
