@@ -1807,7 +1807,7 @@ __global__ __launch_bounds__(128 * WI, (WI == 2 ? 2 : 1)) void k_efx_d(SegsT seg
 // One workgroup (8 waves, 2 x 4) computes 128 output rows x NT = 128, 256 or 512 columns over a K range; wave
 // tile 64 x NT / 4.  Per 32-deep step:
 //   * the factor operand (Qt / Pt: fp16 words, k contiguous) arrives by `dma16` in the swizzled
-//     layout of od_dma.h, two stages;
+//     layout of od_dma.h, SB stages: two at NT = 512, three below;
 //   * the streamed operand arrives raw - the fp32 tile of M and the bf16 tile of G, exactly as
 //     they lie in memory - by `dma16` into three staging stages, so two steps of HBM traffic
 //     (48 KB per CU) are in flight with no staging registers and no compiler-scheduled waits;
@@ -2519,8 +2519,9 @@ hipError_t launch_gram_plain(int nb, int rows, int r, WsArr a, WsArr part, int s
   ga.a = a;
   ga.part = part;
   SegList<GramArgs> segs;
+  // (a launch of its own, so that the matrices of the batch are all there are)
   const int t = ceil_div(r, 128);
-  const int tiles = (int64_t)t * t * splits * nb < 512 ? ceil_div(r, 64) : t;
+  const int tiles = (int64_t)t * t * splits * nb < kSmallGramTiles ? ceil_div(r, 64) : t;
   segs.add(ga, tiles * (tiles + 1) / 2, splits, nb);
   return tiles == t && r > 64 ? segs.launch(k_gram<TileSquare, NumBF<3>, One<GramArgs>>, k_gram<TileSquare, NumBF<3>, Segs<GramArgs>>, TileSquare::THREADS, TileSquare::lds_bytes<NumBF<3>>(), st, 0)
                               : segs.launch(k_gram<TileSmall, NumBF<3>, One<GramArgs>>, k_gram<TileSmall, NumBF<3>, Segs<GramArgs>>, TileSmall::THREADS, TileSmall::lds_bytes<NumBF<3>>(), st, 0);
