@@ -228,8 +228,12 @@ int orthdion_profile_end(orthdion_handle h, float* ms_per_phase, int32_t* count_
  *   RESIDUAL_RATIO  ||M_prev||_F / ||G||_F (0 when G = 0)
  *   INNER           <B, P Q^T>: trace of orth(R)'s triangular factor (QR), sum of the column
  *                   lengths of R (ColNorm)
- *   NU              sigma_1(Q_new), a lower estimate from Q^T Q: 24 Lanczos steps up to r = 256,
- *                   power iteration beyond (relative error (lambda_2 / lambda_1)^256)
+ *   NU              sigma_1(Q_new), an estimate from below (up to fp32 rounding, 3e-5): the root of one of
+ *                   lambda_1(Q^T Q), whose relative error with t the angle between start vector and
+ *                   leading eigenvector is up to r = 256 (24 Lanczos steps) at most
+ *                   d + tan(t)^2 / T_23((1 + d) / (1 - d))^2 for every 0 < d < 1, T_23 the Chebyshev
+ *                   polynomial, so 2.2 % at tan(t)^2 = 256 whatever the spectrum, and beyond (power
+ *                   iteration) at most d + tan(t)^2 (1 - d)^256 (4.6 %), O((lambda_2 / lambda_1)^256)
  *   ERANK           exp(-sum p_i log p_i), p_i = ||R[:, i]|| / sum_j ||R[:, j]||
  *   G_NORM          ||G||_F                                                              */
 typedef enum {

@@ -261,9 +261,14 @@ OD_DEV float block_sumsq(const float* v, int r, float* red) {
 // r <= 256: the matrix fits the registers of one workgroup (64 entries per thread), which takes kLanczosSteps steps of
 // the Lanczos iteration from the same start vector and reports the largest Ritz value.  Like the power it approaches
 // the eigenvalue from below, and closer: over random factors of 8 to 256 columns the largest error of nu is 3e-3 where the
-// power's is 7e-3 (their means 2e-4 and 1e-3 at 256 columns, 4e-6 and 4e-4 at 136), without the seven dependent
-// squarings.  Ghost copies from lost orthogonality repeat Ritz values, they never raise the
-// largest.  What bounds it: 64 fma per thread and step at four waves per SIMD, two sums over the workgroup.
+// power's is 7e-3 (their means 2e-4 and 1e-3 at 256 columns, 4e-6 and 4e-4 at 136), and no larger than the power's over
+// sixteen kinds of spectra (even, dense at the top, one value above a cluster, geometric ...: 7e-3 | 1.5e-2), without the
+// seven dependent squarings.  The relative error of the eigenvalue is at most d + tan(t)^2 / T_23((1 + d) / (1 - d))^2
+// for every d, t the angle between start vector and leading eigenvector: the Rayleigh quotient of T_23, the Chebyshev
+// polynomial of [0, (1 - d) lambda_1], applied to the start vector (Saad, SIAM J. Numer. Anal. 17, 1980); the power's is
+// d + tan(t)^2 (1 - d)^256.  2.2 and 4.6 % at tan(t)^2 = 256.  Ghost copies from lost orthogonality repeat Ritz values and
+// raise the largest by rounding only (nu by up to 2e-5, with two different eigenvalues).
+// What bounds it: 64 fma per thread and step at four waves per SIMD, two sums over the workgroup.
 // r = 256: 86 us (seven squarings of 10 us, two products) -> 35 us; a 2048 x 5632 step with diagnostics, r = 256,
 // 512 -> 462 us.
 // ------------------------------------------------------------------------------------
