@@ -35,9 +35,9 @@ SWEEP = [("C2", 30), ("C4", 10), ("C5-r16", 30), ("C5-r256", 20), ("C5-r1024", 1
 # Kernel groups: the phases orthdion_profile_begin can bracket, gathered by the kernel that
 # does their work, and the name prefixes of those kernels in a rocprofv3 counter summary.
 GROUPS = {
-    "k_proj": (["proj"], ["od::k_proj<", "od::k_stream_d<false"]),
-    "k_back": (["back"], ["od::k_back<", "od::k_stream_d<true"]),
-    "k_efx": (["efx"], ["od::k_efx_d<", "od::k_efx_h<", "od::k_efx<"]),
+    "k_proj": (["proj"], None),              # launched_kernels says which
+    "k_back": (["back"], None),
+    "k_efx": (["efx"], None),
     "k_gram (first pass)": (["gram_left", "gram_right"], []),
     "cholesky chain (k_chol256, k_chol_ahead, k_sgemm_pair)": (["chol_left", "chol_right"], ["od::k_chol256", "od::k_chol_ahead", "od::k_sgemm", "od::k_zero_pair"]),
     "rest of orth (k_apply, k_gram, k_corr | ColNorm)": (["orth_left", "orth_right", "guard_left", "guard_right", "finish_left", "finish_right"],
@@ -111,6 +111,22 @@ def step_work(w, variant):
     for m, n in w.shapes:
         qr += 6 * (m + (n if variant == "qr" else 0)) * w.r * w.r
     return nbytes, flops, flops + qr
+
+
+def launched_kernels(w, group, fast):
+    """Names of the kernels that the launchers of od_kernels.hip pick for the shapes of a workload,
+    for the groups with more than one.  The limits of fast precision are compared with the
+    elements that step together: those of the whole set, unless it is dealt into clusters of
+    2^27 or into two groups, which are far above the limits."""
+    if group not in ("k_proj", "k_back", "k_efx"):
+        return None
+    if not fast:
+        return [group]
+    if group == "k_efx":
+        return ["k_efx_h" if (w.r < 64 or w.r % 32) and w.elements < 1 << 22 else "k_efx_d"]
+    middle = w.elements >= 1 << 21 or (w.elements >= 1 << 20 and w.elements >= len(w.shapes) << 19)
+    direct = {w.x_dtype == "bf16" and w.r > 64 and min(s) >= 32 and (w.r >= 192 or middle) for s in w.shapes}
+    return sorted("k_stream_d<%s>" % ("false" if group == "k_proj" else "true") if d else group for d in direct)
 
 
 def measured_traffic(workload, variant, prefixes):
@@ -248,19 +264,14 @@ def measure(torch, binding, synth, dev, name, variant, precision, steps, warmup,
     dom_launches = sum(prof[p][1] for p in GROUPS[dominant][0] if p in prof) // steps
 
     fast_path = precision == "fast" or (precision == "auto" and w.x_dtype == "bf16")
-    # the kernel the library's launchers pick for this group (same rules as od_kernels.hip)
-    kname = dominant
-    if fast_path and dominant == "k_efx":
-        small = (w.r < 64 or w.r % 32) and sum(m * n for m, n in w.shapes) < 1 << 22
-        kname = "k_efx_h" if small else "k_efx_d"
-    if fast_path and dominant in ("k_proj", "k_back") and w.x_dtype == "bf16" and w.r > 64:
-        kname = "k_stream_d<%s>" % ("false" if dominant == "k_proj" else "true")
+    names = launched_kernels(w, dominant, fast_path)
     nbytes, flops = group_work(w, variant, dominant)
     hbm_frac_k = nbytes / (dom_ms * 1e-3) / 1e9 / HBM_PEAK_GBS
     mfma_frac_k = flops / (dom_ms * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS
     # which roofline binds the kernel: its arithmetic intensity against the ridge of the two peaks
     hbm_bound = flops / max(nbytes, 1) < MFMA_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)
-    traffic = measured_traffic(w.name, variant, GROUPS[dominant][1])
+    prefixes = ["od::" + (k.replace(">", ",") if "<" in k else k + "<") for k in names] if names else GROUPS[dominant][1]
+    traffic = measured_traffic(w.name, variant, prefixes)
     per_launch_ms = dom_ms / max(dom_launches, 1)
     step_bytes, step_flops, step_flops_qr = step_work(w, variant)
     rec = {
@@ -273,7 +284,7 @@ def measure(torch, binding, synth, dev, name, variant, precision, steps, warmup,
             "achieved": (nbytes / (dom_ms * 1e-3) / 1e9) if hbm_bound else (flops / (dom_ms * 1e-3) / 1e12),
             "peak": HBM_PEAK_GBS if hbm_bound else MFMA_PEAK_TFLOPS, "unit": "GB/s" if hbm_bound else "TFLOP/s",
             "frac": hbm_frac_k if hbm_bound else mfma_frac_k,
-            "traffic": traffic, "kernel": kname, "kernel_ms_per_launch": per_launch_ms, "launches_per_step": dom_launches,
+            "traffic": traffic, "kernel": " + ".join(names) if names else dominant, "kernel_ms_per_launch": per_launch_ms, "launches_per_step": dom_launches,
             "kernel_ms_per_step": dom_ms, "share_of_step": dom_ms / ms_per_step,
             "algorithmic_bytes_per_launch": nbytes / max(dom_launches, 1),
             "algorithmic_flops_per_launch": flops / max(dom_launches, 1),
