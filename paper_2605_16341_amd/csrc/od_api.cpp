@@ -790,7 +790,7 @@ extern "C" int orthdion_step_impl(orthdion_handle h, void* const* X, const void*
     }
     return ORTHDION_OK;
   };
-  // nu = sigma_1(Q_new): Gram matrix of the new right factor, then power iteration; the table's row
+  // nu = sigma_1(Q_new): Gram matrix of the new right factor, then Lanczos or, above r = 256, power iteration; the table's row
   auto diagnose = [&](int k) -> int {
     const BatchRef& v = refs[k];
     const ClassDims& d = v.d;
